@@ -169,6 +169,11 @@ void launch_signal_next(hipEvent_t ev);
 bool launch_signal_pending();
 hipEvent_t launch_signal_take();
 hipError_t launch_gemm_simple(const GemmArgs& g, int dtype, hipStream_t s);
+// 64x64 tiles with K split inside the workgroup (kernels_gemm_tile64.hip): every fp32 product whose operands span
+// less than 2 GiB, and bf16 products of few rows; hipErrorNotSupported otherwise.  Honours g.colsum with one band
+// per 64 rows.
+bool gemm_tile64_supported(const GemmArgs& g, int dtype);
+hipError_t launch_gemm_tile64(const GemmArgs& g, int dtype, hipStream_t s);
 // bf16 MFMA path; returns hipErrorNotSupported if the shape/strides do not fit it
 hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s);
 bool gemm_mfma_supported(const GemmArgs& g);
@@ -200,6 +205,10 @@ struct ReduceGroupedArgs {
     Remap64 tbl[3];
 };
 hipError_t launch_reduce_grouped(int dtype, const GemmArgs& g, const ReduceGroupedArgs& r, int accumulate, hipStream_t s);
+// the weight gradients of g.grp over the same K on 64x64 tiles, written through r (with a reduction of its own if it
+// splits K): takes g.n_groups, grp[].{A, B, lda, ldb, M, N}, K and partial (partial_floats long)
+hipError_t launch_gemm_tile64_grouped(const GemmArgs& g, const ReduceGroupedArgs& r, int dtype, int accumulate,
+                                      size_t partial_floats, hipStream_t s);
 // rows of the output tile launch_gemm_mfma would pick (a tile makes two bands of g.colsum)
 int gemm_mfma_tile_rows(const GemmArgs& g);
 // static string naming the kernel instantiation launch_gemm_mfma would pick (for timing records)

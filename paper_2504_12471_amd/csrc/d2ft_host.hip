@@ -272,10 +272,16 @@ hipError_t timed_mfma(const GemmArgs& g, hipStream_t st, hipEvent_t done = nullp
     return e;
 }
 
-// true if run_gemm takes the matrix-core path for g (the only path that honours g.colsum)
+// true if run_gemm takes the large-tile bf16 path for g
 bool on_mfma_path(const GemmArgs& g, const d2ft_block_desc* d) {
     return d->dtype == D2FT_BF16 && !(d->flags & D2FT_FLAG_NO_MFMA) && gemm_mfma_supported(g);
 }
+// true if run_gemm takes the 64x64-tile path for g
+bool on_tile64_path(const GemmArgs& g, const d2ft_block_desc* d) {
+    return d->dtype == D2FT_F32 && gemm_tile64_supported(g, d->dtype);
+}
+// the paths that honour g.colsum
+bool colsum_supported(const GemmArgs& g, const d2ft_block_desc* d) { return on_mfma_path(g, d) || on_tile64_path(g, d); }
 
 // colsum_bands: if non-null, receives the number of rows of g.colsum the launches fill
 // done: if non-null, the call's last matrix-core launch completes it (gemm_mfma_signal_next); the caller checks
@@ -283,6 +289,16 @@ bool on_mfma_path(const GemmArgs& g, const d2ft_block_desc* d) {
 hipError_t run_gemm(const GemmArgs& g, const d2ft_block_desc* d, hipStream_t s, int* colsum_bands = nullptr,
                     hipEvent_t done = nullptr) {
     if (colsum_bands) *colsum_bands = 0;
+    if (on_tile64_path(g, d)) {
+        if (colsum_bands) *colsum_bands = (g.M + 63) / 64;
+        if (done) launch_signal_next(done);
+        timing_begin(s, "gemm");
+        g_timing.label = "gemm_tile64_kernel";
+        g_timing.flops = 2.0 * g.M * g.N * g.K;
+        const hipError_t e = launch_gemm_tile64(g, d->dtype, s);
+        timing_end(s);
+        return e;
+    }
     if (on_mfma_path(g, d)) {
         // Tile plan for shapes of more than one round of the chip's 256 CUs.  The one-per-CU tiles take whole
         // rounds however few tiles the last one has, so three plans are priced in microseconds with per-round
@@ -340,7 +356,7 @@ hipError_t run_gemm(const GemmArgs& g, const d2ft_block_desc* d, hipStream_t s, 
         }
         return timed_mfma(g, s, done);
     }
-    if (g.colsum) return hipErrorNotSupported;   // callers ask on_mfma_path() first
+    if (g.colsum) return hipErrorNotSupported;   // callers ask colsum_supported() first
     timing_begin(s, "gemm");
     g_timing.label = "gemm_simple_kernel";
     g_timing.flops = 2.0 * g.M * g.N * g.K;
@@ -519,7 +535,7 @@ struct WeightGradBatch {
 void weight_grad_batch_init(WeightGradBatch* b, const d2ft_block_desc* d) {
     memset(b, 0, sizeof(*b));
     b->g.splits = 1;
-    b->enabled = d->dtype == D2FT_BF16 && !(d->flags & D2FT_FLAG_NO_MFMA);
+    b->enabled = d->dtype == D2FT_F32 || !(d->flags & D2FT_FLAG_NO_MFMA);
 }
 
 // queue dW[out_rows][out_cols] = Aop^T Bop (arguments as weight_grad); table_slot: which of the batch's three
@@ -603,7 +619,17 @@ d2ft_status weight_grad_flush(WeightGradBatch* b, const d2ft_block_desc* d, cons
     g.partial = part;
     const int accum = (d->flags & D2FT_FLAG_ACCUM_GRADS) ? 1 : 0;
     hipError_t e = hipErrorNotSupported;
-    if (gemm_grouped_slots(g) * 65536 <= part_floats) {
+    if (d->dtype == D2FT_F32) {
+        timing_begin(st, "gemm");
+        g_timing.label = "gemm_tile64_kernel";
+        for (int i = 0; i < g.n_groups; ++i) g_timing.flops += 2.0 * g.grp[i].M * g.grp[i].N * s.M;
+        e = launch_gemm_tile64_grouped(g, b->r, s.dtype, accum, part_floats, st);
+        timing_end(st);
+        if (e == hipSuccess) {
+            g.n_groups = 0;
+            return D2FT_OK;
+        }
+    } else if (gemm_grouped_slots(g) * 65536 <= part_floats) {
         timing_begin(st, "gemm");
         g_timing.label = "gemm_mfma_kernel<256, 256, 64, 2, 4, true, true, 0, false, true, false, 0>";
         for (int i = 0; i < g.n_groups; ++i) g_timing.flops += 2.0 * g.grp[i].M * g.grp[i].N * s.M;
@@ -940,7 +966,7 @@ static d2ft_status block_bwd_impl(const d2ft_block_desc* desc, const d2ft_block_
     // Side stream (see SideStream): for the whole-block matrix-core path, unless the caller asks for one stream,
     // per-kernel timing is on (its durations are those of kernels running alone) or the stream is being captured.
     SideStream* side = nullptr;
-    if (half == PART_BOTH && wgrads.enabled && !(desc->flags & D2FT_FLAG_ONE_STREAM) && !g_timing.on) {
+    if (half == PART_BOTH && s.dtype == D2FT_BF16 && wgrads.enabled && !(desc->flags & D2FT_FLAG_ONE_STREAM) && !g_timing.on) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) side = side_stream();
     }
@@ -1107,7 +1133,7 @@ static d2ft_status block_bwd_impl(const d2ft_block_desc* desc, const d2ft_block_
             g.M = M; g.N = n_hid; g.K = s.D;
             g.C = dz_buf; g.ldc = n_hid;
             g.act = ACT_DGELU; g.Z = const_cast<char*>(sv + SL.z); g.ldz = ld_hid;
-            if (grads->b1 && on_mfma_path(g, desc)) g.colsum = (float*)(ws + WL.colfuse_b1 + cf);   // db1 = column sums of dz
+            if (grads->b1 && colsum_supported(g, desc)) g.colsum = (float*)(ws + WL.colfuse_b1 + cf);   // db1 = column sums of dz
             // micro-batches with their own codes: the saved GELU' is zero where a slice was not p_f, so those
             // products need not be formed
             // if the feed-forward weight gradients go to the side stream behind dz, the dz launch itself completes

@@ -1,0 +1,581 @@
+// GEMM on the matrix cores with a 64x64 output tile per workgroup and K split between the workgroup's wavefronts:
+// the fp32 path (v_mfma_f32_32x32x2_f32) and the bf16 path (v_mfma_f32_32x32x16_bf16) for shapes whose larger
+// tiles would leave most of the chip idle.
+//
+//   C[m][n] = epilogue( sum_k A(m,k) * B(k,n) )
+//
+// A workgroup has WK groups of four wavefronts.  A group multiplies every WK-th K slab (128 bytes of k per row: 64
+// bf16 or 32 fp32) of the same tile, a wavefront of it one 32x32 quarter; the groups' sums are added in group order
+// through LDS before the epilogue, so a small problem gets WK times the wavefronts without a second launch and
+// without partial sums in memory.
+//
+// What bounds it.  fp32: the matrix cores (256 FLOP per clock and CU); a 64x64 tile asks for 16 bytes of operands per
+// clock and CU, which L2 delivers, so a larger tile would gain nothing and the small one deals evenly: four to five
+// workgroups share a CU and cover each other's latencies.  bf16: latency.  A problem of a few hundred rows gives the
+// 128x128 tile a few dozen workgroups with one slab in flight each; here kAhead slabs per group are in flight in
+// registers and there are 4 to 16 times as many groups.
+//
+// Measured against the vector-ALU kernel it replaced for fp32: one block of 260 tokens of width 192, forward and
+// backward, 721 -> 171 us (its 12 products 594 -> 104 us); the products of a 12-block stack of width 384 on 80 x 197
+// tokens 63.5 -> 21.2 ms, i.e. 30 -> 90 TFLOP/s (the vendor library reaches 127-133 on the largest of them).
+//
+// Slabs are kept in LDS without padding, their 16-byte pieces permuted within a row so that both the stores and the
+// fragment reads are free of bank conflicts (piece_offset).  Operands with K strided stay in their natural
+// [k][index] layout: bf16 fragments come out of it by the transposing read, fp32 ones by plain 4-byte reads.
+#include <hip/hip_ext.h>
+#include <type_traits>
+#include <utility>
+
+#include "d2ft_common.h"
+
+namespace d2ft {
+
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4;
+typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8;
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
+
+// One weight gradient of a grouped launch: out[m'][n'] (=|+=) sum_k A[k][m] * B[k][n], (m', n') through the remap
+struct Tile64Group {
+    const void* A;
+    const void* B;
+    void* out;
+    long lda, ldb, ldo;
+    int M, N;
+    int tiles_m, tile0;
+    int remap, table;        // RED_REMAP_*
+};
+struct Tile64Grouped {
+    Tile64Group grp[kMaxGemmGroups];
+    float* partial;          // splits > 1: raw sums, slot (split * total_tiles + tile), 64 x 64 floats each
+    int n, K, splits, slabs_per_split, total_tiles, accumulate;
+    uint16_t tbl[3][kMaxBlocks64];   // the remap tables in units of 64
+};
+
+namespace {
+
+constexpr uint32_t kBufBytes = 0x80000000u;   // declared buffer size; operands are checked to be smaller
+constexpr uint32_t kOutside = 0x80000000u;    // any offset >= kBufBytes reads as zero
+constexpr int kSlabBytes = 64 * 128;          // one operand's slab
+constexpr int kAhead = 3;                     // slabs in flight in registers
+constexpr int kStageStride = 68;              // floats per row of the epilogue's stage
+
+// byte offset in a slab of 16-byte piece `piece` of row `row`.  Row form: 64 rows of 128 bytes ([index][k]); column
+// form: [k][64 indices], i.e. 64 rows of 128 bytes for bf16, 32 rows of 256 for fp32.
+template <typename T, bool COL>
+__device__ __forceinline__ int piece_offset(int row, int piece) {
+    if constexpr (!COL) return row * 128 + ((piece ^ (row & 7)) << 4);               // eight rows, eight slots
+    else if constexpr (sizeof(T) == 2) return row * 128 + ((((piece >> 1) ^ (row & 3)) << 5) | ((piece & 1) << 4));
+    else return row * 256 + ((piece ^ (((row >> 2) & 1) << 3)) << 4);                // rows 4 apart: other half of the banks
+}
+
+// a thread's two 16-byte pieces of a slab: global offsets and LDS offsets
+template <typename T, bool COL>
+struct Loader {
+    static constexpr int kE = 16 / sizeof(T);          // elements per piece
+    static constexpr int kBK = 128 / sizeof(T);        // k per slab
+    __amdgpu_buffer_rsrc_t rsrc;
+    uint32_t base[2], sk;
+    int k_in[2];      // k of the piece within the slab
+
+    // index_of(i): the row (or column) of the operand that tile index i stands for
+    template <typename F>
+    __device__ __forceinline__ void init(const void* p, long s_i, long s_k, int i0, int I, int t, F&& index_of) {
+        rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, kBufBytes, 0x00020000);
+        sk = (uint32_t)s_k * (uint32_t)sizeof(T);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const int id = t + 256 * c;
+            int i;
+            if constexpr (!COL) {
+                i = id >> 3;
+                k_in[c] = (id & 7) * kE;
+            } else {
+                i = (id % (64 / kE)) * kE;
+                k_in[c] = id / (64 / kE);
+            }
+            i += i0;
+            const uint32_t off = ((uint32_t)index_of(i < I ? i : 0) * (uint32_t)s_i + (uint32_t)k_in[c] * (uint32_t)s_k) * (uint32_t)sizeof(T);
+            base[c] = i < I ? off : kOutside;
+        }
+    }
+    // the slab at k0 (valid k < k_end) whose first k sits at k_at in memory
+    __device__ __forceinline__ void load(u32x4 (&v)[2], int k0, int k_at, int k_end) const {
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+            v[c] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, k_in[c] < k_end - k0 ? base[c] : kOutside, (uint32_t)k_at * sk, 0);
+    }
+    static __device__ __forceinline__ void store(const u32x4 (&v)[2], unsigned char* slab, int t) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const int id = t + 256 * c;
+            constexpr int kPerRow = COL ? 64 / kE : 8;
+            *reinterpret_cast<u32x4*>(slab + piece_offset<T, COL>(id / kPerRow, id % kPerRow)) = v[c];
+        }
+    }
+};
+
+// operand fragments of a slab: 32 indices from i0, quarter q of the slab's k.  bf16: the 16 k of one product; fp32:
+// 8 k, lane half h holding k = 8q + 4h + {0..3}, i.e. four products of two k each.
+template <typename T, bool COL>
+__device__ __forceinline__ auto read_frag(const unsigned char* slab, int i0, int q, int lane) {
+    const int c = lane & 31, h = lane >> 5;
+    if constexpr (sizeof(T) == 2) {
+        if constexpr (!COL) {
+            return *reinterpret_cast<const bf16x8*>(slab + piece_offset<T, false>(i0 + c, 2 * q + h));
+        } else {
+            // a group of 16 lanes turns a 4 (k) x 16 (index) block into 4 consecutive k per lane
+            const int j = lane & 15, r = 16 * q + 8 * h + (j >> 2);
+            const int pair = (i0 >> 4) + ((lane >> 4) & 1);
+            const unsigned char* p = slab + r * 128 + ((pair ^ (j >> 2)) << 5) + (j & 3) * 8;
+            typedef s16x4 __attribute__((address_space(3))) * lds_ptr_t;
+            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p));
+            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p + 4 * 128));
+            s16x8 v;
+            v[0] = lo[0]; v[1] = lo[1]; v[2] = lo[2]; v[3] = lo[3];
+            v[4] = hi[0]; v[5] = hi[1]; v[6] = hi[2]; v[7] = hi[3];
+            return __builtin_bit_cast(bf16x8, v);
+        }
+    } else {
+        if constexpr (!COL) {
+            return *reinterpret_cast<const f32x4*>(slab + piece_offset<T, false>(i0 + c, 2 * q + h));
+        } else {
+            const int i = i0 + c;
+            const unsigned char* p = slab + (8 * q + 4 * h) * 256 + (((i >> 2) ^ (h << 3)) << 4) + (i & 3) * 4;
+            f32x4 v;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const float*>(p + j * 256);
+            return v;
+        }
+    }
+}
+__device__ __forceinline__ void mma(f32x16& acc, bf16x8 a, bf16x8 b) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
+}
+__device__ __forceinline__ void mma(f32x16& acc, f32x4 a, f32x4 b) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], b[j], acc, 0, 0, 0);
+}
+
+// workgroup -> tile: workgroup ids with the same value mod 8 (one XCD) get a contiguous range of tiles, walked in
+// groups of 8 tile rows, so that an XCD's workgroups share operand slabs through its L2
+__device__ __forceinline__ void tile_of_block(int pid, int total, int tiles_m, int tiles_n, int& tm, int& tn, int& split) {
+    const int xcd = pid & 7, idx = pid >> 3;
+    const int lid = xcd * (total >> 3) + min(xcd, total & 7) + idx;
+    const int per_split = tiles_m * tiles_n;
+    split = lid / per_split;
+    const int rem = lid - split * per_split;
+    constexpr int GM = 8;
+    const int group = rem / (GM * tiles_n);
+    const int first = group * GM;
+    const int gsize = min(tiles_m - first, GM);
+    const int in_group = rem - group * GM * tiles_n;
+    tm = first + in_group % gsize;
+    tn = in_group / gsize;
+}
+
+template <int N, typename F, int I = 0>
+__device__ __forceinline__ void unroll(F&& f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        unroll<N, F, I + 1>(static_cast<F&&>(f));
+    }
+}
+
+template <typename T, bool A_COL, bool B_COL, int WK, typename Args>
+__global__ __launch_bounds__(256 * WK, WK == 1 ? 4 : 1) void gemm_tile64_kernel(Args g) {
+    constexpr bool GROUPED = std::is_same<Args, Tile64Grouped>::value;
+    static_assert(!GROUPED || (A_COL && B_COL), "weight gradients: both operands with k strided");
+    constexpr int BK = 128 / sizeof(T);
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int kg = wave >> 2, quarter = wave & 3;       // K group; quarter of the tile
+    const int t = threadIdx.x & 255;                    // thread within the K group
+    const int wi = (quarter >> 1) * 32, wj = (quarter & 1) * 32;
+
+    int m0, n0, M, N, kb, ke, split, tile = 0, gi = 0;
+    Loader<T, A_COL> la;
+    Loader<T, B_COL> lb;
+    auto same = [](int i) { return i; };
+    if constexpr (GROUPED) {
+        // units: (split, tile), the tiles of one split next to each other
+        const int total = g.total_tiles * g.splits, xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
+        const int u = xcd * (total >> 3) + min(xcd, total & 7) + idx;
+        split = u / g.total_tiles;
+        tile = u - split * g.total_tiles;
+        while (gi + 1 < g.n && tile >= g.grp[gi + 1].tile0) ++gi;
+        const Tile64Group& G = g.grp[gi];
+        const int lt = tile - G.tile0;
+        M = G.M;
+        N = G.N;
+        m0 = (lt % G.tiles_m) * 64;
+        n0 = (lt / G.tiles_m) * 64;
+        kb = split * g.slabs_per_split * BK;
+        ke = min(g.K, kb + g.slabs_per_split * BK);
+        la.init(G.A, 1, G.lda, m0, M, t, same);
+        lb.init(G.B, 1, G.ldb, n0, N, t, same);
+    } else {
+        const int tiles_m = (g.M + 63) >> 6, tiles_n = (g.N + 63) >> 6;
+        const int splits = g.partial ? g.splits : 1;
+        int tm, tn;
+        tile_of_block(blockIdx.x, tiles_m * tiles_n * splits, tiles_m, tiles_n, tm, tn, split);
+        M = g.M;
+        N = g.N;
+        m0 = tm * 64;
+        n0 = tn * 64;
+        kb = 0;
+        ke = g.K;
+        if (splits > 1) {
+            const int per = ((g.K + splits - 1) / splits + BK - 1) / BK * BK;
+            kb = split * per;
+            ke = min(g.K, kb + per);
+        }
+        la.init(g.A, g.a_rs, g.a_cs, m0, M, t, same);
+        if (g.remap == REMAP_B_N) lb.init(g.B, g.b_cs, g.b_rs, n0, N, t, [&](int i) { return g.tbl(i); });
+        else lb.init(g.B, g.b_cs, g.b_rs, n0, N, t, same);
+    }
+
+    // this group's slabs: kb + (kg + s * WK) * BK, s = 0 .. n_slabs - 1; a slab past the end loads zeros
+    const int n_slabs = ke > kb ? ((ke - kb + BK - 1) / BK + WK - 1) / WK : 0;
+    u32x4 ra[kAhead][2], rb[kAhead][2];
+    auto fetch = [&](int s, u32x4 (&va)[2], u32x4 (&vb)[2]) {
+        const int k0 = kb + (kg + s * WK) * BK;
+        int k_at = k0;   // k of the slab as B is stored
+        if constexpr (!GROUPED) {
+            if (g.remap == REMAP_B_K && k0 < ke) k_at = g.tbl.start[k0 >> 6] + (k0 & 63);
+        }
+        la.load(va, k0, k0, ke);
+        lb.load(vb, k0, k_at, ke);
+    };
+    unsigned char* const mine = smem + kg * 4 * kSlabBytes;   // two buffers of (A, B) slabs
+    unroll<kAhead>([&](auto i) { fetch(i.value, ra[i.value], rb[i.value]); });
+    f32x16 acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    if (n_slabs > 0) {
+        Loader<T, A_COL>::store(ra[0], mine, t);
+        Loader<T, B_COL>::store(rb[0], mine + kSlabBytes, t);
+        fetch(kAhead, ra[0], rb[0]);
+    }
+    // slab s sits in LDS buffer s & 1, slabs s + 1 .. s + kAhead in registers (slab x in slot x % kAhead).  One
+    // barrier per slab: behind it the stores of slab s are visible and buffer (s + 1) & 1 is free.
+    auto step = [&](int s, auto slot_tag) {
+        constexpr int slot = decltype(slot_tag)::value;
+        unsigned char* const cur = mine + (s & 1) * 2 * kSlabBytes;
+        unsigned char* const nxt = mine + ((s + 1) & 1) * 2 * kSlabBytes;
+        __syncthreads();
+        decltype(read_frag<T, A_COL>(cur, 0, 0, 0)) fa[4];
+        decltype(read_frag<T, B_COL>(cur, 0, 0, 0)) fb[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            fa[q] = read_frag<T, A_COL>(cur, wi, q, lane);
+            fb[q] = read_frag<T, B_COL>(cur + kSlabBytes, wj, q, lane);
+        }
+        if (s + 1 < n_slabs) {
+            Loader<T, A_COL>::store(ra[slot], nxt, t);
+            Loader<T, B_COL>::store(rb[slot], nxt + kSlabBytes, t);
+            fetch(s + 1 + kAhead, ra[slot], rb[slot]);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) mma(acc, fa[q], fb[q]);
+    };
+    for (int s = 0; s < n_slabs; s += kAhead)
+        unroll<kAhead>([&](auto i) {
+            if (s + i.value < n_slabs) step(s + i.value, std::integral_constant<int, (i.value + 1) % kAhead>{});
+        });
+    __syncthreads();   // the stage below reuses the operand buffers
+
+    // ---- epilogue: the groups' sums meet in LDS, results leave as 8 consecutive columns per thread ----
+    float* const stage = reinterpret_cast<float*>(smem) + kg * 64 * kStageStride;
+    {
+        const int c = lane & 31, h = lane >> 5;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) stage[(wi + 8 * (e >> 2) + 4 * h + (e & 3)) * kStageStride + wj + c] = acc[e];
+    }
+    __syncthreads();
+    constexpr int kThreads = 256 * WK;
+    float csum[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) csum[i] = 0.f;
+#pragma unroll
+    for (int p0 = 0; p0 < 512; p0 += kThreads) {
+        const int p = p0 + threadIdx.x;
+        if (kThreads > 512 && p >= 512) break;
+        const int r = p >> 3, cc = (p & 7) * 8;
+        const int m = m0 + r, n = n0 + cc;
+        float v[8];
+        load8(reinterpret_cast<float*>(smem) + r * kStageStride + cc, v);
+#pragma unroll
+        for (int w = 1; w < WK; ++w) {
+            float o[8];
+            load8(reinterpret_cast<float*>(smem) + (w * 64 + r) * kStageStride + cc, o);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] += o[i];
+        }
+        if constexpr (GROUPED) {
+            if (g.splits > 1) {
+                store8(g.partial + ((long)split * g.total_tiles + tile) * 4096 + r * 64 + cc, v);
+            } else if (m < M && n < N) {
+                const Tile64Group& G = g.grp[gi];
+                if (G.remap == RED_REMAP_F32) {
+                    store8(static_cast<float*>(G.out) + (long)m * G.ldo + n, v);
+                } else {
+                    const int mo = G.remap == RED_REMAP_ROWS ? g.tbl[G.table][m >> 6] * 64 + (m & 63) : m;
+                    const int no = G.remap == RED_REMAP_COLS ? g.tbl[G.table][n >> 6] * 64 + (n & 63) : n;
+                    T* o = static_cast<T*>(G.out) + (long)mo * G.ldo + no;
+                    if (g.accumulate) {
+                        float old[8];
+                        load8(o, old);
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) v[i] += old[i];
+                    }
+                    store8(o, v);
+                }
+            }
+        } else if (m < M && n < N) {
+            if (g.partial) {
+                store8(g.partial + (long)split * M * N + (long)m * N + n, v);
+                continue;
+            }
+            if (g.bias) {
+                float b[8];
+                load8(static_cast<const T*>(g.bias) + (g.bias_remap ? g.tbl(n) : n), b);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] += b[i];
+            }
+            if (g.act == ACT_GELU) {
+                // Z <- GELU'(z), C <- GELU(z), both of the fp32 pre-activation
+                float d[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    d[i] = gelu_grad_f(v[i]);
+                    v[i] = gelu_f(v[i]);
+                }
+                store8(static_cast<T*>(g.Z) + (long)m * g.ldz + n, d);
+            } else if (g.act == ACT_DGELU) {
+                float d[8];
+                load8(static_cast<const T*>(g.Z) + (long)m * g.ldz + n, d);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] *= d[i];
+            }
+            if (g.residual) {
+                float x[8];
+                load8(static_cast<const T*>(g.residual) + (long)m * g.ldr + n, x);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] += x[i];
+            }
+            store8(static_cast<T*>(g.C) + (long)m * g.ldc + n, v);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) csum[i] += v[i];
+        }
+    }
+    if constexpr (!GROUPED) {
+        if (!g.colsum) return;   // uniform over the grid
+        // column sums of the tile's 64 rows: lanes 8 apart share their columns, then the wavefronts in order
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            float s = csum[i];
+            s += __shfl_xor(s, 8, 64);
+            s += __shfl_xor(s, 16, 64);
+            s += __shfl_xor(s, 32, 64);
+            csum[i] = s;
+        }
+        __syncthreads();
+        float* const red = reinterpret_cast<float*>(smem);
+        constexpr int kWaves = WK < 2 ? 4 : 8;   // wavefronts that hold results
+        if (lane < 8 && wave < kWaves) store8(red + wave * 64 + lane * 8, csum);
+        __syncthreads();
+        if (threadIdx.x < 64 && n0 + (int)threadIdx.x < N) {
+            float s = 0.f;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) s += red[w * 64 + threadIdx.x];
+            g.colsum[(long)(g.colsum_row0 + m0 / 64) * N + n0 + threadIdx.x] = s;
+        }
+    }
+}
+
+// sums of a grouped launch with more than one split: the splits of a tile are added in split order.  blockIdx.x =
+// tile, a thread owns 4 consecutive columns of every 16th row.
+template <typename T>
+__global__ __launch_bounds__(256) void reduce_tile64_kernel(Tile64Grouped g) {
+    const int tile = blockIdx.x;
+    int gi = 0;
+    while (gi + 1 < g.n && tile >= g.grp[gi + 1].tile0) ++gi;
+    const Tile64Group& G = g.grp[gi];
+    const int lt = tile - G.tile0;
+    const int r0 = blockIdx.y * 16 + (threadIdx.x >> 4), c = (threadIdx.x & 15) * 4;
+    const int m = (lt % G.tiles_m) * 64 + r0, n = (lt / G.tiles_m) * 64 + c;
+    if (m >= G.M || n >= G.N) return;
+    const float* src = g.partial + (long)tile * 4096 + r0 * 64 + c;
+    const long stride = (long)g.total_tiles * 4096;
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    int k = 0;
+    for (; k + 4 <= g.splits; k += 4) {
+        f32x4 v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const f32x4*>(src + (k + j) * stride);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s += v[j];
+    }
+    for (; k < g.splits; ++k) s += *reinterpret_cast<const f32x4*>(src + k * stride);
+    if (G.remap == RED_REMAP_F32) {
+        *reinterpret_cast<f32x4*>(static_cast<float*>(G.out) + (long)m * G.ldo + n) = s;
+        return;
+    }
+    const int mo = G.remap == RED_REMAP_ROWS ? g.tbl[G.table][m >> 6] * 64 + (m & 63) : m;
+    const int no = G.remap == RED_REMAP_COLS ? g.tbl[G.table][n >> 6] * 64 + (n & 63) : n;
+    T* o = static_cast<T*>(G.out) + (long)mo * G.ldo + no;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float v = s[i];
+        if (g.accumulate) v += ld<T>(o + i);
+        st<T>(o + i, v);
+    }
+}
+
+template <typename Kernel, typename Args>
+hipError_t launch(Kernel kern, unsigned grid, int wk, hipStream_t s, const Args& a) {
+    const size_t lds = (size_t)wk * 4 * kSlabBytes;
+    static_assert(4 * kSlabBytes >= 64 * kStageStride * 4, "the stage fits the operand buffers");
+    if (hipEvent_t ev = launch_signal_take()) {   // the launch completes the event itself
+        hipExtLaunchKernelGGL(kern, dim3(grid), dim3(256 * wk), lds, s, nullptr, ev, 0, a);
+    } else {
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(256 * wk), lds, s, a);
+    }
+    return hipGetLastError();
+}
+
+template <typename T, bool A_COL, bool B_COL, int WK, typename Args>
+hipError_t launch_wk(unsigned grid, hipStream_t s, const Args& a) {
+    auto kern = gemm_tile64_kernel<T, A_COL, B_COL, WK, Args>;
+    if constexpr (WK * 4 * kSlabBytes > 64 * 1024) {
+        static bool attr_set = false;
+        if (!attr_set) {
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, WK * 4 * kSlabBytes);
+            if (e != hipSuccess) return e;
+            attr_set = true;
+        }
+    }
+    return launch(kern, grid, WK, s, a);
+}
+
+template <typename T, bool A_COL, bool B_COL, typename Args>
+hipError_t launch_form(int wk, unsigned grid, hipStream_t s, const Args& a) {
+    switch (wk) {
+        case 4: return launch_wk<T, A_COL, B_COL, 4>(grid, s, a);
+        case 2: return launch_wk<T, A_COL, B_COL, 2>(grid, s, a);
+        default: return launch_wk<T, A_COL, B_COL, 1>(grid, s, a);
+    }
+}
+
+// K groups per workgroup: as many as it takes to give every CU two workgroups' worth of wavefronts, as long as each
+// group keeps two slabs to multiply
+int pick_wk(long units, int slabs) {
+    int wk = 1;
+    while (wk < 4 && units * wk < 512 && slabs >= 4 * wk) wk *= 2;
+    return wk;
+}
+
+inline bool mult8(long v) { return (v & 7) == 0; }
+inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
+
+}  // namespace
+
+bool gemm_tile64_supported(const GemmArgs& g, int dtype) {
+    const long es = dtype == D2FT_F32 ? 4 : 2;
+    if (g.M <= 0 || g.N <= 0 || g.K <= 0) return false;
+    const bool a_row = (g.a_cs == 1), a_col = (g.a_rs == 1), b_row = (g.b_rs == 1), b_col = (g.b_cs == 1);
+    if (!(a_row || a_col) || !(b_row || b_col) || (!a_row && b_row)) return false;
+    if (a_row ? !(mult8(g.K) && mult8(g.a_rs)) : !(mult8(g.M) && mult8(g.a_cs))) return false;
+    if (b_row ? !(mult8(g.K) && mult8(g.b_cs)) : !mult8(g.b_rs)) return false;
+    if (!al16(g.A) || !al16(g.B) || !mult8(g.N)) return false;
+    const long a_span = a_row ? (long)g.M * g.a_rs : (long)g.K * g.a_cs;
+    long b_n = g.N, b_k = g.K;   // extents of B as stored (through the remap, if any)
+    if (g.remap != REMAP_NONE) {
+        const int nblk = ((g.remap == REMAP_B_N ? g.N : g.K) + 63) / 64;
+        if (nblk > kMaxBlocks64) return false;
+        long top = 0;
+        for (int i = 0; i < nblk; ++i) {
+            if (g.tbl.start[i] < 0) return false;
+            if (g.tbl.start[i] + 64 > top) top = g.tbl.start[i] + 64;
+        }
+        (g.remap == REMAP_B_N ? b_n : b_k) = top;
+    }
+    const long b_span = b_row ? b_n * g.b_cs : b_k * g.b_rs;
+    if (a_span * es >= (1L << 31) || b_span * es >= (1L << 31)) return false;   // 32-bit byte offsets
+    if ((long)((g.M + 63) / 64) * ((g.N + 63) / 64) * (g.partial ? g.splits : 1) > 0x7fffffffL) return false;
+    if (g.colsum && (g.partial || !al16(g.colsum))) return false;
+    if (g.partial) return al16(g.partial);
+    if (!g.C || !al16(g.C) || !mult8(g.ldc)) return false;
+    if (g.bias && !al16(g.bias)) return false;
+    if (g.residual && (!al16(g.residual) || !mult8(g.ldr))) return false;
+    if (g.act != ACT_NONE && (!g.Z || !al16(g.Z) || !mult8(g.ldz))) return false;
+    return true;
+}
+
+template <typename T>
+static hipError_t launch_tile64(const GemmArgs& g, hipStream_t s) {
+    const long units = (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * (g.partial ? g.splits : 1);
+    const int slabs = (g.K / (g.partial ? g.splits : 1) + 128 / (int)sizeof(T) - 1) / (128 / (int)sizeof(T));
+    const int wk = pick_wk(units, slabs);
+    const bool a_col = (g.a_cs != 1), b_col = (g.b_rs != 1);
+    if (!a_col && !b_col) return launch_form<T, false, false>(wk, (unsigned)units, s, g);
+    if (!a_col && b_col) return launch_form<T, false, true>(wk, (unsigned)units, s, g);
+    return launch_form<T, true, true>(wk, (unsigned)units, s, g);
+}
+
+hipError_t launch_gemm_tile64(const GemmArgs& g, int dtype, hipStream_t s) {
+    if (!gemm_tile64_supported(g, dtype)) return hipErrorNotSupported;
+    return dtype == D2FT_F32 ? launch_tile64<float>(g, s) : launch_tile64<bf16>(g, s);
+}
+
+// out_g = A_g^T B_g for the groups of g (grp, n_groups, K, partial), through r's remaps: one launch, and a reduction
+// behind it if K is split.  partial_floats: size of g.partial.
+hipError_t launch_gemm_tile64_grouped(const GemmArgs& g, const ReduceGroupedArgs& r, int dtype, int accumulate,
+                                      size_t partial_floats, hipStream_t s) {
+    const long es = dtype == D2FT_F32 ? 4 : 2;
+    if (g.n_groups < 1 || g.n_groups > kMaxGemmGroups || g.K <= 0) return hipErrorNotSupported;
+    Tile64Grouped a;
+    a.n = g.n_groups;
+    a.K = g.K;
+    a.accumulate = accumulate;
+    a.partial = g.partial;
+    long tiles = 0;
+    for (int i = 0; i < g.n_groups; ++i) {
+        const GemmGroup& G = g.grp[i];
+        if (G.M <= 0 || G.N <= 0 || !al16(G.A) || !al16(G.B) || !mult8(G.M) || !mult8(G.N) || !mult8(G.lda) || !mult8(G.ldb)) return hipErrorNotSupported;
+        if ((long)g.K * G.lda * es >= (1L << 31) || (long)g.K * G.ldb * es >= (1L << 31)) return hipErrorNotSupported;
+        Tile64Group& o = a.grp[i];
+        o.A = G.A; o.B = G.B; o.out = r.grp[i].out;
+        o.lda = G.lda; o.ldb = G.ldb; o.ldo = r.grp[i].ldo;
+        o.M = G.M; o.N = G.N;
+        o.tiles_m = (G.M + 63) / 64;
+        o.tile0 = (int)tiles;
+        o.remap = r.grp[i].remap; o.table = r.grp[i].table;
+        tiles += (long)o.tiles_m * ((G.N + 63) / 64);
+        if (tiles > (1 << 20)) return hipErrorNotSupported;
+    }
+    for (int i = 0; i < 3; ++i)
+        for (int j = 0; j < kMaxBlocks64; ++j) a.tbl[i][j] = (uint16_t)(r.tbl[i].start[j] >> 6);
+    a.total_tiles = (int)tiles;
+    // Splits of K: enough units for four workgroups per CU, while each keeps eight slabs and the partial tiles fit
+    const int bk = 128 / (int)es, slabs = (g.K + bk - 1) / bk;
+    int splits = 1;
+    while (splits < 64 && tiles * splits < 1024 && slabs / (splits + 1) >= 8 && (size_t)(splits + 1) * tiles * 4096 <= partial_floats) ++splits;
+    a.slabs_per_split = (slabs + splits - 1) / splits;
+    a.splits = (slabs + a.slabs_per_split - 1) / a.slabs_per_split;
+    const long units = tiles * a.splits;
+    const int wk = pick_wk(units, a.slabs_per_split);
+    hipError_t e = dtype == D2FT_F32 ? launch_form<float, true, true>(wk, (unsigned)units, s, a)
+                                     : launch_form<bf16, true, true>(wk, (unsigned)units, s, a);
+    if (e != hipSuccess || a.splits == 1) return e;
+    const dim3 grid((unsigned)tiles, 4);
+    if (dtype == D2FT_F32) hipLaunchKernelGGL(reduce_tile64_kernel<float>, grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(reduce_tile64_kernel<bf16>, grid, dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+}  // namespace d2ft

@@ -1,0 +1,31 @@
+"""GPU parity of the 64x64-tile GEMM (kernels_gemm_tile64.hip) through one block forward + backward, at the sizes
+where its tiling can go wrong: rows and widths at and beside the tile edges, one and several K groups per workgroup,
+K shorter than a slab, weight gradients with K split over several partial tiles and with every remap."""
+import pytest
+
+import d2ft_inputs as di
+from test_gpu_block import run_case
+from test_gpu_ffn_gate import run_gated
+
+pytestmark = pytest.mark.gpu
+
+FULL, FWD, SKIP = di.OP_FULL, di.OP_FWD, di.OP_SKIP
+
+
+@pytest.mark.parametrize("batch,tokens,width,heads,mlp", [
+    (1, 3, 8, 1, 8),          # K below one slab everywhere
+    (1, 64, 64, 1, 64),       # one exact tile
+    (5, 13, 56, 2, 72),       # one row and one piece of columns beside the tile edge
+    (1, 63, 136, 2, 264),
+    (8, 197, 192, 3, 768),    # weight gradients in several splits of K, K not a multiple of the slab
+    (40, 50, 320, 5, 1280),
+])
+def test_fp32_tile_edges(batch, tokens, width, heads, mlp):
+    w = di.Workload("tile64_f32", batch, tokens, width, heads, 64, mlp, 1, "f32")
+    ops = [FULL, FWD, SKIP, FULL, FULL][-heads:]
+    run_case(w, ops, seed=71)
+
+
+def test_fp32_gated_slices_through_the_remaps():
+    w = di.Workload("tile64_gate_f32", 6, 197, 256, 4, 64, 1024, 1, "f32")
+    run_gated(w, [FULL, SKIP, FWD, FULL], seed=72)
