@@ -436,6 +436,10 @@ hipError_t run_attn_fwd(const d2ft_block_desc* d, const void* qkv, long ldq, voi
         g_timing.label = "attn_fwd_mfma";
         return launch_attn_fwd_mfma(qkv, ldq, o, ldo, lse, batch, tokens, n_live, n_full, s);
     }
+    if ((d->dtype == D2FT_F32 || !(d->flags & D2FT_FLAG_NO_MFMA)) && attn_stream_supported(d->dtype, tokens, ldq, ldo)) {
+        g_timing.label = "attn_fwd_stream";
+        return launch_attn_fwd_stream(d->dtype, qkv, ldq, o, ldo, lse, batch, tokens, n_live, n_full, s);
+    }
     g_timing.label = "attn_fwd_simple";
     return launch_attn_fwd_simple(d->dtype, qkv, ldq, o, ldo, lse, batch, tokens, n_live, n_full, s);
 }
@@ -463,6 +467,10 @@ hipError_t run_attn_bwd(const d2ft_block_desc* d, const void* qkv, long ldq, con
         return launch_attn_bwd_mfma(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, ld_dqkv, batch, tokens, n_full, s);
     }
     if (bsum) return hipErrorNotSupported;   // callers ask attn_bwd_on_mfma() first
+    if ((d->dtype == D2FT_F32 || !(d->flags & D2FT_FLAG_NO_MFMA)) && attn_stream_supported(d->dtype, tokens, ldq, ldo)) {
+        g_timing.label = "attn_bwd_stream";
+        return launch_attn_bwd_stream(d->dtype, qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, batch, tokens, n_full, s);
+    }
     g_timing.label = "attn_bwd_simple";
     return launch_attn_bwd_simple(d->dtype, qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, delta, batch, tokens, n_full,
                                   s);

@@ -1,6 +1,6 @@
 // Softmax attention forward and backward on the vector ALUs, one wavefront per query row
-// (forward, dQ) or per key row (dK, dV).  Head dimension 64 = one lane per channel.  This is
-// the fp32 path and the path for token counts the MFMA kernels do not take.  Probabilities are
+// (forward, dQ) or per key row (dK, dV).  Head dimension 64 = one lane per channel.  With
+// D2FT_FLAG_NO_MFMA this is the cross-check of the matrix-core kernels.  Probabilities are
 // never stored: the backward pass rebuilds them from the saved log-sum-exp.
 #include "d2ft_common.h"
 

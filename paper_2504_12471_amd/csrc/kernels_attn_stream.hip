@@ -1,0 +1,518 @@
+// Softmax attention on the matrix cores for head dimension 64 with the keys (forward, dQ) or the queries (dK, dV)
+// streamed through LDS: any number of tokens, bf16 and fp32 storage, fp32 accumulate.  It serves fp32 at every token
+// count and bf16 above the 224 tokens that kernels_attn_mfma.hip keeps on chip whole.
+//
+// A wavefront owns 32 queries (or keys): their rows sit in registers as the B operand of every product and their
+// results as accumulators, so nothing but the streamed tiles goes through LDS and no partial sum crosses a
+// wavefront.  Four wavefronts of a workgroup share the streamed tiles, which are double-buffered with the next
+// stage's loads in flight under the current one's products (one barrier per stage).
+//   forward  S^T = K Q^T (a lane owns one query), running maximum and sum per lane, O^T += V^T P^T
+//   dQ       S^T and dP^T = V dO^T from the same tiles, dS^T = P^T (dP^T - delta), dQ^T += K^T dS^T
+//   dK, dV   S = Q K^T and dP = dO V^T (a lane owns one key), dV^T += dO^T P, dK^T += Q^T dS
+// Probabilities are rebuilt from the saved log-sum-exp.  dQ and dK/dV workgroups are independent (both form
+// delta_q = sum_d dO[q][d] O[q][d] for the rows they touch) and share one launch, so that the second kind fills the
+// last round of the first.  S and dP are formed twice, 7 products of 64 x 32 x 32 per tile pair instead of 5: keeping
+// dQ partial sums instead would mean fp32 atomics, whose order is not fixed, or a pass over them.
+//
+// Bound: fp32 by the matrix cores (a 32 x 32 tile pair is 64 products of 64 cycles forward, 224 backward); bf16 by
+// the vector ALUs (16 exponentials, 16 multiply-adds, maxima, sums and conversions per lane and tile pair against
+// 8 products of 32 cycles).
+//
+// Measured against the vector-ALU kernels it replaced (one wavefront per row, every row of K and V from cache for
+// every query), per launch: bf16, 16 images of 577 tokens, 154 live / 115 p_f pairs: forward 1440 -> 30 us, backward
+// 4004 -> 65 us; fp32, 16 images of 197 tokens, 77 / 58 pairs: forward 172 -> 21 us, backward 486 -> 43 us.
+//
+// Result layout of both products: column c = lane % 32, element e <-> row 8*(e/4) + 4h + e%4, h = lane / 32.
+#include <hip/hip_ext.h>
+
+#include "d2ft_common.h"
+
+namespace d2ft {
+
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4;
+typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8;
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
+
+namespace {
+
+constexpr float kScale = 0.125f;   // 1/sqrt(64)
+constexpr float kLog2e = 1.4426950408889634f;
+constexpr int kRows = 32;          // rows of a tile, queries or keys of a wavefront
+constexpr int kWaves = 4;
+
+__device__ __forceinline__ f32x16 zero16() {
+    f32x16 z;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) z[e] = 0.f;
+    return z;
+}
+
+// A streamed tile in LDS: 32 rows of 64 channels, read both row-wise (128-bit) and with the row index as k.
+//   bf16: row r of a group of eight sits at position (0, 2, 4, 6, 1, 3, 5, 7)[r % 8], rows 176 bytes apart, which keeps
+//         the row-wise and the transposing reads free of bank conflicts; fp32: rows 272 bytes apart.
+template <typename T> struct Tile;
+template <> struct Tile<bf16> {
+    static constexpr int kStride = 88, kPieces = 8, kStage = 2;   // kStage: tiles per stage
+    static __device__ __forceinline__ int at(int r) { return ((r & ~7) | ((r & 3) << 1) | ((r >> 2) & 1)) * kStride; }
+};
+template <> struct Tile<float> {
+    static constexpr int kStride = 68, kPieces = 16, kStage = 1;
+    static __device__ __forceinline__ int at(int r) { return r * kStride; }
+};
+template <typename T> constexpr int tile_elems() { return kRows * Tile<T>::kStride; }
+
+// 32 rows x 64 channels as the B operand of row-wise products: this lane's row in registers
+template <typename T> struct RowOp;
+template <> struct RowOp<bf16> {
+    bf16x8 f[4];   // channels 16 kk + 8h .. + 7
+    __device__ __forceinline__ void load(const bf16* row, bool ok, int h) {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+            u32x4 v = {0u, 0u, 0u, 0u};
+            if (ok) v = *reinterpret_cast<const u32x4*>(row + kk * 16 + 8 * h);
+            f[kk] = __builtin_bit_cast(bf16x8, v);
+        }
+    }
+    // sum over this lane's channels of its own row times another
+    static __device__ __forceinline__ float dot(const RowOp& a, const RowOp& b) {
+        float s = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) s = fmaf(static_cast<float>(a.f[kk][i]), static_cast<float>(b.f[kk][i]), s);
+        return s;
+    }
+};
+template <> struct RowOp<float> {
+    f32x4 f[8];    // channels 8 i + 4h .. + 3
+    __device__ __forceinline__ void load(const float* row, bool ok, int h) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            f[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (ok) f[i] = *reinterpret_cast<const f32x4*>(row + 8 * i + 4 * h);
+        }
+    }
+    static __device__ __forceinline__ float dot(const RowOp& a, const RowOp& b) {
+        float s = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) s = fmaf(a.f[i][j], b.f[i][j], s);
+        return s;
+    }
+};
+
+// acc[row of the tile][this wavefront's row] += tile . op^T
+__device__ __forceinline__ void mma_rows(f32x16& acc, const bf16* tile, const RowOp<bf16>& op, int lane) {
+    const bf16* p = tile + Tile<bf16>::at(lane & 31) + 8 * (lane >> 5);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(p + kk * 16), op.f[kk], acc, 0, 0, 0);
+}
+__device__ __forceinline__ void mma_rows(f32x16& acc, const float* tile, const RowOp<float>& op, int lane) {
+    const float* p = tile + Tile<float>::at(lane & 31) + 4 * (lane >> 5);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const f32x4 a = *reinterpret_cast<const f32x4*>(p + 8 * i);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], op.f[i][j], acc, 0, 0, 0);
+    }
+}
+
+// out[channel][this wavefront's row] += tile^T . p, p a result of mma_rows (rows of the tile x the wavefront's rows)
+__device__ __forceinline__ void mma_tr(f32x16 (&out)[2], const bf16* tile, const f32x16& p, int lane) {
+    const int j = lane & 15;
+    // rows t0 + 4h + {0..3} and t0 + 8 + 4h + {0..3} of the tile: the order in which a lane holds 8 result elements
+    const bf16* base = tile + (2 * (j >> 2) + (lane >> 5)) * Tile<bf16>::kStride + 16 * ((lane >> 4) & 1) + 4 * (j & 3);
+    typedef s16x4 __attribute__((address_space(3))) * lds_ptr_t;
+#pragma unroll
+    for (int gp = 0; gp < 2; ++gp) {
+        bf16x8 pf;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) pf[i] = static_cast<__bf16>(p[8 * gp + i]);
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt) {
+            const bf16* q = base + 16 * gp * Tile<bf16>::kStride + 32 * dt;
+            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(q));
+            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(q + 8 * Tile<bf16>::kStride));
+            s16x8 r;
+            r[0] = lo[0]; r[1] = lo[1]; r[2] = lo[2]; r[3] = lo[3];
+            r[4] = hi[0]; r[5] = hi[1]; r[6] = hi[2]; r[7] = hi[3];
+            out[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, r), pf, out[dt], 0, 0, 0);
+        }
+    }
+}
+__device__ __forceinline__ void mma_tr(f32x16 (&out)[2], const float* tile, const f32x16& p, int lane) {
+    const float* base = tile + Tile<float>::at(4 * (lane >> 5)) + (lane & 31);
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt)
+            out[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(base[(8 * (e >> 2) + (e & 3)) * Tile<float>::kStride + 32 * dt], p[e], out[dt], 0, 0, 0);
+}
+
+// transposed result [64 channels][this lane's row] times mul -> the row in memory
+__device__ __forceinline__ void store_row(const f32x16 (&t)[2], float mul, bf16* row, int h, bool ok) {
+    // the two lanes of a row exchange halves, so that each stores 16-byte pieces
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            uint32_t a[2], b[2];
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                a[r] = pack_bf16x2(t[dt][8 * p + 2 * r] * mul, t[dt][8 * p + 2 * r + 1] * mul);
+                b[r] = pack_bf16x2(t[dt][8 * p + 4 + 2 * r] * mul, t[dt][8 * p + 4 + 2 * r + 1] * mul);
+                const auto sw = __builtin_amdgcn_permlane32_swap(a[r], b[r], false, false);
+                a[r] = sw[0];
+                b[r] = sw[1];
+            }
+            if (ok) *reinterpret_cast<uint4*>(row + dt * 32 + 8 * (2 * p + h)) = make_uint4(a[0], a[1], b[0], b[1]);
+        }
+}
+__device__ __forceinline__ void store_row(const f32x16 (&t)[2], float mul, float* row, int h, bool ok) {
+    if (!ok) return;
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const f32x4 v = {t[dt][4 * g] * mul, t[dt][4 * g + 1] * mul, t[dt][4 * g + 2] * mul, t[dt][4 * g + 3] * mul};
+            *reinterpret_cast<f32x4*>(row + dt * 32 + 8 * g + 4 * h) = v;
+        }
+}
+
+// One operand of a stage: kStage tiles of 32 rows, this thread's 16-byte pieces on their way from memory to LDS.  The
+// buffer's declared size ends with the last valid row, rows beyond it read as zeros.
+template <typename T>
+struct Stream {
+    static constexpr int kPer = Tile<T>::kStage * kRows * Tile<T>::kPieces / (64 * kWaves);   // pieces per thread
+    static constexpr int kStep = 64 * kWaves / Tile<T>::kPieces;                              // rows between them
+    __amdgpu_buffer_rsrc_t rsrc;
+    uint32_t off, ld_bytes;
+    u32x4 v[kPer];
+    __device__ __forceinline__ void init(const T* p, long ld, int tokens) {
+        ld_bytes = (uint32_t)ld * (uint32_t)sizeof(T);
+        rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(p), 0, (uint32_t)(tokens - 1) * ld_bytes + 64u * (uint32_t)sizeof(T), 0x00020000);
+        off = (uint32_t)(threadIdx.x / Tile<T>::kPieces) * ld_bytes + (uint32_t)(threadIdx.x % Tile<T>::kPieces) * 16u;
+    }
+    __device__ __forceinline__ void fetch(int row0) {
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) v[k] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off + (uint32_t)(row0 + k * kStep) * ld_bytes, 0, 0);
+    }
+    __device__ __forceinline__ void store(T* lds) const {   // lds: kStage tiles, one after the other
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const int r = threadIdx.x / Tile<T>::kPieces + k * kStep;
+            *reinterpret_cast<u32x4*>(lds + (r / kRows) * tile_elems<T>() + Tile<T>::at(r % kRows) + (threadIdx.x % Tile<T>::kPieces) * (16 / (int)sizeof(T))) = v[k];
+        }
+    }
+};
+
+// workgroup ids of one XCD (equal mod 8) become a contiguous range: the blocks of a pair share its rows through L2
+__device__ __forceinline__ int xcd_order(int pid, int total) {
+    const int xcd = pid & 7;
+    return xcd * (total >> 3) + min(xcd, total & 7) + (pid >> 3);
+}
+
+// ---------------------------------------------------------------------------
+// forward: workgroup = 128 queries of one (image, live head)
+// ---------------------------------------------------------------------------
+template <typename T>
+__global__ __launch_bounds__(64 * kWaves, 3) void attn_fwd_stream_kernel(const T* __restrict__ qkv, long ldq, T* __restrict__ o,
+                                                                         long ldo, float* __restrict__ lse, int tokens,
+                                                                         int n_live, int n_full, long rows_total, int blocks) {
+    constexpr int ST = Tile<T>::kStage;
+    __shared__ __attribute__((aligned(16))) T lds[2][2][ST * tile_elems<T>()];   // [buffer][K, V]
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int c = lane & 31, h = lane >> 5;
+    const int id = xcd_order(blockIdx.x, gridDim.x);
+    const int pair = id / blocks, b = pair / n_live, j = pair % n_live;
+    const long row0 = (long)b * tokens;
+    const T* Qb = qkv + row0 * ldq + j * 192;
+    const int q0 = (id % blocks) * (kRows * kWaves) + wave * kRows, q = q0 + c;
+
+    Stream<T> sk, sv;
+    sk.init(Qb + 64, ldq, tokens);
+    sv.init(Qb + 128, ldq, tokens);
+    sk.fetch(0);
+    sv.fetch(0);
+    RowOp<T> qf;
+    qf.load(Qb + (long)q * ldq, q < tokens, h);
+    f32x16 ot[2] = {zero16(), zero16()};
+    float m = -INFINITY, sum = 0.f;      // of the raw scores; sum over this lane's keys only
+    const float cexp = kScale * kLog2e;
+    const int stages = (tokens + ST * kRows - 1) / (ST * kRows);
+    sk.store(lds[0][0]);
+    sv.store(lds[0][1]);
+    for (int s = 0; s < stages; ++s) {
+        if (s + 1 < stages) {
+            sk.fetch((s + 1) * ST * kRows);
+            sv.fetch((s + 1) * ST * kRows);
+        }
+        __syncthreads();
+        const T* Ks = lds[s & 1][0];
+        const T* Vs = lds[s & 1][1];
+        if (q0 < tokens) {   // uniform over the wavefront
+            f32x16 p[ST];
+#pragma unroll
+            for (int u = 0; u < ST; ++u) {
+                p[u] = zero16();
+                mma_rows(p[u], Ks + u * tile_elems<T>(), qf, lane);
+            }
+            if (s + 1 == stages) {   // keys past the last token
+#pragma unroll
+                for (int u = 0; u < ST; ++u) {
+                    const int lim = tokens - (s * ST + u) * kRows - 4 * h;
+#pragma unroll
+                    for (int e = 0; e < 16; ++e)
+                        if (8 * (e >> 2) + (e & 3) >= lim) p[u][e] = -INFINITY;
+                }
+            }
+            float mt = m;
+#pragma unroll
+            for (int u = 0; u < ST; ++u)
+#pragma unroll
+                for (int e = 0; e < 16; e += 2) mt = fmaxf(fmaxf(mt, p[u][e]), p[u][e + 1]);
+            mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
+            if (__any(mt > m)) {   // a new maximum somewhere: rescale (by exactly 1 where there is none)
+                const float alpha = __builtin_amdgcn_exp2f((m - mt) * cexp);
+                m = mt;
+                sum *= alpha;
+#pragma unroll
+                for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) ot[dt][e] *= alpha;
+            }
+            const float mc = m * cexp;
+#pragma unroll
+            for (int u = 0; u < ST; ++u) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    p[u][e] = __builtin_amdgcn_exp2f(fmaf(p[u][e], cexp, -mc));
+                    sum += p[u][e];
+                }
+                mma_tr(ot, Vs + u * tile_elems<T>(), p[u], lane);
+            }
+        }
+        if (s + 1 < stages) {   // the other buffer was last read before the barrier above
+            sk.store(lds[(s + 1) & 1][0]);
+            sv.store(lds[(s + 1) & 1][1]);
+        }
+    }
+    if (q0 >= tokens) return;
+    sum += __shfl_xor(sum, 32, 64);   // the two lanes of a query hold different keys
+    store_row(ot, 1.0f / sum, o + (row0 + q) * ldo + j * 64, h, q < tokens);
+    if (q < tokens && h == 0 && j < n_full) lse[(long)j * rows_total + row0 + q] = m * kScale + __logf(sum);
+}
+
+// ---------------------------------------------------------------------------
+// backward for p_f heads: the first half of the workgroups 128 keys of one (image, head) each, the rest 128 queries
+// ---------------------------------------------------------------------------
+template <typename T>
+__global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T* __restrict__ qkv, long ldq,
+                                                                         const T* __restrict__ o, long ldo,
+                                                                         const float* __restrict__ lse,
+                                                                         const T* __restrict__ d_o, long ld_do,
+                                                                         T* __restrict__ dqkv, long ld_dqkv, int tokens,
+                                                                         int n_full, long rows_total, int blocks) {
+    constexpr int ST = Tile<T>::kStage;
+    __shared__ __attribute__((aligned(16))) T lds[2][2][ST * tile_elems<T>()];
+    __shared__ __attribute__((aligned(16))) float consts[2][2][ST * kRows];   // log2(e) lse and delta of a stage's queries
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int c = lane & 31, h = lane >> 5;
+    const int half = gridDim.x >> 1;
+    const bool keys = (int)blockIdx.x < half;
+    const int id = xcd_order(keys ? blockIdx.x : blockIdx.x - half, half);
+    const int pair = id / blocks, b = pair / n_full, j = pair % n_full;
+    const long row0 = (long)b * tokens;
+    const T* Qb = qkv + row0 * ldq + j * 192;
+    const T* dOb = d_o + row0 * ld_do + j * 64;
+    const T* Ob = o + row0 * ldo + j * 64;
+    const float* lse_b = lse + (long)j * rows_total + row0;
+    T* dQb = dqkv + row0 * ld_dqkv + j * 192;
+    const int i0 = (id % blocks) * (kRows * kWaves) + wave * kRows, i = i0 + c;   // this wavefront's rows, this lane's row
+    const bool ok = i < tokens;
+    const float cexp = kScale * kLog2e;
+    const int stages = (tokens + ST * kRows - 1) / (ST * kRows);
+
+    if (keys) {
+        RowOp<T> kf, vf;
+        kf.load(Qb + (long)i * ldq + 64, ok, h);
+        vf.load(Qb + (long)i * ldq + 128, ok, h);
+        f32x16 dk[2] = {zero16(), zero16()}, dv[2] = {zero16(), zero16()};
+        Stream<T> sq, sd, so;
+        sq.init(Qb, ldq, tokens);
+        sd.init(dOb, ld_do, tokens);
+        so.init(Ob, ldo, tokens);
+        float l = 0.f;
+        auto fetch = [&](int s) {
+            sq.fetch(s * ST * kRows);
+            sd.fetch(s * ST * kRows);
+            so.fetch(s * ST * kRows);
+            if (threadIdx.x < ST * kRows) {
+                const int q = s * ST * kRows + threadIdx.x;
+                l = q < tokens ? lse_b[q] * kLog2e : INFINITY;   // a query past the last token: P = 0
+            }
+        };
+        auto store = [&](int buf) {
+            sq.store(lds[buf][0]);
+            sd.store(lds[buf][1]);
+            if (threadIdx.x < ST * kRows) consts[buf][0][threadIdx.x] = l;
+            // delta of the rows this thread holds a piece of: the lanes of a row are neighbours
+#pragma unroll
+            for (int k = 0; k < Stream<T>::kPer; ++k) {
+                float dl = 0.f;
+                if constexpr (sizeof(T) == 2) {
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) {
+                        dl = fmaf(__uint_as_float(sd.v[k][x] << 16), __uint_as_float(so.v[k][x] << 16), dl);
+                        dl = fmaf(__uint_as_float(sd.v[k][x] & 0xffff0000u), __uint_as_float(so.v[k][x] & 0xffff0000u), dl);
+                    }
+                } else {
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) dl = fmaf(__uint_as_float(sd.v[k][x]), __uint_as_float(so.v[k][x]), dl);
+                }
+#pragma unroll
+                for (int w = 1; w < Tile<T>::kPieces; w <<= 1) dl += __shfl_xor(dl, w, 64);
+                if (threadIdx.x % Tile<T>::kPieces == 0) consts[buf][1][threadIdx.x / Tile<T>::kPieces + k * Stream<T>::kStep] = dl;
+            }
+        };
+        fetch(0);
+        store(0);
+        for (int s = 0; s < stages; ++s) {
+            if (s + 1 < stages) fetch(s + 1);
+            __syncthreads();
+            if (i0 < tokens) {
+#pragma unroll
+                for (int u = 0; u < ST; ++u) {
+                    const T* Qs = lds[s & 1][0] + u * tile_elems<T>();
+                    const T* dOs = lds[s & 1][1] + u * tile_elems<T>();
+                    f32x16 p = zero16(), dp = zero16();   // element e: query 8*(e/4) + 4h + e%4 of the tile
+                    mma_rows(p, Qs, kf, lane);
+                    mma_rows(dp, dOs, vf, lane);
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const f32x4 lq = *reinterpret_cast<const f32x4*>(&consts[s & 1][0][u * kRows + 8 * g + 4 * h]);
+                        const f32x4 dq = *reinterpret_cast<const f32x4*>(&consts[s & 1][1][u * kRows + 8 * g + 4 * h]);
+#pragma unroll
+                        for (int x = 0; x < 4; ++x) {
+                            p[4 * g + x] = __builtin_amdgcn_exp2f(fmaf(p[4 * g + x], cexp, -lq[x]));
+                            dp[4 * g + x] = p[4 * g + x] * (dp[4 * g + x] - dq[x]);
+                        }
+                    }
+                    mma_tr(dv, dOs, p, lane);
+                    mma_tr(dk, Qs, dp, lane);
+                }
+            }
+            if (s + 1 < stages) store((s + 1) & 1);
+        }
+        if (i0 >= tokens) return;
+        store_row(dk, kScale, dQb + (long)i * ld_dqkv + 64, h, ok);
+        store_row(dv, 1.f, dQb + (long)i * ld_dqkv + 128, h, ok);
+    } else {
+        RowOp<T> qf, df;
+        qf.load(Qb + (long)i * ldq, ok, h);
+        df.load(dOb + (long)i * ld_do, ok, h);
+        float delta;
+        {
+            RowOp<T> of;
+            of.load(Ob + (long)i * ldo, ok, h);
+            delta = RowOp<T>::dot(df, of);
+            delta += __shfl_xor(delta, 32, 64);
+        }
+        const float lq = ok ? lse_b[i] * kLog2e : 0.f;
+        f32x16 dq[2] = {zero16(), zero16()};
+        Stream<T> sk, sv;
+        sk.init(Qb + 64, ldq, tokens);
+        sv.init(Qb + 128, ldq, tokens);
+        sk.fetch(0);
+        sv.fetch(0);
+        sk.store(lds[0][0]);
+        sv.store(lds[0][1]);
+        for (int s = 0; s < stages; ++s) {
+            if (s + 1 < stages) {
+                sk.fetch((s + 1) * ST * kRows);
+                sv.fetch((s + 1) * ST * kRows);
+            }
+            __syncthreads();
+            if (i0 < tokens) {
+#pragma unroll
+                for (int u = 0; u < ST; ++u) {
+                    const T* Ks = lds[s & 1][0] + u * tile_elems<T>();
+                    const T* Vs = lds[s & 1][1] + u * tile_elems<T>();
+                    f32x16 p = zero16(), dp = zero16();   // element e: key 8*(e/4) + 4h + e%4 of the tile
+                    mma_rows(p, Ks, qf, lane);
+                    mma_rows(dp, Vs, df, lane);
+                    if (s + 1 == stages) {   // keys past the last token: P = 0
+                        const int lim = tokens - (s * ST + u) * kRows - 4 * h;
+#pragma unroll
+                        for (int e = 0; e < 16; ++e)
+                            if (8 * (e >> 2) + (e & 3) >= lim) p[e] = -INFINITY;
+                    }
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) dp[e] = __builtin_amdgcn_exp2f(fmaf(p[e], cexp, -lq)) * (dp[e] - delta);
+                    mma_tr(dq, Ks, dp, lane);
+                }
+            }
+            if (s + 1 < stages) {
+                sk.store(lds[(s + 1) & 1][0]);
+                sv.store(lds[(s + 1) & 1][1]);
+            }
+        }
+        if (i0 >= tokens) return;
+        store_row(dq, kScale, dQb + (long)i * ld_dqkv, h, ok);
+    }
+}
+
+inline bool mult8(long v) { return (v & 7) == 0; }
+
+}  // namespace
+
+bool attn_stream_supported(int dtype, int tokens, long ldq, long ldo) {
+    const long es = dtype == D2FT_F32 ? 4 : 2;
+    return tokens >= 1 && mult8(ldq) && mult8(ldo) && (long)(tokens + 63) * (ldq > ldo ? ldq : ldo) * es < (1L << 31);   // 32-bit offsets
+}
+
+hipError_t launch_attn_fwd_stream(int dtype, const void* qkv, long ldq, void* o, long ldo, float* lse, int batch, int tokens,
+                                  int n_live, int n_full, hipStream_t s) {
+    if (n_live <= 0) return hipSuccess;
+    const int blocks = (tokens + kRows * kWaves - 1) / (kRows * kWaves);
+    const dim3 grid((unsigned)((long)batch * n_live * blocks)), block(64 * kWaves);
+    const long rows = (long)batch * tokens;
+    if (dtype == D2FT_F32)
+        hipLaunchKernelGGL(attn_fwd_stream_kernel<float>, grid, block, 0, s, (const float*)qkv, ldq, (float*)o, ldo, lse, tokens,
+                           n_live, n_full, rows, blocks);
+    else
+        hipLaunchKernelGGL(attn_fwd_stream_kernel<bf16>, grid, block, 0, s, (const bf16*)qkv, ldq, (bf16*)o, ldo, lse, tokens,
+                           n_live, n_full, rows, blocks);
+    return hipGetLastError();
+}
+
+template <typename T>
+static hipError_t launch_bwd(const void* qkv, long ldq, const void* o, long ldo, const float* lse, const void* d_o, long ld_do,
+                             void* dqkv, long ld_dqkv, int batch, int tokens, int n_full, hipStream_t s) {
+    const int blocks = (tokens + kRows * kWaves - 1) / (kRows * kWaves);
+    const dim3 grid((unsigned)(2L * batch * n_full * blocks)), block(64 * kWaves);
+    auto kern = attn_bwd_stream_kernel<T>;
+    const T *q = (const T*)qkv, *op = (const T*)o, *dop = (const T*)d_o;
+    T* dq = (T*)dqkv;
+    const long rows = (long)batch * tokens;
+    if (hipEvent_t ev = launch_signal_take())   // the launch completes the event itself
+        hipExtLaunchKernelGGL(kern, grid, block, 0, s, nullptr, ev, 0, q, ldq, op, ldo, lse, dop, ld_do, dq, ld_dqkv, tokens, n_full, rows, blocks);
+    else
+        hipLaunchKernelGGL(kern, grid, block, 0, s, q, ldq, op, ldo, lse, dop, ld_do, dq, ld_dqkv, tokens, n_full, rows, blocks);
+    return hipGetLastError();
+}
+
+hipError_t launch_attn_bwd_stream(int dtype, const void* qkv, long ldq, const void* o, long ldo, const float* lse,
+                                  const void* d_o, long ld_do, void* dqkv, long ld_dqkv, int batch, int tokens, int n_full,
+                                  hipStream_t s) {
+    if (n_full <= 0) return hipSuccess;
+    return dtype == D2FT_F32 ? launch_bwd<float>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, batch, tokens, n_full, s)
+                             : launch_bwd<bf16>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, batch, tokens, n_full, s);
+}
+
+}  // namespace d2ft
