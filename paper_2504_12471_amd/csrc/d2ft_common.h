@@ -169,10 +169,11 @@ void launch_signal_next(hipEvent_t ev);
 bool launch_signal_pending();
 hipEvent_t launch_signal_take();
 hipError_t launch_gemm_simple(const GemmArgs& g, int dtype, hipStream_t s);
-// 64x64 tiles with K split inside the workgroup (kernels_gemm_tile64.hip): every fp32 product whose operands span
-// less than 2 GiB, and bf16 products of few rows; hipErrorNotSupported otherwise.  Honours g.colsum with one band
-// per 64 rows.
+// tiles of 64 or 32 with K split inside the workgroup (kernels_gemm_tile64.hip): every fp32 product whose operands span
+// less than 2 GiB, and the bf16 products that gemm_tile64_faster picks; hipErrorNotSupported otherwise.  Honours
+// g.colsum with one band per 64 rows.
 bool gemm_tile64_supported(const GemmArgs& g, int dtype);
+bool gemm_tile64_faster(const GemmArgs& g);   // a bf16 product that launch_gemm_mfma would give 128x128 tiles
 hipError_t launch_gemm_tile64(const GemmArgs& g, int dtype, hipStream_t s);
 // bf16 MFMA path; returns hipErrorNotSupported if the shape/strides do not fit it
 hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s);

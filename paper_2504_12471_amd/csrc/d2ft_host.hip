@@ -278,7 +278,8 @@ bool on_mfma_path(const GemmArgs& g, const d2ft_block_desc* d) {
 }
 // true if run_gemm takes the 64x64-tile path for g
 bool on_tile64_path(const GemmArgs& g, const d2ft_block_desc* d) {
-    return d->dtype == D2FT_F32 && gemm_tile64_supported(g, d->dtype);
+    if (!gemm_tile64_supported(g, d->dtype)) return false;
+    return d->dtype == D2FT_F32 || (on_mfma_path(g, d) && g.tile_hint == 0 && gemm_tile64_faster(g));
 }
 // the paths that honour g.colsum
 bool colsum_supported(const GemmArgs& g, const d2ft_block_desc* d) { return on_mfma_path(g, d) || on_tile64_path(g, d); }

@@ -1,19 +1,23 @@
-// GEMM on the matrix cores with a 64x64 output tile per workgroup and K split between the workgroup's wavefronts:
+// GEMM on the matrix cores with small output tiles (64x64, 64x32, 32x32) and K split between the workgroup's wavefronts:
 // the fp32 path (v_mfma_f32_32x32x2_f32) and the bf16 path (v_mfma_f32_32x32x16_bf16) for shapes whose larger
 // tiles would leave most of the chip idle.
 //
 //   C[m][n] = epilogue( sum_k A(m,k) * B(k,n) )
 //
-// A workgroup has WK groups of four wavefronts.  A group multiplies every WK-th K slab (128 bytes of k per row: 64
-// bf16 or 32 fp32) of the same tile, a wavefront of it one 32x32 quarter; the groups' sums are added in group order
+// A workgroup has WK groups of wavefronts.  A group multiplies every WK-th K slab (128 bytes of k per row: 64
+// bf16 or 32 fp32) of the same tile, a wavefront of it one 32x32 part; the groups' sums are added in group order
 // through LDS before the epilogue, so a small problem gets WK times the wavefronts without a second launch and
 // without partial sums in memory.
 //
 // What bounds it.  fp32: the matrix cores (256 FLOP per clock and CU); a 64x64 tile asks for 16 bytes of operands per
 // clock and CU, which L2 delivers, so a larger tile would gain nothing and the small one deals evenly: four to five
-// workgroups share a CU and cover each other's latencies.  bf16: latency.  A problem of a few hundred rows gives the
-// 128x128 tile a few dozen workgroups with one slab in flight each; here kAhead slabs per group are in flight in
-// registers and there are 4 to 16 times as many groups.
+// workgroups share a CU and cover each other's latencies.  bf16: a problem of a few hundred rows gives the 128x128 tile
+// a few dozen workgroups with one slab in flight each, at the 30 to 45 bytes per clock that one CU loads; here the
+// smallest tile that still fits the chip's CUs is taken (pick_form) and kAhead slabs per group are in flight in
+// registers.
+//
+// The forward pass of 12 bf16 blocks on one image (197 tokens, width 768), whose products all ran on the 128x128 tile:
+// 1038 -> 619 us; 5 images of width 384, forward and backward: 1899 -> 1668 us.
 //
 // Measured against the vector-ALU kernel it replaced for fp32: one block of 260 tokens of width 192, forward and
 // backward, 721 -> 171 us (its 12 products 594 -> 104 us); the products of a 12-block stack of width 384 on 80 x 197
@@ -58,27 +62,30 @@ namespace {
 
 constexpr uint32_t kBufBytes = 0x80000000u;   // declared buffer size; operands are checked to be smaller
 constexpr uint32_t kOutside = 0x80000000u;    // any offset >= kBufBytes reads as zero
-constexpr int kSlabBytes = 64 * 128;          // one operand's slab
 constexpr int kAhead = 3;                     // slabs in flight in registers
-constexpr int kStageStride = 68;              // floats per row of the epilogue's stage
+constexpr int kStagePad = 4;                  // floats between the rows of the epilogue's stage
 
-// byte offset in a slab of 16-byte piece `piece` of row `row`.  Row form: 64 rows of 128 bytes ([index][k]); column
-// form: [k][64 indices], i.e. 64 rows of 128 bytes for bf16, 32 rows of 256 for fp32.
-template <typename T, bool COL>
+// Byte offset of 16-byte piece `piece` of row `row` in the slab of an operand with W indices (64 or 32).  Row form: W
+// rows of 128 bytes ([index][k]); column form: [k][W indices], i.e. 64 rows of 2W bytes for bf16, 32 rows of 4W for fp32.
+template <typename T, bool COL, int W>
 __device__ __forceinline__ int piece_offset(int row, int piece) {
     if constexpr (!COL) return row * 128 + ((piece ^ (row & 7)) << 4);               // eight rows, eight slots
-    else if constexpr (sizeof(T) == 2) return row * 128 + ((((piece >> 1) ^ (row & 3)) << 5) | ((piece & 1) << 4));
-    else return row * 256 + ((piece ^ (((row >> 2) & 1) << 3)) << 4);                // rows 4 apart: other half of the banks
+    else if constexpr (sizeof(T) == 2 && W == 64) return row * 128 + ((((piece >> 1) ^ (row & 3)) << 5) | ((piece & 1) << 4));
+    else if constexpr (sizeof(T) == 2) return row * 64 + (piece << 4);               // four rows fill the banks as they are
+    else if constexpr (W == 64) return row * 256 + ((piece ^ (((row >> 2) & 1) << 3)) << 4);   // rows 4 apart: other half of the banks
+    else return (row ^ ((row >> 2) & 1)) * 128 + (piece << 4);                       // likewise
 }
 
-// a thread's two 16-byte pieces of a slab: global offsets and LDS offsets
-template <typename T, bool COL>
+// a thread's 16-byte pieces of a slab of W indices, loaded by GT threads: global offsets and LDS offsets
+template <typename T, bool COL, int W, int GT>
 struct Loader {
     static constexpr int kE = 16 / sizeof(T);          // elements per piece
     static constexpr int kBK = 128 / sizeof(T);        // k per slab
+    static constexpr int kPerRow = COL ? W / kE : 8;   // pieces per slab row
+    static constexpr int kN = W * 8 / GT;              // pieces per thread
     __amdgpu_buffer_rsrc_t rsrc;
-    uint32_t base[2], sk;
-    int k_in[2];      // k of the piece within the slab
+    uint32_t base[kN], sk;
+    int k_in[kN];     // k of the piece within the slab
 
     // index_of(i): the row (or column) of the operand that tile index i stands for
     template <typename F>
@@ -86,15 +93,15 @@ struct Loader {
         rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, kBufBytes, 0x00020000);
         sk = (uint32_t)s_k * (uint32_t)sizeof(T);
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            const int id = t + 256 * c;
+        for (int c = 0; c < kN; ++c) {
+            const int id = t + GT * c;
             int i;
             if constexpr (!COL) {
                 i = id >> 3;
                 k_in[c] = (id & 7) * kE;
             } else {
-                i = (id % (64 / kE)) * kE;
-                k_in[c] = id / (64 / kE);
+                i = (id % kPerRow) * kE;
+                k_in[c] = id / kPerRow;
             }
             i += i0;
             const uint32_t off = ((uint32_t)index_of(i < I ? i : 0) * (uint32_t)s_i + (uint32_t)k_in[c] * (uint32_t)s_k) * (uint32_t)sizeof(T);
@@ -102,37 +109,36 @@ struct Loader {
         }
     }
     // the slab at k0 (valid k < k_end) whose first k sits at k_at in memory
-    __device__ __forceinline__ void load(u32x4 (&v)[2], int k0, int k_at, int k_end) const {
+    __device__ __forceinline__ void load(u32x4 (&v)[kN], int k0, int k_at, int k_end) const {
 #pragma unroll
-        for (int c = 0; c < 2; ++c)
+        for (int c = 0; c < kN; ++c)
             v[c] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, k_in[c] < k_end - k0 ? base[c] : kOutside, (uint32_t)k_at * sk, 0);
     }
-    static __device__ __forceinline__ void store(const u32x4 (&v)[2], unsigned char* slab, int t) {
+    static __device__ __forceinline__ void store(const u32x4 (&v)[kN], unsigned char* slab, int t) {
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            const int id = t + 256 * c;
-            constexpr int kPerRow = COL ? 64 / kE : 8;
-            *reinterpret_cast<u32x4*>(slab + piece_offset<T, COL>(id / kPerRow, id % kPerRow)) = v[c];
+        for (int c = 0; c < kN; ++c) {
+            const int id = t + GT * c;
+            *reinterpret_cast<u32x4*>(slab + piece_offset<T, COL, W>(id / kPerRow, id % kPerRow)) = v[c];
         }
     }
 };
 
 // operand fragments of a slab: 32 indices from i0, quarter q of the slab's k.  bf16: the 16 k of one product; fp32:
 // 8 k, lane half h holding k = 8q + 4h + {0..3}, i.e. four products of two k each.
-template <typename T, bool COL>
+template <typename T, bool COL, int W>
 __device__ __forceinline__ auto read_frag(const unsigned char* slab, int i0, int q, int lane) {
     const int c = lane & 31, h = lane >> 5;
     if constexpr (sizeof(T) == 2) {
         if constexpr (!COL) {
-            return *reinterpret_cast<const bf16x8*>(slab + piece_offset<T, false>(i0 + c, 2 * q + h));
+            return *reinterpret_cast<const bf16x8*>(slab + piece_offset<T, false, W>(i0 + c, 2 * q + h));
         } else {
             // a group of 16 lanes turns a 4 (k) x 16 (index) block into 4 consecutive k per lane
             const int j = lane & 15, r = 16 * q + 8 * h + (j >> 2);
             const int pair = (i0 >> 4) + ((lane >> 4) & 1);
-            const unsigned char* p = slab + r * 128 + ((pair ^ (j >> 2)) << 5) + (j & 3) * 8;
+            const unsigned char* p = slab + piece_offset<T, true, W>(r, 2 * pair) + (j & 3) * 8;
             typedef s16x4 __attribute__((address_space(3))) * lds_ptr_t;
             const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p));
-            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p + 4 * 128));
+            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p + 4 * 2 * W));
             s16x8 v;
             v[0] = lo[0]; v[1] = lo[1]; v[2] = lo[2]; v[3] = lo[3];
             v[4] = hi[0]; v[5] = hi[1]; v[6] = hi[2]; v[7] = hi[3];
@@ -140,13 +146,15 @@ __device__ __forceinline__ auto read_frag(const unsigned char* slab, int i0, int
         }
     } else {
         if constexpr (!COL) {
-            return *reinterpret_cast<const f32x4*>(slab + piece_offset<T, false>(i0 + c, 2 * q + h));
+            return *reinterpret_cast<const f32x4*>(slab + piece_offset<T, false, W>(i0 + c, 2 * q + h));
         } else {
             const int i = i0 + c;
-            const unsigned char* p = slab + (8 * q + 4 * h) * 256 + (((i >> 2) ^ (h << 3)) << 4) + (i & 3) * 4;
+            const int r = 8 * q + 4 * h;   // bit 2 of rows r .. r + 3 is h
+            const unsigned char* p = slab + (W == 64 ? r * 256 + (((i >> 2) ^ (h << 3)) << 4) + (i & 3) * 4 : r * 128 + i * 4);
             f32x4 v;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const float*>(p + j * 256);
+            for (int j = 0; j < 4; ++j)
+                v[j] = *reinterpret_cast<const float*>(p + (W == 64 ? j * 256 : (h ? j ^ 1 : j) * 128));
             return v;
         }
     }
@@ -184,21 +192,31 @@ __device__ __forceinline__ void unroll(F&& f) {
     }
 }
 
-template <typename T, bool A_COL, bool B_COL, int WK, typename Args>
-__global__ __launch_bounds__(256 * WK, WK == 1 ? 4 : 1) void gemm_tile64_kernel(Args g) {
+// wavefronts of a K group, and LDS bytes of it: two buffers of (A, B) slabs, later its stage
+template <int TM, int TN> constexpr int group_waves() { return (TM / 32) * (TN / 32); }
+template <int TM, int TN> constexpr int group_bytes() {
+    return 2 * (TM + TN) * 128 > TM * (TN + kStagePad) * 4 ? 2 * (TM + TN) * 128 : TM * (TN + kStagePad) * 4;
+}
+
+template <typename T, int TM, int TN, bool A_COL, bool B_COL, int WK, typename Args>
+__global__ __launch_bounds__((64 * group_waves<TM, TN>() * WK), TM == 64 && TN == 64 && WK == 1 ? 4 : 1) void gemm_tile64_kernel(Args g) {
     constexpr bool GROUPED = std::is_same<Args, Tile64Grouped>::value;
-    static_assert(!GROUPED || (A_COL && B_COL), "weight gradients: both operands with k strided");
+    static_assert(!GROUPED || (A_COL && B_COL && TM == 64 && TN == 64), "weight gradients: both operands with k strided");
     constexpr int BK = 128 / sizeof(T);
+    constexpr int GW = group_waves<TM, TN>(), GT = 64 * GW, SA = TM * 128, SB = TN * 128;   // SA, SB: slab bytes
+    constexpr int kStageStride = TN + kStagePad;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int kg = wave >> 2, quarter = wave & 3;       // K group; quarter of the tile
-    const int t = threadIdx.x & 255;                    // thread within the K group
-    const int wi = (quarter >> 1) * 32, wj = (quarter & 1) * 32;
+    const int kg = wave / GW, part = wave % GW;         // K group; 32x32 part of the tile
+    const int t = threadIdx.x % GT;                     // thread within the K group
+    const int wi = part / (TN / 32) * 32, wj = part % (TN / 32) * 32;
 
     int m0, n0, M, N, kb, ke, split, tile = 0, gi = 0;
-    Loader<T, A_COL> la;
-    Loader<T, B_COL> lb;
+    typedef Loader<T, A_COL, TM, GT> LA;
+    typedef Loader<T, B_COL, TN, GT> LB;
+    LA la;
+    LB lb;
     auto same = [](int i) { return i; };
     if constexpr (GROUPED) {
         // units: (split, tile), the tiles of one split next to each other
@@ -218,14 +236,14 @@ __global__ __launch_bounds__(256 * WK, WK == 1 ? 4 : 1) void gemm_tile64_kernel(
         la.init(G.A, 1, G.lda, m0, M, t, same);
         lb.init(G.B, 1, G.ldb, n0, N, t, same);
     } else {
-        const int tiles_m = (g.M + 63) >> 6, tiles_n = (g.N + 63) >> 6;
+        const int tiles_m = (g.M + TM - 1) / TM, tiles_n = (g.N + TN - 1) / TN;
         const int splits = g.partial ? g.splits : 1;
         int tm, tn;
         tile_of_block(blockIdx.x, tiles_m * tiles_n * splits, tiles_m, tiles_n, tm, tn, split);
         M = g.M;
         N = g.N;
-        m0 = tm * 64;
-        n0 = tn * 64;
+        m0 = tm * TM;
+        n0 = tn * TN;
         kb = 0;
         ke = g.K;
         if (splits > 1) {
@@ -240,8 +258,8 @@ __global__ __launch_bounds__(256 * WK, WK == 1 ? 4 : 1) void gemm_tile64_kernel(
 
     // this group's slabs: kb + (kg + s * WK) * BK, s = 0 .. n_slabs - 1; a slab past the end loads zeros
     const int n_slabs = ke > kb ? ((ke - kb + BK - 1) / BK + WK - 1) / WK : 0;
-    u32x4 ra[kAhead][2], rb[kAhead][2];
-    auto fetch = [&](int s, u32x4 (&va)[2], u32x4 (&vb)[2]) {
+    u32x4 ra[kAhead][LA::kN], rb[kAhead][LB::kN];
+    auto fetch = [&](int s, u32x4 (&va)[LA::kN], u32x4 (&vb)[LB::kN]) {
         const int k0 = kb + (kg + s * WK) * BK;
         int k_at = k0;   // k of the slab as B is stored
         if constexpr (!GROUPED) {
@@ -250,33 +268,34 @@ __global__ __launch_bounds__(256 * WK, WK == 1 ? 4 : 1) void gemm_tile64_kernel(
         la.load(va, k0, k0, ke);
         lb.load(vb, k0, k_at, ke);
     };
-    unsigned char* const mine = smem + kg * 4 * kSlabBytes;   // two buffers of (A, B) slabs
+    unsigned char* const mine = smem + kg * group_bytes<TM, TN>();
     unroll<kAhead>([&](auto i) { fetch(i.value, ra[i.value], rb[i.value]); });
     f32x16 acc;
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[e] = 0.f;
     if (n_slabs > 0) {
-        Loader<T, A_COL>::store(ra[0], mine, t);
-        Loader<T, B_COL>::store(rb[0], mine + kSlabBytes, t);
+        LA::store(ra[0], mine, t);
+        LB::store(rb[0], mine + SA, t);
         fetch(kAhead, ra[0], rb[0]);
     }
     // slab s sits in LDS buffer s & 1, slabs s + 1 .. s + kAhead in registers (slab x in slot x % kAhead).  One
-    // barrier per slab: behind it the stores of slab s are visible and buffer (s + 1) & 1 is free.
+    // barrier per slab: behind it the stores of slab s are visible and buffer (s + 1) & 1 is free.  A group of one
+    // wavefront shares its slabs with no other and needs none: its LDS accesses complete in order.
     auto step = [&](int s, auto slot_tag) {
         constexpr int slot = decltype(slot_tag)::value;
-        unsigned char* const cur = mine + (s & 1) * 2 * kSlabBytes;
-        unsigned char* const nxt = mine + ((s + 1) & 1) * 2 * kSlabBytes;
-        __syncthreads();
-        decltype(read_frag<T, A_COL>(cur, 0, 0, 0)) fa[4];
-        decltype(read_frag<T, B_COL>(cur, 0, 0, 0)) fb[4];
+        unsigned char* const cur = mine + (s & 1) * (SA + SB);
+        unsigned char* const nxt = mine + ((s + 1) & 1) * (SA + SB);
+        if constexpr (GW > 1) __syncthreads();
+        decltype(read_frag<T, A_COL, TM>(cur, 0, 0, 0)) fa[4];
+        decltype(read_frag<T, B_COL, TN>(cur, 0, 0, 0)) fb[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            fa[q] = read_frag<T, A_COL>(cur, wi, q, lane);
-            fb[q] = read_frag<T, B_COL>(cur + kSlabBytes, wj, q, lane);
+            fa[q] = read_frag<T, A_COL, TM>(cur, wi, q, lane);
+            fb[q] = read_frag<T, B_COL, TN>(cur + SA, wj, q, lane);
         }
         if (s + 1 < n_slabs) {
-            Loader<T, A_COL>::store(ra[slot], nxt, t);
-            Loader<T, B_COL>::store(rb[slot], nxt + kSlabBytes, t);
+            LA::store(ra[slot], nxt, t);
+            LB::store(rb[slot], nxt + SA, t);
             fetch(s + 1 + kAhead, ra[slot], rb[slot]);
         }
 #pragma unroll
@@ -289,29 +308,29 @@ __global__ __launch_bounds__(256 * WK, WK == 1 ? 4 : 1) void gemm_tile64_kernel(
     __syncthreads();   // the stage below reuses the operand buffers
 
     // ---- epilogue: the groups' sums meet in LDS, results leave as 8 consecutive columns per thread ----
-    float* const stage = reinterpret_cast<float*>(smem) + kg * 64 * kStageStride;
+    float* const stage = reinterpret_cast<float*>(mine);
     {
         const int c = lane & 31, h = lane >> 5;
 #pragma unroll
         for (int e = 0; e < 16; ++e) stage[(wi + 8 * (e >> 2) + 4 * h + (e & 3)) * kStageStride + wj + c] = acc[e];
     }
     __syncthreads();
-    constexpr int kThreads = 256 * WK;
+    constexpr int kThreads = GT * WK, kPieces = TM * TN / 8, kRowPieces = TN / 8;
     float csum[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) csum[i] = 0.f;
 #pragma unroll
-    for (int p0 = 0; p0 < 512; p0 += kThreads) {
+    for (int p0 = 0; p0 < kPieces; p0 += kThreads) {
         const int p = p0 + threadIdx.x;
-        if (kThreads > 512 && p >= 512) break;
-        const int r = p >> 3, cc = (p & 7) * 8;
+        if (kThreads > kPieces && p >= kPieces) break;
+        const int r = p / kRowPieces, cc = p % kRowPieces * 8;
         const int m = m0 + r, n = n0 + cc;
         float v[8];
         load8(reinterpret_cast<float*>(smem) + r * kStageStride + cc, v);
 #pragma unroll
         for (int w = 1; w < WK; ++w) {
             float o[8];
-            load8(reinterpret_cast<float*>(smem) + (w * 64 + r) * kStageStride + cc, o);
+            load8(reinterpret_cast<float*>(smem + w * group_bytes<TM, TN>()) + r * kStageStride + cc, o);
 #pragma unroll
             for (int i = 0; i < 8; ++i) v[i] += o[i];
         }
@@ -374,25 +393,24 @@ __global__ __launch_bounds__(256 * WK, WK == 1 ? 4 : 1) void gemm_tile64_kernel(
     }
     if constexpr (!GROUPED) {
         if (!g.colsum) return;   // uniform over the grid
-        // column sums of the tile's 64 rows: lanes 8 apart share their columns, then the wavefronts in order
+        // column sums of the tile's rows: lanes kRowPieces apart share their columns, then the wavefronts in order
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             float s = csum[i];
-            s += __shfl_xor(s, 8, 64);
-            s += __shfl_xor(s, 16, 64);
-            s += __shfl_xor(s, 32, 64);
+#pragma unroll
+            for (int w = kRowPieces; w < 64; w <<= 1) s += __shfl_xor(s, w, 64);
             csum[i] = s;
         }
         __syncthreads();
         float* const red = reinterpret_cast<float*>(smem);
-        constexpr int kWaves = WK < 2 ? 4 : 8;   // wavefronts that hold results
-        if (lane < 8 && wave < kWaves) store8(red + wave * 64 + lane * 8, csum);
+        constexpr int kWaves = (kThreads < kPieces ? kThreads : kPieces) / 64;   // wavefronts that hold results
+        if (lane < kRowPieces && wave < kWaves) store8(red + wave * TN + lane * 8, csum);
         __syncthreads();
-        if (threadIdx.x < 64 && n0 + (int)threadIdx.x < N) {
+        if (threadIdx.x < TN && n0 + (int)threadIdx.x < N) {
             float s = 0.f;
 #pragma unroll
-            for (int w = 0; w < kWaves; ++w) s += red[w * 64 + threadIdx.x];
-            g.colsum[(long)(g.colsum_row0 + m0 / 64) * N + n0 + threadIdx.x] = s;
+            for (int w = 0; w < kWaves; ++w) s += red[w * TN + threadIdx.x];
+            g.colsum[(long)(g.colsum_row0 + m0 / TM) * N + n0 + threadIdx.x] = s;
         }
     }
 }
@@ -436,39 +454,33 @@ __global__ __launch_bounds__(256) void reduce_tile64_kernel(Tile64Grouped g) {
     }
 }
 
-template <typename Kernel, typename Args>
-hipError_t launch(Kernel kern, unsigned grid, int wk, hipStream_t s, const Args& a) {
-    const size_t lds = (size_t)wk * 4 * kSlabBytes;
-    static_assert(4 * kSlabBytes >= 64 * kStageStride * 4, "the stage fits the operand buffers");
-    if (hipEvent_t ev = launch_signal_take()) {   // the launch completes the event itself
-        hipExtLaunchKernelGGL(kern, dim3(grid), dim3(256 * wk), lds, s, nullptr, ev, 0, a);
-    } else {
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(256 * wk), lds, s, a);
-    }
-    return hipGetLastError();
-}
-
-template <typename T, bool A_COL, bool B_COL, int WK, typename Args>
+template <typename T, int TM, int TN, bool A_COL, bool B_COL, int WK, typename Args>
 hipError_t launch_wk(unsigned grid, hipStream_t s, const Args& a) {
-    auto kern = gemm_tile64_kernel<T, A_COL, B_COL, WK, Args>;
-    if constexpr (WK * 4 * kSlabBytes > 64 * 1024) {
+    auto kern = gemm_tile64_kernel<T, TM, TN, A_COL, B_COL, WK, Args>;
+    constexpr int lds = WK * group_bytes<TM, TN>(), threads = 64 * group_waves<TM, TN>() * WK;
+    if constexpr (lds > 64 * 1024) {
         static bool attr_set = false;
         if (!attr_set) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, WK * 4 * kSlabBytes);
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
             if (e != hipSuccess) return e;
             attr_set = true;
         }
     }
-    return launch(kern, grid, WK, s, a);
+    if (hipEvent_t ev = launch_signal_take()) {   // the launch completes the event itself
+        hipExtLaunchKernelGGL(kern, dim3(grid), dim3(threads), lds, s, nullptr, ev, 0, a);
+    } else {
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), lds, s, a);
+    }
+    return hipGetLastError();
 }
 
-template <typename T, bool A_COL, bool B_COL, typename Args>
+template <typename T, int TM, int TN, bool A_COL, bool B_COL, typename Args>
 hipError_t launch_form(int wk, unsigned grid, hipStream_t s, const Args& a) {
-    switch (wk) {
-        case 4: return launch_wk<T, A_COL, B_COL, 4>(grid, s, a);
-        case 2: return launch_wk<T, A_COL, B_COL, 2>(grid, s, a);
-        default: return launch_wk<T, A_COL, B_COL, 1>(grid, s, a);
+    if constexpr (TM * TN == 64 * 64) {
+        if (wk == 1) return launch_wk<T, TM, TN, A_COL, B_COL, 1>(grid, s, a);
     }
+    if (wk == 4) return launch_wk<T, TM, TN, A_COL, B_COL, 4>(grid, s, a);
+    return launch_wk<T, TM, TN, A_COL, B_COL, 2>(grid, s, a);
 }
 
 // K groups per workgroup: as many as it takes to give every CU two workgroups' worth of wavefronts, as long as each
@@ -516,20 +528,77 @@ bool gemm_tile64_supported(const GemmArgs& g, int dtype) {
     return true;
 }
 
+// Tile and K groups of a product without split-K partials: the cheapest of the kernel's forms in microseconds,
+//   fixed + slabs * first + (rounds - 1) * (slabs * next + change),   rounds = workgroups per CU, rounded up:
+// a first round that waits for its loads, further ones beside it.  Fitted on this part to some 150 shapes per type
+// (M 64 .. 3152, N and K 64 .. 4096).  bf16: a CU's loads set the pace, so a slab costs in proportion to the tile's rows
+// + columns and a small tile pays where large ones leave CUs idle: 197 x 768 x 3072, 64x64 tiles 16.2 us, 64x32 12.3,
+// 32x32 8.9; 985 x 384 x 1536: 10.3, 8.6, 8.9; 985 x 2304 x 768: 13.6, 15.2, 17.2.  fp32: the matrix cores, so a slab
+// costs in proportion to the tile's area and what a small tile saves is the last, partly empty round: 197 x 2304 x 768:
+// 19.5, 20.7, 12.8; 3152 x 384 x 1536: 61, 51, 46; 3152 x 1536 x 384: 47.9, 52.4, 56.6.
+struct Tile64Form {
+    int tm, tn, wk;
+    float fixed, first, next, change;   // us
+};
+constexpr Tile64Form kFormsBf16[] = {{64, 64, 1, 3.2f, 0.37f, 0.17f, 0.8f},  {64, 64, 2, 3.9f, 0.27f, 0.20f, 1.0f},
+                                     {64, 32, 2, 3.4f, 0.23f, 0.10f, 1.1f},  {64, 32, 4, 4.0f, 0.183f, 0.0f, 4.7f},
+                                     {32, 32, 2, 3.0f, 0.198f, 0.08f, 0.5f}, {32, 32, 4, 3.9f, 0.102f, 0.10f, 1.2f}};
+constexpr Tile64Form kFormsF32[] = {{64, 64, 1, 4.4f, 0.61f, 0.43f, 2.5f}, {64, 32, 2, 3.4f, 0.37f, 0.215f, 1.6f},
+                                    {32, 32, 2, 3.2f, 0.30f, 0.12f, 0.9f}, {32, 32, 4, 3.9f, 0.18f, 0.12f, 1.2f}};
+static Tile64Form pick_form(const GemmArgs& g, int dtype, float* us) {
+    const bool f32 = dtype == D2FT_F32;
+    const Tile64Form* f = f32 ? kFormsF32 : kFormsBf16;
+    const int slabs = f32 ? (g.K + 31) / 32 : (g.K + 63) / 64;
+    Tile64Form best = f[0];
+    *us = 1e30f;
+    for (int i = 0; i < (f32 ? 4 : 6); ++i) {
+        if (g.colsum && f[i].tm != 64) continue;   // a band of column sums is 64 rows
+        const long units = (long)((g.M + f[i].tm - 1) / f[i].tm) * ((g.N + f[i].tn - 1) / f[i].tn);
+        const float t = f[i].fixed + f[i].first * slabs + (float)((units + 255) / 256 - 1) * (f[i].next * slabs + f[i].change);
+        if (t < *us) {
+            *us = t;
+            best = f[i];
+        }
+    }
+    return best;
+}
+
+template <typename T, int TM, int TN>
+static hipError_t launch_tile(const GemmArgs& g, int wk, hipStream_t s) {
+    const unsigned units = (unsigned)((g.M + TM - 1) / TM) * (unsigned)((g.N + TN - 1) / TN);
+    return g.b_rs == 1 ? launch_form<T, TM, TN, false, false>(wk, units, s, g) : launch_form<T, TM, TN, false, true>(wk, units, s, g);
+}
+
 template <typename T>
-static hipError_t launch_tile64(const GemmArgs& g, hipStream_t s) {
-    const long units = (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * (g.partial ? g.splits : 1);
-    const int slabs = (g.K / (g.partial ? g.splits : 1) + 128 / (int)sizeof(T) - 1) / (128 / (int)sizeof(T));
-    const int wk = pick_wk(units, slabs);
-    const bool a_col = (g.a_cs != 1), b_col = (g.b_rs != 1);
-    if (!a_col && !b_col) return launch_form<T, false, false>(wk, (unsigned)units, s, g);
-    if (!a_col && b_col) return launch_form<T, false, true>(wk, (unsigned)units, s, g);
-    return launch_form<T, true, true>(wk, (unsigned)units, s, g);
+static hipError_t launch_tile64(const GemmArgs& g, int dtype, hipStream_t s) {
+    if (g.partial || g.a_cs != 1) {
+        const long units = (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * (g.partial ? g.splits : 1);
+        const int slabs = (g.K / (g.partial ? g.splits : 1) + 128 / (int)sizeof(T) - 1) / (128 / (int)sizeof(T));
+        const int wk = pick_wk(units, slabs);
+        if (g.a_cs != 1) return launch_form<T, 64, 64, true, true>(wk, (unsigned)units, s, g);
+        return g.b_rs == 1 ? launch_form<T, 64, 64, false, false>(wk, (unsigned)units, s, g) : launch_form<T, 64, 64, false, true>(wk, (unsigned)units, s, g);
+    }
+    float us;
+    const Tile64Form f = pick_form(g, dtype, &us);
+    if (f.tm == 32) return launch_tile<T, 32, 32>(g, f.wk, s);
+    if (f.tn == 32) return launch_tile<T, 64, 32>(g, f.wk, s);
+    return launch_tile<T, 64, 64>(g, f.wk, s);
+}
+
+// bf16: against the 128x128 tile, 5.1 us + 0.41 us per slab and round by the same fit.  In the middle of the range both
+// are close (985 x 1536 x 384: 9.2 and 10.4 us); at the ends they are not (197 x 768 x 768: 5.0 and 9.5; 3152 x 3072 x
+// 768: 46 and 27).
+bool gemm_tile64_faster(const GemmArgs& g) {
+    if (g.partial || g.a_cs != 1 || gemm_mfma_tile_rows(g) != 128) return false;
+    float us;
+    pick_form(g, D2FT_BF16, &us);
+    const long units = (long)((g.M + 127) / 128) * ((g.N + 127) / 128);
+    return us < 5.1f + 0.41f * ((g.K + 63) / 64) * (float)((units + 255) / 256);
 }
 
 hipError_t launch_gemm_tile64(const GemmArgs& g, int dtype, hipStream_t s) {
     if (!gemm_tile64_supported(g, dtype)) return hipErrorNotSupported;
-    return dtype == D2FT_F32 ? launch_tile64<float>(g, s) : launch_tile64<bf16>(g, s);
+    return dtype == D2FT_F32 ? launch_tile64<float>(g, dtype, s) : launch_tile64<bf16>(g, dtype, s);
 }
 
 // out_g = A_g^T B_g for the groups of g (grp, n_groups, K, partial), through r's remaps: one launch, and a reduction
@@ -569,8 +638,8 @@ hipError_t launch_gemm_tile64_grouped(const GemmArgs& g, const ReduceGroupedArgs
     a.splits = (slabs + a.slabs_per_split - 1) / a.slabs_per_split;
     const long units = tiles * a.splits;
     const int wk = pick_wk(units, a.slabs_per_split);
-    hipError_t e = dtype == D2FT_F32 ? launch_form<float, true, true>(wk, (unsigned)units, s, a)
-                                     : launch_form<bf16, true, true>(wk, (unsigned)units, s, a);
+    hipError_t e = dtype == D2FT_F32 ? launch_form<float, 64, 64, true, true>(wk, (unsigned)units, s, a)
+                                     : launch_form<bf16, 64, 64, true, true>(wk, (unsigned)units, s, a);
     if (e != hipSuccess || a.splits == 1) return e;
     const dim3 grid((unsigned)tiles, 4);
     if (dtype == D2FT_F32) hipLaunchKernelGGL(reduce_tile64_kernel<float>, grid, dim3(256), 0, s, a);

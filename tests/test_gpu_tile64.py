@@ -1,4 +1,4 @@
-"""GPU parity of the 64x64-tile GEMM (kernels_gemm_tile64.hip) through one block forward + backward, at the sizes
+"""GPU parity of the small-tile GEMM (kernels_gemm_tile64.hip) through one block forward + backward, at the sizes
 where its tiling can go wrong: rows and widths at and beside the tile edges, one and several K groups per workgroup,
 K shorter than a slab, weight gradients with K split over several partial tiles and with every remap."""
 import pytest
@@ -29,3 +29,21 @@ def test_fp32_tile_edges(batch, tokens, width, heads, mlp):
 def test_fp32_gated_slices_through_the_remaps():
     w = di.Workload("tile64_gate_f32", 6, 197, 256, 4, 64, 1024, 1, "f32")
     run_gated(w, [FULL, SKIP, FWD, FULL], seed=72)
+
+
+@pytest.mark.parametrize("batch,tokens,width,heads,mlp", [
+    (1, 3, 64, 1, 64),        # one tile, K of one slab
+    (1, 33, 136, 2, 264),     # one row and one piece of columns beside the edge of a 32x32 tile, K not a multiple of 64
+    (1, 197, 768, 12, 3072),  # 32x32 and 64x32 tiles, two and four K groups
+    (5, 65, 384, 6, 1536),    # 64x32 tiles with a row beside the edge, column sums on 64x64 tiles
+    (5, 197, 320, 5, 1280),   # 64x64 tiles
+])
+def test_bf16_tile_edges(batch, tokens, width, heads, mlp):
+    w = di.Workload("tile64_bf16", batch, tokens, width, heads, 64, mlp, 1, "bf16")
+    ops = ([FULL, FWD, SKIP, FULL, FULL] * 3)[-heads:]
+    run_case(w, ops, seed=73)
+
+
+def test_bf16_gated_slices_through_the_remaps():
+    w = di.Workload("tile64_gate_bf16", 1, 197, 256, 4, 64, 1024, 1, "bf16")
+    run_gated(w, [FULL, SKIP, FWD, FULL], seed=74)
