@@ -207,9 +207,11 @@ struct ReduceGroupedArgs {
 };
 hipError_t launch_reduce_grouped(int dtype, const GemmArgs& g, const ReduceGroupedArgs& r, int accumulate, hipStream_t s);
 // the weight gradients of g.grp over the same K on 64x64 tiles, written through r (with a reduction of its own if it
-// splits K): takes g.n_groups, grp[].{A, B, lda, ldb, M, N}, K and partial (partial_floats long)
+// splits K): takes g.n_groups, grp[].{A, B, lda, ldb, M, N}, K and partial (partial_floats long); tail, if given, rides
+// along
+struct TailJobs;
 hipError_t launch_gemm_tile64_grouped(const GemmArgs& g, const ReduceGroupedArgs& r, int dtype, int accumulate,
-                                      size_t partial_floats, hipStream_t s);
+                                      size_t partial_floats, TailJobs* tail, hipStream_t s);
 // rows of the output tile launch_gemm_mfma would pick (a tile makes two bands of g.colsum)
 int gemm_mfma_tile_rows(const GemmArgs& g);
 // static string naming the kernel instantiation launch_gemm_mfma would pick (for timing records)
@@ -267,8 +269,8 @@ hipError_t launch_classifier(int dtype, const void* tokens, const void* ln_g, co
                              float* logits, float* dl, float* loss_b, float* dh, void* dtokens, void* g_w_c, void* g_b_c,
                              void* g_ln_g, void* g_ln_b, float* loss, int accumulate, hipStream_t s);
 
-// several independent column reductions out[c] = sum over chunks of partial[chunk][c] in one launch
-// (the bias gradients of one block); remap_cols = 1 or 2 sends column c to tbl_a(c) or tbl_b(c)
+// several independent column reductions out[c] = sum over chunks of partial[chunk][c]
+// (the bias gradients of one block); remap_cols = 1 or 2 sends column c through table a or b
 struct ColReduceJob {
     const float* partial;
     void* out;
@@ -278,21 +280,24 @@ struct ColReduceBatch {
     ColReduceJob job[4];
     int n;
 };
-hipError_t launch_col_reduce_batch(int dtype, const ColReduceBatch& batch, const Remap64& tbl_a, const Remap64& tbl_b,
-                                   int accumulate, hipStream_t s);
-
-
 struct HeadList {
     int32_t n;
     uint8_t h[D2FT_MAX_HEADS];
 };
-// write +0.0 to every gradient slice of the listed heads (null pointers are skipped)
-hipError_t launch_zero_head_slices(int dtype, const HeadList& heads, int H, int D, int r, void* g_wqkv, void* g_bqkv,
-                                   void* g_wo, void* g_la_q, void* g_la_v, void* g_lb_q, void* g_lb_v,
-                                   hipStream_t s);
-// +0.0 into the feed-forward gradient slices (w1 rows, b1, w2 columns) of the listed heads; slice = Dm / H
-hipError_t launch_zero_ffn_slices(int dtype, const HeadList& heads, int slice, int D, int Dm, void* g_w1, void* g_b1,
-                                  void* g_w2, hipStream_t s);
+// What ends a backward call, as workgroups of one launch: the column reductions of red and +0.0 into the gradient
+// slices of the heads listed in zero (w_qkv rows, b_qkv, w_o columns, the adapters; with slice > 0 also their
+// feed-forward slices: w1 rows, b1, w2 columns; null pointers are skipped).  A launch of its own (launch_tail) or a
+// rider on the call's grouped weight-gradient launch (launch_gemm_tile64_grouped).
+struct TailJobs {
+    ColReduceBatch red;
+    HeadList zero;
+    int H, D, r, slice, Dm, accumulate;
+    void *w_qkv, *b_qkv, *w_o, *la_q, *la_v, *lb_q, *lb_v, *w1, *b1, *w2;
+    uint16_t tbl[2][kMaxBlocks64];   // remap tables a and b of red in units of 64
+    int red_blocks, blocks;          // filled by tail_blocks: workgroups of red, and all
+};
+void tail_blocks(TailJobs* t);       // counts the workgroups; 0 blocks: nothing to do
+hipError_t launch_tail(int dtype, TailJobs* t, hipStream_t s);
 
 // SGD with momentum over spans of tensors: for list entry y (blockIdx.y) the elements
 // first + heads.h[y]*head_stride + r*stride + c, r < rows, c < 8*cols8, of w (storage dtype), g (storage

@@ -534,6 +534,7 @@ d2ft_status weight_grad(const d2ft_block_desc* d, const Dims& s, const void* Aop
 // third of the split-K partial traffic that separate launches need.
 struct WeightGradBatch {
     bool enabled;
+    bool small;      // bf16: on 64x64 tiles, as fp32 always is
     GemmArgs g;
     ReduceGroupedArgs r;
     // a group with remap RED_REMAP_F32 leaves its fp32 product for a consumer: after the flush f32_splits says
@@ -612,10 +613,11 @@ bool side_fork(SideStream* S, hipStream_t st) {
     return hipEventRecord(S->fork, st) == hipSuccess && hipStreamWaitEvent(S->stream, S->fork, 0) == hipSuccess;
 }
 
+// tail: if given, what ends the call; it rides on the launch where the launch can carry it (its job counts are then 0)
 // part_used: if given, the floats at the start of `part` that earlier flushes of the same call own (their
 // launches may still be running on the other stream); this flush takes the next ones
 d2ft_status weight_grad_flush(WeightGradBatch* b, const d2ft_block_desc* d, const Dims& s, float* part, size_t part_floats,
-                              hipStream_t st, size_t* part_used = nullptr, int max_units = 0) {
+                              hipStream_t st, size_t* part_used = nullptr, int max_units = 0, TailJobs* tail = nullptr) {
     if (b->g.n_groups == 0) return D2FT_OK;
     GemmArgs& g = b->g;
     g.K = (int)s.M;
@@ -628,14 +630,15 @@ d2ft_status weight_grad_flush(WeightGradBatch* b, const d2ft_block_desc* d, cons
     g.partial = part;
     const int accum = (d->flags & D2FT_FLAG_ACCUM_GRADS) ? 1 : 0;
     hipError_t e = hipErrorNotSupported;
-    if (d->dtype == D2FT_F32) {
+    if (d->dtype == D2FT_F32 || b->small) {
         timing_begin(st, "gemm");
         g_timing.label = "gemm_tile64_kernel";
         for (int i = 0; i < g.n_groups; ++i) g_timing.flops += 2.0 * g.grp[i].M * g.grp[i].N * s.M;
-        e = launch_gemm_tile64_grouped(g, b->r, s.dtype, accum, part_floats, st);
+        e = launch_gemm_tile64_grouped(g, b->r, s.dtype, accum, part_floats, tail, st);
         timing_end(st);
         if (e == hipSuccess) {
             g.n_groups = 0;
+            if (tail) tail->red.n = tail->zero.n = 0;   // they rode along
             return D2FT_OK;
         }
     } else if (gemm_grouped_slots(g) * 65536 <= part_floats) {
@@ -672,7 +675,7 @@ d2ft_status weight_grad_flush(WeightGradBatch* b, const d2ft_block_desc* d, cons
 }
 
 // bias gradient, first half: column sums of X over row chunks into its own partial region; the reduction
-// over the chunks is queued and done for all of a block's biases by one launch (flush_bias_grads)
+// over the chunks is queued and done with those of all of a block's biases (TailJobs)
 d2ft_status bias_grad(const Dims& s, const void* X, long ldx, int cols, float* region, void* out, int remap_cols,
                       ColReduceBatch* batch, hipStream_t st) {
     const int chunks = pick_chunks(s.M);
@@ -696,13 +699,18 @@ void queue_bias_reduce(ColReduceBatch* batch, const float* region, int bands, in
     j.remap_cols = remap_cols;
 }
 
-d2ft_status flush_bias_grads(const d2ft_block_desc* d, const Dims& s, ColReduceBatch* batch, const Remap64& tbl_a,
-                             const Remap64& tbl_b, hipStream_t st) {
+// the column reductions and zero fills that no weight-gradient launch took along
+d2ft_status flush_tail(const Dims& s, TailJobs* tail, hipStream_t st) {
+    if (tail->red.n == 0 && tail->zero.n == 0) return D2FT_OK;
     double nbytes = 0;
-    for (int i = 0; i < batch->n; ++i) nbytes += 4.0 * batch->job[i].chunks * batch->job[i].cols;
-    D2FT_TRY_BYTES(nbytes, launch_col_reduce_batch(s.dtype, *batch, tbl_a, tbl_b, (d->flags & D2FT_FLAG_ACCUM_GRADS) ? 1 : 0, st));
-    batch->n = 0;
+    for (int i = 0; i < tail->red.n; ++i) nbytes += 4.0 * tail->red.job[i].chunks * tail->red.job[i].cols;
+    D2FT_TRY_BYTES(nbytes, launch_tail(s.dtype, tail, st));
+    tail->red.n = tail->zero.n = 0;
     return D2FT_OK;
+}
+
+void fill_tail_table(uint16_t (&t)[kMaxBlocks64], const Remap64& tbl) {
+    for (int i = 0; i < kMaxBlocks64; ++i) t[i] = (uint16_t)(tbl.start[i] >> 6);
 }
 
 }  // namespace
@@ -960,8 +968,11 @@ static d2ft_status block_bwd_impl(const d2ft_block_desc* desc, const d2ft_block_
     float* part = (float*)(ws + WL.part);
     float* colpart = (float*)(ws + WL.colpart);
     float* ln_part = colpart + 4 * WL.colpart_stride;
-    ColReduceBatch bias_batch;
-    memset(&bias_batch, 0, sizeof(bias_batch));
+    TailJobs tail;   // bias reductions and zero fills, for the call's end
+    memset(&tail, 0, sizeof(tail));
+    ColReduceBatch& bias_batch = tail.red;
+    tail.accumulate = accum;
+    tail.H = s.H; tail.D = s.D; tail.r = s.r; tail.Dm = s.Dm;
     WeightGradBatch wgrads;
     weight_grad_batch_init(&wgrads, desc);
     Remap64 none;
@@ -972,10 +983,24 @@ static d2ft_status block_bwd_impl(const d2ft_block_desc* desc, const d2ft_block_
     // are projected from it once the batch has run
     bool lora_queued = false;
     HeadList lora_heads; lora_heads.n = 0;
-    // Side stream (see SideStream): for the whole-block matrix-core path, unless the caller asks for one stream,
-    // per-kernel timing is on (its durations are those of kernels running alone) or the stream is being captured.
+    // How the weight gradients run depends on their size, here in multiply-adds of the call.  Measured per stack of six
+    // bf16 blocks of 197 tokens, forward and backward, host included (a fork and join of streams costs the host about
+    // 25 us, a launch 3 to 4).  64x64 tiles against 256x256 tiles with a reduction: width 768, 5 images (6e9) 1035 and
+    // 1116 us, 10 images (12e9) 1696 and 1732, 20 images 1995 and 1796; width 384, 40 images (12e9) 1448 and 1374.  One
+    // stream against two: width 384, 5 images (1.5e9) 701 and 768 us, 10 images (3e9) 797 and 806, 20 images (6e9) 1142
+    // and 1086; width 768, 5 images (6e9) 1061 and 1035.
+    // Measured up to 8000 rows; LoRA's single narrow gradient over more of them is better off as it was.
+    constexpr double kSmallTileMacs = 10e9, kOneStreamMacs = 4.5e9;
+    constexpr long kSmallRows = 8192;
+    const double hidden = (desc->flags & D2FT_FLAG_GATE_FFN) ? (double)s.Dm / s.H * nf : s.Dm;
+    const double wgrad_macs = (double)s.M * s.D * (hidden * ((grads->w1 ? 1 : 0) + (grads->w2 ? 1 : 0)) +
+                                                   nf * (64.0 * (grads->w_o ? 1 : 0) + 192.0 * (grads->w_qkv || s.r > 0 ? 1 : 0)));
+    wgrads.small = s.dtype == D2FT_BF16 && s.M <= kSmallRows && wgrad_macs <= kSmallTileMacs;
+    // Side stream (see SideStream): for the whole-block matrix-core path, unless the call is small, the caller asks for
+    // one stream, per-kernel timing is on (its durations are those of kernels running alone) or the stream is being
+    // captured.
     SideStream* side = nullptr;
-    if (half == PART_BOTH && s.dtype == D2FT_BF16 && wgrads.enabled && !(desc->flags & D2FT_FLAG_ONE_STREAM) && !g_timing.on) {
+    if (half == PART_BOTH && s.dtype == D2FT_BF16 && wgrads.enabled && (s.M > kSmallRows || wgrad_macs > kOneStreamMacs) && !(desc->flags & D2FT_FLAG_ONE_STREAM) && !g_timing.on) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) side = side_stream();
     }
@@ -1015,9 +1040,9 @@ static d2ft_status block_bwd_impl(const d2ft_block_desc* desc, const d2ft_block_
     hipStream_t const st_side = side ? side->stream : st;
     size_t part_used = 0;   // floats of `part` owned by weight-gradient launches that may still be running
     // the weight gradients collected so far (and what follows from them) on stream `st`
-    auto flush_wgrads = [&](hipStream_t st, int max_units = 0) -> d2ft_status {
+    auto flush_wgrads = [&](hipStream_t st, int max_units = 0, TailJobs* rider = nullptr) -> d2ft_status {
         float* const mine = part + part_used;
-        const d2ft_status rw = weight_grad_flush(&wgrads, desc, s, part, WL.part_floats, st, &part_used, max_units);
+        const d2ft_status rw = weight_grad_flush(&wgrads, desc, s, part, WL.part_floats, st, &part_used, max_units, rider);
         if (rw != D2FT_OK) return rw;
         if (lora_queued) {
             lora_queued = false;
@@ -1031,24 +1056,6 @@ static d2ft_status block_bwd_impl(const d2ft_block_desc* desc, const d2ft_block_
     };
     // hand the weight gradients collected so far to the side stream, which picks them up behind what the
     // caller's stream holds now; without a side stream nothing happens here and they wait for the call's end
-    // Zero fills of the gradient slices of subnets that are not p_f: nothing in the call reads them and the
-    // reductions write other slices, so with the join deferred they wait for the next hand-over and ride on the
-    // side stream behind it instead of taking a turn on the caller's.
-    HeadList zero_list; zero_list.n = 0;
-    bool zero_heads_due = false, zero_ffn_due = false;
-    int zero_slice = 0;
-    auto launch_zeros = [&](hipStream_t st) -> d2ft_status {
-        if (zero_ffn_due) {
-            zero_ffn_due = false;
-            D2FT_TRY(launch_zero_ffn_slices(s.dtype, zero_list, zero_slice, s.D, s.Dm, grads->w1, grads->b1, grads->w2, st));
-        }
-        if (zero_heads_due) {
-            zero_heads_due = false;
-            D2FT_TRY(launch_zero_head_slices(s.dtype, zero_list, s.H, s.D, s.r, grads->w_qkv, grads->b_qkv, grads->w_o,
-                                             grads->lora_a_q, grads->lora_a_v, grads->lora_b_q, grads->lora_b_v, st));
-        }
-        return D2FT_OK;
-    };
     bool fork_recorded = false;   // the last launch on the caller's stream completes side->fork itself
     auto hand_over = [&](int max_units) -> d2ft_status {
         if (!side || wgrads.g.n_groups == 0) return D2FT_OK;
@@ -1059,19 +1066,14 @@ static d2ft_status block_bwd_impl(const d2ft_block_desc* desc, const d2ft_block_
             return D2FT_EDEVICE;
         }
         side_used = true;
-        const d2ft_status rw = flush_wgrads(st_side, max_units);
-        return rw != D2FT_OK ? rw : launch_zeros(st_side);
+        return flush_wgrads(st_side, max_units);
     };
-    // the call's last launches: the collected weight gradients, then the bias reductions, then the join
-    auto finish = [&](const Remap64& tbl_a, const Remap64& tbl_b) -> d2ft_status {
-        const d2ft_status rw = flush_wgrads(st_main);
+    // the call's last launches: the collected weight gradients, then what is left of the tail, then the join
+    auto finish = [&]() -> d2ft_status {
+        const d2ft_status rw = flush_wgrads(st_main, 0, &tail);
         if (rw != D2FT_OK) return rw;
-        const d2ft_status rz = launch_zeros(st_main);   // no hand-over took them along
-        if (rz != D2FT_OK) return rz;
-        if (bias_batch.n > 0) {
-            const d2ft_status rb = flush_bias_grads(desc, s, &bias_batch, tbl_a, tbl_b, st_main);
-            if (rb != D2FT_OK) return rb;
-        }
+        const d2ft_status rt = flush_tail(s, &tail, st_main);
+        if (rt != D2FT_OK) return rt;
         const d2ft_status rl = late_join();
         if (rl != D2FT_OK) return rl;
         if (side_used) {
@@ -1094,18 +1096,23 @@ static d2ft_status block_bwd_impl(const d2ft_block_desc* desc, const d2ft_block_
     const int n_hid = gate ? nf * slice : s.Dm;       // hidden units that take part in backward
     Remap64 ffn_tbl;
     memset(&ffn_tbl, 0, sizeof(ffn_tbl));
-    if (gate) fill_ffn_table(ffn_tbl, live, nf, slice);
-    if (gate && !accum) {   // feed-forward slices of subnets that are not p_f: +0.0
-        HeadList nonfull; nonfull.n = 0;
+    if (gate) {
+        fill_ffn_table(ffn_tbl, live, nf, slice);
+        fill_tail_table(tail.tbl[1], ffn_tbl);
+    }
+    // subnets that are not p_f: gradient slices are +0.0 in overwrite mode, untouched in accumulate mode.  Nothing in
+    // the call reads them and the other launches write other slices: they are part of the tail.
+    if (!accum && half != PART_MLP) {
         for (int h = 0; h < s.H; ++h)
-            if (ops[h] != D2FT_OP_FULL) nonfull.h[nonfull.n++] = (uint8_t)h;
-        if (bias_on_side) {
-            zero_list = nonfull;
-            zero_slice = slice;
-            zero_ffn_due = true;
-        } else {
-            D2FT_TRY(launch_zero_ffn_slices(s.dtype, nonfull, slice, s.D, s.Dm, grads->w1, grads->b1, grads->w2, st));
+            if (ops[h] != D2FT_OP_FULL) tail.zero.h[tail.zero.n++] = (uint8_t)h;
+        tail.w_qkv = grads->w_qkv; tail.b_qkv = grads->b_qkv; tail.w_o = grads->w_o;
+        tail.la_q = grads->lora_a_q; tail.la_v = grads->lora_a_v; tail.lb_q = grads->lora_b_q; tail.lb_v = grads->lora_b_v;
+        if (gate) {
+            tail.slice = slice;
+            tail.w1 = grads->w1; tail.b1 = grads->b1; tail.w2 = grads->w2;
         }
+    }
+    if (gate && !accum) {
         if (nl == 0 && grads->b2 && w->b2)   // bias was not applied: its gradient is zero
             D2FT_TRY(launch_reduce_partials(s.dtype, colpart, 0, 0, 1, s.D, grads->b2, s.D, RED_REMAP_NONE, none, 0, st));
         if (nf == 0) {
@@ -1227,7 +1234,7 @@ static d2ft_status block_bwd_impl(const d2ft_block_desc* desc, const d2ft_block_
         }
         dx1 = out;
     }
-    if (half == PART_MLP) return finish(none, ffn_tbl);
+    if (half == PART_MLP) return finish();
 
     // ---- attention side ----
     sv = sva;
@@ -1237,18 +1244,7 @@ static d2ft_status block_bwd_impl(const d2ft_block_desc* desc, const d2ft_block_
         rc = bias_grad(s, dx1, s.D, s.D, colpart + 2 * WL.colpart_stride, grads->b_o, 0, &bias_batch, st);
         if (rc != D2FT_OK) return rc;
     }
-    // heads that are not p_f: gradient slices are +0.0 in overwrite mode, untouched in accumulate mode
     if (!accum) {
-        HeadList nonfull; nonfull.n = 0;
-        for (int h = 0; h < s.H; ++h)
-            if (ops[h] != D2FT_OP_FULL) nonfull.h[nonfull.n++] = (uint8_t)h;
-        if (bias_on_side) {
-            zero_list = nonfull;
-            zero_heads_due = true;
-        } else {
-            D2FT_TRY(launch_zero_head_slices(s.dtype, nonfull, s.H, s.D, s.r, grads->w_qkv, grads->b_qkv, grads->w_o,
-                                             grads->lora_a_q, grads->lora_a_v, grads->lora_b_q, grads->lora_b_v, st));
-        }
         if (nl == 0 && grads->b_o && w->b_o) {   // bias was not applied: its gradient is zero
             // a [1][D] "partial" of zero splits writes +0.0
             D2FT_TRY(launch_reduce_partials(s.dtype, colpart, 0, 0, 1, s.D, grads->b_o, s.D, RED_REMAP_NONE, none, 0, st));
@@ -1265,7 +1261,7 @@ static d2ft_status block_bwd_impl(const d2ft_block_desc* desc, const d2ft_block_
             timing_end(st);
             if (e != hipSuccess) return D2FT_EDEVICE;
         }
-        return finish(none, ffn_tbl);
+        return finish();
     }
 
     const long ldq = (long)nl * 192, ldo = (long)nl * 64;
@@ -1275,6 +1271,7 @@ static d2ft_status block_bwd_impl(const d2ft_block_desc* desc, const d2ft_block_
     memset(&qkv_tbl, 0, sizeof(qkv_tbl));
     fill_head_table(head_tbl, live, nf);
     fill_qkv_table(qkv_tbl, live, nf, s.H);
+    fill_tail_table(tail.tbl[0], qkv_tbl);
     {   // dO = dx1 Wo[:, p_f heads]
         GemmArgs g = gemm_base();
         g.tbl = head_tbl;
@@ -1346,12 +1343,12 @@ static d2ft_status block_bwd_impl(const d2ft_block_desc* desc, const d2ft_block_
         const bool forked = side && wgrads.g.n_groups > 0;   // hand_over orders the side stream behind this point
         rc = hand_over(0);   // little is left beside it: as fast as it can
         if (rc != D2FT_OK) return rc;
-        if (bias_on_side && forked && bias_batch.n > 0) {
+        if (bias_on_side && forked) {
             bool fused_only = true;   // sums a column-sum pass left in the (single) colpart regions stay on the caller's stream
             for (int i = 0; i < bias_batch.n; ++i)
                 if (bias_batch.job[i].partial >= colpart && bias_batch.job[i].partial < colpart + 6 * WL.colpart_stride) fused_only = false;
             if (fused_only) {
-                rc = flush_bias_grads(desc, s, &bias_batch, qkv_tbl, ffn_tbl, st_side);
+                rc = flush_tail(s, &tail, st_side);
                 if (rc != D2FT_OK) return rc;
             }
         }
@@ -1386,13 +1383,13 @@ static d2ft_status block_bwd_impl(const d2ft_block_desc* desc, const d2ft_block_
             D2FT_TRY(launch_reduce_partials(s.dtype, pb, chunks, s.D, 1, s.D, grads->ln1_b, s.D, RED_REMAP_NONE, none, accum, st));
     }
     if (dx1 == dx) {   // the rows of dx1 are about to be rewritten in place: its weight gradients go first
-        rc = flush_wgrads(st_main);
+        rc = flush_wgrads(st_main, 0, &tail);
         if (rc != D2FT_OK) return rc;
     }
     // dx = dx1 + LN1bwd(du)
     D2FT_TRY_BYTES(4.0 * s.M * s.D * s.es + 8.0 * s.M, launch_ln_bwd(s.dtype, ws + WL.du, x, (const float*)(sv + SL.mean1), (const float*)(sv + SL.rstd1), w->ln1_g,
                            dx1, dx, M, s.D, st));
-    return finish(qkv_tbl, ffn_tbl);
+    return finish();
 }
 
 d2ft_status d2ft_block_bwd(const d2ft_block_desc* desc, const d2ft_block_weights* w, const uint8_t* ops,
@@ -1853,11 +1850,12 @@ d2ft_status d2ft_patch_embed_bwd(const d2ft_embed_desc* d, const void* dtokens, 
         if (rc != D2FT_OK) return rc;
     }
     if (g_b_pe) {
-        ColReduceBatch batch;
-        memset(&batch, 0, sizeof(batch));
-        d2ft_status rc = bias_grad(s, ws + L.dproj, d->width, d->width, (float*)(ws + L.colpart), g_b_pe, 0, &batch, st);
+        TailJobs tail;
+        memset(&tail, 0, sizeof(tail));
+        tail.accumulate = accum;
+        d2ft_status rc = bias_grad(s, ws + L.dproj, d->width, d->width, (float*)(ws + L.colpart), g_b_pe, 0, &tail.red, st);
         if (rc != D2FT_OK) return rc;
-        rc = flush_bias_grads(&hd, s, &batch, none, none, st);
+        rc = flush_tail(s, &tail, st);
         if (rc != D2FT_OK) return rc;
     }
     return D2FT_OK;

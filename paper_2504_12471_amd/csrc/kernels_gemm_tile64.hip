@@ -31,6 +31,7 @@
 #include <utility>
 
 #include "d2ft_common.h"
+#include "tail_jobs.h"
 
 namespace d2ft {
 
@@ -54,7 +55,8 @@ struct Tile64Group {
 struct Tile64Grouped {
     Tile64Group grp[kMaxGemmGroups];
     float* partial;          // splits > 1: raw sums, slot (split * total_tiles + tile), 64 x 64 floats each
-    int n, K, splits, slabs_per_split, total_tiles, accumulate;
+    int n, K, splits, slabs_per_split, total_tiles, units, accumulate;   // units: workgroups that multiply, then tail's
+    TailJobs tail;
     uint16_t tbl[3][kMaxBlocks64];   // the remap tables in units of 64
 };
 
@@ -219,8 +221,12 @@ __global__ __launch_bounds__((64 * group_waves<TM, TN>() * WK), TM == 64 && TN =
     LB lb;
     auto same = [](int i) { return i; };
     if constexpr (GROUPED) {
+        if ((int)blockIdx.x >= g.units) {
+            tail_work<T>(g.tail, blockIdx.x - g.units, threadIdx.x, 256 * WK, smem);
+            return;
+        }
         // units: (split, tile), the tiles of one split next to each other
-        const int total = g.total_tiles * g.splits, xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
+        const int total = g.units, xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
         const int u = xcd * (total >> 3) + min(xcd, total & 7) + idx;
         split = u / g.total_tiles;
         tile = u - split * g.total_tiles;
@@ -604,7 +610,7 @@ hipError_t launch_gemm_tile64(const GemmArgs& g, int dtype, hipStream_t s) {
 // out_g = A_g^T B_g for the groups of g (grp, n_groups, K, partial), through r's remaps: one launch, and a reduction
 // behind it if K is split.  partial_floats: size of g.partial.
 hipError_t launch_gemm_tile64_grouped(const GemmArgs& g, const ReduceGroupedArgs& r, int dtype, int accumulate,
-                                      size_t partial_floats, hipStream_t s) {
+                                      size_t partial_floats, TailJobs* tail, hipStream_t s) {
     const long es = dtype == D2FT_F32 ? 4 : 2;
     if (g.n_groups < 1 || g.n_groups > kMaxGemmGroups || g.K <= 0) return hipErrorNotSupported;
     Tile64Grouped a;
@@ -630,16 +636,24 @@ hipError_t launch_gemm_tile64_grouped(const GemmArgs& g, const ReduceGroupedArgs
     for (int i = 0; i < 3; ++i)
         for (int j = 0; j < kMaxBlocks64; ++j) a.tbl[i][j] = (uint16_t)(r.tbl[i].start[j] >> 6);
     a.total_tiles = (int)tiles;
-    // Splits of K: enough units for four workgroups per CU, while each keeps eight slabs and the partial tiles fit
-    const int bk = 128 / (int)es, slabs = (g.K + bk - 1) / bk;
+    // Splits of K: enough units for four workgroups per CU (bf16: one, its partial sums cost more than an idle slot),
+    // while each keeps eight slabs and the partial tiles fit
+    const int bk = 128 / (int)es, slabs = (g.K + bk - 1) / bk, enough = dtype == D2FT_F32 ? 1024 : 256;
     int splits = 1;
-    while (splits < 64 && tiles * splits < 1024 && slabs / (splits + 1) >= 8 && (size_t)(splits + 1) * tiles * 4096 <= partial_floats) ++splits;
+    while (splits < 64 && tiles * splits < enough && slabs / (splits + 1) >= 8 && (size_t)(splits + 1) * tiles * 4096 <= partial_floats) ++splits;
     a.slabs_per_split = (slabs + splits - 1) / splits;
     a.splits = (slabs + a.slabs_per_split - 1) / a.slabs_per_split;
     const long units = tiles * a.splits;
     const int wk = pick_wk(units, a.slabs_per_split);
-    hipError_t e = dtype == D2FT_F32 ? launch_form<float, 64, 64, true, true>(wk, (unsigned)units, s, a)
-                                     : launch_form<bf16, 64, 64, true, true>(wk, (unsigned)units, s, a);
+    a.units = (int)units;
+    a.tail.blocks = 0;
+    if (tail) {
+        tail_blocks(tail);
+        a.tail = *tail;
+    }
+    const unsigned grid_all = (unsigned)(units + a.tail.blocks);
+    hipError_t e = dtype == D2FT_F32 ? launch_form<float, 64, 64, true, true>(wk, grid_all, s, a)
+                                     : launch_form<bf16, 64, 64, true, true>(wk, grid_all, s, a);
     if (e != hipSuccess || a.splits == 1) return e;
     const dim3 grid((unsigned)tiles, 4);
     if (dtype == D2FT_F32) hipLaunchKernelGGL(reduce_tile64_kernel<float>, grid, dim3(256), 0, s, a);

@@ -3,6 +3,7 @@
 // reduces with cross-lane shuffles; column reductions write fp32 partials per row chunk and
 // a second kernel sums the partials in a fixed order, so results do not depend on timing.
 #include "d2ft_common.h"
+#include "tail_jobs.h"
 
 namespace d2ft {
 
@@ -463,78 +464,12 @@ __global__ __launch_bounds__(256) void reduce_grouped_kernel(const float* __rest
 }
 
 // ---------------------------------------------------------------------------
-// up to four column reductions in one launch: blockIdx.y picks the job.  A workgroup owns 32 columns
-// (8 threads x 4 columns) and spreads the chunks over 32 row lanes: lane l adds chunks l, l + 32, ... in
-// index order (eight loads in flight at a time), then the 32 lanes' sums are added in lane order.
+// what ends a backward call whose weight gradients do not take it along (tail_jobs.h)
 // ---------------------------------------------------------------------------
 template <typename T>
-__global__ __launch_bounds__(256) void col_reduce_batch_kernel(ColReduceBatch batch, int accumulate, Remap64 tbl_a,
-                                                                Remap64 tbl_b) {
-    __shared__ float4 red[32][8];
-    const ColReduceJob job = batch.job[blockIdx.y];
-    const int cg = threadIdx.x & 7, rl = threadIdx.x >> 3;
-    const int c = blockIdx.x * 32 + cg * 4;
-    if (blockIdx.x * 32 >= job.cols) return;   // uniform over the workgroup
-    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (c < job.cols) {
-        const float* src = job.partial + c;
-        int k = rl;
-        for (; k + 7 * 32 < job.chunks; k += 8 * 32) {
-            float4 v[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const float4*>(src + (long)(k + 32 * j) * job.cols);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) { s.x += v[j].x; s.y += v[j].y; s.z += v[j].z; s.w += v[j].w; }
-        }
-        for (; k < job.chunks; k += 32) {
-            const float4 v = *reinterpret_cast<const float4*>(src + (long)k * job.cols);
-            s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-        }
-    }
-    red[rl][cg] = s;
-    __syncthreads();
-    if (rl != 0 || c >= job.cols) return;
-#pragma unroll 8
-    for (int l = 1; l < 32; ++l) {
-        const float4 v = red[l][cg];
-        s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-    }
-    T* o = static_cast<T*>(job.out) + (job.remap_cols == 1 ? tbl_a(c) : (job.remap_cols == 2 ? tbl_b(c) : c));
-    if (accumulate) {
-        s.x += ld<T>(o); s.y += ld<T>(o + 1); s.z += ld<T>(o + 2); s.w += ld<T>(o + 3);
-    }
-    st<T>(o, s.x); st<T>(o + 1, s.y); st<T>(o + 2, s.z); st<T>(o + 3, s.w);
-}
-
-// ---------------------------------------------------------------------------
-// +0.0 into every gradient slice of the listed heads
-// ---------------------------------------------------------------------------
-template <typename T>
-__device__ __forceinline__ void zero_span(T* base, long count, int tid, int nth) {
-    if (!base) return;
-    for (long i = tid; i < count; i += nth) base[i] = static_cast<T>(0.0f);
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void zero_head_slices_kernel(HeadList heads, int H, int D, int r, T* g_wqkv,
-                                                               T* g_bqkv, T* g_wo, T* g_la_q, T* g_la_v, T* g_lb_q,
-                                                               T* g_lb_v) {
-    const int h = heads.h[blockIdx.y];
-    const int tid = blockIdx.x * 256 + threadIdx.x, nth = gridDim.x * 256;
-    for (int p = 0; p < 3; ++p) {
-        if (g_wqkv) zero_span(g_wqkv + ((long)(p * H + h) * 64) * D, (long)64 * D, tid, nth);
-        if (g_bqkv) zero_span(g_bqkv + (long)(p * H + h) * 64, 64, tid, nth);
-    }
-    if (g_wo) {
-        const long hd = (long)H * 64;
-        for (long i = tid; i < (long)D * 64; i += nth) g_wo[(i >> 6) * hd + h * 64 + (i & 63)] = static_cast<T>(0.0f);
-    }
-    if (r > 0) {
-        if (g_la_q) zero_span(g_la_q + (long)h * r * D, (long)r * D, tid, nth);
-        if (g_la_v) zero_span(g_la_v + (long)h * r * D, (long)r * D, tid, nth);
-        if (g_lb_q) zero_span(g_lb_q + (long)h * 64 * r, (long)64 * r, tid, nth);
-        if (g_lb_v) zero_span(g_lb_v + (long)h * 64 * r, (long)64 * r, tid, nth);
-    }
+__global__ __launch_bounds__(256) void tail_kernel(TailJobs t) {
+    __shared__ float4 lds[kTailLds / sizeof(float4)];
+    tail_work<T>(t, blockIdx.x, threadIdx.x, 256, lds);
 }
 
 // zero the [tokens][width] block (in x, and in x2 if given) of every (image, position) pair that is
@@ -556,21 +491,6 @@ __global__ __launch_bounds__(256) void zero_pairs_kernel(T* x, T* x2, long ld, i
         *reinterpret_cast<float4*>(x + off) = z;
         if (x2) *reinterpret_cast<float4*>(x2 + off) = z;
     }
-}
-
-// ---------------------------------------------------------------------------
-// +0.0 into the feed-forward gradient slices of the listed heads: rows [h*S, (h+1)*S) of w1 [Dm][D]
-// and of b1, columns [h*S, (h+1)*S) of w2 [D][Dm]
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void zero_ffn_slices_kernel(HeadList heads, int S, int D, int Dm, T* g_w1, T* g_b1,
-                                                              T* g_w2) {
-    const int h = heads.h[blockIdx.y];
-    const int tid = blockIdx.x * 256 + threadIdx.x, nth = gridDim.x * 256;
-    if (g_w1) zero_span(g_w1 + (long)h * S * D, (long)S * D, tid, nth);
-    if (g_b1) zero_span(g_b1 + (long)h * S, S, tid, nth);
-    if (g_w2)
-        for (long i = tid; i < (long)D * S; i += nth) g_w2[(i / S) * Dm + (long)h * S + (i % S)] = static_cast<T>(0.0f);
 }
 
 // ---------------------------------------------------------------------------
@@ -904,22 +824,16 @@ hipError_t launch_sgd(int dtype, const SgdArgs& a, const HeadList& heads, hipStr
     return hipGetLastError();
 }
 
-hipError_t launch_col_reduce_batch(int dtype, const ColReduceBatch& batch, const Remap64& tbl_a, const Remap64& tbl_b,
-                                   int accumulate, hipStream_t s) {
-    if (batch.n <= 0) return hipSuccess;
-    int cols = 0;
-    for (int i = 0; i < batch.n; ++i) cols = batch.job[i].cols > cols ? batch.job[i].cols : cols;   // multiples of 8
-    const dim3 grid((unsigned)((cols + 31) / 32), batch.n), block(256);
-    D2FT_DISPATCH(dtype, hipLaunchKernelGGL(col_reduce_batch_kernel<T>, grid, block, 0, s, batch, accumulate, tbl_a, tbl_b);)
-    return hipGetLastError();
+void tail_blocks(TailJobs* t) {
+    t->red_blocks = 0;
+    for (int i = 0; i < t->red.n; ++i) t->red_blocks += (t->red.job[i].cols + 31) / 32;   // multiples of 8 columns
+    t->blocks = t->red_blocks + t->zero.n * kZeroBlocks;
 }
 
-hipError_t launch_zero_ffn_slices(int dtype, const HeadList& heads, int slice, int D, int Dm, void* g_w1, void* g_b1,
-                                  void* g_w2, hipStream_t s) {
-    if (heads.n <= 0 || (!g_w1 && !g_b1 && !g_w2)) return hipSuccess;
-    const dim3 grid(32, heads.n), block(256);
-    D2FT_DISPATCH(dtype, hipLaunchKernelGGL(zero_ffn_slices_kernel<T>, grid, block, 0, s, heads, slice, D, Dm, (T*)g_w1,
-                                            (T*)g_b1, (T*)g_w2);)
+hipError_t launch_tail(int dtype, TailJobs* t, hipStream_t s) {
+    tail_blocks(t);
+    if (t->blocks == 0) return hipSuccess;
+    D2FT_DISPATCH(dtype, hipLaunchKernelGGL(tail_kernel<T>, dim3((unsigned)t->blocks), dim3(256), 0, s, *t);)
     return hipGetLastError();
 }
 
@@ -929,17 +843,6 @@ hipError_t launch_zero_pairs(int dtype, void* x, void* x2, long ld, int batch, i
     const dim3 grid(batch * n_pos), block(256);
     D2FT_DISPATCH(dtype, hipLaunchKernelGGL(zero_pairs_kernel<T>, grid, block, 0, s, (T*)x, (T*)x2, ld, tokens, n_pos, width,
                                             which, mask);)
-    return hipGetLastError();
-}
-
-hipError_t launch_zero_head_slices(int dtype, const HeadList& heads, int H, int D, int r, void* g_wqkv, void* g_bqkv,
-                                   void* g_wo, void* g_la_q, void* g_la_v, void* g_lb_q, void* g_lb_v,
-                                   hipStream_t s) {
-    if (heads.n <= 0) return hipSuccess;
-    const dim3 grid(32, heads.n), block(256);
-    D2FT_DISPATCH(dtype, hipLaunchKernelGGL(zero_head_slices_kernel<T>, grid, block, 0, s, heads, H, D, r,
-                                            (T*)g_wqkv, (T*)g_bqkv, (T*)g_wo, (T*)g_la_q, (T*)g_la_v, (T*)g_lb_q,
-                                            (T*)g_lb_v);)
     return hipGetLastError();
 }
 

@@ -37,6 +37,7 @@ def test_fp32_gated_slices_through_the_remaps():
     (1, 197, 768, 12, 3072),  # 32x32 and 64x32 tiles, two and four K groups
     (5, 65, 384, 6, 1536),    # 64x32 tiles with a row beside the edge, column sums on 64x64 tiles
     (5, 197, 320, 5, 1280),   # 64x64 tiles
+    (8, 197, 192, 3, 768),    # weight gradients in several splits of K, the call's tail riding along
 ])
 def test_bf16_tile_edges(batch, tokens, width, heads, mlp):
     w = di.Workload("tile64_bf16", batch, tokens, width, heads, 64, mlp, 1, "bf16")
