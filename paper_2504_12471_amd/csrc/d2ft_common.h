@@ -403,6 +403,6 @@ struct KnapsackArgs {
     uint8_t* selected;          // [K*2 problems][n]           0/1 tables of the two stages
     long stride;                // max capacity + 1, rounded up
 };
-hipError_t launch_knapsack(const KnapsackArgs& a, uint8_t* ops_dev, hipStream_t s);
+hipError_t launch_knapsack(const KnapsackArgs& a, long cmax, uint8_t* ops_dev, hipStream_t s);
 
 }  // namespace d2ft

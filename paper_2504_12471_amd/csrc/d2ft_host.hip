@@ -1982,7 +1982,7 @@ static d2ft_status knapsack_run(int32_t n_knapsacks, int32_t n_items, const doub
     D2FT_TRY(hipMemcpyAsync(d_cb, cost_bwd, (size_t)n_knapsacks * 4, hipMemcpyHostToDevice, st));
     D2FT_TRY(hipMemcpyAsync(d_capf, cap_full, (size_t)n_knapsacks * 4, hipMemcpyHostToDevice, st));
     D2FT_TRY(hipMemcpyAsync(d_capo, cap_fwd, (size_t)n_knapsacks * 4, hipMemcpyHostToDevice, st));
-    D2FT_TRY(launch_knapsack(a, d_ops, st));
+    D2FT_TRY(launch_knapsack(a, cmax, d_ops, st));
     D2FT_TRY(hipMemcpyAsync(ops_out, d_ops, nsc, hipMemcpyDeviceToHost, st));
     D2FT_TRY(hipStreamSynchronize(st));
     return D2FT_OK;

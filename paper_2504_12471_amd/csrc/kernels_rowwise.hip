@@ -675,31 +675,59 @@ __global__ __launch_bounds__(256) void score_partial_kernel(ScoreArgs a, int kin
     const T* base = static_cast<const T*>(sp.p) + sp.first + (long)h * sp.head_stride;
     const int n8 = sp.rows * sp.cols8;
     double acc = 0.0;
-    for (int i8 = (cidx - sp.chunk0) * 256 + threadIdx.x; i8 < n8; i8 += sp.nchunks * 256) {
-        const int r = i8 / sp.cols8, c8 = i8 - r * sp.cols8;
+    const int step = sp.nchunks * 256;
+    auto add = [&](const Raw8<T>& raw) {
         float v[8];
-        load8(base + (long)r * sp.stride + c8 * 8, v);
+        raw.get(v);
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const double d = (double)v[j];
             acc += kind == 0 ? d * d : fabs(d);
         }
+    };
+    // four pieces in flight, added in index order
+    for (int i8 = (cidx - sp.chunk0) * 256 + threadIdx.x; i8 < n8; i8 += 4 * step) {
+        Raw8<T> raw[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int at = i8 + u * step;
+            if (at < n8) {
+                const int r = at / sp.cols8, c8 = at - r * sp.cols8;
+                raw[u].load(base + (long)r * sp.stride + c8 * 8);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (i8 + u * step < n8) add(raw[u]);
     }
+    // pairs 128, 64, .., 1 apart: through LDS between wavefronts, then inside the first one
     red[threadIdx.x] = acc;
     __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) partial[(long)h * a.total_chunks + cidx] = red[0];
+    if (threadIdx.x >= 64) return;
+    const int t = threadIdx.x;
+    double s = (red[t] + red[t + 128]) + (red[t + 64] + red[t + 192]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+    if (t == 0) partial[(long)h * a.total_chunks + cidx] = s;
 }
 
-__global__ void score_final_kernel(const double* __restrict__ partial, int chunks, int H, double* __restrict__ out) {
-    const int h = blockIdx.x * blockDim.x + threadIdx.x;
-    if (h >= H) return;
+// one workgroup per head: the chunks' sums on chip in one round trip, added in chunk order by one lane (from memory that
+// chain was a load per chunk, 10 us for 76 chunks)
+__global__ __launch_bounds__(256) void score_final_kernel(const double* __restrict__ partial, int chunks, double* __restrict__ out) {
+    __shared__ double v[256];
+    const double* src = partial + (long)blockIdx.x * chunks;
     double s = 0.0;
-    for (int c = 0; c < chunks; ++c) s += partial[(long)h * chunks + c];
-    out[h] = s;
+    for (int c0 = 0; c0 < chunks; c0 += 256) {
+        if (c0 + (int)threadIdx.x < chunks) v[threadIdx.x] = src[c0 + threadIdx.x];
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const int n = min(256, chunks - c0);
+#pragma unroll 8
+            for (int c = 0; c < n; ++c) s += v[c];
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
 // ---------------------------------------------------------------------------
@@ -813,7 +841,7 @@ hipError_t launch_subnet_scores(int dtype, const ScoreArgs& a, int kind, double*
     D2FT_DISPATCH(dtype, hipLaunchKernelGGL(score_partial_kernel<T>, grid, block, 0, s, a, kind, partial);)
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(score_final_kernel, dim3((a.H + 63) / 64), dim3(64), 0, s, partial, a.total_chunks, a.H, out);
+    hipLaunchKernelGGL(score_final_kernel, dim3(a.H), dim3(256), 0, s, partial, a.total_chunks, out);
     return hipGetLastError();
 }
 

@@ -56,3 +56,17 @@ def test_micro_batch_schedule_shape():
     got = gpu_select(ks)
     assert np.array_equal(got, oracle_select(ks))
     assert np.all((got == di.OP_FULL).sum(axis=1) == 3) and np.all((got == di.OP_SKIP).sum(axis=1) == 2)
+
+
+@pytest.mark.parametrize("n,cap_full,cap_fwd", [
+    (1, 0, 0), (1, 63, 64), (65, 62, 63), (9, 511, 512), (20, 1100, 5),   # around whole wavefronts and rounds of threads
+    (384, 1036, 200),    # tables of one knapsack nearly fill a CU's LDS
+    (700, 1300, 40), (5, 6000, 10),   # beyond it: tables in the workspace
+])
+def test_table_sizes(n, cap_full, cap_fwd):
+    rng = np.random.default_rng(n + cap_full)
+    ks = di.KnapsackInputs(
+        score_full=rng.random((2, n)), score_fwd=rng.integers(0, 3, (2, n)) * 0.5,
+        cost_fwd=np.array([1, 2], np.int32), cost_bwd=np.array([2, 5], np.int32),
+        cap_full=np.array([cap_full, cap_full // 2], np.int32), cap_fwd=np.array([cap_fwd // 3, cap_fwd], np.int32))
+    assert np.array_equal(gpu_select(ks), oracle_select(ks))
