@@ -403,6 +403,7 @@ struct KnapsackArgs {
     uint8_t* selected;          // [K*2 problems][n]           0/1 tables of the two stages
     long stride;                // max capacity + 1, rounded up
 };
+bool knapsack_on_chip(int n_items, long cmax);   // launch_knapsack keeps the tables in LDS and reads each input once
 hipError_t launch_knapsack(const KnapsackArgs& a, long cmax, uint8_t* ops_dev, hipStream_t s);
 
 }  // namespace d2ft

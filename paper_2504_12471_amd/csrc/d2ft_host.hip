@@ -5,6 +5,7 @@
 #include <string.h>
 
 #include <map>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -608,6 +609,53 @@ d2ft_status join_pending(hipStream_t st) {
     S->pending = false;
     return hipStreamWaitEvent(st, S->join, 0) == hipSuccess ? D2FT_OK : D2FT_EDEVICE;
 }
+// Host memory that the GPU reads and writes directly, for calls that return a few numbers to the host: the kernel writes
+// them there and the call only waits for its stream.  A copy to pageable memory costs such a call 13 us on top of its 14,
+// the six copies to the device that a selection made 34 us.  Buffers are of one size and kept for the next call; a call
+// holds one for its own, so calls on several threads and streams share nothing.  No more than kKept are held back.
+class PinnedBuffer {
+public:
+    static constexpr size_t kBytes = 64 * 1024;
+    explicit PinnedBuffer(size_t need) {
+        if (need > kBytes) return;
+        {
+            std::lock_guard<std::mutex> lock(mutex());
+            if (!kept().empty()) {
+                p_ = kept().back();
+                kept().pop_back();
+                return;
+            }
+        }
+        if (hipHostMalloc(&p_, kBytes, hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            p_ = nullptr;
+        }
+    }
+    PinnedBuffer(const PinnedBuffer&) = delete;
+    PinnedBuffer& operator=(const PinnedBuffer&) = delete;
+    ~PinnedBuffer() {
+        if (!p_ || !idle_) return;   // work may still refer to it: it stays as it is
+        {
+            std::lock_guard<std::mutex> lock(mutex());
+            if (kept().size() < kKept) {
+                kept().push_back(p_);
+                return;
+            }
+        }
+        (void)hipHostFree(p_);
+    }
+    void* get() const { return p_; }        // null: too much asked for, or no memory; the call copies instead
+    void in_use() { idle_ = false; }        // before the first launch that refers to it
+    void done() { idle_ = true; }           // the stream has been waited for
+
+private:
+    static constexpr size_t kKept = 16;
+    static std::mutex& mutex() { static std::mutex* m = new std::mutex; return *m; }   // both outlive every caller
+    static std::vector<void*>& kept() { static auto* v = new std::vector<void*>; return *v; }
+    void* p_ = nullptr;
+    bool idle_ = true;
+};
+
 // work launched on S->stream from here on starts after what `st` holds now
 bool side_fork(SideStream* S, hipStream_t st) {
     return hipEventRecord(S->fork, st) == hipSuccess && hipStreamWaitEvent(S->stream, S->fork, 0) == hipSuccess;
@@ -1660,6 +1708,15 @@ d2ft_status d2ft_subnet_scores(const d2ft_block_desc* desc, const d2ft_block_wei
         for (int h = 0; h < desc->heads; ++h) scores_out[h] = 0.0;
         return D2FT_OK;
     }
+    PinnedBuffer host((size_t)desc->heads * sizeof(double));
+    if (host.get()) {
+        host.in_use();
+        D2FT_TRY(launch_subnet_scores(desc->dtype, a, kind, partial, static_cast<double*>(host.get()), st));
+        if (hipStreamSynchronize(st) != hipSuccess) return D2FT_EDEVICE;
+        host.done();
+        memcpy(scores_out, host.get(), (size_t)desc->heads * sizeof(double));
+        return D2FT_OK;
+    }
     D2FT_TRY(launch_subnet_scores(desc->dtype, a, kind, partial, out, st));
     if (hipMemcpyAsync(scores_out, out, (size_t)desc->heads * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess)
         return D2FT_EDEVICE;
@@ -1935,11 +1992,12 @@ size_t d2ft_knapsack_workspace_bytes(int32_t n_knapsacks, int32_t n_items, const
     return total;
 }
 
-// validation and launch sequence shared by the two knapsack entry points; `workspace` is device memory
+// validation and launch sequence shared by the two knapsack entry points; `workspace` is device memory, allocate: host
+// memory may be allocated
 static d2ft_status knapsack_run(int32_t n_knapsacks, int32_t n_items, const double* score_full,
                                 const double* score_fwd, const int32_t* cost_fwd, const int32_t* cost_bwd,
                                 const int32_t* cap_full, const int32_t* cap_fwd, uint8_t* ops_out, void* workspace,
-                                size_t workspace_bytes, hipStream_t st) {
+                                size_t workspace_bytes, bool allocate, hipStream_t st) {
     if (!score_full || !score_fwd || !cost_fwd || !cost_bwd || !cap_full || !cap_fwd || !ops_out || !workspace)
         return D2FT_EINVAL;
     if (n_knapsacks < 1 || n_items < 1) return D2FT_ESHAPE;
@@ -1976,6 +2034,30 @@ static d2ft_status knapsack_run(int32_t n_knapsacks, int32_t n_items, const doub
     uint8_t* d_ops = (uint8_t*)take(nsc);
     a.score_full = d_sf; a.score_fwd = d_so; a.cost_fwd = d_cf; a.cost_bwd = d_cb; a.cap_full = d_capf; a.cap_fwd = d_capo;
 
+    // where the kernel keeps its tables on chip it reads every input once: straight from the host
+    const size_t in_bytes = nsc * 16 + (size_t)n_knapsacks * 16;
+    PinnedBuffer host(allocate && knapsack_on_chip(n_items, cmax) ? in_bytes + nsc : (size_t)-1);
+    if (host.get()) {
+        double* sf = static_cast<double*>(host.get());
+        double* so = sf + nsc;
+        int* cost = reinterpret_cast<int*>(so + nsc);
+        uint8_t* ops = reinterpret_cast<uint8_t*>(cost + 4 * (size_t)n_knapsacks);
+        memcpy(sf, score_full, nsc * 8);
+        memcpy(so, score_fwd, nsc * 8);
+        memcpy(cost, cost_fwd, (size_t)n_knapsacks * 4);
+        memcpy(cost + n_knapsacks, cost_bwd, (size_t)n_knapsacks * 4);
+        memcpy(cost + 2 * (size_t)n_knapsacks, cap_full, (size_t)n_knapsacks * 4);
+        memcpy(cost + 3 * (size_t)n_knapsacks, cap_fwd, (size_t)n_knapsacks * 4);
+        a.score_full = sf; a.score_fwd = so;
+        a.cost_fwd = cost; a.cost_bwd = cost + n_knapsacks;
+        a.cap_full = cost + 2 * (size_t)n_knapsacks; a.cap_fwd = cost + 3 * (size_t)n_knapsacks;
+        host.in_use();
+        D2FT_TRY(launch_knapsack(a, cmax, ops, st));
+        if (hipStreamSynchronize(st) != hipSuccess) return D2FT_EDEVICE;
+        host.done();
+        memcpy(ops_out, ops, nsc);
+        return D2FT_OK;
+    }
     D2FT_TRY(hipMemcpyAsync(d_sf, score_full, nsc * 8, hipMemcpyHostToDevice, st));
     D2FT_TRY(hipMemcpyAsync(d_so, score_fwd, nsc * 8, hipMemcpyHostToDevice, st));
     D2FT_TRY(hipMemcpyAsync(d_cf, cost_fwd, (size_t)n_knapsacks * 4, hipMemcpyHostToDevice, st));
@@ -1993,7 +2075,7 @@ d2ft_status d2ft_select_knapsack(int32_t n_knapsacks, int32_t n_items, const dou
                                  const int32_t* cap_full, const int32_t* cap_fwd, uint8_t* ops_out, void* workspace,
                                  size_t workspace_bytes, void* hip_stream) {
     return knapsack_run(n_knapsacks, n_items, score_full, score_fwd, cost_fwd, cost_bwd, cap_full, cap_fwd, ops_out,
-                        workspace, workspace_bytes, static_cast<hipStream_t>(hip_stream));
+                        workspace, workspace_bytes, true, static_cast<hipStream_t>(hip_stream));
 }
 
 // ---- the knapsack selection for callers that cannot allocate ----
@@ -2029,7 +2111,7 @@ d2ft_status d2ft_select_knapsack_static(int32_t n_knapsacks, int32_t n_items, co
     // nothing in the workspace has to start at zero: the kernel initialises the table row, the selection
     // flags and every change flag it later reads, so what the previous call left behind is harmless
     return knapsack_run(n_knapsacks, n_items, score_full, score_fwd, cost_fwd, cost_bwd, cap_full, cap_fwd, ops_out,
-                        g_scratch_ptr[dev], sizeof(scratch), static_cast<hipStream_t>(hip_stream));
+                        g_scratch_ptr[dev], sizeof(scratch), false, static_cast<hipStream_t>(hip_stream));
 }
 
 }  // extern "C"

@@ -153,12 +153,17 @@ __global__ void knapsack_merge_kernel(const uint8_t* __restrict__ selected, uint
     ops[idx] = pf ? D2FT_OP_FULL : (po ? D2FT_OP_FWD : D2FT_OP_SKIP);
 }
 
+constexpr size_t kLds = 160 * 1024;
+bool knapsack_on_chip(int n_items, long cmax) {
+    const long padded = (cmax + 64) / 64 * 64;
+    return padded <= (long)kLds / 32 && n_items <= (int)kLds / 16 && lds_bytes(n_items, padded) <= kLds;
+}
+
 // cmax: the largest capacity.  The LDS form costs a knapsack one workgroup of a whole CU: also with many of them it is
 // the better one, as the other form's steps are some ten times as long.
 hipError_t launch_knapsack(const KnapsackArgs& a, long cmax, uint8_t* ops_dev, hipStream_t s) {
-    const long padded = (cmax + 64) / 64 * 64;
-    constexpr size_t kLds = 160 * 1024;
-    if (padded <= (long)kLds / 32 && a.n_items <= (int)kLds / 16 && lds_bytes(a.n_items, padded) <= kLds) {
+    if (knapsack_on_chip(a.n_items, cmax)) {
+        const long padded = (cmax + 64) / 64 * 64;
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(knapsack_lds_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
         if (e != hipSuccess) return e;
         const int per_stage = padded < 512 ? (int)padded : 512;
