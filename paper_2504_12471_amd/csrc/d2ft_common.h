@@ -148,6 +148,7 @@ struct GemmArgs {
     float* partial;       // non-null: split-K mode, raw fp32 sums go to partial[split][M][N]
     int splits;
     int tile_hint;        // 0: kernel chooses its tile, 1: 256x256, 2: 128x128, 3: 192x256
+    int shared;           // the launch has another stream's launches beside it
     // grouped mode (n_groups > 0; launch_gemm_grouped): the problems share K.  Every 256x256 tile of every
     // problem is cut into `splits` runs of units_per_wg K slabs; unit u = split * total_tiles + tile leaves its
     // fp32 sums in slot u of `partial` ([slots][256][256]); reduce_grouped adds a tile's slots in split order.
@@ -214,6 +215,8 @@ hipError_t launch_gemm_tile64_grouped(const GemmArgs& g, const ReduceGroupedArgs
                                       size_t partial_floats, TailJobs* tail, hipStream_t s);
 // rows of the output tile launch_gemm_mfma would pick (a tile makes two bands of g.colsum)
 int gemm_mfma_tile_rows(const GemmArgs& g);
+// > 0: better as two launches, this many rows on 256x256 tiles (tile_hint 1) and the rest on 128x128 tiles (2)
+int gemm_mfma_split_rows(const GemmArgs& g);
 // static string naming the kernel instantiation launch_gemm_mfma would pick (for timing records)
 const char* gemm_mfma_config_name(const GemmArgs& g);
 

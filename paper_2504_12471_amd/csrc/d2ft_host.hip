@@ -302,54 +302,23 @@ hipError_t run_gemm(const GemmArgs& g, const d2ft_block_desc* d, hipStream_t s, 
         return e;
     }
     if (on_mfma_path(g, d)) {
-        // Tile plan for shapes of more than one round of the chip's 256 CUs.  The one-per-CU tiles take whole
-        // rounds however few tiles the last one has, so three plans are priced in microseconds with per-round
-        // costs measured on this part (a round = fixed cost + slabs of 64 of K; ep = the epilogue's extra work):
-        // all 256x256 tiles; the rows of the whole rounds as 256x256 tiles and the remaining rows as 128x128
-        // tiles, two of which share a CU; all 192x256 tiles.
-        if (!g.partial && g.tile_hint == 0 && g.M >= 512 && g.N >= 256) {
-            const long tn = (g.N + 255) / 256, tm = (g.M + 255) / 256, total = tm * tn;
-            const double slabs = (g.K + 63) / 64;
-            const double ep = g.act == ACT_GELU ? 8.0 : ((g.act == ACT_DGELU || g.residual) ? 3.0 : 0.0);
-            auto rounds_of = [](long tiles, long per_round) { return (double)((tiles + per_round - 1) / per_round); };
-            const double r256 = 8.5 + 1.6 * slabs + ep, r192 = 9.0 + 1.1 * slabs + 0.75 * ep, r128 = 8.0 + 1.2 * slabs + 0.4 * ep;
-            if (total > 256) {
-                const double c_all256 = rounds_of(total, 256) * r256;
-                const double c_all192 = rounds_of((long)((g.M + 191) / 192) * tn, 256) * r192;
-                const long rounds = total / 256;
-                const long tm_big = rounds * 256 / tn;
-                const long m_split = tm_big * 256;
-                double c_split = 1e30;
-                if (m_split > 0 && m_split < g.M) {
-                    const long rest_tiles = ((g.M - m_split + 127) / 128) * ((g.N + 127) / 128);
-                    c_split = rounds_of(tm_big * tn, 256) * r256 + rounds_of(rest_tiles, 512) * r128;
-                }
-                if (c_split < c_all256 && c_split < c_all192) {
-                    GemmArgs big = g, rest = g;
-                    big.M = (int)m_split;
-                    big.tile_hint = 1;
-                    rest.M = g.M - (int)m_split;
-                    rest.tile_hint = 2;
-                    const size_t es = 2;
-                    rest.A = static_cast<const char*>(g.A) + m_split * g.a_rs * es;
-                    rest.C = static_cast<char*>(g.C) + m_split * g.ldc * es;
-                    if (g.residual) rest.residual = static_cast<const char*>(g.residual) + m_split * g.ldr * es;
-                    if (g.Z) rest.Z = static_cast<char*>(g.Z) + m_split * g.ldz * es;
-                    rest.colsum_row0 = g.colsum_row0 + 2 * (int)tm_big;
-                    if (gemm_mfma_supported(big) && gemm_mfma_supported(rest)) {
-                        if (colsum_bands) *colsum_bands = 2 * (int)tm_big + 2 * ((rest.M + 127) / 128);
-                        hipError_t e = timed_mfma(big, s);
-                        if (e != hipSuccess) return e;
-                        return timed_mfma(rest, s, done);
-                    }
-                } else if (c_all192 < c_all256) {
-                    GemmArgs t = g;
-                    t.tile_hint = 3;
-                    if (gemm_mfma_supported(t)) {
-                        if (colsum_bands) *colsum_bands = 2 * ((g.M + 191) / 192);
-                        return timed_mfma(t, s, done);
-                    }
-                }
+        if (const int m_split = gemm_mfma_split_rows(g)) {
+            GemmArgs big = g, rest = g;
+            big.M = m_split;
+            big.tile_hint = 1;
+            rest.M = g.M - m_split;
+            rest.tile_hint = 2;
+            const size_t es = 2;
+            rest.A = static_cast<const char*>(g.A) + m_split * g.a_rs * es;
+            rest.C = static_cast<char*>(g.C) + m_split * g.ldc * es;
+            if (g.residual) rest.residual = static_cast<const char*>(g.residual) + m_split * g.ldr * es;
+            if (g.Z) rest.Z = static_cast<char*>(g.Z) + m_split * g.ldz * es;
+            rest.colsum_row0 = g.colsum_row0 + 2 * (m_split / 256);
+            if (gemm_mfma_supported(big) && gemm_mfma_supported(rest)) {
+                if (colsum_bands) *colsum_bands = 2 * (m_split / 256) + 2 * ((rest.M + 127) / 128);
+                hipError_t e = timed_mfma(big, s);
+                if (e != hipSuccess) return e;
+                return timed_mfma(rest, s, done);
             }
         }
         if (colsum_bands) {
@@ -1190,6 +1159,7 @@ static d2ft_status block_bwd_impl(const d2ft_block_desc* desc, const d2ft_block_
         }
         {   // dz = (dy W2[:, hidden]) * GELU'(z)
             GemmArgs g = gemm_base();
+            g.shared = side ? 1 : 0;
             g.tbl = ffn_tbl;
             g.A = dy; g.a_rs = s.D; g.a_cs = 1;
             g.B = w->w2; g.b_rs = s.Dm; g.b_cs = 1;   // B(k = width index, n = hidden index) = W2[k][n]
@@ -1243,6 +1213,7 @@ static d2ft_status block_bwd_impl(const d2ft_block_desc* desc, const d2ft_block_
         }
         {   // dv = dz W1[hidden]
             GemmArgs g = gemm_base();
+            g.shared = side ? 1 : 0;
             g.tbl = ffn_tbl;
             g.A = dz_buf; g.a_rs = n_hid; g.a_cs = 1;
             g.B = w->w1; g.b_rs = s.D; g.b_cs = 1; g.remap = gate ? REMAP_B_K : REMAP_NONE;
@@ -1322,6 +1293,7 @@ static d2ft_status block_bwd_impl(const d2ft_block_desc* desc, const d2ft_block_
     fill_tail_table(tail.tbl[0], qkv_tbl);
     {   // dO = dx1 Wo[:, p_f heads]
         GemmArgs g = gemm_base();
+        g.shared = side ? 1 : 0;
         g.tbl = head_tbl;
         g.A = dx1; g.a_rs = s.D; g.a_cs = 1;
         g.B = w->w_o; g.b_rs = (long)s.H * 64; g.b_cs = 1; g.remap = REMAP_B_N;
@@ -1404,6 +1376,7 @@ static d2ft_status block_bwd_impl(const d2ft_block_desc* desc, const d2ft_block_
     fork_recorded = false;   // it stood for this point of the stream only
     {   // du = dQKV W_eff (rows of the p_f heads)
         GemmArgs g = gemm_base();
+        g.shared = side ? 1 : 0;
         g.tbl = qkv_tbl;
         g.A = ws + WL.dqkv; g.a_rs = ld_dq; g.a_cs = 1;
         if (s.r > 0) {   // the forward call's merged weights; the p_f heads are their first nf * 192 rows

@@ -985,18 +985,52 @@ bool gemm_mfma_supported(const GemmArgs& g) {
     return true;
 }
 
-// Tile choice: 0 = 128x128 (two workgroups per CU), 1 = 256x256, 3 = 192x256 (one workgroup per CU each).
-// The 256x256 tile moves the fewest operand bytes per FLOP and measures fastest even when it leaves CUs
-// idle, down to about 100 workgroups; when its grid is under one round of the chip's 256 CUs, the
-// 192-row tile spreads the same work over more of them.
+// Microseconds of a product on one of the three tiles (0 = 128x128, two workgroups per CU; 1 = 256x256 and 3 = 192x256,
+// one per CU):  launch + rounds * (start + slab * slabs of 64 of K + epilogue).  A round that fills only part of the
+// chip costs `least` of a full one and more the fuller it is.  Fitted on this part to 482 products of 2048 to 18912 rows,
+// widths 384 to 1024, with the model's four epilogues and both forms of B: rms error 3 % for the large tiles, 8 % for
+// the small one; the tile it picks is 0.1 % slower than the best of the three on average (the rule before it, by rounds
+// alone, 1.5 %: 12608 x 1536 x 384 with the GELU' product took 34.8 us on 256x256 tiles, 29.8 on 128x128).
+static float product_us(const GemmArgs& g, int tile, int M) {
+    struct Cost { int bm, bn, at_once; float launch, least, start, slab, gelu, dgelu, residual, b_col; };
+    constexpr Cost kCost[3] = {{128, 128, 512, 4.85f, 0.22f, 3.07f, 0.965f, 4.37f, 0.60f, 0.54f, 0.022f},
+                               {256, 256, 256, 2.34f, 0.665f, 9.11f, 1.32f, 8.87f, 1.91f, 0.70f, 0.012f},
+                               {192, 256, 256, 2.55f, 0.625f, 6.92f, 1.088f, 6.97f, 1.05f, 0.14f, 0.015f}};
+    const Cost& c = kCost[tile == 3 ? 2 : tile];
+    const long units = (long)((M + c.bm - 1) / c.bm) * ((g.N + c.bn - 1) / c.bn) * (g.partial ? g.splits : 1);
+    float rounds = (float)(units / c.at_once);
+    if (const int rest = (int)(units % c.at_once)) rounds += c.least + (1.0f - c.least) * (float)rest / (float)c.at_once;
+    if (tile == 0 && rounds < 0.42f) rounds = 0.42f;   // a few workgroups: their own latency
+    const float slabs = (float)((g.K + 63) / 64);
+    const float epilogue = g.act == ACT_GELU ? c.gelu : (g.act == ACT_DGELU ? c.dgelu : (g.residual ? c.residual : 0.0f));
+    return c.launch + rounds * (c.start + slabs * (c.slab + (g.b_rs != 1 ? c.b_col : 0.0f)) + epilogue);
+}
+
+// Beside another stream's launches the small tile is not the better one where it would be alone: its workgroups cover
+// all CUs and take 1.5 times the operand bytes, the large ones leave CUs to the other stream (width 1024, 6304 rows:
+// 24 blocks 13.2 ms with dv on 128x128 tiles, 12.8 with 192x256).
+static float small_us(const GemmArgs& g) {
+    if (g.shared && g.M >= 256 && g.N >= 256 && (long)((g.M + 255) / 256) * ((g.N + 255) / 256) >= 96) return 1e30f;
+    return product_us(g, 0, g.M);
+}
+
 static int pick_tile(const GemmArgs& g) {
     if (g.tile_hint) return g.tile_hint == 2 ? 0 : g.tile_hint;
-    const long tn = (g.N + 255) / 256, splits = g.partial ? g.splits : 1;
-    const long big = (long)((g.M + 255) / 256) * tn * splits;
-    if (!(big >= 96 && g.M >= 256 && g.N >= 256)) return 0;
-    const long mid = (long)((g.M + 191) / 192) * tn * splits;
-    if (big < 256 && mid <= 256 && mid > big) return 3;
-    return 1;
+    if (g.N < 256 || g.M < 192) return 0;
+    const float small = small_us(g), mid = product_us(g, 3, g.M);
+    const float big = g.M >= 256 ? product_us(g, 1, g.M) : 1e30f;
+    return small <= mid && small <= big ? 0 : (mid <= big ? 3 : 1);
+}
+
+// The rows of the whole rounds of 256x256 tiles if those, with the remaining rows on 128x128 tiles, are cheaper than any
+// one tile for all rows; 0 otherwise.
+int gemm_mfma_split_rows(const GemmArgs& g) {
+    const long tn = (g.N + 255) / 256, total = (long)((g.M + 255) / 256) * tn;
+    if (g.partial || g.tile_hint || g.M < 512 || g.N < 256 || total <= 256) return 0;
+    const int rows = (int)(total / 256 * 256 / tn * 256);
+    if (rows <= 0 || rows >= g.M) return 0;
+    const float two = product_us(g, 1, rows) + product_us(g, 0, g.M - rows);
+    return two < small_us(g) && two < product_us(g, 1, g.M) && two < product_us(g, 3, g.M) ? rows : 0;
 }
 
 int gemm_mfma_tile_rows(const GemmArgs& g) {
