@@ -1,0 +1,108 @@
+// What the small-tile products (kernels_gemm_tile64.hip) and the split fp32 products (kernels_gemm_split.hip) share: the
+// arguments of a grouped weight-gradient launch, the order in which workgroups take tiles, and what happens to results.
+#pragma once
+
+#include "tail_jobs.h"
+
+namespace d2ft {
+
+// One weight gradient of a grouped launch: out[m'][n'] (=|+=) sum_k A[k][m] * B[k][n], (m', n') through the remap
+struct Tile64Group {
+    const void* A;
+    const void* B;
+    void* out;
+    long lda, ldb, ldo;
+    int M, N;
+    int tiles_m, tile0;
+    int remap, table;        // RED_REMAP_*
+};
+struct Tile64Grouped {
+    Tile64Group grp[kMaxGemmGroups];
+    float* partial;          // splits > 1: raw sums, slot (split * total_tiles + tile), 64 x 64 floats each
+    int n, K, splits, slabs_per_split, total_tiles, units, accumulate;   // units: workgroups that multiply, then tail's
+    TailJobs tail;
+    uint16_t tbl[3][kMaxBlocks64];   // the remap tables in units of 64
+};
+
+constexpr uint32_t kBufBytes = 0x80000000u;   // declared buffer size; operands are checked to be smaller
+constexpr uint32_t kOutside = 0x80000000u;    // any offset >= kBufBytes reads as zero
+
+// workgroup -> tile: workgroup ids with the same value mod 8 (one XCD) get a contiguous range of tiles, walked in
+// groups of 8 tile rows, so that an XCD's workgroups share operand slabs through its L2
+__device__ __forceinline__ void tile_of_block(int pid, int total, int tiles_m, int tiles_n, int& tm, int& tn, int& split) {
+    const int xcd = pid & 7, idx = pid >> 3;
+    const int lid = xcd * (total >> 3) + min(xcd, total & 7) + idx;
+    const int per_split = tiles_m * tiles_n;
+    split = lid / per_split;
+    const int rem = lid - split * per_split;
+    constexpr int GM = 8;
+    const int group = rem / (GM * tiles_n);
+    const int first = group * GM;
+    const int gsize = min(tiles_m - first, GM);
+    const int in_group = rem - group * GM * tiles_n;
+    tm = first + in_group % gsize;
+    tn = in_group / gsize;
+}
+
+// results of row m, columns n .. n + 7, through the epilogue; v returns what was stored
+template <typename T>
+__device__ __forceinline__ void emit(const GemmArgs& g, int m, int n, float (&v)[8]) {
+    if (g.bias) {
+        float b[8];
+        load8(static_cast<const T*>(g.bias) + (g.bias_remap ? g.tbl(n) : n), b);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] += b[i];
+    }
+    if (g.act == ACT_GELU) {
+        // Z <- GELU'(z), C <- GELU(z), both of the fp32 pre-activation
+        float d[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            d[i] = gelu_grad_f(v[i]);
+            v[i] = gelu_f(v[i]);
+        }
+        store8(static_cast<T*>(g.Z) + (long)m * g.ldz + n, d);
+    } else if (g.act == ACT_DGELU) {
+        float d[8];
+        load8(static_cast<const T*>(g.Z) + (long)m * g.ldz + n, d);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] *= d[i];
+    }
+    if (g.residual) {
+        float x[8];
+        load8(static_cast<const T*>(g.residual) + (long)m * g.ldr + n, x);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] += x[i];
+    }
+    store8(static_cast<T*>(g.C) + (long)m * g.ldc + n, v);
+}
+
+// the same of weight gradient gi of a grouped launch
+template <typename T>
+__device__ __forceinline__ void emit_grouped(const Tile64Grouped& g, int gi, int m, int n, float (&v)[8]) {
+    const Tile64Group& G = g.grp[gi];
+    if (G.remap == RED_REMAP_F32) {
+        store8(static_cast<float*>(G.out) + (long)m * G.ldo + n, v);
+    } else {
+        const int mo = G.remap == RED_REMAP_ROWS ? g.tbl[G.table][m >> 6] * 64 + (m & 63) : m;
+        const int no = G.remap == RED_REMAP_COLS ? g.tbl[G.table][n >> 6] * 64 + (n & 63) : n;
+        T* o = static_cast<T*>(G.out) + (long)mo * G.ldo + no;
+        if (g.accumulate) {
+            float old[8];
+            load8(o, old);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] += old[i];
+        }
+        store8(o, v);
+    }
+}
+
+// fp32 products by bf16 parts (kernels_gemm_split.hip), for what gemm_tile64_supported takes: microseconds, 1e30 if the
+// form is not one of it
+float gemm_split_us(const GemmArgs& g);
+hipError_t launch_gemm_split(const GemmArgs& g, hipStream_t s);
+// fills the tiles, splits and units of a for its groups; microseconds with the reduction
+float gemm_split_grouped_plan(Tile64Grouped* a, size_t partial_floats);
+hipError_t launch_gemm_split_grouped(const Tile64Grouped& a, hipStream_t s);
+
+}  // namespace d2ft

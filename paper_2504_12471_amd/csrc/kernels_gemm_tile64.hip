@@ -31,7 +31,7 @@
 #include <utility>
 
 #include "d2ft_common.h"
-#include "tail_jobs.h"
+#include "gemm_tile.h"
 
 namespace d2ft {
 
@@ -42,28 +42,8 @@ typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4;
 typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 
-// One weight gradient of a grouped launch: out[m'][n'] (=|+=) sum_k A[k][m] * B[k][n], (m', n') through the remap
-struct Tile64Group {
-    const void* A;
-    const void* B;
-    void* out;
-    long lda, ldb, ldo;
-    int M, N;
-    int tiles_m, tile0;
-    int remap, table;        // RED_REMAP_*
-};
-struct Tile64Grouped {
-    Tile64Group grp[kMaxGemmGroups];
-    float* partial;          // splits > 1: raw sums, slot (split * total_tiles + tile), 64 x 64 floats each
-    int n, K, splits, slabs_per_split, total_tiles, units, accumulate;   // units: workgroups that multiply, then tail's
-    TailJobs tail;
-    uint16_t tbl[3][kMaxBlocks64];   // the remap tables in units of 64
-};
-
 namespace {
 
-constexpr uint32_t kBufBytes = 0x80000000u;   // declared buffer size; operands are checked to be smaller
-constexpr uint32_t kOutside = 0x80000000u;    // any offset >= kBufBytes reads as zero
 constexpr int kAhead = 3;                     // slabs in flight in registers
 constexpr int kStagePad = 4;                  // floats between the rows of the epilogue's stage
 
@@ -167,23 +147,6 @@ __device__ __forceinline__ void mma(f32x16& acc, bf16x8 a, bf16x8 b) {
 __device__ __forceinline__ void mma(f32x16& acc, f32x4 a, f32x4 b) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], b[j], acc, 0, 0, 0);
-}
-
-// workgroup -> tile: workgroup ids with the same value mod 8 (one XCD) get a contiguous range of tiles, walked in
-// groups of 8 tile rows, so that an XCD's workgroups share operand slabs through its L2
-__device__ __forceinline__ void tile_of_block(int pid, int total, int tiles_m, int tiles_n, int& tm, int& tn, int& split) {
-    const int xcd = pid & 7, idx = pid >> 3;
-    const int lid = xcd * (total >> 3) + min(xcd, total & 7) + idx;
-    const int per_split = tiles_m * tiles_n;
-    split = lid / per_split;
-    const int rem = lid - split * per_split;
-    constexpr int GM = 8;
-    const int group = rem / (GM * tiles_n);
-    const int first = group * GM;
-    const int gsize = min(tiles_m - first, GM);
-    const int in_group = rem - group * GM * tiles_n;
-    tm = first + in_group % gsize;
-    tn = in_group / gsize;
 }
 
 template <int N, typename F, int I = 0>
@@ -344,55 +307,14 @@ __global__ __launch_bounds__((64 * group_waves<TM, TN>() * WK), TM == 64 && TN =
             if (g.splits > 1) {
                 store8(g.partial + ((long)split * g.total_tiles + tile) * 4096 + r * 64 + cc, v);
             } else if (m < M && n < N) {
-                const Tile64Group& G = g.grp[gi];
-                if (G.remap == RED_REMAP_F32) {
-                    store8(static_cast<float*>(G.out) + (long)m * G.ldo + n, v);
-                } else {
-                    const int mo = G.remap == RED_REMAP_ROWS ? g.tbl[G.table][m >> 6] * 64 + (m & 63) : m;
-                    const int no = G.remap == RED_REMAP_COLS ? g.tbl[G.table][n >> 6] * 64 + (n & 63) : n;
-                    T* o = static_cast<T*>(G.out) + (long)mo * G.ldo + no;
-                    if (g.accumulate) {
-                        float old[8];
-                        load8(o, old);
-#pragma unroll
-                        for (int i = 0; i < 8; ++i) v[i] += old[i];
-                    }
-                    store8(o, v);
-                }
+                emit_grouped<T>(g, gi, m, n, v);
             }
         } else if (m < M && n < N) {
             if (g.partial) {
                 store8(g.partial + (long)split * M * N + (long)m * N + n, v);
                 continue;
             }
-            if (g.bias) {
-                float b[8];
-                load8(static_cast<const T*>(g.bias) + (g.bias_remap ? g.tbl(n) : n), b);
-#pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] += b[i];
-            }
-            if (g.act == ACT_GELU) {
-                // Z <- GELU'(z), C <- GELU(z), both of the fp32 pre-activation
-                float d[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    d[i] = gelu_grad_f(v[i]);
-                    v[i] = gelu_f(v[i]);
-                }
-                store8(static_cast<T*>(g.Z) + (long)m * g.ldz + n, d);
-            } else if (g.act == ACT_DGELU) {
-                float d[8];
-                load8(static_cast<const T*>(g.Z) + (long)m * g.ldz + n, d);
-#pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] *= d[i];
-            }
-            if (g.residual) {
-                float x[8];
-                load8(static_cast<const T*>(g.residual) + (long)m * g.ldr + n, x);
-#pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] += x[i];
-            }
-            store8(static_cast<T*>(g.C) + (long)m * g.ldc + n, v);
+            emit<T>(g, m, n, v);
 #pragma unroll
             for (int i = 0; i < 8; ++i) csum[i] += v[i];
         }
@@ -549,8 +471,8 @@ struct Tile64Form {
 constexpr Tile64Form kFormsBf16[] = {{64, 64, 1, 3.2f, 0.37f, 0.17f, 0.8f},  {64, 64, 2, 3.9f, 0.27f, 0.20f, 1.0f},
                                      {64, 32, 2, 3.4f, 0.23f, 0.10f, 1.1f},  {64, 32, 4, 4.0f, 0.183f, 0.0f, 4.7f},
                                      {32, 32, 2, 3.0f, 0.198f, 0.08f, 0.5f}, {32, 32, 4, 3.9f, 0.102f, 0.10f, 1.2f}};
-constexpr Tile64Form kFormsF32[] = {{64, 64, 1, 4.4f, 0.61f, 0.43f, 2.5f}, {64, 32, 2, 3.4f, 0.37f, 0.215f, 1.6f},
-                                    {32, 32, 2, 3.2f, 0.30f, 0.12f, 0.9f}, {32, 32, 4, 3.9f, 0.18f, 0.12f, 1.2f}};
+constexpr Tile64Form kFormsF32[] = {{64, 64, 1, 4.4f, 0.61f, 0.52f, 3.0f}, {64, 32, 2, 3.4f, 0.37f, 0.26f, 1.9f},
+                                    {32, 32, 2, 3.2f, 0.30f, 0.145f, 1.1f}, {32, 32, 4, 3.9f, 0.18f, 0.145f, 1.4f}};
 static Tile64Form pick_form(const GemmArgs& g, int dtype, float* us) {
     const bool f32 = dtype == D2FT_F32;
     const Tile64Form* f = f32 ? kFormsF32 : kFormsBf16;
@@ -586,6 +508,8 @@ static hipError_t launch_tile64(const GemmArgs& g, int dtype, hipStream_t s) {
     }
     float us;
     const Tile64Form f = pick_form(g, dtype, &us);
+    // fp32 by bf16 parts: 15760 x 1536 x 384 with the GELU epilogue 156 against 212 us here, 3152 x 384 x 1536 57 and 44
+    if (std::is_same<T, float>::value && gemm_split_us(g) < us) return launch_gemm_split(g, s);
     if (f.tm == 32) return launch_tile<T, 32, 32>(g, f.wk, s);
     if (f.tn == 32) return launch_tile<T, 64, 32>(g, f.wk, s);
     return launch_tile<T, 64, 64>(g, f.wk, s);
@@ -650,6 +574,12 @@ hipError_t launch_gemm_tile64_grouped(const GemmArgs& g, const ReduceGroupedArgs
     if (tail) {
         tail_blocks(tail);
         a.tail = *tail;
+    }
+    if (dtype == D2FT_F32) {   // by bf16 parts, or here (one K group per workgroup at these sizes)
+        Tile64Grouped b = a;
+        const float us = gemm_split_grouped_plan(&b, partial_floats);
+        const float here = 4.4f + 0.61f * a.slabs_per_split + (float)((units + 255) / 256 - 1) * (0.52f * a.slabs_per_split + 3.0f) + (a.splits > 1 ? 4.0f : 0.0f);
+        if (us < here) return launch_gemm_split_grouped(b, s);
     }
     const unsigned grid_all = (unsigned)(units + a.tail.blocks);
     hipError_t e = dtype == D2FT_F32 ? launch_form<float, 64, 64, true, true>(wk, grid_all, s, a)
