@@ -342,13 +342,16 @@ hipError_t launch_attn_bwd_simple(int dtype, const void* qkv, long ldq, const vo
                                   int tokens, int n_full, hipStream_t s);
 
 // the same on the matrix cores with the tokens streamed through LDS, any number of tokens (kernels_attn_stream.hip);
-// the backward needs no delta buffer
+// the backward needs no delta buffer; bsum, if given, receives column sums of dqkv, one row of n_full * 192 floats per image
+// and block of attn_stream_blocks(tokens)
+int attn_stream_blocks(int tokens);
+bool attn_bwd_stream_faster(int tokens, int pairs);
 bool attn_stream_supported(int dtype, int tokens, long ldq, long ldo);
 hipError_t launch_attn_fwd_stream(int dtype, const void* qkv, long ldq, void* o, long ldo, float* lse, int batch, int tokens,
                                   int n_live, int n_full, hipStream_t s);
 hipError_t launch_attn_bwd_stream(int dtype, const void* qkv, long ldq, const void* o, long ldo, const float* lse,
-                                  const void* d_o, long ld_do, void* dqkv, long ld_dqkv, int batch, int tokens, int n_full,
-                                  hipStream_t s);
+                                  const void* d_o, long ld_do, void* dqkv, long ld_dqkv, float* bsum, int batch, int tokens,
+                                  int n_full, hipStream_t s);
 
 // MFMA attention (bf16, head dimension 64, up to 256 tokens forward, 224 backward); same argument meaning as the simple launchers
 // Which (micro-batch, compacted head position) pairs take part when one launch covers several

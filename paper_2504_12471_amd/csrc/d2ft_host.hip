@@ -115,7 +115,7 @@ ScratchLayout scratch_layout(const Dims& s) {
     L.colfuse_b1 = take(((size_t)s.M / 64 + 8) * s.Dm * 4);
     L.colfuse_b2 = take((size_t)ln_bwd_sums_bands((int)s.M) * s.D * 4);
     L.colfuse_bo = take((size_t)ln_bwd_sums_bands((int)s.M) * s.D * 4);
-    L.colfuse_bqkv = take((size_t)s.B * s.H * 192 * 4);   // per image, from the attention backward
+    L.colfuse_bqkv = take((size_t)s.B * attn_stream_blocks(s.T) * s.H * 192 * 4);   // per image, from the attention backward
     // and a second set of the four: consecutive backward calls alternate, so that a call may write its sums
     // while the reduction of the call before, left on the side stream (D2FT_FLAG_DEFER_JOIN), still reads its own
     L.colfuse_set = take(0) - L.colfuse_b1;
@@ -415,10 +415,20 @@ hipError_t run_attn_fwd(const d2ft_block_desc* d, const void* qkv, long ldq, voi
     return launch_attn_fwd_simple(d->dtype, qkv, ldq, o, ldo, lse, batch, tokens, n_live, n_full, s);
 }
 
-// the matrix-core backward also sums the columns of dqkv per image (bsum, see launch_attn_bwd_mfma)
-static bool attn_bwd_on_mfma(const d2ft_block_desc* d, int tokens, long ldq, long ldo, long ld_do, long ld_dqkv) {
-    return d->dtype == D2FT_BF16 && !(d->flags & D2FT_FLAG_NO_MFMA) && attn_bwd_mfma_supported(tokens, ldq, ldo) &&
-           (ld_do % 8) == 0 && (ld_dqkv % 8) == 0;
+// Which kernel runs the attention backward.  The matrix-core ones also sum the columns of dqkv: bands = rows of such sums
+// per image (bsum, see launch_attn_bwd_mfma and launch_attn_bwd_stream), 0 where there are none.
+enum AttnBwd { ATTN_BWD_MFMA, ATTN_BWD_STREAM, ATTN_BWD_SIMPLE };
+static AttnBwd pick_attn_bwd(const d2ft_block_desc* d, int batch, int tokens, int n_full, long ldq, long ldo, long ld_do, long ld_dqkv,
+                             int* bands) {
+    const bool mfma_ok = d->dtype == D2FT_BF16 && !(d->flags & D2FT_FLAG_NO_MFMA) && attn_bwd_mfma_supported(tokens, ldq, ldo) &&
+                         (ld_do % 8) == 0 && (ld_dqkv % 8) == 0;
+    const bool stream_ok = (d->dtype == D2FT_F32 || !(d->flags & D2FT_FLAG_NO_MFMA)) && attn_stream_supported(d->dtype, tokens, ldq, ldo);
+    if (mfma_ok && !(stream_ok && attn_bwd_stream_faster(tokens, batch * n_full))) {
+        *bands = 1;
+        return ATTN_BWD_MFMA;
+    }
+    *bands = stream_ok ? attn_stream_blocks(tokens) : 0;
+    return stream_ok ? ATTN_BWD_STREAM : ATTN_BWD_SIMPLE;
 }
 
 // done: if non-null, the matrix-core launch completes it (the caller checks launch_signal_pending() for the path
@@ -433,15 +443,17 @@ hipError_t run_attn_bwd(const d2ft_block_desc* d, const void* qkv, long ldq, con
         return launch_attn_bwd_mfma_masked(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, ld_dqkv, batch, tokens,
                                            n_full, *mask, s);
     }
-    if (attn_bwd_on_mfma(d, tokens, ldq, ldo, ld_do, ld_dqkv)) {
+    int bands;
+    const AttnBwd kind = pick_attn_bwd(d, batch, tokens, n_full, ldq, ldo, ld_do, ld_dqkv, &bands);
+    if (kind == ATTN_BWD_MFMA) {
         g_timing.label = "attn_bwd_mfma";
         return launch_attn_bwd_mfma(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, ld_dqkv, batch, tokens, n_full, s);
     }
-    if (bsum) return hipErrorNotSupported;   // callers ask attn_bwd_on_mfma() first
-    if ((d->dtype == D2FT_F32 || !(d->flags & D2FT_FLAG_NO_MFMA)) && attn_stream_supported(d->dtype, tokens, ldq, ldo)) {
+    if (kind == ATTN_BWD_STREAM) {
         g_timing.label = "attn_bwd_stream";
-        return launch_attn_bwd_stream(d->dtype, qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, batch, tokens, n_full, s);
+        return launch_attn_bwd_stream(d->dtype, qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, batch, tokens, n_full, s);
     }
+    if (bsum) return hipErrorNotSupported;   // callers ask pick_attn_bwd() first
     g_timing.label = "attn_bwd_simple";
     return launch_attn_bwd_simple(d->dtype, qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, delta, batch, tokens, n_full,
                                   s);
@@ -1306,8 +1318,10 @@ static d2ft_status block_bwd_impl(const d2ft_block_desc* desc, const d2ft_block_
                                RED_REMAP_COLS, head_tbl, 1, st);
         if (rc != D2FT_OK) return rc;
     }
-    // the matrix-core attention backward also leaves per-image column sums of dQKV: the QKV bias gradient
-    const bool fuse_bqkv = grads->b_qkv && (mask || attn_bwd_on_mfma(desc, s.T, ldq, ldo, ld_do, ld_dq));
+    // the matrix-core attention backward also leaves column sums of dQKV per image: the QKV bias gradient
+    int bqkv_bands = 1;
+    if (!mask) (void)pick_attn_bwd(desc, s.B, s.T, nf, ldq, ldo, ld_do, ld_dq, &bqkv_bands);
+    const bool fuse_bqkv = grads->b_qkv && bqkv_bands > 0;
     float* bqkv_part = fuse_bqkv ? (float*)(ws + WL.colfuse_bqkv + cf) : nullptr;
     const bool want_lora = s.r > 0 && (grads->lora_a_q || grads->lora_a_v || grads->lora_b_q || grads->lora_b_v);
     // If the side stream takes over right behind the attention backward (nothing else is launched on the caller's
@@ -1348,7 +1362,7 @@ static d2ft_status block_bwd_impl(const d2ft_block_desc* desc, const d2ft_block_
         }
     }
     if (fuse_bqkv) {
-        queue_bias_reduce(&bias_batch, bqkv_part, s.B, nf * 192, grads->b_qkv, 1);   // table a
+        queue_bias_reduce(&bias_batch, bqkv_part, s.B * bqkv_bands, nf * 192, grads->b_qkv, 1);   // table a
     } else if (grads->b_qkv) {
         rc = bias_grad(s, ws + WL.dqkv, ld_dq, nf * 192, colpart + 3 * WL.colpart_stride, grads->b_qkv, 1, &bias_batch, st);   // table a
         if (rc != D2FT_OK) return rc;

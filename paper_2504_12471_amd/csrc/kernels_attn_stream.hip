@@ -1,6 +1,7 @@
 // Softmax attention on the matrix cores for head dimension 64 with the keys (forward, dQ) or the queries (dK, dV)
 // streamed through LDS: any number of tokens, bf16 and fp32 storage, fp32 accumulate.  It serves fp32 at every token
-// count and bf16 above the 224 tokens that kernels_attn_mfma.hip keeps on chip whole.
+// count, bf16 above the 224 tokens that kernels_attn_mfma.hip keeps on chip whole, and below them the backward of few
+// pairs (attn_bwd_stream_faster).
 //
 // A wavefront owns 32 queries (or keys): their rows sit in registers as the B operand of every product and their
 // results as accumulators, so nothing but the streamed tiles goes through LDS and no partial sum crosses a
@@ -211,6 +212,30 @@ struct Stream {
     }
 };
 
+// Column sums of a workgroup's rows: t holds a row per lane (transposed result), ok = the row exists.  All wavefronts call
+// it; lds: the operand buffers, red: a row of 64 per wavefront.  Through LDS and in a short loop: shuffles between the
+// lanes take a third of the time once the instructions are cached, but in a pass of different kernels they are not, and
+// fetching the unrolled exchange cost 11 us a launch.
+__device__ __forceinline__ void store_colsum(const f32x16 (&t)[2], float mul, bool ok, float* lds, float (*red)[64], float* out) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = lane & 31, h = lane >> 5;
+    constexpr int kStride = 68;
+    float* const mine = lds + wave * kRows * kStride;
+    __syncthreads();   // the last stage has been read
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int dt = i >> 2, g = 4 * (i & 3);
+        const f32x4 v = {t[dt][g] * mul, t[dt][g + 1] * mul, t[dt][g + 2] * mul, t[dt][g + 3] * mul};
+        *reinterpret_cast<f32x4*>(mine + c * kStride + 32 * dt + 2 * g + 4 * h) = ok ? v : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    __syncthreads();
+    float s = 0.f;
+#pragma unroll 4
+    for (int r = 0; r < kRows; ++r) s += mine[r * kStride + lane];
+    red[wave][lane] = s;
+    __syncthreads();
+    if (wave == 0) out[lane] = red[0][lane] + red[1][lane] + red[2][lane] + red[3][lane];
+}
+
 // workgroup ids of one XCD (equal mod 8) become a contiguous range: the blocks of a pair share its rows through L2
 __device__ __forceinline__ int xcd_order(int pid, int total) {
     const int xcd = pid & 7;
@@ -316,11 +341,14 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
                                                                          const T* __restrict__ o, long ldo,
                                                                          const float* __restrict__ lse,
                                                                          const T* __restrict__ d_o, long ld_do,
-                                                                         T* __restrict__ dqkv, long ld_dqkv, int tokens,
+                                                                         T* __restrict__ dqkv, long ld_dqkv,
+                                                                         float* __restrict__ bsum, int tokens,
                                                                          int n_full, long rows_total, int blocks) {
     constexpr int ST = Tile<T>::kStage;
     __shared__ __attribute__((aligned(16))) T lds[2][2][ST * tile_elems<T>()];
     __shared__ __attribute__((aligned(16))) float consts[2][2][ST * kRows];   // log2(e) lse and delta of a stage's queries
+    __shared__ float red[kWaves][64];
+    static_assert(sizeof(lds) >= kWaves * kRows * 68 * 4 && kWaves == 4, "store_colsum");
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c = lane & 31, h = lane >> 5;
     const int half = gridDim.x >> 1;
@@ -409,9 +437,15 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
             }
             if (s + 1 < stages) store((s + 1) & 1);
         }
-        if (i0 >= tokens) return;
-        store_row(dk, kScale, dQb + (long)i * ld_dqkv + 64, h, ok);
-        store_row(dv, 1.f, dQb + (long)i * ld_dqkv + 128, h, ok);
+        if (i0 < tokens) {
+            store_row(dk, kScale, dQb + (long)i * ld_dqkv + 64, h, ok);
+            store_row(dv, 1.f, dQb + (long)i * ld_dqkv + 128, h, ok);
+        }
+        if (bsum) {   // softmax does not see a common shift of the keys: the columns of dK sum to zero
+            float* const row = bsum + ((long)b * blocks + id % blocks) * n_full * 192 + j * 192;
+            if (threadIdx.x < 64) row[64 + threadIdx.x] = 0.f;
+            store_colsum(dv, 1.f, ok, reinterpret_cast<float*>(lds), red, row + 128);
+        }
     } else {
         RowOp<T> qf, df;
         qf.load(Qb + (long)i * ldq, ok, h);
@@ -462,8 +496,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
                 sv.store(lds[(s + 1) & 1][1]);
             }
         }
-        if (i0 >= tokens) return;
-        store_row(dq, kScale, dQb + (long)i * ld_dqkv, h, ok);
+        if (i0 < tokens) store_row(dq, kScale, dQb + (long)i * ld_dqkv, h, ok);
+        if (bsum) store_colsum(dq, kScale, ok, reinterpret_cast<float*>(lds), red, bsum + ((long)b * blocks + id % blocks) * n_full * 192 + j * 192);
     }
 }
 
@@ -471,15 +505,26 @@ inline bool mult8(long v) { return (v & 7) == 0; }
 
 }  // namespace
 
+int attn_stream_blocks(int tokens) { return (tokens + kRows * kWaves - 1) / (kRows * kWaves); }
+
 bool attn_stream_supported(int dtype, int tokens, long ldq, long ldo) {
     const long es = dtype == D2FT_F32 ? 4 : 2;
     return tokens >= 1 && mult8(ldq) && mult8(ldo) && (long)(tokens + 63) * (ldq > ldo ? ldq : ldo) * es < (1L << 31);   // 32-bit offsets
 }
 
+// bf16 backward of up to 224 tokens: against the kernel with one workgroup per pair, which needs a round of the chip for up
+// to 256 pairs however few they are.  197 tokens: 12 pairs 11.1 against 16.6 us, 112 14.2 and 17.7, 320 33.5 and 36.3,
+// 448 44.0 and 39.9, 768 68 and 61.  Where the tokens fill this kernel's blocks of 128, or half of one, it is the better
+// one at any number: 128 tokens, 448 pairs 18.9 and 23.9 us; 50 tokens, 768 pairs 14.6 and 19.9 us (but 96 tokens 27.6
+// and 24.2).
+bool attn_bwd_stream_faster(int tokens, int pairs) {
+    return pairs <= 160 || (tokens > 96 && tokens <= 128) || (tokens > 48 && tokens <= 64);
+}
+
 hipError_t launch_attn_fwd_stream(int dtype, const void* qkv, long ldq, void* o, long ldo, float* lse, int batch, int tokens,
                                   int n_live, int n_full, hipStream_t s) {
     if (n_live <= 0) return hipSuccess;
-    const int blocks = (tokens + kRows * kWaves - 1) / (kRows * kWaves);
+    const int blocks = attn_stream_blocks(tokens);
     const dim3 grid((unsigned)((long)batch * n_live * blocks)), block(64 * kWaves);
     const long rows = (long)batch * tokens;
     if (dtype == D2FT_F32)
@@ -493,26 +538,26 @@ hipError_t launch_attn_fwd_stream(int dtype, const void* qkv, long ldq, void* o,
 
 template <typename T>
 static hipError_t launch_bwd(const void* qkv, long ldq, const void* o, long ldo, const float* lse, const void* d_o, long ld_do,
-                             void* dqkv, long ld_dqkv, int batch, int tokens, int n_full, hipStream_t s) {
-    const int blocks = (tokens + kRows * kWaves - 1) / (kRows * kWaves);
+                             void* dqkv, long ld_dqkv, float* bsum, int batch, int tokens, int n_full, hipStream_t s) {
+    const int blocks = attn_stream_blocks(tokens);
     const dim3 grid((unsigned)(2L * batch * n_full * blocks)), block(64 * kWaves);
     auto kern = attn_bwd_stream_kernel<T>;
     const T *q = (const T*)qkv, *op = (const T*)o, *dop = (const T*)d_o;
     T* dq = (T*)dqkv;
     const long rows = (long)batch * tokens;
     if (hipEvent_t ev = launch_signal_take())   // the launch completes the event itself
-        hipExtLaunchKernelGGL(kern, grid, block, 0, s, nullptr, ev, 0, q, ldq, op, ldo, lse, dop, ld_do, dq, ld_dqkv, tokens, n_full, rows, blocks);
+        hipExtLaunchKernelGGL(kern, grid, block, 0, s, nullptr, ev, 0, q, ldq, op, ldo, lse, dop, ld_do, dq, ld_dqkv, bsum, tokens, n_full, rows, blocks);
     else
-        hipLaunchKernelGGL(kern, grid, block, 0, s, q, ldq, op, ldo, lse, dop, ld_do, dq, ld_dqkv, tokens, n_full, rows, blocks);
+        hipLaunchKernelGGL(kern, grid, block, 0, s, q, ldq, op, ldo, lse, dop, ld_do, dq, ld_dqkv, bsum, tokens, n_full, rows, blocks);
     return hipGetLastError();
 }
 
 hipError_t launch_attn_bwd_stream(int dtype, const void* qkv, long ldq, const void* o, long ldo, const float* lse,
-                                  const void* d_o, long ld_do, void* dqkv, long ld_dqkv, int batch, int tokens, int n_full,
-                                  hipStream_t s) {
+                                  const void* d_o, long ld_do, void* dqkv, long ld_dqkv, float* bsum, int batch, int tokens,
+                                  int n_full, hipStream_t s) {
     if (n_full <= 0) return hipSuccess;
-    return dtype == D2FT_F32 ? launch_bwd<float>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, batch, tokens, n_full, s)
-                             : launch_bwd<bf16>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, batch, tokens, n_full, s);
+    return dtype == D2FT_F32 ? launch_bwd<float>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, batch, tokens, n_full, s)
+                             : launch_bwd<bf16>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, batch, tokens, n_full, s);
 }
 
 }  // namespace d2ft

@@ -23,3 +23,8 @@ def test_bf16_token_edges(tokens):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_most_tokens(dtype):
     run_case(di.Workload("stream_max", 1, 1024, 64, 2, 64, 64, 1, dtype), [FULL, FWD], seed=83)
+
+
+@pytest.mark.parametrize("tokens", [17, 64, 65, 128, 129, 197, 224])
+def test_bf16_few_pairs_below_225_tokens(tokens):
+    run_case(di.Workload("stream_few", 3, tokens, 128, 3, 64, 64, 1, "bf16"), [FULL, FWD, FULL], seed=84)
