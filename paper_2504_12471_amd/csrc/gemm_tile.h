@@ -58,8 +58,9 @@ __device__ __forceinline__ void emit(const GemmArgs& g, int m, int n, float (&v)
         float d[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            d[i] = gelu_grad_f(v[i]);
-            v[i] = gelu_f(v[i]);
+            const float z = v[i], cdf = 0.5f * (1.0f + erff(z * 0.70710678118654752440f));   // one erff for both: it is long
+            d[i] = fmaf(z, 0.39894228040143267794f * __expf(-0.5f * z * z), cdf);
+            v[i] = z * cdf;
         }
         store8(static_cast<T*>(g.Z) + (long)m * g.ldz + n, d);
     } else if (g.act == ACT_DGELU) {

@@ -312,7 +312,7 @@ __global__ __launch_bounds__(256, 4) void gemm_split_kernel(Args g) {
             for (int e = 0; e < 16; ++e) stage[(8 * (e >> 2) + 4 * h + (e & 3)) * kStride + 32 * j + c] = acc[i][j][e];
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
-#pragma unroll
+#pragma unroll 1
         for (int u = 0; u < 32 * kPer / 64; ++u) {
             const int p = u * 64 + lane, r = p / kPer, cc = p % kPer * 8;
             const int rt = wi + 32 * i + r, ct = wj + cc;   // within the tile

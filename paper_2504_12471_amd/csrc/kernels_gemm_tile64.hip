@@ -288,7 +288,7 @@ __global__ __launch_bounds__((64 * group_waves<TM, TN>() * WK), TM == 64 && TN =
     float csum[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) csum[i] = 0.f;
-#pragma unroll
+#pragma unroll 1   // short code: a launch fetches its instructions from memory
     for (int p0 = 0; p0 < kPieces; p0 += kThreads) {
         const int p = p0 + threadIdx.x;
         if (kThreads > kPieces && p >= kPieces) break;
