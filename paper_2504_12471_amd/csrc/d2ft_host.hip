@@ -113,8 +113,8 @@ ScratchLayout scratch_layout(const Dims& s) {
     // column sums that the producing kernels write themselves, one row of partial sums per band of rows:
     // the dz GEMM's epilogue (bands of 64 or more rows) for b1, the LayerNorm backward for b2 and b_o
     L.colfuse_b1 = take(((size_t)s.M / 64 + 8) * s.Dm * 4);
-    L.colfuse_b2 = take((size_t)ln_bwd_sums_bands((int)s.M) * s.D * 4);
-    L.colfuse_bo = take((size_t)ln_bwd_sums_bands((int)s.M) * s.D * 4);
+    L.colfuse_b2 = take((size_t)ln_bwd_sums_most_bands((int)s.M) * s.D * 4);
+    L.colfuse_bo = take((size_t)ln_bwd_sums_most_bands((int)s.M) * s.D * 4);
     L.colfuse_bqkv = take((size_t)s.B * attn_stream_blocks(s.T) * s.H * 192 * 4);   // per image, from the attention backward
     // and a second set of the four: consecutive backward calls alternate, so that a call may write its sums
     // while the reduction of the call before, left on the side stream (D2FT_FLAG_DEFER_JOIN), still reads its own
