@@ -1,6 +1,7 @@
 // C ABI entry points of libd2ft: argument validation, head compaction, buffer layout and the
 // launch sequence of one block's forward and backward pass.  All device work is in the
-// kernels_*.hip files; nothing here allocates device memory or keeps state between calls.
+// kernels_*.hip files; nothing here allocates device memory, and what outlives a call is a second stream per device
+// (SideStream) and a few pinned host buffers (PinnedBuffer).
 #include <math.h>
 #include <string.h>
 
