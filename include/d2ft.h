@@ -20,7 +20,9 @@
  *   - The caller owns every buffer.  The library allocates no device memory
  *     and keeps no tensor state between calls (per device it keeps launch
  *     parameters it has looked up, a HIP stream and two events of its own,
- *     see D2FT_FLAG_ONE_STREAM, and the timing records of d2ft_timing_enable).
+ *     see D2FT_FLAG_ONE_STREAM, and the timing records of d2ft_timing_enable;
+ *     per process up to 16 pinned host buffers of 64 KiB through which scores
+ *     and selections return).
  *   - Block calls are asynchronous on the given HIP stream (a hipStream_t
  *     passed as void*; NULL is the default stream): when a call returns, all
  *     of its work is ordered on that stream (unless the caller opts out with
