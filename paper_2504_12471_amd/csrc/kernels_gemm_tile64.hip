@@ -249,12 +249,18 @@ __global__ __launch_bounds__((64 * group_waves<TM, TN>() * WK), TM == 64 && TN =
     }
     // slab s sits in LDS buffer s & 1, slabs s + 1 .. s + kAhead in registers (slab x in slot x % kAhead).  One
     // barrier per slab: behind it the stores of slab s are visible and buffer (s + 1) & 1 is free.  A group of one
-    // wavefront shares its slabs with no other and needs none: its LDS accesses complete in order.
+    // wavefront shares its slabs with no other, and its LDS accesses complete in order: a fence at wavefront scope,
+    // which costs no instruction, keeps the compiler from moving one lane's reads over another lane's stores.
     auto step = [&](int s, auto slot_tag) {
         constexpr int slot = decltype(slot_tag)::value;
         unsigned char* const cur = mine + (s & 1) * (SA + SB);
         unsigned char* const nxt = mine + ((s + 1) & 1) * (SA + SB);
-        if constexpr (GW > 1) __syncthreads();
+        if constexpr (GW > 1) {
+            __syncthreads();
+        } else {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
         decltype(read_frag<T, A_COL, TM>(cur, 0, 0, 0)) fa[4];
         decltype(read_frag<T, B_COL, TN>(cur, 0, 0, 0)) fb[4];
 #pragma unroll

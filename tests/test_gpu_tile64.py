@@ -35,6 +35,7 @@ def test_fp32_gated_slices_through_the_remaps():
     (1, 3, 64, 1, 64),        # one tile, K of one slab
     (1, 33, 136, 2, 264),     # one row and one piece of columns beside the edge of a 32x32 tile, K not a multiple of 64
     (1, 197, 768, 12, 3072),  # 32x32 and 64x32 tiles, two and four K groups
+    (1, 33, 64, 1, 4096),     # 32x32 tiles over a long K: a wavefront exchanges 16 slabs between its lanes
     (5, 65, 384, 6, 1536),    # 64x32 tiles with a row beside the edge, column sums on 64x64 tiles
     (5, 197, 320, 5, 1280),   # 64x64 tiles
     (8, 197, 192, 3, 768),    # weight gradients in several splits of K, the call's tail riding along
