@@ -1,7 +1,7 @@
 // Softmax attention on the matrix cores for head dimension 64 with the keys (forward, dQ) or the queries (dK, dV)
 // streamed through LDS: any number of tokens, bf16 and fp32 storage, fp32 accumulate.  It serves fp32 at every token
-// count, bf16 above the 224 tokens that kernels_attn_mfma.hip keeps on chip whole, and below them the backward of few
-// pairs (attn_bwd_stream_faster).
+// count, bf16 above the tokens that kernels_attn_mfma.hip keeps on chip whole (256 forward, 224 backward), and below them
+// the backward of few pairs (attn_bwd_stream_faster).
 //
 // A wavefront owns 32 queries (or keys): their rows sit in registers as the B operand of every product and their
 // results as accumulators, so nothing but the streamed tiles goes through LDS and no partial sum crosses a
@@ -10,18 +10,26 @@
 //   forward  S^T = K Q^T (a lane owns one query), running maximum and sum per lane, O^T += V^T P^T
 //   dQ       S^T and dP^T = V dO^T from the same tiles, dS^T = P^T (dP^T - delta), dQ^T += K^T dS^T
 //   dK, dV   S = Q K^T and dP = dO V^T (a lane owns one key), dV^T += dO^T P, dK^T += Q^T dS
-// Probabilities are rebuilt from the saved log-sum-exp.  dQ and dK/dV workgroups are independent (both form
-// delta_q = sum_d dO[q][d] O[q][d] for the rows they touch) and share one launch, so that the second kind fills the
-// last round of the first.  S and dP are formed twice, 7 products of 64 x 32 x 32 per tile pair instead of 5: keeping
+// Probabilities are rebuilt from the saved log-sum-exp.  P and dS enter the second products with all their bits: as fp32
+// operands, or for bf16 storage as three bf16 parts each (cut8), three products instead of one.  Up to 224 tokens the bf16
+// backward rounds them to bf16, as kernels_attn_mfma.hip does, which runs the other calls of those lengths (TR_PARTS).
+// Relative 2-norm error against fp64 of O / dQ / dV, N(0, 1) operands, 577 tokens: bf16 1.66e-3 / 1.68e-3 / 1.66e-3, the
+// same as the vector-ALU kernels (with P and dS rounded to bf16 2.18e-3 / 2.39e-3 / 2.38e-3); fp32 4.8e-7 / 6.1e-7 /
+// 5.8e-7, the vector-ALU kernels 5.3e-7 / 6.5e-7 / 6.3e-7; with scores of 16 times the spread 8.5e-7 / 2.5e-6 / 1.4e-6
+// and 1.5e-6 / 3.8e-6 / 1.8e-6.
+//
+// dQ and dK/dV workgroups are independent (both form delta_q = sum_d dO[q][d] O[q][d] for the rows they touch) and
+// share one launch, so that the second kind fills the last round of the first.  S and dP are formed twice, 7 products of 64 x 32 x 32 per tile pair instead of 5: keeping
 // dQ partial sums instead would mean fp32 atomics, whose order is not fixed, or a pass over them.
 //
-// Bound: fp32 by the matrix cores (a 32 x 32 tile pair is 64 products of 64 cycles forward, 224 backward); bf16 by
-// the vector ALUs (16 exponentials, 16 multiply-adds, maxima, sums and conversions per lane and tile pair against
-// 8 products of 32 cycles).
+// Bound: fp32 by the matrix cores (a 32 x 32 tile pair is 64 products of 64 cycles forward, 224 backward); bf16 by the
+// matrix cores and the vector ALUs alike (forward 16 products of 32 cycles per tile pair, beside 16 exponentials, twice as
+// many subtractions and multiplications, maxima, sums and the cutting into parts, 5.5 operations for each of 16 elements).
 //
 // Measured against the vector-ALU kernels it replaced (one wavefront per row, every row of K and V from cache for
-// every query), per launch: bf16, 16 images of 577 tokens, 154 live / 115 p_f pairs: forward 1440 -> 30 us, backward
-// 4004 -> 65 us; fp32, 16 images of 197 tokens, 77 / 58 pairs: forward 172 -> 21 us, backward 486 -> 43 us.
+// every query), per launch: bf16, 16 images of 577 tokens, 160 live / 112 p_f pairs: forward 1440 -> 53 us, backward
+// 4004 -> 94 us (30 and 65 with P and dS in one part); fp32, 16 images of 197 tokens, 80 / 64 pairs: forward 172 -> 21 us,
+// backward 486 -> 40 us.
 //
 // Result layout of both products: column c = lane % 32, element e <-> row 8*(e/4) + 4h + e%4, h = lane / 32.
 #include <hip/hip_ext.h>
@@ -96,34 +104,62 @@ template <> struct RowOp<float> {
             if (ok) f[i] = *reinterpret_cast<const f32x4*>(row + 8 * i + 4 * h);
         }
     }
-    static __device__ __forceinline__ float dot(const RowOp& a, const RowOp& b) {
-        float s = 0.f;
+    static __device__ __forceinline__ float dot(const RowOp& a, const RowOp& b) {   // short chains: few roundings
+        float s[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < 8; ++i) {
+            s[i] = a.f[i][0] * b.f[i][0];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) s = fmaf(a.f[i][j], b.f[i][j], s);
-        return s;
+            for (int j = 1; j < 4; ++j) s[i] = fmaf(a.f[i][j], b.f[i][j], s[i]);
+        }
+        return ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
     }
 };
 
-// acc[row of the tile][this wavefront's row] += tile . op^T
+// acc[row of the tile][this wavefront's row] += tile . op^T; CHAINS: of sums along the channels, for fp32.  Two halve the
+// roundings of the scores, which an exponential follows; for both products of the backward they would not fit the registers.
+template <int CHAINS>
 __device__ __forceinline__ void mma_rows(f32x16& acc, const bf16* tile, const RowOp<bf16>& op, int lane) {
     const bf16* p = tile + Tile<bf16>::at(lane & 31) + 8 * (lane >> 5);
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(p + kk * 16), op.f[kk], acc, 0, 0, 0);
 }
+template <int CHAINS>
 __device__ __forceinline__ void mma_rows(f32x16& acc, const float* tile, const RowOp<float>& op, int lane) {
     const float* p = tile + Tile<float>::at(lane & 31) + 4 * (lane >> 5);
+    f32x16 other = zero16();
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const f32x4 a = *reinterpret_cast<const f32x4*>(p + 8 * i);
+        f32x16& to = CHAINS == 2 && (i & 1) ? other : acc;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], op.f[i][j], acc, 0, 0, 0);
+        for (int j = 0; j < 4; ++j) to = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], op.f[i][j], to, 0, 0, 0);
+    }
+    if constexpr (CHAINS == 2) acc += other;
+}
+
+// elements first .. first + 7 of p as PARTS bf16 parts, the largest first; the sum of three has every bit of p down to 2^-133
+template <int PARTS>
+__device__ __forceinline__ void cut8(const f32x16& p, int first, bf16x8 (&part)[PARTS]) {
+    float x[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = p[first + i];
+#pragma unroll
+    for (int k = 0; k < PARTS; ++k) {
+        u32x4 v;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            v[i] = pack_bf16x2(x[2 * i], x[2 * i + 1]);
+            x[2 * i] -= __uint_as_float(v[i] << 16);
+            x[2 * i + 1] -= __uint_as_float(v[i] & 0xffff0000u);
+        }
+        part[k] = __builtin_bit_cast(bf16x8, v);
     }
 }
 
 // out[channel][this wavefront's row] += tile^T . p, p a result of mma_rows (rows of the tile x the wavefront's rows)
+template <int PARTS>
 __device__ __forceinline__ void mma_tr(f32x16 (&out)[2], const bf16* tile, const f32x16& p, int lane) {
     const int j = lane & 15;
     // rows t0 + 4h + {0..3} and t0 + 8 + 4h + {0..3} of the tile: the order in which a lane holds 8 result elements
@@ -131,9 +167,8 @@ __device__ __forceinline__ void mma_tr(f32x16 (&out)[2], const bf16* tile, const
     typedef s16x4 __attribute__((address_space(3))) * lds_ptr_t;
 #pragma unroll
     for (int gp = 0; gp < 2; ++gp) {
-        bf16x8 pf;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) pf[i] = static_cast<__bf16>(p[8 * gp + i]);
+        bf16x8 pf[PARTS];
+        cut8(p, 8 * gp, pf);
 #pragma unroll
         for (int dt = 0; dt < 2; ++dt) {
             const bf16* q = base + 16 * gp * Tile<bf16>::kStride + 32 * dt;
@@ -142,10 +177,13 @@ __device__ __forceinline__ void mma_tr(f32x16 (&out)[2], const bf16* tile, const
             s16x8 r;
             r[0] = lo[0]; r[1] = lo[1]; r[2] = lo[2]; r[3] = lo[3];
             r[4] = hi[0]; r[5] = hi[1]; r[6] = hi[2]; r[7] = hi[3];
-            out[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, r), pf, out[dt], 0, 0, 0);
+#pragma unroll
+            for (int k = PARTS - 1; k >= 0; --k)   // the small parts first
+                out[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, r), pf[k], out[dt], 0, 0, 0);
         }
     }
 }
+template <int>
 __device__ __forceinline__ void mma_tr(f32x16 (&out)[2], const float* tile, const f32x16& p, int lane) {
     const float* base = tile + Tile<float>::at(4 * (lane >> 5)) + (lane & 31);
 #pragma unroll
@@ -285,7 +323,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void attn_fwd_stream_kernel(const T
 #pragma unroll
             for (int u = 0; u < ST; ++u) {
                 p[u] = zero16();
-                mma_rows(p[u], Ks + u * tile_elems<T>(), qf, lane);
+                mma_rows<2>(p[u], Ks + u * tile_elems<T>(), qf, lane);
             }
             if (s + 1 == stages) {   // keys past the last token
 #pragma unroll
@@ -311,15 +349,18 @@ __global__ __launch_bounds__(64 * kWaves, 3) void attn_fwd_stream_kernel(const T
 #pragma unroll
                     for (int e = 0; e < 16; ++e) ot[dt][e] *= alpha;
             }
-            const float mc = m * cexp;
+            // the difference first: folded into one multiply-add, the rounding of m * cexp would reach every probability
 #pragma unroll
             for (int u = 0; u < ST; ++u) {
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    p[u][e] = __builtin_amdgcn_exp2f(fmaf(p[u][e], cexp, -mc));
-                    sum += p[u][e];
-                }
-                mma_tr(ot, Vs + u * tile_elems<T>(), p[u], lane);
+                for (int e = 0; e < 16; ++e) p[u][e] = __builtin_amdgcn_exp2f((p[u][e] - m) * cexp);
+                f32x16 t = p[u];
+#pragma unroll
+                for (int w = 8; w > 0; w >>= 1)
+#pragma unroll
+                    for (int e = 0; e < w; ++e) t[e] += t[e + w];
+                sum += t[0];
+                mma_tr<3>(ot, Vs + u * tile_elems<T>(), p[u], lane);
             }
         }
         if (s + 1 < stages) {   // the other buffer was last read before the barrier above
@@ -336,7 +377,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void attn_fwd_stream_kernel(const T
 // ---------------------------------------------------------------------------
 // backward for p_f heads: the first half of the workgroups 128 keys of one (image, head) each, the rest 128 queries
 // ---------------------------------------------------------------------------
-template <typename T>
+template <typename T, int TR_PARTS>
 __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T* __restrict__ qkv, long ldq,
                                                                          const T* __restrict__ o, long ldo,
                                                                          const float* __restrict__ lse,
@@ -346,7 +387,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
                                                                          int n_full, long rows_total, int blocks) {
     constexpr int ST = Tile<T>::kStage;
     __shared__ __attribute__((aligned(16))) T lds[2][2][ST * tile_elems<T>()];
-    __shared__ __attribute__((aligned(16))) float consts[2][2][ST * kRows];   // log2(e) lse and delta of a stage's queries
+    __shared__ __attribute__((aligned(16))) float consts[2][2][ST * kRows];   // lse (see prob) and delta of a stage's queries
     __shared__ float red[kWaves][64];
     static_assert(sizeof(lds) >= kWaves * kRows * 68 * 4 && kWaves == 4, "store_colsum");
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -363,8 +404,15 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
     T* dQb = dqkv + row0 * ld_dqkv + j * 192;
     const int i0 = (id % blocks) * (kRows * kWaves) + wave * kRows, i = i0 + c;   // this wavefront's rows, this lane's row
     const bool ok = i < tokens;
-    const float cexp = kScale * kLog2e;
     const int stages = (tokens + ST * kRows - 1) / (ST * kRows);
+    // probability of raw score s under the log-sum-exp l of its query.  In one multiply-add, with l in units of log2(e),
+    // where P is rounded to bf16; else the difference first, so that the roundings of the two products do not reach P.
+    constexpr bool kExact = sizeof(T) == 4 || TR_PARTS == 3;
+    constexpr float kLse = kExact ? 1.f : kLog2e;
+    auto prob = [](float s, float l) {
+        if constexpr (kExact) return __builtin_amdgcn_exp2f(fmaf(s, kScale, -l) * kLog2e);
+        else return __builtin_amdgcn_exp2f(fmaf(s, kScale * kLog2e, -l));
+    };
 
     if (keys) {
         RowOp<T> kf, vf;
@@ -382,7 +430,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
             so.fetch(s * ST * kRows);
             if (threadIdx.x < ST * kRows) {
                 const int q = s * ST * kRows + threadIdx.x;
-                l = q < tokens ? lse_b[q] * kLog2e : INFINITY;   // a query past the last token: P = 0
+                l = q < tokens ? lse_b[q] * kLse : INFINITY;   // a query past the last token: P = 0
             }
         };
         auto store = [&](int buf) {
@@ -419,20 +467,20 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
                     const T* Qs = lds[s & 1][0] + u * tile_elems<T>();
                     const T* dOs = lds[s & 1][1] + u * tile_elems<T>();
                     f32x16 p = zero16(), dp = zero16();   // element e: query 8*(e/4) + 4h + e%4 of the tile
-                    mma_rows(p, Qs, kf, lane);
-                    mma_rows(dp, dOs, vf, lane);
+                    mma_rows<2>(p, Qs, kf, lane);
+                    mma_rows<1>(dp, dOs, vf, lane);
 #pragma unroll
                     for (int g = 0; g < 4; ++g) {
                         const f32x4 lq = *reinterpret_cast<const f32x4*>(&consts[s & 1][0][u * kRows + 8 * g + 4 * h]);
                         const f32x4 dq = *reinterpret_cast<const f32x4*>(&consts[s & 1][1][u * kRows + 8 * g + 4 * h]);
 #pragma unroll
                         for (int x = 0; x < 4; ++x) {
-                            p[4 * g + x] = __builtin_amdgcn_exp2f(fmaf(p[4 * g + x], cexp, -lq[x]));
+                            p[4 * g + x] = prob(p[4 * g + x], lq[x]);
                             dp[4 * g + x] = p[4 * g + x] * (dp[4 * g + x] - dq[x]);
                         }
                     }
-                    mma_tr(dv, dOs, p, lane);
-                    mma_tr(dk, Qs, dp, lane);
+                    mma_tr<TR_PARTS>(dv, dOs, p, lane);
+                    mma_tr<TR_PARTS>(dk, Qs, dp, lane);
                 }
             }
             if (s + 1 < stages) store((s + 1) & 1);
@@ -457,7 +505,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
             delta = RowOp<T>::dot(df, of);
             delta += __shfl_xor(delta, 32, 64);
         }
-        const float lq = ok ? lse_b[i] * kLog2e : 0.f;
+        const float lq = ok ? lse_b[i] * kLse : 0.f;
         f32x16 dq[2] = {zero16(), zero16()};
         Stream<T> sk, sv;
         sk.init(Qb + 64, ldq, tokens);
@@ -478,8 +526,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
                     const T* Ks = lds[s & 1][0] + u * tile_elems<T>();
                     const T* Vs = lds[s & 1][1] + u * tile_elems<T>();
                     f32x16 p = zero16(), dp = zero16();   // element e: key 8*(e/4) + 4h + e%4 of the tile
-                    mma_rows(p, Ks, qf, lane);
-                    mma_rows(dp, Vs, df, lane);
+                    mma_rows<2>(p, Ks, qf, lane);
+                    mma_rows<1>(dp, Vs, df, lane);
                     if (s + 1 == stages) {   // keys past the last token: P = 0
                         const int lim = tokens - (s * ST + u) * kRows - 4 * h;
 #pragma unroll
@@ -487,8 +535,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
                             if (8 * (e >> 2) + (e & 3) >= lim) p[e] = -INFINITY;
                     }
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) dp[e] = __builtin_amdgcn_exp2f(fmaf(p[e], cexp, -lq)) * (dp[e] - delta);
-                    mma_tr(dq, Ks, dp, lane);
+                    for (int e = 0; e < 16; ++e) dp[e] = prob(p[e], lq) * (dp[e] - delta);
+                    mma_tr<TR_PARTS>(dq, Ks, dp, lane);
                 }
             }
             if (s + 1 < stages) {
@@ -536,12 +584,12 @@ hipError_t launch_attn_fwd_stream(int dtype, const void* qkv, long ldq, void* o,
     return hipGetLastError();
 }
 
-template <typename T>
+template <typename T, int TR_PARTS>
 static hipError_t launch_bwd(const void* qkv, long ldq, const void* o, long ldo, const float* lse, const void* d_o, long ld_do,
                              void* dqkv, long ld_dqkv, float* bsum, int batch, int tokens, int n_full, hipStream_t s) {
     const int blocks = attn_stream_blocks(tokens);
     const dim3 grid((unsigned)(2L * batch * n_full * blocks)), block(64 * kWaves);
-    auto kern = attn_bwd_stream_kernel<T>;
+    auto kern = attn_bwd_stream_kernel<T, TR_PARTS>;
     const T *q = (const T*)qkv, *op = (const T*)o, *dop = (const T*)d_o;
     T* dq = (T*)dqkv;
     const long rows = (long)batch * tokens;
@@ -556,8 +604,9 @@ hipError_t launch_attn_bwd_stream(int dtype, const void* qkv, long ldq, const vo
                                   const void* d_o, long ld_do, void* dqkv, long ld_dqkv, float* bsum, int batch, int tokens,
                                   int n_full, hipStream_t s) {
     if (n_full <= 0) return hipSuccess;
-    return dtype == D2FT_F32 ? launch_bwd<float>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, batch, tokens, n_full, s)
-                             : launch_bwd<bf16>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, batch, tokens, n_full, s);
+    if (dtype == D2FT_F32) return launch_bwd<float, 1>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, batch, tokens, n_full, s);
+    if (tokens <= 224) return launch_bwd<bf16, 1>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, batch, tokens, n_full, s);
+    return launch_bwd<bf16, 3>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, batch, tokens, n_full, s);
 }
 
 }  // namespace d2ft

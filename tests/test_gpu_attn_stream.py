@@ -1,8 +1,10 @@
 """GPU parity of the streaming attention kernels (kernels_attn_stream.hip) through one block forward + backward: token
 counts at and beside the edges of tiles, stages and workgroups, the smallest and the largest."""
+import numpy as np
 import pytest
 
 import d2ft_inputs as di
+from helpers import TOL, gpu_block, oracle_block, rel_inf
 from test_gpu_block import run_case
 
 pytestmark = pytest.mark.gpu
@@ -28,3 +30,95 @@ def test_most_tokens(dtype):
 @pytest.mark.parametrize("tokens", [17, 64, 65, 128, 129, 197, 224])
 def test_bf16_few_pairs_below_225_tokens(tokens):
     run_case(di.Workload("stream_few", 3, tokens, 128, 3, 64, 64, 1, "bf16"), [FULL, FWD, FULL], seed=84)
+
+
+# ---------------------------------------------------------------------------
+# crafted scores: one head, tokens x = s * e with e = (+1, -1, ..) and s = +-1, so that LayerNorm gives exactly x
+# ---------------------------------------------------------------------------
+E = np.where(np.arange(64) % 2 == 0, 1.0, -1.0).astype(np.float32)
+
+
+def crafted(s, dtype, q, k, v, w_o, ln_eps=1e-6):
+    """Workload, weights and x of one image of len(s) tokens.  q, k, v: (constant, coefficient of s) per channel [64]."""
+    T = len(s)
+    w = di.Workload("crafted", 1, T, 64, 1, 64, 64, 1, dtype, ln_eps=ln_eps)
+    z = lambda *sh: np.zeros(sh, np.float32)
+    w_qkv, b_qkv = z(3, 1, 64, 64), z(3, 1, 64)
+    for p, (const, coef) in enumerate((q, k, v)):
+        b_qkv[p, 0] = const
+        w_qkv[p, 0] = (np.broadcast_to(np.asarray(coef, np.float32), 64) / 64)[:, None] * E[None, :]
+    wt = {"ln1_g": z(64) + 1, "ln1_b": z(64), "w_qkv": w_qkv, "b_qkv": b_qkv, "w_o": np.eye(64, dtype=np.float32) * np.float32(w_o),
+          "b_o": z(64), "ln2_g": z(64) + 1, "ln2_b": z(64), "w1": z(64, 64), "b1": z(64), "w2": z(64, 64), "b2": z(64)}
+    x = (np.asarray(s, np.float32)[:, None] * E[None, :])[None]
+    return w, wt, x
+
+
+def channel(c, value):
+    a = np.zeros(64, np.float32)
+    a[c] = value
+    return a
+
+
+@pytest.mark.parametrize("tokens", [258, 288, 578])
+def test_bf16_probabilities_keep_their_bits(tokens):
+    """Two kinds of keys whose probabilities differ by 2^-10 of themselves, less than bf16 resolves, and values that
+    cancel: O and dV are that difference alone."""
+    s = np.where(np.arange(tokens) % 2 == 0, 1.0, -1.0)
+    a = channel(0, 2.0 ** -4)
+    w, wt, x = crafted(s, "bf16", (0, a), (0, a), (0, 1.0), 2.0 ** 14)
+    dy = (s[:, None] * np.full((1, 64), 2.0 ** -14))[None].astype(np.float32)
+    y, _, g = gpu_block(w, wt, [FULL], x, dy, ("w_qkv",))
+    ry, _, rg, _ = oracle_block(w, wt, [FULL], x, dy)
+    # O and dV are rounded to bf16 once (2^-9), the weight gradient again
+    assert rel_inf(y, ry) < 1e-2 and rel_inf(g["w_qkv"][2], rg["w_qkv"][2]) < 1e-2
+
+
+def test_bf16_score_gradients_keep_their_bits():
+    """Equal probabilities and score gradients of two sizes whose sum is zero, multiplied with 128 +- 1: rounded to bf16
+    they leave a rest of 2.5 % of the result."""
+    s = np.where(np.arange(288) % 6 == 0, 1.0, -1.0)
+    w, wt, x = crafted(s, "bf16", (channel(0, 128), channel(0, 1)), (channel(1, 128), channel(1, 1)), (2.0, 3.0), 1.0)
+    dy = ((2 + 3 * s)[:, None] * np.ones((1, 64)))[None].astype(np.float32)
+    _, _, g = gpu_block(w, wt, [FULL], x, dy, ("w_qkv",))
+    rg = oracle_block(w, wt, [FULL], x, dy)[2]
+    for p in (0, 1):
+        assert rel_inf(g["w_qkv"][p], rg["w_qkv"][p]) < 1e-2
+
+
+def test_fp32_probability_of_a_single_key_is_one():
+    """Scores of some 1e5: in one multiply-add with a rounded log-sum-exp the exponent would be off by 1e-2."""
+    rng = np.random.default_rng(85)
+    w = di.Workload("one_key", 8, 1, 64, 1, 64, 64, 1, "f32")
+    _, wt, _ = crafted([1.0], "f32", (rng.standard_normal(64) * 600, 1.0), (rng.standard_normal(64) * 600, 1.0), (0, 1.0), 1.0)
+    x = rng.standard_normal((8, 1, 64)).astype(np.float32)
+    dy = rng.standard_normal((8, 1, 64)).astype(np.float32)
+    _, _, g = gpu_block(w, wt, [FULL], x, dy, ("w_qkv",))
+    rg = oracle_block(w, wt, [FULL], x, dy)[2]
+    assert rel_inf(g["w_qkv"][2], rg["w_qkv"][2]) < 1e-5   # sums of eight fp32 products
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("slope", [0.4, -0.4])
+@pytest.mark.parametrize("tokens", [100, 577])
+def test_maximum_in_every_stage(dtype, slope, tokens):
+    """Scores that rise (or fall) by slope / 8 per token: the running maximum moves in every stage, or never."""
+    rng = np.random.default_rng(86)
+    n = np.arange(tokens)
+    bits = np.where((n[:, None] >> np.arange(10)) & 1, 1.0, -1.0)
+    x = np.concatenate([bits, -bits, np.broadcast_to(E[:44], (tokens, 44))], 1).astype(np.float32)[None]   # LayerNorm gives x
+    w, wt, _ = crafted([1.0] * tokens, dtype, (0, 0), (0, 0), (0, 0), 4.0)
+    half = 2.0 ** np.arange(10) / 2                       # key channel b: bit b of the position, times 2^b
+    wt["b_qkv"][0, 0, :10] = di.round_to_bf16(np.full(1, slope, np.float32)) if dtype == "bf16" else slope
+    wt["b_qkv"][1, 0, :10] = half
+    wt["w_qkv"][1, 0, np.arange(10), np.arange(10)] = half
+    wt["w_qkv"][2, 0] = np.sign(rng.standard_normal((64, 64))) / 8
+    dy = np.sign(rng.standard_normal(x.shape)).astype(np.float32)
+    fields = ("w_qkv", "w_o")
+    y, dx, g = gpu_block(w, wt, [FULL], x, dy, fields)
+    ry, rdx, rg, _ = oracle_block(w, wt, [FULL], x, dy)
+    errs = {"y": rel_inf(y, ry), "dx": rel_inf(dx, rdx), "w_o": rel_inf(g["w_o"], rg["w_o"])}
+    # With bf16 storage the sum of a query's score gradients is not zero but the rounding of its O, up to 2^-9, and keys of up
+    # to 512 multiply it: dW_q may be off by 2^-9 * 512 of a score gradient whatever the kernel.  The other planes are not.
+    for p in (0, 1, 2) if dtype == "f32" else (1, 2):
+        errs[p] = rel_inf(g["w_qkv"][p], rg["w_qkv"][p])
+    assert max(errs.values()) <= TOL[dtype], errs
