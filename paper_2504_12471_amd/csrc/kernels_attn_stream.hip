@@ -305,7 +305,9 @@ __global__ __launch_bounds__(64 * kWaves, 3) void attn_fwd_stream_kernel(const T
     RowOp<T> qf;
     qf.load(Qb + (long)q * ldq, q < tokens, h);
     f32x16 ot[2] = {zero16(), zero16()};
-    float m = -INFINITY, sum = 0.f;      // of the raw scores; sum over this lane's keys only
+    // of the raw scores; sum over this lane's keys only.  The maximum starts at a finite value: a query whose scores so far
+    // are all minus infinity keeps a defined difference from it, and probabilities of zero.
+    float m = -3.402823466e38f, sum = 0.f;
     const float cexp = kScale * kLog2e;
     const int stages = (tokens + ST * kRows - 1) / (ST * kRows);
     sk.store(lds[0][0]);

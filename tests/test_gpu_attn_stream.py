@@ -122,3 +122,18 @@ def test_maximum_in_every_stage(dtype, slope, tokens):
     for p in (0, 1, 2) if dtype == "f32" else (1, 2):
         errs[p] = rel_inf(g["w_qkv"][p], rg["w_qkv"][p])
     assert max(errs.values()) <= TOL[dtype], errs
+
+
+@pytest.mark.parametrize("dtype,tokens", [("f32", 33), ("f32", 100), ("f32", 193), ("bf16", 300)])
+def test_scores_that_overflow_to_minus_infinity(dtype, tokens):
+    """Keys whose scores are below fp32's range have no part in the softmax, wherever they stand: here one query's first
+    and last keys, whole tiles and stages of them."""
+    n = np.arange(tokens)
+    s = np.where((n < min(70, tokens // 2)) | (n > tokens - 4), -1.0, 1.0)
+    big = 2.0 ** 66
+    # q = 2^66, k = 0 or -2^66 in the same channel; LayerNorm's epsilon is small enough for k to be exactly 0
+    w, wt, x = crafted(s, dtype, (channel(0, big), 0), (channel(0, -big / 2), channel(0, big / 2)), (0.5, 1.0), 4.0, ln_eps=1e-12)
+    dy = ((2 + s)[:, None] * np.ones((1, 64)))[None].astype(np.float32)
+    y, _, g = gpu_block(w, wt, [FULL], x, dy, ("w_qkv",))
+    ry, _, rg, _ = oracle_block(w, wt, [FULL], x, dy)
+    assert rel_inf(y, ry) < TOL[dtype] and rel_inf(g["w_qkv"][2], rg["w_qkv"][2]) < TOL[dtype]
