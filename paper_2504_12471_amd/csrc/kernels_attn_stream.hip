@@ -432,7 +432,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
             so.fetch(s * ST * kRows);
             if (threadIdx.x < ST * kRows) {
                 const int q = s * ST * kRows + threadIdx.x;
-                l = q < tokens ? lse_b[q] * kLse : INFINITY;   // a query past the last token: P = 0
+                l = q < tokens ? lse_b[q] * kLse : 0.f;
             }
         };
         auto store = [&](int buf) {
@@ -480,6 +480,12 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
                             p[4 * g + x] = prob(p[4 * g + x], lq[x]);
                             dp[4 * g + x] = p[4 * g + x] * (dp[4 * g + x] - dq[x]);
                         }
+                    }
+                    if (s + 1 == stages) {   // queries past the last token: also under keys and values that are not finite
+                        const int lim = tokens - (s * ST + u) * kRows - 4 * h;
+#pragma unroll
+                        for (int e = 0; e < 16; ++e)
+                            if (8 * (e >> 2) + (e & 3) >= lim) p[e] = dp[e] = 0.f;
                     }
                     mma_tr<TR_PARTS>(dv, dOs, p, lane);
                     mma_tr<TR_PARTS>(dk, Qs, dp, lane);

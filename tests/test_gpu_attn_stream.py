@@ -137,3 +137,21 @@ def test_scores_that_overflow_to_minus_infinity(dtype, tokens):
     y, _, g = gpu_block(w, wt, [FULL], x, dy, ("w_qkv",))
     ry, _, rg, _ = oracle_block(w, wt, [FULL], x, dy)
     assert rel_inf(y, ry) < TOL[dtype] and rel_inf(g["w_qkv"][2], rg["w_qkv"][2]) < TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype,tokens", [("f32", 33), ("f32", 197), ("bf16", 300)])
+def test_keys_that_are_not_finite_reach_no_query_past_the_last(dtype, tokens):
+    """A key of minus infinity under positive queries has probability zero, and its dV is zero, not NaN from 0 * infinity
+    with the empty rows of the last tile."""
+    s = np.where(np.arange(tokens) == 5, -1.0, 1.0)
+    w, wt, x = crafted(s, dtype, (channel(0, 1.0), 0), (0, 0), (0.5, 1.0), 4.0, ln_eps=1e-12)
+    # k of token 5: -(max + max), of the others: max - max
+    top = float(np.float32(3.4e38) if dtype == "f32" else di.round_to_bf16(np.full(1, 3.3e38, np.float32))[0])
+    wt["w_qkv"][1, 0, 0, 0] = top
+    wt["b_qkv"][1, 0, 0] = -top
+    dy = np.ones(x.shape, np.float32)
+    y, _, g = gpu_block(w, wt, [FULL], x, dy, ("w_qkv",))
+    # the same without that key: its probability is zero either way
+    wt["w_qkv"][1, 0, 0, 0], wt["b_qkv"][1, 0, 0] = 2.0 ** 20, -(2.0 ** 20)
+    ry, _, rg, _ = oracle_block(w, wt, [FULL], x, dy)
+    assert rel_inf(y, ry) < TOL[dtype] and rel_inf(g["w_qkv"][2], rg["w_qkv"][2]) < TOL[dtype]
