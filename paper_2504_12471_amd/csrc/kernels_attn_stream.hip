@@ -224,22 +224,27 @@ __device__ __forceinline__ void store_row(const f32x16 (&t)[2], float mul, float
 }
 
 // One operand of a stage: kStage tiles of 32 rows, this thread's 16-byte pieces on their way from memory to LDS.  The
-// buffer's declared size ends with the last valid row, rows beyond it read as zeros.
-template <typename T>
+// buffer's declared size ends with the last valid row, rows beyond it read as zeros; REPEAT: as the last valid row, so
+// that a probability of zero times them is not finite only where that row's own product is not.
+template <typename T, bool REPEAT = false>
 struct Stream {
     static constexpr int kPer = Tile<T>::kStage * kRows * Tile<T>::kPieces / (64 * kWaves);   // pieces per thread
     static constexpr int kStep = 64 * kWaves / Tile<T>::kPieces;                              // rows between them
     __amdgpu_buffer_rsrc_t rsrc;
-    uint32_t off, ld_bytes;
+    uint32_t off, ld_bytes, last;
     u32x4 v[kPer];
     __device__ __forceinline__ void init(const T* p, long ld, int tokens) {
         ld_bytes = (uint32_t)ld * (uint32_t)sizeof(T);
         rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(p), 0, (uint32_t)(tokens - 1) * ld_bytes + 64u * (uint32_t)sizeof(T), 0x00020000);
         off = (uint32_t)(threadIdx.x / Tile<T>::kPieces) * ld_bytes + (uint32_t)(threadIdx.x % Tile<T>::kPieces) * 16u;
+        last = (uint32_t)(tokens - 1) * ld_bytes + (uint32_t)(threadIdx.x % Tile<T>::kPieces) * 16u;
     }
     __device__ __forceinline__ void fetch(int row0) {
 #pragma unroll
-        for (int k = 0; k < kPer; ++k) v[k] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off + (uint32_t)(row0 + k * kStep) * ld_bytes, 0, 0);
+        for (int k = 0; k < kPer; ++k) {
+            const uint32_t at = off + (uint32_t)(row0 + k * kStep) * ld_bytes;
+            v[k] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, REPEAT ? min(at, last) : at, 0, 0);
+        }
     }
     __device__ __forceinline__ void store(T* lds) const {   // lds: kStage tiles, one after the other
 #pragma unroll
@@ -421,7 +426,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
         kf.load(Qb + (long)i * ldq + 64, ok, h);
         vf.load(Qb + (long)i * ldq + 128, ok, h);
         f32x16 dk[2] = {zero16(), zero16()}, dv[2] = {zero16(), zero16()};
-        Stream<T> sq, sd, so;
+        Stream<T, true> sq, sd, so;
         sq.init(Qb, ldq, tokens);
         sd.init(dOb, ld_do, tokens);
         so.init(Ob, ldo, tokens);
@@ -432,7 +437,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
             so.fetch(s * ST * kRows);
             if (threadIdx.x < ST * kRows) {
                 const int q = s * ST * kRows + threadIdx.x;
-                l = q < tokens ? lse_b[q] * kLse : 0.f;
+                l = q < tokens ? lse_b[q] * kLse : INFINITY;   // a query past the last token: P = 0
             }
         };
         auto store = [&](int buf) {
@@ -481,12 +486,6 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
                             dp[4 * g + x] = p[4 * g + x] * (dp[4 * g + x] - dq[x]);
                         }
                     }
-                    if (s + 1 == stages) {   // queries past the last token: also under keys and values that are not finite
-                        const int lim = tokens - (s * ST + u) * kRows - 4 * h;
-#pragma unroll
-                        for (int e = 0; e < 16; ++e)
-                            if (8 * (e >> 2) + (e & 3) >= lim) p[e] = dp[e] = 0.f;
-                    }
                     mma_tr<TR_PARTS>(dv, dOs, p, lane);
                     mma_tr<TR_PARTS>(dk, Qs, dp, lane);
                 }
@@ -497,7 +496,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
             store_row(dk, kScale, dQb + (long)i * ld_dqkv + 64, h, ok);
             store_row(dv, 1.f, dQb + (long)i * ld_dqkv + 128, h, ok);
         }
-        if (bsum) {   // softmax does not see a common shift of the keys: the columns of dK sum to zero
+        if (bsum) {
             float* const row = bsum + ((long)b * blocks + id % blocks) * n_full * 192 + j * 192;
             if (threadIdx.x < 64) row[64 + threadIdx.x] = 0.f;
             store_colsum(dv, 1.f, ok, reinterpret_cast<float*>(lds), red, row + 128);
