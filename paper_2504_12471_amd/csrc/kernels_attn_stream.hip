@@ -498,7 +498,12 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
         }
         if (bsum) {
             float* const row = bsum + ((long)b * blocks + id % blocks) * n_full * 192 + j * 192;
-            if (threadIdx.x < 64) row[64 + threadIdx.x] = 0.f;
+            // softmax does not see a common shift of the keys: the columns of dK sum to zero, unless some are not finite
+            float odd = 0.f;   // stays 0, or becomes NaN
+#pragma unroll
+            for (int e = 0; e < 16; ++e) odd = fmaf(dk[0][e], 0.f, fmaf(dk[1][e], 0.f, odd));
+            if (__syncthreads_or(ok && odd != 0.f)) store_colsum(dk, kScale, ok, reinterpret_cast<float*>(lds), red, row + 64);
+            else if (threadIdx.x < 64) row[64 + threadIdx.x] = 0.f;
             store_colsum(dv, 1.f, ok, reinterpret_cast<float*>(lds), red, row + 128);
         }
     } else {

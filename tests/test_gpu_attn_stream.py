@@ -5,7 +5,7 @@ import pytest
 
 import d2ft_inputs as di
 from helpers import TOL, gpu_block, oracle_block, rel_inf
-from test_gpu_block import run_case
+from test_gpu_block import draw_block, run_case
 
 pytestmark = pytest.mark.gpu
 
@@ -155,3 +155,14 @@ def test_keys_that_are_not_finite_reach_no_query_past_the_last(dtype, tokens):
     wt["w_qkv"][1, 0, 0, 0], wt["b_qkv"][1, 0, 0] = 2.0 ** 20, -(2.0 ** 20)
     ry, _, rg, _ = oracle_block(w, wt, [FULL], x, dy)
     assert rel_inf(y, ry) < TOL[dtype] and rel_inf(g["w_qkv"][2], rg["w_qkv"][2]) < TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype,tokens", [("f32", 65), ("f32", 197), ("bf16", 300)])
+def test_key_bias_gradient_shows_what_is_not_finite(dtype, tokens):
+    w = di.Workload("nan_token", 2, tokens, 128, 2, 64, 64, 1, dtype)
+    x, wt, dy = draw_block(w, 87)
+    clean = gpu_block(w, wt, [FULL, FULL], x, dy, ("b_qkv",))[2]["b_qkv"]
+    assert np.all(clean[1] == 0)   # a common shift of the keys changes nothing
+    x[1, 3, 5] = np.nan
+    b = gpu_block(w, wt, [FULL, FULL], x, dy, ("b_qkv",))[2]["b_qkv"]
+    assert np.isnan(b).all()
