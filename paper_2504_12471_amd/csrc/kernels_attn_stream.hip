@@ -572,13 +572,22 @@ bool attn_stream_supported(int dtype, int tokens, long ldq, long ldo) {
     return tokens >= 1 && mult8(ldq) && mult8(ldo) && (long)(tokens + 63) * (ldq > ldo ? ldq : ldo) * es < (1L << 31);   // 32-bit offsets
 }
 
-// bf16 backward of up to 224 tokens: against the kernel with one workgroup per pair, which needs a round of the chip for up
-// to 256 pairs however few they are.  197 tokens: 12 pairs 11.1 against 16.6 us, 112 14.2 and 17.7, 320 33.5 and 36.3,
-// 448 44.0 and 39.9, 768 68 and 61.  Where the tokens fill this kernel's blocks of 128, or half of one, it is the better
-// one at any number: 128 tokens, 448 pairs 18.9 and 23.9 us; 50 tokens, 768 pairs 14.6 and 19.9 us (but 96 tokens 27.6
-// and 24.2).
+// bf16 backward of up to 224 tokens, against the kernel of kernels_attn_mfma.hip with one workgroup per pair, which needs a
+// round of the chip however few the pairs are.  This one has two workgroups per pair and block of 128 tokens, and 512 of
+// them fill the chip.
+//   129 to 224 tokens (two blocks): 129 tokens, 12 pairs 9.3 against 12.2 us, 128 pairs 12.0 and 13.1, 136 pairs 18.5 and
+//     13.0; 197 tokens, 12 pairs 10.9 and 16.8, 128 pairs 14.4 and 18.4, 136 pairs 22.1 and 18.4.
+//   97 to 128: 97 tokens, 256 pairs 10.9 and 11.9, 320 pairs 15.7 and 20.6, 2048 pairs 69 and 86; 128 tokens, 768 pairs 35.4
+//     and 37.6, 2048 pairs 82 and 92.
+//   49 to 64: the other kernel takes 512 pairs a round, so this one wins where the last round is at most half full: 64
+//     tokens, 256 pairs 7.9 and 9.2, 260 pairs 11.2 and 10.3, 512 pairs 12.7 and 12.4, 520 pairs 15.5 and 19.3, 1024 pairs
+//     27.2 and 24.6, 1152 pairs 30.2 and 31.1.
+//   the rest: 96 tokens, 160 pairs 9.6 and 9.7, 320 pairs 15.7 and 14.0; 17 tokens, 160 pairs 5.8 and 6.4.
 bool attn_bwd_stream_faster(int tokens, int pairs) {
-    return pairs <= 160 || (tokens > 96 && tokens <= 128) || (tokens > 48 && tokens <= 64);
+    if (tokens > 128) return pairs <= 128;
+    if (tokens > 96) return true;
+    if (tokens > 48 && tokens <= 64) return pairs % 512 > 0 && pairs % 512 <= 256;
+    return pairs <= 160;
 }
 
 hipError_t launch_attn_fwd_stream(int dtype, const void* qkv, long ldq, void* o, long ldo, float* lse, int batch, int tokens,

@@ -166,3 +166,18 @@ def test_key_bias_gradient_shows_what_is_not_finite(dtype, tokens):
     x[1, 3, 5] = np.nan
     b = gpu_block(w, wt, [FULL, FULL], x, dy, ("b_qkv",))[2]["b_qkv"]
     assert np.isnan(b).all()
+
+
+@pytest.mark.parametrize("tokens,images,stream", [(129, 32, True), (129, 33, False), (128, 33, True), (96, 40, True), (96, 41, False),
+                                                  (64, 64, True), (64, 65, False), (49, 128, False), (49, 129, True)])
+def test_which_kernel_runs_the_bf16_backward(tokens, images, stream):
+    """Four heads per image: beside the counts of pairs at which the streamed kernel stops being the faster one."""
+    import paper_2504_12471_amd as P
+    w = di.Workload("which", images, tokens, 64, 4, 64, 64, 1, "bf16")
+    P.d2ft_timing_enable(True)
+    try:
+        run_case(w, [FULL] * 4, seed=88)
+        names = {r["name"] for r in P.d2ft_timing_read()}
+    finally:
+        P.d2ft_timing_enable(False)
+    assert ("attn_bwd_stream" in names) == stream and ("attn_bwd_mfma" in names) == (not stream), names
