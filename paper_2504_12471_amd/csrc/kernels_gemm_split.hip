@@ -1,19 +1,21 @@
 // fp32 products on the bf16 matrix cores: every operand element is cut into three bf16 parts, x = hi + mid + lo, and six
 // of the nine products of parts are summed in fp32,
 //   a b = (hi lo + lo hi + mid mid + hi mid + mid hi) + hi hi,
-// what is left out (mid lo, lo mid, lo lo) being below 2^-25 of the product.  The parts are exact: 8 + 8 + 8 significant
-// bits.  Against fp64, relative 2-norm error over normal inputs, K = 384 / 768 / 1536: this kernel 1.1e-7 / 1.5e-7 /
+// what is left out (mid lo, lo mid, lo lo) being below 2^-25 of the product.  The parts are exact, 8 + 8 + 8 significant
+// bits, because they are parts of x * 2^24: no bit of it is below bf16's smallest normal value, whatever x (parts of x itself
+// would lose bits below |x| = 2^-110).  The results are multiplied by 2^-48.  Against fp64, relative 2-norm error over normal inputs, K = 384 / 768 / 1536: this kernel 1.1e-7 / 1.5e-7 /
 // 2.5e-7, the fp32 matrix instruction 3.5e-7 / 4.9e-7 / 7.2e-7: sixteen products enter the accumulator per rounding instead
 // of two, and the small products have one of their own (in one accumulator with the others, with parts cut off instead
 // of rounded: 3.8e-7 / 5.5e-7 / 1.1e-6).
 //
-// A part of an infinity or NaN is a NaN, and a part may round up to infinity: a wavefront that finds a value that is not
-// finite among its results forms them again with the fp32 instruction, so those come out as they always did.
+// A part of an infinity or NaN is a NaN, an operand of 2^104 and more has no parts, and a scaled sum of 2^128 and more
+// overflows: a wavefront that finds a value that is not finite among its results forms them again with the fp32
+// instruction, so those come out as they always did.
 //
 //   C[m][n] = epilogue( sum_k A(m,k) * B(k,n) )
 //
 // A workgroup makes a 128 x 64 tile with four wavefronts of 64 x 32; a slab is 32 of k.  The next slab is in flight in
-// registers while the present one is multiplied; its parts are cut on the way to LDS, once per element and workgroup (5.5
+// registers while the present one is multiplied; its parts are cut on the way to LDS, once per element and workgroup (6.5
 // vector instructions per element).  LDS holds one slab (36 KB), so that four workgroups share a CU and some cut and
 // store while others multiply.  A 128 x 128 tile was measured equal (15760 x 1536 x 384: 120 us both) to slower.
 //
@@ -42,14 +44,17 @@ namespace {
 
 constexpr int BK = 32;
 constexpr int TM = 128, TN = 64;
+constexpr float kUp = 16777216.f;            // 2^24
+constexpr float kDown = 3.5527136788e-15f;   // 2^-48
+static_assert(kDown * kUp * kUp == 1.f, "powers of two");
 
-// eight floats -> their three parts, eight bf16 each
+// eight floats -> the three parts of them times kUp, eight bf16 each
 __device__ __forceinline__ void cut(const u32x4& x0, const u32x4& x1, u32x4 (&part)[3]) {
     float x[8];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        x[i] = __uint_as_float(x0[i]);
-        x[4 + i] = __uint_as_float(x1[i]);
+        x[i] = __uint_as_float(x0[i]) * kUp;
+        x[4 + i] = __uint_as_float(x1[i]) * kUp;
     }
 #pragma unroll
     for (int p = 0; p < 3; ++p)
@@ -243,7 +248,7 @@ __global__ __launch_bounds__(256, 4) void gemm_split_kernel(Args g) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < NT; ++j) acc[i][j] += low[i][j];
+        for (int j = 0; j < NT; ++j) acc[i][j] = (acc[i][j] + low[i][j]) * kDown;
 
     const int c = lane & 31, h = lane >> 5;
     // results that are not finite: again with the fp32 instruction, operands from memory

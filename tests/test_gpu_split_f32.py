@@ -76,3 +76,15 @@ def test_error_against_fp64_and_operands_without_parts():
     for part in (ok & ~big, ok & big):
         err = np.linalg.norm((got[part] - ref64[part]) / np.abs(ref64[part]).max()) / np.linalg.norm(ref64[part] / np.abs(ref64[part]).max())
         assert err < 1e-6, err
+
+
+@pytest.mark.parametrize("up", [-126, -120, -108, 110])
+def test_error_of_small_and_large_operands(up):
+    """Operands far from 1, subnormal ones among them: their parts hold every bit, or the fp32 instruction takes over."""
+    rng = np.random.default_rng(84)
+    images = np.ldexp(rng.standard_normal((32, 3, 224, 224)).astype(np.float32), up)
+    w = np.ldexp(rng.standard_normal((384, 768)).astype(np.float32), -up if abs(up) < 110 else (100 if up < 0 else -100))
+    ref = patches(images).astype(np.float64) @ w.astype(np.float64).T
+    got = patch_embed(images, w)
+    err = np.linalg.norm((got - ref) / np.abs(ref).max()) / np.linalg.norm(ref / np.abs(ref).max())
+    assert err < 1e-6, err   # as above
