@@ -27,6 +27,13 @@ struct Tile64Grouped {
 constexpr uint32_t kBufBytes = 0x80000000u;   // declared buffer size; operands are checked to be smaller
 constexpr uint32_t kOutside = 0x80000000u;    // any offset >= kBufBytes reads as zero
 
+// scalar offset of the loads of the slab at k0 (valid k < k_end), whose first k sits at k_at in memory.  The next slabs'
+// loads run past the end of K; there it is 0 and the lanes' own offsets are kOutside.  An offset beyond the buffer's size
+// must not be asked for: the bounds check compares the lane's offset with the size less the scalar one.
+__host__ __device__ __forceinline__ uint32_t slab_offset(int k0, int k_at, int k_end, uint32_t sk_bytes) {
+    return k0 < k_end ? (uint32_t)k_at * sk_bytes : 0u;
+}
+
 // workgroup -> tile: workgroup ids with the same value mod 8 (one XCD) get a contiguous range of tiles, walked in
 // groups of 8 tile rows, so that an XCD's workgroups share operand slabs through its L2
 __device__ __forceinline__ void tile_of_block(int pid, int total, int tiles_m, int tiles_n, int& tm, int& tn, int& split) {

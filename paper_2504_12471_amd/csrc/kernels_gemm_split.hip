@@ -101,11 +101,12 @@ struct Loader {
     }
     // the slab at k0 (valid k < k_end) whose first k sits at k_at in memory
     __device__ __forceinline__ void fetch(int k0, int k_at, int k_end) {
+        const uint32_t slab = slab_offset(k0, k_at, k_end, sk);
 #pragma unroll
         for (int c = 0; c < kN; ++c) {
             const uint32_t at = k_in[c] < k_end - k0 ? base[c] : kOutside;
-            raw[c][0] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, at, (uint32_t)k_at * sk, 0);
-            raw[c][1] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, at + 16u, (uint32_t)k_at * sk, 0);
+            raw[c][0] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, at, slab, 0);
+            raw[c][1] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, at + 16u, slab, 0);
         }
     }
     __device__ __forceinline__ void cut_all(u32x4 (&part)[kN][3]) const {

@@ -92,9 +92,10 @@ struct Loader {
     }
     // the slab at k0 (valid k < k_end) whose first k sits at k_at in memory
     __device__ __forceinline__ void load(u32x4 (&v)[kN], int k0, int k_at, int k_end) const {
+        const uint32_t slab = slab_offset(k0, k_at, k_end, sk);
 #pragma unroll
         for (int c = 0; c < kN; ++c)
-            v[c] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, k_in[c] < k_end - k0 ? base[c] : kOutside, (uint32_t)k_at * sk, 0);
+            v[c] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, k_in[c] < k_end - k0 ? base[c] : kOutside, slab, 0);
     }
     static __device__ __forceinline__ void store(const u32x4 (&v)[kN], unsigned char* slab, int t) {
 #pragma unroll
