@@ -56,7 +56,9 @@ typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 // 64-bit select per use)
 typedef __attribute__((address_space(3))) bf16 lds_bf16;
 constexpr uint32_t kBufBytes = 0x80000000u;   // declared buffer size; operands are checked to be smaller
-constexpr uint32_t kOutside = 0x80000000u;    // any offset >= kBufBytes reads as zero
+// Any offset >= kBufBytes reads as zero, under any scalar offset below kBufBytes: the bounds check compares the lane's
+// offset with the size less the scalar one.
+constexpr uint32_t kOutside = 0x80000000u;
 
 template <int BI, int BK, bool COL, int kThreads>
 struct SlabLoader {
@@ -101,6 +103,7 @@ struct SlabLoader {
         const uint32_t kstart = REMAP_K ? (uint32_t)tbl.start[k0 >> 6] : (uint32_t)k0;
         uint32_t koff = kstart * sk_bytes;   // uniform over the workgroup
         if constexpr (kOneBase) koff += (uint32_t)(c * kRowStep) * sk_bytes;
+        if constexpr (kOneBase && TAIL) koff = min(koff, kBufBytes - 1u);   // rows past the end: see the bounds check above
         const uint32_t mine = base[kOneBase ? 0 : c];
         const uint32_t off = (!TAIL || k_local(c) < k_end - k0) ? mine : kOutside;
         v[c] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, koff, 0);
