@@ -27,6 +27,7 @@
 // fragment reads are free of bank conflicts (piece_offset).  Operands with K strided stay in their natural
 // [k][index] layout: bf16 fragments come out of it by the transposing read, fp32 ones by plain 4-byte reads.
 #include <hip/hip_ext.h>
+#include <atomic>
 #include <type_traits>
 #include <utility>
 
@@ -394,11 +395,14 @@ hipError_t launch_wk(unsigned grid, hipStream_t s, const Args& a) {
     auto kern = gemm_tile64_kernel<T, TM, TN, A_COL, B_COL, WK, Args>;
     constexpr int lds = WK * group_bytes<TM, TN>(), threads = 64 * group_waves<TM, TN>() * WK;
     if constexpr (lds > 64 * 1024) {
-        static bool attr_set = false;
-        if (!attr_set) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        static std::atomic<uint32_t> set_on{0};   // devices, one bit each: the attribute belongs to a device's copy of the kernel
+        int dev = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        if (dev >= 32 || !(set_on.load() >> dev & 1)) {
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
             if (e != hipSuccess) return e;
-            attr_set = true;
+            if (dev < 32) set_on.fetch_or(1u << dev);
         }
     }
     if (hipEvent_t ev = launch_signal_take()) {   // the launch completes the event itself
