@@ -510,12 +510,14 @@ static hipError_t launch_tile(const GemmArgs& g, int wk, hipStream_t s) {
 
 template <typename T>
 static hipError_t launch_tile64(const GemmArgs& g, int dtype, hipStream_t s) {
-    if (g.partial || g.a_cs != 1) {
-        const long units = (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * (g.partial ? g.splits : 1);
-        const int slabs = (g.K / (g.partial ? g.splits : 1) + 128 / (int)sizeof(T) - 1) / (128 / (int)sizeof(T));
-        const int wk = pick_wk(units, slabs);
-        if (g.a_cs != 1) return launch_form<T, 64, 64, true, true>(wk, (unsigned)units, s, g);
-        return g.b_rs == 1 ? launch_form<T, 64, 64, false, false>(wk, (unsigned)units, s, g) : launch_form<T, 64, 64, false, true>(wk, (unsigned)units, s, g);
+    if constexpr (std::is_same<T, float>::value) {   // bf16: gemm_tile64_faster takes neither
+        if (g.partial || g.a_cs != 1) {
+            const long units = (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * (g.partial ? g.splits : 1);
+            const int slabs = (g.K / (g.partial ? g.splits : 1) + 31) / 32;
+            const int wk = pick_wk(units, slabs);
+            if (g.a_cs != 1) return launch_form<T, 64, 64, true, true>(wk, (unsigned)units, s, g);
+            return g.b_rs == 1 ? launch_form<T, 64, 64, false, false>(wk, (unsigned)units, s, g) : launch_form<T, 64, 64, false, true>(wk, (unsigned)units, s, g);
+        }
     }
     float us;
     const Tile64Form f = pick_form(g, dtype, &us);
