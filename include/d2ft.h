@@ -63,8 +63,8 @@ enum {
      *    written as +0.0.  1: gradients are added to what the buffers hold, and
      *    the slices of heads that are not p_f are left untouched. */
     D2FT_FLAG_ACCUM_GRADS = 1u,
-    /* bf16 only: run the vector-ALU kernels instead of the MFMA kernels (a cross-check
-     * of the two kernel families; fp32 calls ignore it). */
+    /* run the vector-ALU kernels instead of the matrix-core kernels (a cross-check of the
+     * two kernel families). */
     D2FT_FLAG_NO_MFMA = 2u,
     /* The op code of head h also governs hidden units [h*mlp_hidden/heads, (h+1)*mlp_hidden/heads)
      * of the feed-forward network, i.e. the whole subnet of Sec. II-A.1 (one attention head plus

@@ -281,7 +281,7 @@ bool on_mfma_path(const GemmArgs& g, const d2ft_block_desc* d) {
 // true if run_gemm takes the 64x64-tile path for g
 bool on_tile64_path(const GemmArgs& g, const d2ft_block_desc* d) {
     if (!gemm_tile64_supported(g, d->dtype)) return false;
-    return d->dtype == D2FT_F32 || (on_mfma_path(g, d) && g.tile_hint == 0 && gemm_tile64_faster(g));
+    return d->dtype == D2FT_F32 ? !(d->flags & D2FT_FLAG_NO_MFMA) : on_mfma_path(g, d) && g.tile_hint == 0 && gemm_tile64_faster(g);
 }
 // the paths that honour g.colsum
 bool colsum_supported(const GemmArgs& g, const d2ft_block_desc* d) { return on_mfma_path(g, d) || on_tile64_path(g, d); }
@@ -408,7 +408,7 @@ hipError_t run_attn_fwd(const d2ft_block_desc* d, const void* qkv, long ldq, voi
         g_timing.label = "attn_fwd_mfma";
         return launch_attn_fwd_mfma(qkv, ldq, o, ldo, lse, batch, tokens, n_live, n_full, s);
     }
-    if ((d->dtype == D2FT_F32 || !(d->flags & D2FT_FLAG_NO_MFMA)) && attn_stream_supported(d->dtype, tokens, ldq, ldo)) {
+    if (!(d->flags & D2FT_FLAG_NO_MFMA) && attn_stream_supported(d->dtype, tokens, ldq, ldo)) {
         g_timing.label = "attn_fwd_stream";
         return launch_attn_fwd_stream(d->dtype, qkv, ldq, o, ldo, lse, batch, tokens, n_live, n_full, s);
     }
@@ -423,7 +423,7 @@ static AttnBwd pick_attn_bwd(const d2ft_block_desc* d, int batch, int tokens, in
                              int* bands) {
     const bool mfma_ok = d->dtype == D2FT_BF16 && !(d->flags & D2FT_FLAG_NO_MFMA) && attn_bwd_mfma_supported(tokens, ldq, ldo) &&
                          (ld_do % 8) == 0 && (ld_dqkv % 8) == 0;
-    const bool stream_ok = (d->dtype == D2FT_F32 || !(d->flags & D2FT_FLAG_NO_MFMA)) && attn_stream_supported(d->dtype, tokens, ldq, ldo);
+    const bool stream_ok = !(d->flags & D2FT_FLAG_NO_MFMA) && attn_stream_supported(d->dtype, tokens, ldq, ldo);
     if (mfma_ok && !(stream_ok && attn_bwd_stream_faster(tokens, batch * n_full))) {
         *bands = 1;
         return ATTN_BWD_MFMA;
@@ -528,7 +528,7 @@ struct WeightGradBatch {
 void weight_grad_batch_init(WeightGradBatch* b, const d2ft_block_desc* d) {
     memset(b, 0, sizeof(*b));
     b->g.splits = 1;
-    b->enabled = d->dtype == D2FT_F32 || !(d->flags & D2FT_FLAG_NO_MFMA);
+    b->enabled = !(d->flags & D2FT_FLAG_NO_MFMA);
 }
 
 // queue dW[out_rows][out_cols] = Aop^T Bop (arguments as weight_grad); table_slot: which of the batch's three

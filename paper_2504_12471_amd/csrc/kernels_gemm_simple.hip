@@ -1,6 +1,6 @@
 // General strided GEMM on the vector ALUs with fp32 accumulation: the path for what the matrix-core
 // kernels do not take (odd strides, unaligned extents, operands of 2 GiB and more) and, with
-// D2FT_FLAG_NO_MFMA, the cross-check of the bf16 ones.  64x64 output tile per 256-thread workgroup,
+// D2FT_FLAG_NO_MFMA, the cross-check of those kernels.  64x64 output tile per 256-thread workgroup,
 // 4x4 outputs per thread, K staged through LDS 16 at a time.
 #include "d2ft_common.h"
 

@@ -49,3 +49,19 @@ def test_bf16_tile_edges(batch, tokens, width, heads, mlp):
 def test_bf16_gated_slices_through_the_remaps():
     w = di.Workload("tile64_gate_bf16", 1, 197, 256, 4, 64, 1024, 1, "bf16")
     run_gated(w, [FULL, SKIP, FWD, FULL], seed=74)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("lora", [0, 4])
+def test_vector_alu_kernels_on_request(dtype, lora):
+    """D2FT_FLAG_NO_MFMA: the other kernel family, in either type."""
+    import paper_2504_12471_amd as P
+    w = di.Workload("vector", 2, 65, 128, 3, 64, 264, 1, dtype, lora_rank=lora, lora_b_zero=False)
+    P.d2ft_timing_enable(True)
+    try:
+        run_case(w, [FULL, FWD, FULL], seed=75, flags=P.FLAG_NO_MFMA)
+        names = {r["name"] for r in P.d2ft_timing_read()}
+    finally:
+        P.d2ft_timing_enable(False)
+    assert {"gemm_simple_kernel", "attn_fwd_simple", "attn_bwd_simple"} <= names
+    assert not [n for n in names if "mfma" in n or "tile64" in n or "split" in n or "stream" in n], names
