@@ -169,6 +169,8 @@ struct GemmArgs {
 void launch_signal_next(hipEvent_t ev);
 bool launch_signal_pending();
 hipEvent_t launch_signal_take();
+// name of the kernel a launcher has picked, as a profiler prints it, for the timing record that is open; the string stays
+void launch_label(const char* name);
 hipError_t launch_gemm_simple(const GemmArgs& g, int dtype, hipStream_t s);
 // tiles of 64 or 32 with K split inside the workgroup (kernels_gemm_tile64.hip): every fp32 product whose operands span
 // less than 2 GiB, and the bf16 products that gemm_tile64_faster picks; hipErrorNotSupported otherwise.  Honours

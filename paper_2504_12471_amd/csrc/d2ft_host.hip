@@ -296,7 +296,6 @@ hipError_t run_gemm(const GemmArgs& g, const d2ft_block_desc* d, hipStream_t s, 
         if (colsum_bands) *colsum_bands = (g.M + 63) / 64;
         if (done) launch_signal_next(done);
         timing_begin(s, "gemm");
-        g_timing.label = "gemm_tile64_kernel";
         g_timing.flops = 2.0 * g.M * g.N * g.K;
         const hipError_t e = launch_gemm_tile64(g, d->dtype, s);
         timing_end(s);
@@ -661,8 +660,7 @@ d2ft_status weight_grad_flush(WeightGradBatch* b, const d2ft_block_desc* d, cons
     const int accum = (d->flags & D2FT_FLAG_ACCUM_GRADS) ? 1 : 0;
     hipError_t e = hipErrorNotSupported;
     if (d->dtype == D2FT_F32 || b->small) {
-        timing_begin(st, "gemm");
-        g_timing.label = "gemm_tile64_kernel";
+        timing_begin(st, "gemm");   // with the reduction, if K is split
         for (int i = 0; i < g.n_groups; ++i) g_timing.flops += 2.0 * g.grp[i].M * g.grp[i].N * s.M;
         e = launch_gemm_tile64_grouped(g, b->r, s.dtype, accum, part_floats, tail, st);
         timing_end(st);
@@ -746,6 +744,7 @@ void fill_tail_table(uint16_t (&t)[kMaxBlocks64], const Remap64& tbl) {
 }  // namespace
 
 void launch_signal_next(hipEvent_t ev) { g_launch_signal = ev; }
+void launch_label(const char* name) { g_timing.label = name; }
 bool launch_signal_pending() { return g_launch_signal != nullptr; }
 hipEvent_t launch_signal_take() {
     hipEvent_t ev = g_launch_signal;

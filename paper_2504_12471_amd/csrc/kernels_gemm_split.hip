@@ -381,7 +381,8 @@ __global__ __launch_bounds__(256) void reduce_split_kernel(Tile64Grouped g) {
 }
 
 template <typename Kernel, typename Args>
-hipError_t launch(Kernel kern, unsigned grid, hipStream_t s, const Args& a) {
+hipError_t launch(const char* name, Kernel kern, unsigned grid, hipStream_t s, const Args& a) {
+    launch_label(name);
     if (hipEvent_t ev = launch_signal_take()) hipExtLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, s, nullptr, ev, 0, a);
     else hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, s, a);
     return hipGetLastError();
@@ -405,8 +406,8 @@ float gemm_split_us(const GemmArgs& g) {
 
 hipError_t launch_gemm_split(const GemmArgs& g, hipStream_t s) {
     const unsigned grid = (unsigned)((g.M + TM - 1) / TM) * (unsigned)((g.N + TN - 1) / TN);
-    if (g.b_rs == 1) return launch(gemm_split_kernel<false, false, GemmArgs>, grid, s, g);
-    return launch(gemm_split_kernel<false, true, GemmArgs>, grid, s, g);
+    if (g.b_rs == 1) return launch("gemm_split_kernel<false, false, d2ft::GemmArgs>", gemm_split_kernel<false, false, GemmArgs>, grid, s, g);
+    return launch("gemm_split_kernel<false, true, d2ft::GemmArgs>", gemm_split_kernel<false, true, GemmArgs>, grid, s, g);
 }
 
 float gemm_split_grouped_plan(Tile64Grouped* a, size_t partial_floats) {
@@ -434,7 +435,7 @@ float gemm_split_grouped_plan(Tile64Grouped* a, size_t partial_floats) {
 }
 
 hipError_t launch_gemm_split_grouped(const Tile64Grouped& a, hipStream_t s) {
-    hipError_t e = launch(gemm_split_kernel<true, true, Tile64Grouped>, (unsigned)(a.units + a.tail.blocks), s, a);
+    hipError_t e = launch("gemm_split_kernel<true, true, d2ft::Tile64Grouped>", gemm_split_kernel<true, true, Tile64Grouped>, (unsigned)(a.units + a.tail.blocks), s, a);
     if (e != hipSuccess || a.splits == 1) return e;
     hipLaunchKernelGGL(reduce_split_kernel, dim3((unsigned)a.total_tiles, TM / 16), dim3(256), 0, s, a);
     return hipGetLastError();

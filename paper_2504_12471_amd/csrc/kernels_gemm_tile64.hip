@@ -27,6 +27,8 @@
 // fragment reads are free of bank conflicts (piece_offset).  Operands with K strided stay in their natural
 // [k][index] layout: bf16 fragments come out of it by the transposing read, fp32 ones by plain 4-byte reads.
 #include <hip/hip_ext.h>
+#include <stdio.h>
+
 #include <atomic>
 #include <type_traits>
 #include <utility>
@@ -390,8 +392,18 @@ __global__ __launch_bounds__(256) void reduce_tile64_kernel(Tile64Grouped g) {
     }
 }
 
+struct KernelName {
+    char s[96];
+    KernelName(const char* type, int tm, int tn, bool a_col, bool b_col, int wk, bool grouped) {
+        snprintf(s, sizeof(s), "gemm_tile64_kernel<%s, %d, %d, %s, %s, %d, d2ft::%s>", type, tm, tn, a_col ? "true" : "false",
+                 b_col ? "true" : "false", wk, grouped ? "Tile64Grouped" : "GemmArgs");
+    }
+};
+
 template <typename T, int TM, int TN, bool A_COL, bool B_COL, int WK, typename Args>
 hipError_t launch_wk(unsigned grid, hipStream_t s, const Args& a) {
+    static const KernelName name(sizeof(T) == 4 ? "float" : "__bf16", TM, TN, A_COL, B_COL, WK, std::is_same<Args, Tile64Grouped>::value);
+    launch_label(name.s);
     auto kern = gemm_tile64_kernel<T, TM, TN, A_COL, B_COL, WK, Args>;
     constexpr int lds = WK * group_bytes<TM, TN>(), threads = 64 * group_waves<TM, TN>() * WK;
     if constexpr (lds > 64 * 1024) {
