@@ -1205,7 +1205,8 @@ static d2ft_status block_bwd_impl(const d2ft_block_desc* desc, const d2ft_block_
         // leave that stream CUs: the launch is held to 128 workgroups, or to two runs of K per tile if that is
         // more.  Measured per step: vit_b16 (72 tiles) 2 runs 8.41 ms, the 3 runs the launch would pick alone 8.56,
         // 1 run 9.10; gated at 7 p_f subnets (42 tiles) 3 runs 7.18 ms, the 6 runs it would pick alone 7.39, 2 runs
-        // 7.26, everything in one launch behind the attention backward 7.30.
+        // 7.26, everything in one launch behind the attention backward 7.30.  The limit is for the 256x256 tiles: a
+        // small call's launch on 64x64 tiles (wgrads.small) is not held and covers the chip.
         if (side) {
             long tiles = 0;
             for (int i = 0; i < wgrads.g.n_groups; ++i)

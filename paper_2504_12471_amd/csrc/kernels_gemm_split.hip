@@ -10,7 +10,9 @@
 //
 // A part of an infinity or NaN is a NaN, an operand of 2^104 and more has no parts, and a scaled sum of 2^128 and more
 // overflows: a wavefront that finds a value that is not finite among its results forms them again with the fp32
-// instruction, so those come out as they always did.
+// instruction, so those come out as they always did.  That redo loads single elements: a pass over the small fp32 model (12
+// blocks, width 384, 80 images of 197 tokens) takes 22 ms, with an infinity in the output gradient 42 to 51 ms, with a NaN
+// in every image 82 ms.
 //
 //   C[m][n] = epilogue( sum_k A(m,k) * B(k,n) )
 //

@@ -10,8 +10,8 @@
 // What bounds it is the latency of two serial chains, n items forward and n items back.  Where the tables of a
 // knapsack fit the LDS of a CU (the change flags then as one bit per cell), one workgroup runs both stages and
 // the merge in it; otherwise one workgroup runs one stage with its tables in the workspace, where a step of either
-// chain is a round trip to L2.  144 items, capacities 259 and 1: 133 us for the two launches of the second form,
-// 43 us for the first (52 with a barrier for every item).
+// chain is a round trip to L2.  144 items, capacities 259 and 1, from a host call: 133 us for the two launches of the second
+// form, 43 us for the first (52 with a barrier for every item); back to back with warm caches 99 and 41 us.
 #include "d2ft_common.h"
 
 namespace d2ft {
@@ -159,8 +159,10 @@ bool knapsack_on_chip(int n_items, long cmax) {
     return padded <= (long)kLds / 32 && n_items <= (int)kLds / 16 && lds_bytes(n_items, padded) <= kLds;
 }
 
-// cmax: the largest capacity.  The LDS form costs a knapsack one workgroup of a whole CU: also with many of them it is
-// the better one, as the other form's steps are some ten times as long.
+// cmax: the largest capacity.  The LDS form, wherever the tables fit, also with many knapsacks, of which only as many run at
+// once as there are CUs with room for their tables: 12 items, 1 / 4096 knapsacks 5.4 / 11.0 us against 8.9 / 36.9 us for the
+// other form; 144 items, 1 / 256 / 4096 knapsacks 41 / 45 / 389 us against 99 / 120 / 947; 384 items (one table per CU),
+// 256 / 1024 knapsacks 156 / 601 us against 480 / 1255.
 hipError_t launch_knapsack(const KnapsackArgs& a, long cmax, uint8_t* ops_dev, hipStream_t s) {
     if (knapsack_on_chip(a.n_items, cmax)) {
         const long padded = (cmax + 64) / 64 * 64;
