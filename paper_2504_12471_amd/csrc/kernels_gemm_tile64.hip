@@ -480,22 +480,22 @@ bool gemm_tile64_supported(const GemmArgs& g, int dtype) {
 }
 
 // Tile and K groups of a product without split-K partials: the cheapest of the kernel's forms in microseconds,
-//   fixed + slabs * first + (rounds - 1) * (slabs * next + change),   rounds = workgroups per CU, rounded up:
-// a first round that waits for its loads, further ones beside it.  Fitted on this part to some 150 shapes per type
-// (M 64 .. 3152, N and K 64 .. 4096).  bf16: a CU's loads set the pace, so a slab costs in proportion to the tile's rows
+//   fixed + slabs * first + (rounds - 1) * (slabs * next + change) + rounds * gelu,   rounds = workgroups per CU, rounded up:
+// a first round that waits for its loads, further ones beside it.  Fitted on this part, bf16 to 1766 shapes (M 17 .. 12608,
+// N and K 64 .. 8192; rms error 5 to 8 %), fp32 to some 150 (M 64 .. 3152, N and K 64 .. 4096).  bf16: a CU's loads set the pace, so a slab costs in proportion to the tile's rows
 // + columns and a small tile pays where large ones leave CUs idle: 197 x 768 x 3072, 64x64 tiles 16.2 us, 64x32 12.3,
 // 32x32 8.9; 985 x 384 x 1536: 10.3, 8.6, 8.9; 985 x 2304 x 768: 13.6, 15.2, 17.2.  fp32: the matrix cores, so a slab
 // costs in proportion to the tile's area and what a small tile saves is the last, partly empty round: 197 x 2304 x 768:
 // 19.5, 20.7, 12.8; 3152 x 384 x 1536: 61, 51, 46; 3152 x 1536 x 384: 47.9, 52.4, 56.6.
 struct Tile64Form {
     int tm, tn, wk;
-    float fixed, first, next, change;   // us
+    float fixed, first, next, change, gelu;   // us
 };
-constexpr Tile64Form kFormsBf16[] = {{64, 64, 1, 3.2f, 0.37f, 0.17f, 0.8f},  {64, 64, 2, 3.9f, 0.27f, 0.20f, 1.0f},
-                                     {64, 32, 2, 3.4f, 0.23f, 0.10f, 1.1f},  {64, 32, 4, 4.0f, 0.183f, 0.0f, 4.7f},
-                                     {32, 32, 2, 3.0f, 0.198f, 0.08f, 0.5f}, {32, 32, 4, 3.9f, 0.102f, 0.10f, 1.2f}};
-constexpr Tile64Form kFormsF32[] = {{64, 64, 1, 4.4f, 0.61f, 0.52f, 3.0f}, {64, 32, 2, 3.4f, 0.37f, 0.26f, 1.9f},
-                                    {32, 32, 2, 3.2f, 0.30f, 0.145f, 1.1f}, {32, 32, 4, 3.9f, 0.18f, 0.145f, 1.4f}};
+constexpr Tile64Form kFormsBf16[] = {{64, 64, 1, 3.71f, 0.370f, 0.183f, 0.77f, 0.77f}, {64, 64, 2, 3.91f, 0.262f, 0.208f, 1.24f, 0.77f},
+                                     {64, 32, 2, 3.67f, 0.217f, 0.133f, 0.77f, 0.36f}, {64, 32, 4, 4.47f, 0.171f, 0.181f, 2.99f, 0.75f},
+                                     {32, 32, 2, 3.49f, 0.168f, 0.082f, 0.55f, 0.19f}, {32, 32, 4, 3.94f, 0.111f, 0.084f, 1.22f, 0.33f}};
+constexpr Tile64Form kFormsF32[] = {{64, 64, 1, 4.4f, 0.61f, 0.52f, 3.0f, 0.0f}, {64, 32, 2, 3.4f, 0.37f, 0.26f, 1.9f, 0.0f},
+                                    {32, 32, 2, 3.2f, 0.30f, 0.145f, 1.1f, 0.0f}, {32, 32, 4, 3.9f, 0.18f, 0.145f, 1.4f, 0.0f}};
 static Tile64Form pick_form(const GemmArgs& g, int dtype, float* us) {
     const bool f32 = dtype == D2FT_F32;
     const Tile64Form* f = f32 ? kFormsF32 : kFormsBf16;
@@ -505,7 +505,8 @@ static Tile64Form pick_form(const GemmArgs& g, int dtype, float* us) {
     for (int i = 0; i < (f32 ? 4 : 6); ++i) {
         if (g.colsum && f[i].tm != 64) continue;   // a band of column sums is 64 rows
         const long units = (long)((g.M + f[i].tm - 1) / f[i].tm) * ((g.N + f[i].tn - 1) / f[i].tn);
-        const float t = f[i].fixed + f[i].first * slabs + (float)((units + 255) / 256 - 1) * (f[i].next * slabs + f[i].change);
+        const float rounds = (float)((units + 255) / 256);
+        const float t = f[i].fixed + f[i].first * slabs + (rounds - 1.0f) * (f[i].next * slabs + f[i].change) + (g.act == ACT_GELU ? rounds * f[i].gelu : 0.0f);
         if (t < *us) {
             *us = t;
             best = f[i];
@@ -540,15 +541,18 @@ static hipError_t launch_tile64(const GemmArgs& g, int dtype, hipStream_t s) {
     return launch_tile<T, 64, 64>(g, f.wk, s);
 }
 
-// bf16: against the 128x128 tile, 5.1 us + 0.41 us per slab and round by the same fit.  In the middle of the range both
-// are close (985 x 1536 x 384: 9.2 and 10.4 us); at the ends they are not (197 x 768 x 768: 5.0 and 9.5; 3152 x 3072 x
-// 768: 46 and 27).
+// bf16: against the 128x128 tile with a CU for each workgroup, by a fitted cost (1086 products, rms error 5 %).  In the middle
+// of the range both are close (985 x 1536 x 384: 9.2 and 10.4 us); at the ends they are not (197 x 768 x 768: 5.0 and 9.5;
+// 1576 x 768 x 3072: 37 and 25).  Where that tile has more workgroups than the chip CUs, it leaves none idle (8192 x 576 x 256,
+// 320 workgroups: 9.7 us and 11.4 on 64x64 tiles; 3152 x 3072 x 768: 27 and 46).
 bool gemm_tile64_faster(const GemmArgs& g) {
     if (g.partial || g.a_cs != 1 || gemm_mfma_tile_rows(g) != 128) return false;
+    const long units = (long)((g.M + 127) / 128) * ((g.N + 127) / 128);
+    if (units > 256) return false;
     float us;
     pick_form(g, D2FT_BF16, &us);
-    const long units = (long)((g.M + 127) / 128) * ((g.N + 127) / 128);
-    return us < 5.1f + 0.41f * ((g.K + 63) / 64) * (float)((units + 255) / 256);
+    const float slabs = (float)((g.K + 63) / 64), epilogue = g.act == ACT_GELU ? 2.6f : 0.0f;
+    return us < 0.95f * (5.2f + 0.365f * slabs * (1.0f + 0.404f * (float)units / 256.0f) + epilogue);
 }
 
 hipError_t launch_gemm_tile64(const GemmArgs& g, int dtype, hipStream_t s) {

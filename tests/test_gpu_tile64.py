@@ -65,3 +65,17 @@ def test_vector_alu_kernels_on_request(dtype, lora):
         P.d2ft_timing_enable(False)
     assert {"gemm_simple_kernel", "attn_fwd_simple", "attn_bwd_simple"} <= names
     assert not [n for n in names if "mfma" in n or "tile64" in n or "split" in n or "stream" in n], names
+
+
+@pytest.mark.parametrize("images,width,small", [(8, 768, False), (1, 768, True)])
+def test_small_tiles_leave_long_products_to_the_large_ones(images, width, small):
+    """The feed-forward products of eight images have K or N of 3072 and enough rows for the 128x128 tile; of one image not."""
+    import paper_2504_12471_amd as P
+    w = di.Workload("long", images, 197, width, 2, 64, 4 * width, 1, "bf16")
+    P.d2ft_timing_enable(True)
+    try:
+        run_case(w, [SKIP, SKIP], seed=76)
+        names = {r["name"] for r in P.d2ft_timing_read()}
+    finally:
+        P.d2ft_timing_enable(False)
+    assert any("gemm_tile64" in n and "GemmArgs" in n for n in names) == small, names
