@@ -228,10 +228,10 @@ hipError_t launch_ln_fwd(int dtype, const void* x, const void* gamma, const void
 hipError_t launch_ln_bwd(int dtype, const void* d, const void* x, const float* mean, const float* rstd,
                          const void* gamma, const void* res, void* dx, int rows, int width, hipStream_t s);
 // the same, also writing column sums of res (sum_res) and of dx (sum_out) over bands of rows:
-// [ln_bwd_sums_bands(rows)][width] fp32 each; either may be null.  res must be given; width <= 2048.
+// [ln_bwd_sums_bands(rows, width)][width] fp32 each; either may be null.  res must be given; width <= 2048.
 bool ln_bwd_sums_supported(int width);
-int ln_bwd_sums_bands(int rows);
-int ln_bwd_sums_most_bands(int rows);   // of any number of rows up to this one (a scratch layout grows with the rows)
+int ln_bwd_sums_bands(int rows, int width);
+int ln_bwd_sums_most_bands(int rows);   // of any width and any number of rows up to this one (a scratch layout grows with the rows)
 hipError_t launch_ln_bwd_sums(int dtype, const void* d, const void* x, const float* mean, const float* rstd,
                               const void* gamma, const void* res, void* dx, int rows, int width, float* sum_res,
                               float* sum_out, hipStream_t s);

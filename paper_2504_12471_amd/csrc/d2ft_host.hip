@@ -1257,7 +1257,7 @@ static d2ft_status block_bwd_impl(const d2ft_block_desc* desc, const d2ft_block_
             float* sum_out = want_bo ? (float*)(ws + WL.colfuse_bo + cf) : nullptr;
             D2FT_TRY_BYTES(4.0 * s.M * s.D * s.es + 8.0 * s.M, launch_ln_bwd_sums(s.dtype, ws + WL.dv, x1, (const float*)(sv + SL.mean2),
                                         (const float*)(sv + SL.rstd2), w->ln2_g, dy, out, M, s.D, sum_res, sum_out, st));
-            const int bands = ln_bwd_sums_bands(M);
+            const int bands = ln_bwd_sums_bands(M, s.D);
             if (want_b2) queue_bias_reduce(&bias_batch, sum_res, bands, s.D, grads->b2, 0);
             if (want_bo) queue_bias_reduce(&bias_batch, sum_out, bands, s.D, grads->b_o, 0);
         } else {

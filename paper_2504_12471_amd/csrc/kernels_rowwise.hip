@@ -813,17 +813,21 @@ hipError_t launch_ln_fwd(int dtype, const void* x, const void* gamma, const void
 
 bool ln_bwd_sums_supported(int width) { return width <= 2048; }
 // Rows of a workgroup: many for few partial sums, few where the rows would not fill the chip.  With 4 / 8 / 16: 985 x 384
-// 3.2 / 3.8 / 5.1 us, 3152 x 384 4.8 / 4.8 / 5.6, 3152 x 1024 9.1 / 8.3 / 8.4, 6304 x 1024 15.1 / 14.7 / 13.3.
-static int ln_sum_rows(int rows) { return rows <= 2048 ? 4 : (rows <= 4096 ? 8 : 16); }
-int ln_bwd_sums_bands(int rows) { return (rows + ln_sum_rows(rows) - 1) / ln_sum_rows(rows); }
+// 3.2 / 3.8 / 5.1 us, 3152 x 384 4.8 / 4.8 / 5.6, 3152 x 1024 9.1 / 8.3 / 8.4, 6304 x 1024 15.1 / 14.7 / 13.3.  Above width 1024
+// a CU holds one workgroup, and a second round costs more than longer workgroups do: 3152 x 2048 with 8 / 16 18.4 / 14.7.
+static int ln_sum_rows(int rows, int width) {
+    const int r = width > 1024 ? 2 * rows : rows;
+    return r <= 2048 ? 4 : (r <= 4096 ? 8 : 16);
+}
+int ln_bwd_sums_bands(int rows, int width) { return (rows + ln_sum_rows(rows, width) - 1) / ln_sum_rows(rows, width); }
 int ln_bwd_sums_most_bands(int rows) { return rows <= 2048 ? (rows + 3) / 4 : (rows <= 16 * 512 ? 512 : (rows + 15) / 16); }
 
 hipError_t launch_ln_bwd_sums(int dtype, const void* d, const void* x, const float* mean, const float* rstd,
                               const void* gamma, const void* res, void* dx, int rows, int width, float* sum_res,
                               float* sum_out, hipStream_t s) {
     if (!ln_bwd_sums_supported(width) || !res) return hipErrorNotSupported;
-    const int per = ln_sum_rows(rows);
-    const dim3 grid(ln_bwd_sums_bands(rows)), block(256);
+    const int per = ln_sum_rows(rows, width);
+    const dim3 grid(ln_bwd_sums_bands(rows, width)), block(256);
 #define D2FT_LN_BWD_SUMS(NV)                                                                                         \
     D2FT_DISPATCH(dtype, hipLaunchKernelGGL((ln_bwd_sums_kernel<T, NV>), grid, block, 0, s, (const T*)d, (const T*)x, \
                                             mean, rstd, (const T*)gamma, (const T*)res, (T*)dx, rows, width, per, sum_res, \

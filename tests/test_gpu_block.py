@@ -328,3 +328,10 @@ def test_deferred_join_over_consecutive_backward_calls():
             for k, v in plain[1][l].items():
                 if v is not None:
                     assert torch.equal(got[1][l][k], v), (l, k)
+
+
+@pytest.mark.parametrize("tokens", [31, 64, 65, 129])
+def test_wide_layernorm_sums_per_workgroup_rows(tokens):
+    """Above width 1024 the column sums of the LayerNorm backward change their rows per workgroup at 1024 and 2048 rows:
+    beside both, and a last workgroup with one row."""
+    run_case(di.Workload("wide_ln", 16, tokens, 1032, 1, 64, 64, 1, "bf16"), [FULL], seed=89, grad_fields=("b_o", "b2", "w_o"))
