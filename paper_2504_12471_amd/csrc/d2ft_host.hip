@@ -1018,18 +1018,24 @@ static d2ft_status block_bwd_impl(const d2ft_block_desc* desc, const d2ft_block_
     // 1116 us, 10 images (12e9) 1696 and 1732, 20 images 1995 and 1796; width 384, 40 images (12e9) 1448 and 1374.  One
     // stream against two: width 384, 5 images (1.5e9) 701 and 768 us, 10 images (3e9) 797 and 806, 20 images (6e9) 1142
     // and 1086; width 768, 5 images (6e9) 1061 and 1035.
-    // Measured up to 8000 rows; LoRA's single narrow gradient over more of them is better off as it was.
-    constexpr double kSmallTileMacs = 10e9, kOneStreamMacs = 4.5e9;
-    constexpr long kSmallRows = 8192;
+    // One launch by itself, of many rows: 5910 rows, width 384 (9.3e9) 48.8 us on 64x64 tiles, 42.2 and a tail of 5 us on
+    // 256x256; 8192 rows, width 256 (5.4e9) 36.4 against 32.1 and 5; 4096 rows, width 384 (4.8e9) 30.4 and 30.7.  Beside the
+    // second stream's partner they also take its CUs: 6698 rows, width 256 (5.3e9), six blocks 1068 and 1045 us.
+    // The second stream's use lies in what runs beside the weight gradients, so its line is drawn by the products that lead
+    // to dx, of the same size where everything is trained: with adapters alone (width 384, 6304 rows, 12e9 against 2.3e9 of
+    // weight gradients) six blocks take 1350 us on two streams, 1410 on one.
+    constexpr double kSmallTileMacs = 10e9, kSmallTileMacsManyRows = 4.5e9, kOneStreamMacs = 4.5e9;
+    constexpr long kManyRows = 4096, kSmallRows = 8192;
     const double hidden = (desc->flags & D2FT_FLAG_GATE_FFN) ? (double)s.Dm / s.H * nf : s.Dm;
     const double wgrad_macs = (double)s.M * s.D * (hidden * ((grads->w1 ? 1 : 0) + (grads->w2 ? 1 : 0)) +
                                                    nf * (64.0 * (grads->w_o ? 1 : 0) + 192.0 * (grads->w_qkv || s.r > 0 ? 1 : 0)));
-    wgrads.small = s.dtype == D2FT_BF16 && s.M <= kSmallRows && wgrad_macs <= kSmallTileMacs;
+    const double chain_macs = (double)s.M * s.D * (2 * hidden + nf * 256.0);
+    wgrads.small = s.dtype == D2FT_BF16 && s.M <= kSmallRows && wgrad_macs <= (s.M <= kManyRows ? kSmallTileMacs : kSmallTileMacsManyRows);
     // Side stream (see SideStream): for the whole-block matrix-core path, unless the call is small, the caller asks for
     // one stream, per-kernel timing is on (its durations are those of kernels running alone) or the stream is being
     // captured.
     SideStream* side = nullptr;
-    if (half == PART_BOTH && s.dtype == D2FT_BF16 && wgrads.enabled && (s.M > kSmallRows || wgrad_macs > kOneStreamMacs) && !(desc->flags & D2FT_FLAG_ONE_STREAM) && !g_timing.on) {
+    if (half == PART_BOTH && s.dtype == D2FT_BF16 && wgrads.enabled && (s.M > kSmallRows || chain_macs > kOneStreamMacs) && !(desc->flags & D2FT_FLAG_ONE_STREAM) && !g_timing.on) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) side = side_stream();
     }

@@ -79,3 +79,18 @@ def test_small_tiles_leave_long_products_to_the_large_ones(images, width, small)
     finally:
         P.d2ft_timing_enable(False)
     assert any("gemm_tile64" in n and "GemmArgs" in n for n in names) == small, names
+
+
+@pytest.mark.parametrize("rows,width,heads,mlp,lora,small", [
+    (4096, 128, 2, 512, 0, True), (4480, 384, 6, 1536, 0, False), (4480, 128, 2, 512, 0, True), (2048, 64, 1, 64, 8, True)])
+def test_which_tiles_the_weight_gradients_take(rows, width, heads, mlp, lora, small):
+    """bf16: on either side of the lines by multiply-adds and rows."""
+    import paper_2504_12471_amd as P
+    w = di.Workload("wgrad", rows // 64, 64, width, heads, 64, mlp, 1, "bf16", lora_rank=lora, lora_b_zero=False)
+    P.d2ft_timing_enable(True)
+    try:
+        run_case(w, [FULL] * heads, seed=77, grad_fields=[k for k in di.WEIGHT_FIELDS if k.startswith("lora") == (lora > 0)])
+        names = {r["name"] for r in P.d2ft_timing_read()}
+    finally:
+        P.d2ft_timing_enable(False)
+    assert any("Tile64Grouped" in n for n in names) == small, names
