@@ -335,3 +335,17 @@ def test_wide_layernorm_sums_per_workgroup_rows(tokens):
     """Above width 1024 the column sums of the LayerNorm backward change their rows per workgroup at 1024 and 2048 rows:
     beside both, and a last workgroup with one row."""
     run_case(di.Workload("wide_ln", 16, tokens, 1032, 1, 64, 64, 1, "bf16"), [FULL], seed=89, grad_fields=("b_o", "b2", "w_o"))
+
+
+def test_bias_gradient_sums_in_short_chains():
+    """db2 is the column sum of dy over 260 rows, 65 partial sums of four.  Eight seeds of 192 columns: the relative error of
+    the kernel's order (rows by fours, 32 lanes of two or three partial sums, four chains of eight) comes to 8.1e-8, that of
+    one chain over the lanes to 1.1e-7."""
+    w = di.Workload("bias_sum", 4, 65, 192, 3, 64, 64, 1, "f32")
+    err = 0.0
+    for seed in range(90, 98):
+        x, wt, dy = draw_block(w, seed)
+        b2 = gpu_block(w, wt, [FULL] * 3, x, dy, ("b2",))[2]["b2"]
+        ref = dy.astype(np.float64).sum((0, 1))
+        err += np.linalg.norm(b2 - ref) / np.linalg.norm(ref) / 8
+    assert err < 9.5e-8, err
