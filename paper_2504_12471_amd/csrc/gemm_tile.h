@@ -51,12 +51,31 @@ __device__ __forceinline__ void tile_of_block(int pid, int total, int tiles_m, i
     tn = in_group / gsize;
 }
 
+// What the epilogue reads for columns n .. n + 7 of row m, as it lies in memory: the bias, and Z or the residual
+template <typename T>
+struct EpilogueOperands {
+    static constexpr int kN = 8 * sizeof(T) / 16;
+    uint4 bias[kN], other[kN];
+    static __device__ __forceinline__ void load(uint4 (&v)[kN], const void* p, long at) {
+#pragma unroll
+        for (int i = 0; i < kN; ++i) v[i] = reinterpret_cast<const uint4*>(static_cast<const T*>(p) + at)[i];
+    }
+    static __device__ __forceinline__ void values(const uint4 (&v)[kN], float (&o)[8]) {
+        load8(reinterpret_cast<const T*>(v), o);
+    }
+    __device__ __forceinline__ void request(const GemmArgs& g, int m, int n) {
+        if (g.bias) load(bias, g.bias, g.bias_remap ? g.tbl(n) : n);
+        if (g.act == ACT_DGELU) load(other, g.Z, (long)m * g.ldz + n);
+        else if (g.residual) load(other, g.residual, (long)m * g.ldr + n);
+    }
+};
+
 // results of row m, columns n .. n + 7, through the epilogue; v returns what was stored
 template <typename T>
-__device__ __forceinline__ void emit(const GemmArgs& g, int m, int n, float (&v)[8]) {
+__device__ __forceinline__ void emit(const GemmArgs& g, int m, int n, float (&v)[8], const EpilogueOperands<T>& with) {
     if (g.bias) {
         float b[8];
-        load8(static_cast<const T*>(g.bias) + (g.bias_remap ? g.tbl(n) : n), b);
+        with.values(with.bias, b);
 #pragma unroll
         for (int i = 0; i < 8; ++i) v[i] += b[i];
     }
@@ -72,17 +91,24 @@ __device__ __forceinline__ void emit(const GemmArgs& g, int m, int n, float (&v)
         store8(static_cast<T*>(g.Z) + (long)m * g.ldz + n, d);
     } else if (g.act == ACT_DGELU) {
         float d[8];
-        load8(static_cast<const T*>(g.Z) + (long)m * g.ldz + n, d);
+        with.values(with.other, d);
 #pragma unroll
         for (int i = 0; i < 8; ++i) v[i] *= d[i];
     }
     if (g.residual) {
         float x[8];
-        load8(static_cast<const T*>(g.residual) + (long)m * g.ldr + n, x);
+        if (g.act == ACT_DGELU) load8(static_cast<const T*>(g.residual) + (long)m * g.ldr + n, x);
+        else with.values(with.other, x);
 #pragma unroll
         for (int i = 0; i < 8; ++i) v[i] += x[i];
     }
     store8(static_cast<T*>(g.C) + (long)m * g.ldc + n, v);
+}
+template <typename T>
+__device__ __forceinline__ void emit(const GemmArgs& g, int m, int n, float (&v)[8]) {
+    EpilogueOperands<T> with;
+    with.request(g, m, n);
+    emit<T>(g, m, n, v, with);
 }
 
 // the same of weight gradient gi of a grouped launch

@@ -243,6 +243,15 @@ __global__ __launch_bounds__((64 * group_waves<TM, TN>() * WK), TM == 64 && TN =
     };
     unsigned char* const mine = smem + kg * group_bytes<TM, TN>();
     unroll<kAhead>([&](auto i) { fetch(i.value, ra[i.value], rb[i.value]); });
+    // The thread's piece of the tile and what the epilogue reads for it, requested here, so that a launch of few workgroups
+    // does not end with the latency of one more load.  The larger tiles have no registers for it.
+    constexpr bool kEarly = !GROUPED && TN == 32 && (TM == 32 || sizeof(T) == 2);
+    constexpr int kThreads = GT * WK, kPieces = TM * TN / 8, kRowPieces = TN / 8;
+    const int r0 = threadIdx.x / kRowPieces, c0 = threadIdx.x % kRowPieces * 8;
+    EpilogueOperands<T> early;
+    if constexpr (kEarly) {
+        if (!g.partial && (kThreads <= kPieces || (int)threadIdx.x < kPieces) && m0 + r0 < M && n0 + c0 < N) early.request(g, m0 + r0, n0 + c0);
+    }
     f32x16 acc;
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[e] = 0.f;
@@ -294,7 +303,6 @@ __global__ __launch_bounds__((64 * group_waves<TM, TN>() * WK), TM == 64 && TN =
         for (int e = 0; e < 16; ++e) stage[(wi + 8 * (e >> 2) + 4 * h + (e & 3)) * kStageStride + wj + c] = acc[e];
     }
     __syncthreads();
-    constexpr int kThreads = GT * WK, kPieces = TM * TN / 8, kRowPieces = TN / 8;
     float csum[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) csum[i] = 0.f;
@@ -324,7 +332,12 @@ __global__ __launch_bounds__((64 * group_waves<TM, TN>() * WK), TM == 64 && TN =
                 store8(g.partial + (long)split * M * N + (long)m * N + n, v);
                 continue;
             }
-            emit<T>(g, m, n, v);
+            if constexpr (kEarly) {
+                static_assert(kThreads >= kPieces, "one piece per thread");
+                emit<T>(g, m, n, v, early);
+            } else {
+                emit<T>(g, m, n, v);
+            }
 #pragma unroll
             for (int i = 0; i < 8; ++i) csum[i] += v[i];
         }
