@@ -10,29 +10,37 @@
 //   forward  S^T = K Q^T (a lane owns one query), running maximum and sum per lane, O^T += V^T P^T
 //   dQ       S^T and dP^T = V dO^T from the same tiles, dS^T = P^T (dP^T - delta), dQ^T += K^T dS^T
 //   dK, dV   S = Q K^T and dP = dO V^T (a lane owns one key), dV^T += dO^T P, dK^T += Q^T dS
-// Probabilities are rebuilt from the saved log-sum-exp.  P and dS enter the second products with all their bits: as fp32
-// operands, or for bf16 storage as three bf16 parts each (cut8), three products instead of one.  Up to 224 tokens the bf16
+// Probabilities are rebuilt from the saved log-sum-exp.  P and dS enter the second products with all their bits: as three
+// bf16 parts each (cut8), for bf16 storage three products instead of one.  fp32 operands are cut likewise, on their way to LDS or
+// registers, and six of the nine products of parts are formed (kernels_gemm_split.hip): 1152 cycles of the matrix cores where
+// the fp32 instruction takes 3072 for the same k.  Up to 224 tokens the bf16
 // backward rounds them to bf16, as kernels_attn_mfma.hip does, which runs the other calls of those lengths (TR_PARTS).
 // Relative 2-norm error against fp64 of O / dQ / dV, N(0, 1) operands, 577 tokens: bf16 1.66e-3 / 1.68e-3 / 1.66e-3, the
-// same as the vector-ALU kernels (with P and dS rounded to bf16 2.18e-3 / 2.39e-3 / 2.38e-3); fp32 4.8e-7 / 6.1e-7 /
-// 5.8e-7, the vector-ALU kernels 5.3e-7 / 6.5e-7 / 6.3e-7; with scores of 16 times the spread 8.5e-7 / 2.5e-6 / 1.4e-6
-// and 1.5e-6 / 3.8e-6 / 1.8e-6.
+// same as the vector-ALU kernels (with P and dS rounded to bf16 2.18e-3 / 2.39e-3 / 2.38e-3); fp32 4.0e-7 / 5.4e-7 /
+// 5.3e-7 (by the fp32 instruction 4.8e-7 / 6.1e-7 / 5.8e-7, the vector-ALU kernels 5.3e-7 / 6.5e-7 / 6.3e-7); with scores of
+// 16 times the spread 5.5e-7 / 1.9e-6 / 1.2e-6 (8.5e-7 / 2.5e-6 / 1.4e-6 and 1.5e-6 / 3.8e-6 / 1.8e-6).
 //
 // dQ and dK/dV workgroups are independent (both form delta_q = sum_d dO[q][d] O[q][d] for the rows they touch) and
 // share one launch, so that the second kind fills the last round of the first.  S and dP are formed twice, 7 products of 64 x 32 x 32 per tile pair instead of 5: keeping
 // dQ partial sums instead would mean fp32 atomics, whose order is not fixed, or a pass over them.
 //
-// Bound: fp32 by the matrix cores (a 32 x 32 tile pair is 64 products of 64 cycles forward, 224 backward); bf16 by the
+// Bound: fp32 by the matrix cores (a 32 x 32 tile pair is 48 products of 32 cycles forward, 168 backward) and by what runs
+// between them: a part of an infinity is a NaN and an operand of 2^104 and more has no parts, so a workgroup with a result
+// that is not finite forms its rows again with the fp32 instruction.  The backward holds two row operands in parts (96
+// registers): one wavefront per SIMD.  bf16 by the
 // matrix cores and the vector ALUs alike (forward 16 products of 32 cycles per tile pair, beside 16 exponentials, twice as
 // many subtractions and multiplications, maxima, sums and the cutting into parts, 5.5 operations for each of 16 elements).
 //
 // Measured against the vector-ALU kernels it replaced (one wavefront per row, every row of K and V from cache for
 // every query), per launch: bf16, 16 images of 577 tokens, 160 live / 112 p_f pairs: forward 1440 -> 53 us, backward
-// 4004 -> 94 us (30 and 65 with P and dS in one part); fp32, 16 images of 197 tokens, 80 / 64 pairs: forward 172 -> 21 us,
-// backward 486 -> 40 us.
+// 4004 -> 94 us (30 and 65 with P and dS in one part); fp32, 16 images of 197 tokens, 80 / 64 pairs: forward 172 -> 21 -> 17 us,
+// backward 486 -> 39 -> 30 us (by the fp32 instruction, by parts); 400 / 320 pairs 68 -> 46 and 159 -> 131; 4 images of 65
+// tokens, 8 / 4 pairs 10.3 -> 8.9 and 18.2 -> 14.9.
 //
 // Result layout of both products: column c = lane % 32, element e <-> row 8*(e/4) + 4h + e%4, h = lane / 32.
 #include <hip/hip_ext.h>
+#include <atomic>
+#include <type_traits>
 
 #include "d2ft_common.h"
 
@@ -46,6 +54,23 @@ typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 
 namespace {
+
+// How fp32 storage is multiplied: Parts, as three bf16 parts of each element on the bf16 matrix cores, or float, by the fp32
+// instruction, which a workgroup falls back on when a result of the parts is not finite.  bf16 is its own.
+struct Parts {};
+template <typename Op> struct Storage { typedef Op type; };      // in memory
+template <> struct Storage<Parts> { typedef float type; };
+template <typename Op> struct InTile { typedef Op type; };       // in LDS
+template <> struct InTile<Parts> { typedef bf16 type; };
+
+// The parts are those of x * 2^24, exact whatever x (kernels_gemm_split.hip); products are 2^48 of theirs.
+constexpr float kUp = 16777216.f;            // 2^24
+constexpr float kDown = 3.5527136788e-15f;   // 2^-48
+static_assert(kDown * kUp * kUp == 1.f, "powers of two");
+template <typename Op> constexpr float unscale() { return 1.f; }
+template <> constexpr float unscale<Parts>() { return kDown; }
+// pairs of parts that are multiplied, the small products first (what is left out is below 2^-25 of the product)
+constexpr int kPa[6] = {2, 0, 1, 1, 0, 0}, kPb[6] = {0, 2, 1, 0, 1, 0};
 
 constexpr float kScale = 0.125f;   // 1/sqrt(64)
 constexpr float kLog2e = 1.4426950408889634f;
@@ -71,7 +96,31 @@ template <> struct Tile<float> {
     static constexpr int kStride = 68, kPieces = 16, kStage = 1;
     static __device__ __forceinline__ int at(int r) { return r * kStride; }
 };
+template <> struct Tile<Parts> {   // each part like a bf16 tile, one after the other
+    static constexpr int kStride = 88, kPieces = 16, kStage = 1;
+    static __device__ __forceinline__ int at(int r) { return Tile<bf16>::at(r); }
+};
+constexpr int kPartElems = kRows * Tile<Parts>::kStride;
 template <typename T> constexpr int tile_elems() { return kRows * Tile<T>::kStride; }
+template <> constexpr int tile_elems<Parts>() { return 3 * kPartElems; }
+
+// N floats times kUp as three bf16 parts each
+template <int N>
+__device__ __forceinline__ void cut_up(const float (&in)[N], uint32_t (&part)[3][N / 2]) {
+    float x[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = in[i] * kUp;
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int i = 0; i < N / 2; ++i) {
+            asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(part[k][i]) : "v"(x[2 * i]), "v"(x[2 * i + 1]));   // written as conversions, half of them are made twice
+            if (k < 2) {
+                x[2 * i] -= __uint_as_float(part[k][i] << 16);
+                x[2 * i + 1] -= __uint_as_float(part[k][i] & 0xffff0000u);
+            }
+        }
+}
 
 // 32 rows x 64 channels as the B operand of row-wise products: this lane's row in registers
 template <typename T> struct RowOp;
@@ -116,6 +165,21 @@ template <> struct RowOp<float> {
     }
 };
 
+template <> struct RowOp<Parts> {
+    bf16x8 f[3][4];   // [part]: channels 16 kk + 8h .. + 7
+    __device__ __forceinline__ void load(const float* row, bool ok, int h) {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+            float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            if (ok) load8(row + kk * 16 + 8 * h, x);
+            uint32_t part[3][4];
+            cut_up(x, part);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) f[k][kk] = __builtin_bit_cast(bf16x8, u32x4{part[k][0], part[k][1], part[k][2], part[k][3]});
+        }
+    }
+};
+
 // acc[row of the tile][this wavefront's row] += tile . op^T; CHAINS: of sums along the channels, for fp32.  Two halve the
 // roundings of the scores, which an exponential follows; for both products of the backward they would not fit the registers.
 template <int CHAINS>
@@ -139,6 +203,24 @@ __device__ __forceinline__ void mma_rows(f32x16& acc, const float* tile, const R
     if constexpr (CHAINS == 2) acc += other;
 }
 
+template <int CHAINS>   // acc: zero
+__device__ __forceinline__ void mma_rows(f32x16& acc, const bf16* tile, const RowOp<Parts>& op, int lane) {
+    const bf16* p = tile + Tile<Parts>::at(lane & 31) + 8 * (lane >> 5);
+    f32x16 low = zero16();   // the small products have an accumulator of their own
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+        bf16x8 a[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) a[k] = *reinterpret_cast<const bf16x8*>(p + k * kPartElems + kk * 16);
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+            f32x16& to = q == 5 ? acc : low;
+            to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kPa[q]], op.f[kPb[q]][kk], to, 0, 0, 0);
+        }
+    }
+    acc = (acc + low) * kDown;
+}
+
 // elements first .. first + 7 of p as PARTS bf16 parts, the largest first; the sum of three has every bit of p down to 2^-133
 template <int PARTS>
 __device__ __forceinline__ void cut8(const f32x16& p, int first, bf16x8 (&part)[PARTS]) {
@@ -159,8 +241,41 @@ __device__ __forceinline__ void cut8(const f32x16& p, int first, bf16x8 (&part)[
 }
 
 // out[channel][this wavefront's row] += tile^T . p, p a result of mma_rows (rows of the tile x the wavefront's rows)
-template <int PARTS>
-__device__ __forceinline__ void mma_tr(f32x16 (&out)[2], const bf16* tile, const f32x16& p, int lane) {
+template <typename Op, int PARTS>
+__device__ __forceinline__ std::enable_if_t<std::is_same<Op, Parts>::value> mma_tr(f32x16 (&out)[2], const bf16* tile, const f32x16& p, int lane) {
+    const int j = lane & 15;
+    const bf16* base = tile + (2 * (j >> 2) + (lane >> 5)) * Tile<Parts>::kStride + 16 * ((lane >> 4) & 1) + 4 * (j & 3);
+    typedef s16x4 __attribute__((address_space(3))) * lds_ptr_t;
+#pragma unroll
+    for (int gp = 0; gp < 2; ++gp) {
+        float x[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = p[8 * gp + i];
+        uint32_t part[3][4];
+        cut_up(x, part);
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt) {
+            bf16x8 a[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const bf16* q = base + k * kPartElems + 16 * gp * Tile<Parts>::kStride + 32 * dt;
+                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(q));
+                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(q + 8 * Tile<Parts>::kStride));
+                s16x8 r;
+                r[0] = lo[0]; r[1] = lo[1]; r[2] = lo[2]; r[3] = lo[3];
+                r[4] = hi[0]; r[5] = hi[1]; r[6] = hi[2]; r[7] = hi[3];
+                a[k] = __builtin_bit_cast(bf16x8, r);
+            }
+#pragma unroll
+            for (int q = 0; q < 6; ++q) {
+                const bf16x8 b = __builtin_bit_cast(bf16x8, u32x4{part[kPb[q]][0], part[kPb[q]][1], part[kPb[q]][2], part[kPb[q]][3]});
+                out[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kPa[q]], b, out[dt], 0, 0, 0);
+            }
+        }
+    }
+}
+template <typename Op, int PARTS>
+__device__ __forceinline__ std::enable_if_t<std::is_same<Op, bf16>::value> mma_tr(f32x16 (&out)[2], const bf16* tile, const f32x16& p, int lane) {
     const int j = lane & 15;
     // rows t0 + 4h + {0..3} and t0 + 8 + 4h + {0..3} of the tile: the order in which a lane holds 8 result elements
     const bf16* base = tile + (2 * (j >> 2) + (lane >> 5)) * Tile<bf16>::kStride + 16 * ((lane >> 4) & 1) + 4 * (j & 3);
@@ -183,8 +298,8 @@ __device__ __forceinline__ void mma_tr(f32x16 (&out)[2], const bf16* tile, const
         }
     }
 }
-template <int>
-__device__ __forceinline__ void mma_tr(f32x16 (&out)[2], const float* tile, const f32x16& p, int lane) {
+template <typename Op, int>
+__device__ __forceinline__ std::enable_if_t<std::is_same<Op, float>::value> mma_tr(f32x16 (&out)[2], const float* tile, const f32x16& p, int lane) {
     const float* base = tile + Tile<float>::at(4 * (lane >> 5)) + (lane & 31);
 #pragma unroll
     for (int e = 0; e < 16; ++e)
@@ -226,18 +341,19 @@ __device__ __forceinline__ void store_row(const f32x16 (&t)[2], float mul, float
 // One operand of a stage: kStage tiles of 32 rows, this thread's 16-byte pieces on their way from memory to LDS.  The
 // buffer's declared size ends with the last valid row, rows beyond it read as zeros; REPEAT: as the last valid row, so
 // that a probability of zero times them is not finite only where that row's own product is not.
-template <typename T, bool REPEAT = false>
+template <typename Op, bool REPEAT = false>
 struct Stream {
-    static constexpr int kPer = Tile<T>::kStage * kRows * Tile<T>::kPieces / (64 * kWaves);   // pieces per thread
-    static constexpr int kStep = 64 * kWaves / Tile<T>::kPieces;                              // rows between them
+    typedef typename Storage<Op>::type T;
+    static constexpr int kPer = Tile<Op>::kStage * kRows * Tile<Op>::kPieces / (64 * kWaves);   // pieces per thread
+    static constexpr int kStep = 64 * kWaves / Tile<Op>::kPieces;                              // rows between them
     __amdgpu_buffer_rsrc_t rsrc;
     uint32_t off, ld_bytes, last;
     u32x4 v[kPer];
     __device__ __forceinline__ void init(const T* p, long ld, int tokens) {
         ld_bytes = (uint32_t)ld * (uint32_t)sizeof(T);
         rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(p), 0, (uint32_t)(tokens - 1) * ld_bytes + 64u * (uint32_t)sizeof(T), 0x00020000);
-        off = (uint32_t)(threadIdx.x / Tile<T>::kPieces) * ld_bytes + (uint32_t)(threadIdx.x % Tile<T>::kPieces) * 16u;
-        last = (uint32_t)(tokens - 1) * ld_bytes + (uint32_t)(threadIdx.x % Tile<T>::kPieces) * 16u;
+        off = (uint32_t)(threadIdx.x / Tile<Op>::kPieces) * ld_bytes + (uint32_t)(threadIdx.x % Tile<Op>::kPieces) * 16u;
+        last = (uint32_t)(tokens - 1) * ld_bytes + (uint32_t)(threadIdx.x % Tile<Op>::kPieces) * 16u;
     }
     __device__ __forceinline__ void fetch(int row0) {
 #pragma unroll
@@ -246,11 +362,18 @@ struct Stream {
             v[k] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, REPEAT ? min(at, last) : at, 0, 0);
         }
     }
-    __device__ __forceinline__ void store(T* lds) const {   // lds: kStage tiles, one after the other
+    __device__ __forceinline__ void store(typename InTile<Op>::type* lds) const {   // lds: kStage tiles, one after the other
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {
-            const int r = threadIdx.x / Tile<T>::kPieces + k * kStep;
-            *reinterpret_cast<u32x4*>(lds + (r / kRows) * tile_elems<T>() + Tile<T>::at(r % kRows) + (threadIdx.x % Tile<T>::kPieces) * (16 / (int)sizeof(T))) = v[k];
+            const int r = threadIdx.x / Tile<Op>::kPieces + k * kStep;
+            if constexpr (std::is_same<Op, Parts>::value) {
+                const float x[4] = {__uint_as_float(v[k][0]), __uint_as_float(v[k][1]), __uint_as_float(v[k][2]), __uint_as_float(v[k][3])};
+                uint32_t part[3][2];
+                cut_up(x, part);
+                bf16* const to = lds + Tile<Op>::at(r) + (threadIdx.x % Tile<Op>::kPieces) * 4;
+#pragma unroll
+                for (int w = 0; w < 3; ++w) *reinterpret_cast<uint2*>(to + w * kPartElems) = make_uint2(part[w][0], part[w][1]);
+            } else *reinterpret_cast<u32x4*>(lds + (r / kRows) * tile_elems<Op>() + Tile<Op>::at(r % kRows) + (threadIdx.x % Tile<Op>::kPieces) * (16 / (int)sizeof(T))) = v[k];
         }
     }
 };
@@ -288,12 +411,15 @@ __device__ __forceinline__ int xcd_order(int pid, int total) {
 // ---------------------------------------------------------------------------
 // forward: workgroup = 128 queries of one (image, live head)
 // ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(64 * kWaves, 3) void attn_fwd_stream_kernel(const T* __restrict__ qkv, long ldq, T* __restrict__ o,
-                                                                         long ldo, float* __restrict__ lse, int tokens,
-                                                                         int n_live, int n_full, long rows_total, int blocks) {
-    constexpr int ST = Tile<T>::kStage;
-    __shared__ __attribute__((aligned(16))) T lds[2][2][ST * tile_elems<T>()];   // [buffer][K, V]
+template <typename Op> constexpr int lds_bytes() { return 4 * Tile<Op>::kStage * tile_elems<Op>() * (int)sizeof(typename InTile<Op>::type); }
+
+// true, for Parts: a result is not finite and nothing has been written
+template <typename Op, typename T>
+__device__ __forceinline__ bool fwd_body(const T* __restrict__ qkv, long ldq, T* __restrict__ o, long ldo, float* __restrict__ lse,
+                                         int tokens, int n_live, int n_full, long rows_total, int blocks, unsigned char* smem) {
+    typedef typename InTile<Op>::type E;
+    constexpr int ST = Tile<Op>::kStage;
+    E (&lds)[2][2][ST * tile_elems<Op>()] = *reinterpret_cast<E (*)[2][2][ST * tile_elems<Op>()]>(smem);   // [buffer][K, V]
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c = lane & 31, h = lane >> 5;
     const int id = xcd_order(blockIdx.x, gridDim.x);
@@ -302,12 +428,12 @@ __global__ __launch_bounds__(64 * kWaves, 3) void attn_fwd_stream_kernel(const T
     const T* Qb = qkv + row0 * ldq + j * 192;
     const int q0 = (id % blocks) * (kRows * kWaves) + wave * kRows, q = q0 + c;
 
-    Stream<T> sk, sv;
+    Stream<Op> sk, sv;
     sk.init(Qb + 64, ldq, tokens);
     sv.init(Qb + 128, ldq, tokens);
     sk.fetch(0);
     sv.fetch(0);
-    RowOp<T> qf;
+    RowOp<Op> qf;
     qf.load(Qb + (long)q * ldq, q < tokens, h);
     f32x16 ot[2] = {zero16(), zero16()};
     // of the raw scores; sum over this lane's keys only.  The maximum starts at a finite value: a query whose scores so far
@@ -323,14 +449,14 @@ __global__ __launch_bounds__(64 * kWaves, 3) void attn_fwd_stream_kernel(const T
             sv.fetch((s + 1) * ST * kRows);
         }
         __syncthreads();
-        const T* Ks = lds[s & 1][0];
-        const T* Vs = lds[s & 1][1];
+        const E* Ks = lds[s & 1][0];
+        const E* Vs = lds[s & 1][1];
         if (q0 < tokens) {   // uniform over the wavefront
             f32x16 p[ST];
 #pragma unroll
             for (int u = 0; u < ST; ++u) {
                 p[u] = zero16();
-                mma_rows<2>(p[u], Ks + u * tile_elems<T>(), qf, lane);
+                mma_rows<2>(p[u], Ks + u * tile_elems<Op>(), qf, lane);
             }
             if (s + 1 == stages) {   // keys past the last token
 #pragma unroll
@@ -367,7 +493,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void attn_fwd_stream_kernel(const T
 #pragma unroll
                     for (int e = 0; e < w; ++e) t[e] += t[e + w];
                 sum += t[0];
-                mma_tr<3>(ot, Vs + u * tile_elems<T>(), p[u], lane);
+                mma_tr<Op, 3>(ot, Vs + u * tile_elems<Op>(), p[u], lane);
             }
         }
         if (s + 1 < stages) {   // the other buffer was last read before the barrier above
@@ -375,28 +501,65 @@ __global__ __launch_bounds__(64 * kWaves, 3) void attn_fwd_stream_kernel(const T
             sv.store(lds[(s + 1) & 1][1]);
         }
     }
-    if (q0 >= tokens) return;
     sum += __shfl_xor(sum, 32, 64);   // the two lanes of a query hold different keys
-    store_row(ot, 1.0f / sum, o + (row0 + q) * ldo + j * 64, h, q < tokens);
+    if constexpr (std::is_same<Op, Parts>::value) {
+        float odd = fmaf(sum, 0.f, 0.f);   // stays 0, or becomes NaN
+#pragma unroll
+        for (int e = 0; e < 16; ++e) odd = fmaf(ot[0][e], 0.f, fmaf(ot[1][e], 0.f, odd));
+        if (__syncthreads_or(q < tokens && (odd != 0.f || sum == 0.f))) return true;
+    }
+    if (q0 >= tokens) return false;
+    store_row(ot, unscale<Op>() / sum, o + (row0 + q) * ldo + j * 64, h, q < tokens);
     if (q < tokens && h == 0 && j < n_full) lse[(long)j * rows_total + row0 + q] = m * kScale + __logf(sum);
+    return false;
 }
+
+template <typename T>
+__global__ __launch_bounds__(64 * kWaves, sizeof(T) == 4 ? 2 : 3) void attn_fwd_stream_kernel(const T* __restrict__ qkv, long ldq,
+                                                                         T* __restrict__ o, long ldo, float* __restrict__ lse,
+                                                                         int tokens, int n_live, int n_full, long rows_total,
+                                                                         int blocks) {
+    if constexpr (sizeof(T) == 4) {
+        static_assert(lds_bytes<Parts>() >= lds_bytes<float>(), "");
+        extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
+        if (!fwd_body<Parts>(qkv, ldq, o, ldo, lse, tokens, n_live, n_full, rows_total, blocks, dyn)) return;
+        __syncthreads();   // the last stage has been read
+        fwd_body<float>(qkv, ldq, o, ldo, lse, tokens, n_live, n_full, rows_total, blocks, dyn);
+    } else {
+        __shared__ __attribute__((aligned(16))) unsigned char smem[lds_bytes<T>()];
+        fwd_body<T>(qkv, ldq, o, ldo, lse, tokens, n_live, n_full, rows_total, blocks, smem);
+    }
+}
+
 
 // ---------------------------------------------------------------------------
 // backward for p_f heads: the first half of the workgroups 128 keys of one (image, head) each, the rest 128 queries
 // ---------------------------------------------------------------------------
-template <typename T, int TR_PARTS>
-__global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T* __restrict__ qkv, long ldq,
-                                                                         const T* __restrict__ o, long ldo,
-                                                                         const float* __restrict__ lse,
-                                                                         const T* __restrict__ d_o, long ld_do,
-                                                                         T* __restrict__ dqkv, long ld_dqkv,
-                                                                         float* __restrict__ bsum, int tokens,
-                                                                         int n_full, long rows_total, int blocks) {
-    constexpr int ST = Tile<T>::kStage;
-    __shared__ __attribute__((aligned(16))) T lds[2][2][ST * tile_elems<T>()];
-    __shared__ __attribute__((aligned(16))) float consts[2][2][ST * kRows];   // lse (see prob) and delta of a stage's queries
-    __shared__ float red[kWaves][64];
-    static_assert(sizeof(lds) >= kWaves * kRows * 68 * 4 && kWaves == 4, "store_colsum");
+struct BwdShared {
+    float consts[2][2][2 * kRows];   // [buffer]: lse (see prob) and delta of a stage's queries
+    float red[kWaves][64];
+};
+
+// true, for Parts: a result is not finite and nothing has been written
+template <typename Op, int TR_PARTS, typename T>
+__device__ __forceinline__ bool bwd_body(const T* __restrict__ qkv, long ldq, const T* __restrict__ o, long ldo,
+                                         const float* __restrict__ lse, const T* __restrict__ d_o, long ld_do,
+                                         T* __restrict__ dqkv, long ld_dqkv, float* __restrict__ bsum, int tokens, int n_full,
+                                         long rows_total, int blocks, unsigned char* smem, BwdShared& sh) {
+    typedef typename InTile<Op>::type E;
+    constexpr int ST = Tile<Op>::kStage;
+    E (&lds)[2][2][ST * tile_elems<Op>()] = *reinterpret_cast<E (*)[2][2][ST * tile_elems<Op>()]>(smem);
+    auto& consts = sh.consts;
+    auto& red = sh.red;
+    static_assert(lds_bytes<Op>() >= kWaves * kRows * 68 * 4 && kWaves == 4, "store_colsum");
+    constexpr bool kParts = std::is_same<Op, Parts>::value;
+    constexpr float kBack = unscale<Op>();
+    auto odd_of = [](const f32x16 (&t)[2]) {   // 0, or NaN
+        float odd = 0.f;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) odd = fmaf(t[0][e], 0.f, fmaf(t[1][e], 0.f, odd));
+        return odd;
+    };
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c = lane & 31, h = lane >> 5;
     const int half = gridDim.x >> 1;
@@ -422,11 +585,11 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
     };
 
     if (keys) {
-        RowOp<T> kf, vf;
+        RowOp<Op> kf, vf;
         kf.load(Qb + (long)i * ldq + 64, ok, h);
         vf.load(Qb + (long)i * ldq + 128, ok, h);
         f32x16 dk[2] = {zero16(), zero16()}, dv[2] = {zero16(), zero16()};
-        Stream<T, true> sq, sd, so;
+        Stream<Op, true> sq, sd, so;
         sq.init(Qb, ldq, tokens);
         sd.init(dOb, ld_do, tokens);
         so.init(Ob, ldo, tokens);
@@ -446,7 +609,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
             if (threadIdx.x < ST * kRows) consts[buf][0][threadIdx.x] = l;
             // delta of the rows this thread holds a piece of: the lanes of a row are neighbours
 #pragma unroll
-            for (int k = 0; k < Stream<T>::kPer; ++k) {
+            for (int k = 0; k < Stream<Op>::kPer; ++k) {
                 float dl = 0.f;
                 if constexpr (sizeof(T) == 2) {
 #pragma unroll
@@ -459,8 +622,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
                     for (int x = 0; x < 4; ++x) dl = fmaf(__uint_as_float(sd.v[k][x]), __uint_as_float(so.v[k][x]), dl);
                 }
 #pragma unroll
-                for (int w = 1; w < Tile<T>::kPieces; w <<= 1) dl += __shfl_xor(dl, w, 64);
-                if (threadIdx.x % Tile<T>::kPieces == 0) consts[buf][1][threadIdx.x / Tile<T>::kPieces + k * Stream<T>::kStep] = dl;
+                for (int w = 1; w < Tile<Op>::kPieces; w <<= 1) dl += __shfl_xor(dl, w, 64);
+                if (threadIdx.x % Tile<Op>::kPieces == 0) consts[buf][1][threadIdx.x / Tile<Op>::kPieces + k * Stream<Op>::kStep] = dl;
             }
         };
         fetch(0);
@@ -471,8 +634,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
             if (i0 < tokens) {
 #pragma unroll
                 for (int u = 0; u < ST; ++u) {
-                    const T* Qs = lds[s & 1][0] + u * tile_elems<T>();
-                    const T* dOs = lds[s & 1][1] + u * tile_elems<T>();
+                    const E* Qs = lds[s & 1][0] + u * tile_elems<Op>();
+                    const E* dOs = lds[s & 1][1] + u * tile_elems<Op>();
                     f32x16 p = zero16(), dp = zero16();   // element e: query 8*(e/4) + 4h + e%4 of the tile
                     mma_rows<2>(p, Qs, kf, lane);
                     mma_rows<1>(dp, dOs, vf, lane);
@@ -486,40 +649,42 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
                             dp[4 * g + x] = p[4 * g + x] * (dp[4 * g + x] - dq[x]);
                         }
                     }
-                    mma_tr<TR_PARTS>(dv, dOs, p, lane);
-                    mma_tr<TR_PARTS>(dk, Qs, dp, lane);
+                    mma_tr<Op, TR_PARTS>(dv, dOs, p, lane);
+                    mma_tr<Op, TR_PARTS>(dk, Qs, dp, lane);
                 }
             }
             if (s + 1 < stages) store((s + 1) & 1);
         }
+        const float odd = odd_of(dk);
+        if constexpr (kParts) {
+            if (__syncthreads_or(ok && (odd != 0.f || odd_of(dv) != 0.f))) return true;
+        }
         if (i0 < tokens) {
-            store_row(dk, kScale, dQb + (long)i * ld_dqkv + 64, h, ok);
-            store_row(dv, 1.f, dQb + (long)i * ld_dqkv + 128, h, ok);
+            store_row(dk, kScale * kBack, dQb + (long)i * ld_dqkv + 64, h, ok);
+            store_row(dv, kBack, dQb + (long)i * ld_dqkv + 128, h, ok);
         }
         if (bsum) {
             float* const row = bsum + ((long)b * blocks + id % blocks) * n_full * 192 + j * 192;
             // softmax does not see a common shift of the keys: the columns of dK sum to zero, unless some are not finite
-            float odd = 0.f;   // stays 0, or becomes NaN
-#pragma unroll
-            for (int e = 0; e < 16; ++e) odd = fmaf(dk[0][e], 0.f, fmaf(dk[1][e], 0.f, odd));
-            if (__syncthreads_or(ok && odd != 0.f)) store_colsum(dk, kScale, ok, reinterpret_cast<float*>(lds), red, row + 64);
+            if (!kParts && __syncthreads_or(ok && odd != 0.f)) store_colsum(dk, kScale, ok, reinterpret_cast<float*>(lds), red, row + 64);
             else if (threadIdx.x < 64) row[64 + threadIdx.x] = 0.f;
-            store_colsum(dv, 1.f, ok, reinterpret_cast<float*>(lds), red, row + 128);
+            store_colsum(dv, kBack, ok, reinterpret_cast<float*>(lds), red, row + 128);
         }
     } else {
-        RowOp<T> qf, df;
-        qf.load(Qb + (long)i * ldq, ok, h);
-        df.load(dOb + (long)i * ld_do, ok, h);
         float delta;
         {
-            RowOp<T> of;
+            RowOp<T> of, df;
             of.load(Ob + (long)i * ldo, ok, h);
+            df.load(dOb + (long)i * ld_do, ok, h);
             delta = RowOp<T>::dot(df, of);
             delta += __shfl_xor(delta, 32, 64);
         }
+        RowOp<Op> qf, df;
+        qf.load(Qb + (long)i * ldq, ok, h);
+        df.load(dOb + (long)i * ld_do, ok, h);
         const float lq = ok ? lse_b[i] * kLse : 0.f;
         f32x16 dq[2] = {zero16(), zero16()};
-        Stream<T> sk, sv;
+        Stream<Op> sk, sv;
         sk.init(Qb + 64, ldq, tokens);
         sv.init(Qb + 128, ldq, tokens);
         sk.fetch(0);
@@ -535,8 +700,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
             if (i0 < tokens) {
 #pragma unroll
                 for (int u = 0; u < ST; ++u) {
-                    const T* Ks = lds[s & 1][0] + u * tile_elems<T>();
-                    const T* Vs = lds[s & 1][1] + u * tile_elems<T>();
+                    const E* Ks = lds[s & 1][0] + u * tile_elems<Op>();
+                    const E* Vs = lds[s & 1][1] + u * tile_elems<Op>();
                     f32x16 p = zero16(), dp = zero16();   // element e: key 8*(e/4) + 4h + e%4 of the tile
                     mma_rows<2>(p, Ks, qf, lane);
                     mma_rows<1>(dp, Vs, df, lane);
@@ -548,7 +713,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
                     }
 #pragma unroll
                     for (int e = 0; e < 16; ++e) dp[e] = prob(p[e], lq) * (dp[e] - delta);
-                    mma_tr<TR_PARTS>(dq, Ks, dp, lane);
+                    mma_tr<Op, TR_PARTS>(dq, Ks, dp, lane);
                 }
             }
             if (s + 1 < stages) {
@@ -556,12 +721,47 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bwd_stream_kernel(const T
                 sv.store(lds[(s + 1) & 1][1]);
             }
         }
-        if (i0 < tokens) store_row(dq, kScale, dQb + (long)i * ld_dqkv, h, ok);
-        if (bsum) store_colsum(dq, kScale, ok, reinterpret_cast<float*>(lds), red, bsum + ((long)b * blocks + id % blocks) * n_full * 192 + j * 192);
+        if constexpr (kParts) {
+            if (__syncthreads_or(ok && odd_of(dq) != 0.f)) return true;
+        }
+        if (i0 < tokens) store_row(dq, kScale * kBack, dQb + (long)i * ld_dqkv, h, ok);
+        if (bsum) store_colsum(dq, kScale * kBack, ok, reinterpret_cast<float*>(lds), red, bsum + ((long)b * blocks + id % blocks) * n_full * 192 + j * 192);
+    }
+    return false;
+}
+
+template <typename T, int TR_PARTS>
+__global__ __launch_bounds__(64 * kWaves, sizeof(T) == 4 ? 1 : 2) void attn_bwd_stream_kernel(const T* __restrict__ qkv, long ldq,
+                                                                         const T* __restrict__ o, long ldo,
+                                                                         const float* __restrict__ lse,
+                                                                         const T* __restrict__ d_o, long ld_do,
+                                                                         T* __restrict__ dqkv, long ld_dqkv,
+                                                                         float* __restrict__ bsum, int tokens,
+                                                                         int n_full, long rows_total, int blocks) {
+    __shared__ __attribute__((aligned(16))) BwdShared sh;
+    if constexpr (sizeof(T) == 4) {
+        extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
+        if (!bwd_body<Parts, 1>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, tokens, n_full, rows_total, blocks, dyn, sh)) return;
+        __syncthreads();   // the last stage has been read
+        bwd_body<float, 1>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, tokens, n_full, rows_total, blocks, dyn, sh);
+    } else {
+        __shared__ __attribute__((aligned(16))) unsigned char smem[lds_bytes<T>()];
+        bwd_body<T, TR_PARTS>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, tokens, n_full, rows_total, blocks, smem, sh);
     }
 }
 
+
 inline bool mult8(long v) { return (v & 7) == 0; }
+
+// The fp32 kernels' dynamic LDS is above the default limit: raised once per device.
+hipError_t allow_lds(const void* kern, std::atomic<uint32_t>& set_on) {   // set_on: devices, one bit each
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess || (dev < 32 && (set_on.load() >> dev & 1))) return e;
+    e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes<Parts>());
+    if (e == hipSuccess && dev < 32) set_on.fetch_or(1u << dev);
+    return e;
+}
 
 }  // namespace
 
@@ -596,10 +796,13 @@ hipError_t launch_attn_fwd_stream(int dtype, const void* qkv, long ldq, void* o,
     const int blocks = attn_stream_blocks(tokens);
     const dim3 grid((unsigned)((long)batch * n_live * blocks)), block(64 * kWaves);
     const long rows = (long)batch * tokens;
-    if (dtype == D2FT_F32)
-        hipLaunchKernelGGL(attn_fwd_stream_kernel<float>, grid, block, 0, s, (const float*)qkv, ldq, (float*)o, ldo, lse, tokens,
+    if (dtype == D2FT_F32) {
+        static std::atomic<uint32_t> set_on{0};
+        const hipError_t e = allow_lds(reinterpret_cast<const void*>(attn_fwd_stream_kernel<float>), set_on);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(attn_fwd_stream_kernel<float>, grid, block, lds_bytes<Parts>(), s, (const float*)qkv, ldq, (float*)o, ldo, lse, tokens,
                            n_live, n_full, rows, blocks);
-    else
+    } else
         hipLaunchKernelGGL(attn_fwd_stream_kernel<bf16>, grid, block, 0, s, (const bf16*)qkv, ldq, (bf16*)o, ldo, lse, tokens,
                            n_live, n_full, rows, blocks);
     return hipGetLastError();
@@ -614,10 +817,17 @@ static hipError_t launch_bwd(const void* qkv, long ldq, const void* o, long ldo,
     const T *q = (const T*)qkv, *op = (const T*)o, *dop = (const T*)d_o;
     T* dq = (T*)dqkv;
     const long rows = (long)batch * tokens;
+    int lds = 0;
+    if (sizeof(T) == 4) {
+        static std::atomic<uint32_t> set_on{0};
+        const hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), set_on);
+        if (e != hipSuccess) return e;
+        lds = lds_bytes<Parts>();
+    }
     if (hipEvent_t ev = launch_signal_take())   // the launch completes the event itself
-        hipExtLaunchKernelGGL(kern, grid, block, 0, s, nullptr, ev, 0, q, ldq, op, ldo, lse, dop, ld_do, dq, ld_dqkv, bsum, tokens, n_full, rows, blocks);
+        hipExtLaunchKernelGGL(kern, grid, block, lds, s, nullptr, ev, 0, q, ldq, op, ldo, lse, dop, ld_do, dq, ld_dqkv, bsum, tokens, n_full, rows, blocks);
     else
-        hipLaunchKernelGGL(kern, grid, block, 0, s, q, ldq, op, ldo, lse, dop, ld_do, dq, ld_dqkv, bsum, tokens, n_full, rows, blocks);
+        hipLaunchKernelGGL(kern, grid, block, lds, s, q, ldq, op, ldo, lse, dop, ld_do, dq, ld_dqkv, bsum, tokens, n_full, rows, blocks);
     return hipGetLastError();
 }
 

@@ -181,3 +181,24 @@ def test_which_kernel_runs_the_bf16_backward(tokens, images, stream):
     finally:
         P.d2ft_timing_enable(False)
     assert ("attn_bwd_stream" in names) == stream and ("attn_bwd_mfma" in names) == (not stream), names
+
+
+@pytest.mark.parametrize("tokens", [65, 197])
+def test_fp32_values_without_bf16_parts(tokens):
+    """A value channel of 2^105 has no bf16 parts: its workgroups form their rows again with the fp32 instruction, and
+    everything else comes out as it does without it.  The channel's rows of W_o bring it back to ordinary size."""
+    w = di.Workload("no_parts", 2, tokens, 128, 2, 64, 64, 1, "f32")
+    x, wt, dy = draw_block(w, 92)
+    wt["b_qkv"][2, 1, 7] = np.float32(2.0 ** 105)
+    wt["w_o"][:, 64 + 7] *= np.float32(2.0 ** -105)
+    fields = ("w_qkv", "b_qkv", "w_o")
+    y, dx, g = gpu_block(w, wt, [FULL, FULL], x, dy, fields)
+    ry, rdx, rg, _ = oracle_block(w, wt, [FULL, FULL], x, dy)
+    assert rel_inf(y, ry) < TOL["f32"] and rel_inf(dx, rdx) < TOL["f32"]
+    for k in ("w_qkv", "b_qkv"):
+        for p in range(3):
+            # the key bias gradient is what rounding leaves of zero
+            assert rel_inf(g[k][p], rg[k][p]) < TOL["f32"] or (k, p) == ("b_qkv", 1), (k, p)
+    keep = [c for c in range(128) if c != 64 + 7]
+    assert rel_inf(g["w_o"][:, keep], rg["w_o"][:, keep]) < TOL["f32"]
+    assert rel_inf(g["w_o"][:, 64 + 7], rg["w_o"][:, 64 + 7]) < TOL["f32"]
