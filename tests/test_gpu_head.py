@@ -106,6 +106,45 @@ def test_head_frozen_norm_and_single_class_count_edge():
     run_head("f32", 3, 2, 16, 300, 124, frozen_ln=True)     # more classes than threads in a workgroup
 
 
+@pytest.mark.parametrize("dtype,B,T,D,n", [("f32", 257, 2, 264, 33), ("bf16", 3, 40, 520, 9), ("bf16", 2, 65, 1032, 1000),
+                                           ("f32", 1, 1, 512, 8)])
+def test_head_at_the_edges_of_its_pieces(dtype, B, T, D, n):
+    """Images are staged by 256, channels taken by 512 and 256, classes by 8 and 32, cleared rows by 32 KiB."""
+    run_head(dtype, B, T, D, n, 125)
+
+
+@pytest.mark.parametrize("B", [7, 8, 9, 41])
+def test_embed_images_over_the_lanes(B):
+    run_embed("f32", B, 1, 16, 24, 8, 40, 126)              # 7 tokens x 5 pieces: the second workgroup is part empty
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_head_takes_pointers_of_element_alignment(dtype):
+    """Every tensor one element past a 16-byte boundary: the same bits as from aligned ones."""
+    import torch
+    import paper_2504_12471_amd as Pk
+    rng = np.random.default_rng(127)
+    B, T, D, n = 3, 5, 72, 11
+    labels = rng.integers(0, n, size=B)
+    desc = Pk.HeadDesc(B, T, D, n, 1e-6, Pk.BF16 if dtype == "bf16" else Pk.F32, 0)
+    h = {k: Pk.to_device(rng.standard_normal(s).astype(np.float32), dtype)
+         for k, s in dict(tokens=(B, T, D), ln_g=D, ln_b=D, w_c=(n, D), b_c=n).items()}
+
+    def shifted(t, by):
+        return torch.empty(t.numel() + 8, dtype=t.dtype, device=t.device)[by:by + t.numel()].view(t.shape).copy_(t)
+
+    def run(by):
+        i = {k: shifted(t, by) for k, t in h.items()}
+        o = {k: shifted(torch.full_like(t, float("nan")), by) for k, t in h.items()}
+        scratch = torch.empty(Pk.d2ft_head_scratch_bytes(desc), dtype=torch.uint8, device="cuda")
+        loss = Pk.d2ft_classifier_fwd_bwd(desc, i["tokens"], i["ln_g"], i["ln_b"], i["w_c"], i["b_c"], labels, o["tokens"],
+                                          o["ln_g"], o["ln_b"], o["w_c"], o["b_c"], scratch)
+        return loss, o
+
+    (l0, o0), (l1, o1) = run(0), run(1)
+    assert l0 == l1 and all(torch.equal(o0[k], o1[k]) for k in o0)
+
+
 def test_bad_labels_and_shapes_are_rejected():
     import torch
     import paper_2504_12471_amd as Pk
