@@ -56,17 +56,37 @@ __device__ __forceinline__ void store8(bf16* p, const float (&v)[8]) {
 }
 
 // ---------------------------------------------------------------------------
-// wavefront reductions (all 64 lanes take part and receive the result)
+// wavefront reductions (all 64 lanes take part and receive the result): inside a row of 16 lanes as operands of the
+// additions themselves (DPP), then over the four rows' results by scalar reads.  A lane exchange through LDS costs some 100
+// cycles, and a reduction is a chain of six; LayerNorm, whose time is such latencies, takes two reductions a row.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float lane_value(float v, int lane) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+constexpr int kDppXor1 = 0xb1, kDppXor2 = 0x4e;             // quad_perm [1,0,3,2] and [2,3,0,1]
+constexpr int kDppHalfMirror = 0x141, kDppMirror = 0x140;   // of 8 and of 16 lanes: the other four, the other eight
+// the sum over a lane's row of 16
+__device__ __forceinline__ float row16_sum(float v) {
+    v += dpp<kDppXor1>(v);
+    v += dpp<kDppXor2>(v);
+    v += dpp<kDppHalfMirror>(v);
+    v += dpp<kDppMirror>(v);
     return v;
 }
+__device__ __forceinline__ float wave_sum(float v) {
+    v = row16_sum(v);
+    return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-    return v;
+    v = fmaxf(v, dpp<kDppXor1>(v));
+    v = fmaxf(v, dpp<kDppXor2>(v));
+    v = fmaxf(v, dpp<kDppHalfMirror>(v));
+    v = fmaxf(v, dpp<kDppMirror>(v));
+    return fmaxf(fmaxf(lane_value(v, 0), lane_value(v, 16)), fmaxf(lane_value(v, 32), lane_value(v, 48)));
 }
 
 // exact (erf) GELU and its derivative
