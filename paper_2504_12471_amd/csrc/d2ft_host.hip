@@ -336,6 +336,30 @@ hipError_t run_gemm(const GemmArgs& g, const d2ft_block_desc* d, hipStream_t s, 
     return e;
 }
 
+// LayerNorm of the rows of x into n.y, g's A operand
+hipError_t run_ln(const void* x, const LnArgs& n, const GemmArgs& g, const d2ft_block_desc* d, hipStream_t s) {
+    timing_begin(s, "launch_ln_fwd");
+    const hipError_t e = launch_ln_fwd(d->dtype, x, n.gamma, n.beta, n.y, n.mean, n.rstd, g.M, g.K, n.eps, s);
+    g_timing.bytes = 2.0 * g.M * g.K * (d->dtype == D2FT_F32 ? 4 : 2) + 8.0 * g.M;
+    timing_end(s);
+    return e;
+}
+
+// LayerNorm of the rows of x into n.y and the product g of the result, in one launch where that is faster
+hipError_t run_ln_gemm(const void* x, const LnArgs& n, const GemmArgs& g, const d2ft_block_desc* d, hipStream_t s) {
+    GemmArgs f = g;
+    f.A = x;
+    if (!(d->flags & D2FT_FLAG_NO_MFMA) && gemm_ln_faster(f, n, d->dtype)) {
+        timing_begin(s, "gemm");
+        g_timing.flops = 2.0 * g.M * g.N * g.K;
+        const hipError_t e = launch_gemm_ln(f, n, d->dtype, s);
+        timing_end(s);
+        return e;
+    }
+    const hipError_t e = run_ln(x, n, g, d, s);
+    return e == hipSuccess ? run_gemm(g, d, s) : e;
+}
+
 // A gated feed-forward product over the whole batch whose micro-batches have their own codes: the rows of
 // micro-batch i times the slices (positions of `slice` columns) in pos_of[i], zeros elsewhere; 256x256 tiles
 // that no micro-batch needs are not multiplied.  hipErrorNotSupported (nothing launched) if the shape does not
@@ -862,8 +886,7 @@ static d2ft_status block_fwd_impl(const d2ft_block_desc* desc, const d2ft_block_
     const void* x1 = x;   // all heads shortcut: the attention residual is x itself
     if (part != PART_MLP && nl > 0) {
         void* u = sv + SL.u;
-        D2FT_TRY_BYTES(2.0 * s.M * s.D * s.es + 8.0 * s.M, launch_ln_fwd(s.dtype, x, w->ln1_g, w->ln1_b, u, (float*)(sv + SL.mean1), (float*)(sv + SL.rstd1), M,
-                               s.D, desc->ln_eps, st));
+        const LnArgs norm = {w->ln1_g, w->ln1_b, u, (float*)(sv + SL.mean1), (float*)(sv + SL.rstd1), desc->ln_eps};
         // Q, K, V of the live heads only
         GemmArgs g = gemm_base();
         fill_qkv_table(g.tbl, live, nl, s.H);
@@ -880,7 +903,7 @@ static d2ft_status block_fwd_impl(const d2ft_block_desc* desc, const d2ft_block_
         } else {
             g.B = w->w_qkv; g.b_rs = 1; g.b_cs = s.D; g.remap = REMAP_B_N;
         }
-        D2FT_TRY_UNTIMED(run_gemm(g, desc, st));
+        D2FT_TRY_UNTIMED(run_ln_gemm(x, norm, g, desc, st));
         // softmax attention per (image, live head); log-sum-exp kept for p_f heads only
         D2FT_TRY(run_attn_fwd(desc, sv + SL.qkv, nl * 192, sv + SL.o, nl * 64, (float*)(sv + SL.lse), s.B, s.T, nl, nf,
                               st, mask));
@@ -925,8 +948,7 @@ static d2ft_status block_fwd_impl(const d2ft_block_desc* desc, const d2ft_block_
     memset(&ffn_tbl, 0, sizeof(ffn_tbl));
     if (gate) fill_ffn_table(ffn_tbl, live, nl, slice);
     void* v = sv + SL.v;
-    D2FT_TRY_BYTES(2.0 * s.M * s.D * s.es + 8.0 * s.M, launch_ln_fwd(s.dtype, x1, w->ln2_g, w->ln2_b, v, (float*)(sv + SL.mean2), (float*)(sv + SL.rstd2), M, s.D,
-                           desc->ln_eps, st));
+    const LnArgs norm = {w->ln2_g, w->ln2_b, v, (float*)(sv + SL.mean2), (float*)(sv + SL.rstd2), desc->ln_eps};
     {   // z = v W1^T + b1, g = GELU(z)
         GemmArgs g = gemm_base();
         g.tbl = ffn_tbl;
@@ -938,12 +960,17 @@ static d2ft_status block_fwd_impl(const d2ft_block_desc* desc, const d2ft_block_
         g.act = ACT_GELU; g.Z = sv + SL.z; g.ldz = n_hid;
         // a subnet skipped in a micro-batch adds nothing to that micro-batch's rows: left out of the product, or
         // zeroed behind it
-        hipError_t es = (gate && mask) ? run_gemm_segments(g, desc, *mask, mask->live, s.T, slice, st) : hipErrorNotSupported;
-        if (es == hipErrorNotSupported) {
-            D2FT_TRY_UNTIMED(run_gemm(g, desc, st));
-            if (gate && mask) D2FT_TRY(launch_zero_pairs(s.dtype, sv + SL.g, sv + SL.z, n_hid, s.B, s.T, nl, slice, PAIRS_SKIPPED, *mask, st));
-        } else if (es != hipSuccess) {
-            return D2FT_EDEVICE;
+        if (gate && mask) {
+            D2FT_TRY_UNTIMED(run_ln(x1, norm, g, desc, st));
+            const hipError_t es = run_gemm_segments(g, desc, *mask, mask->live, s.T, slice, st);
+            if (es == hipErrorNotSupported) {
+                D2FT_TRY_UNTIMED(run_gemm(g, desc, st));
+                D2FT_TRY(launch_zero_pairs(s.dtype, sv + SL.g, sv + SL.z, n_hid, s.B, s.T, nl, slice, PAIRS_SKIPPED, *mask, st));
+            } else if (es != hipSuccess) {
+                return D2FT_EDEVICE;
+            }
+        } else {
+            D2FT_TRY_UNTIMED(run_ln_gemm(x1, norm, g, desc, st));
         }
     }
     {   // y = x1 + g W2^T + b2
