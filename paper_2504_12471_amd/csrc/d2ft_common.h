@@ -199,14 +199,14 @@ bool gemm_tile64_supported(const GemmArgs& g, int dtype);
 bool gemm_tile64_faster(const GemmArgs& g);   // a bf16 product that launch_gemm_mfma would give 128x128 tiles
 hipError_t launch_gemm_tile64(const GemmArgs& g, int dtype, hipStream_t s);
 // LayerNorm of the rows of g.A and the product of its result with B in one launch (kernels_gemm_ln.hip): rows of at most
-// 2 KB in whole multiples of 128 bytes; hipErrorNotSupported otherwise
+// 2 KB in whole multiples of 128 bytes, and where that is faster than two launches; hipErrorNotSupported otherwise
 struct LnArgs {
     const void *gamma, *beta;
     void* y;             // [M][K]
     float *mean, *rstd;  // [M]
     float eps;
 };
-bool gemm_ln_faster(const GemmArgs& g, const LnArgs& n, int dtype);   // supported, and faster than as two launches
+bool gemm_ln_faster(const GemmArgs& g, const LnArgs& n, int dtype);
 hipError_t launch_gemm_ln(const GemmArgs& g, const LnArgs& n, int dtype, hipStream_t s);
 // bf16 MFMA path; returns hipErrorNotSupported if the shape/strides do not fit it
 hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s);

@@ -1,6 +1,6 @@
 """GPU parity of LayerNorm fused into the product behind it (kernels_gemm_ln.hip) through one block forward + backward, at
-the sizes where it can go wrong: rows and columns at and beside the edges of its 32x64 tile, rows of x that end inside and
-at the ends of the four lengths it is built for, both types, the remaps and merged weights."""
+the sizes where it can go wrong: rows and columns at and beside the edges of its 32x64 and 32x96 tiles, rows of x that end
+inside and at the ends of the four lengths it is built for, both types, the remaps and merged weights."""
 import pytest
 
 import d2ft_inputs as di
@@ -22,33 +22,41 @@ def kernels_of(run):
         P.d2ft_timing_enable(False)
 
 
-@pytest.mark.parametrize("dtype,batch,tokens,width,heads,mlp,length", [
-    ("bf16", 1, 3, 64, 1, 64, 1),          # one slab of K: three of the four K groups have none
-    ("bf16", 1, 33, 256, 2, 264, 1),       # one row and one piece of columns beside the tile; rows of 512 bytes
-    ("bf16", 1, 31, 320, 3, 1280, 2),
-    ("bf16", 2, 16, 512, 2, 520, 2),       # rows of 1024 bytes, one exact tile of rows
-    ("bf16", 1, 65, 576, 2, 1032, 3),
-    ("bf16", 1, 197, 768, 4, 1536, 3),     # rows of 1536 bytes
-    ("bf16", 1, 33, 832, 1, 832, 4),
-    ("bf16", 1, 65, 1024, 2, 1032, 4),     # the longest rows
-    ("f32", 1, 3, 32, 1, 64, 1),
-    ("f32", 1, 33, 128, 2, 264, 1),
-    ("f32", 4, 65, 192, 3, 768, 2),
-    ("f32", 4, 65, 288, 3, 1032, 3),
-    ("f32", 2, 197, 384, 3, 1536, 3),
-    ("f32", 1, 197, 512, 4, 2048, 4),
+@pytest.mark.parametrize("dtype,batch,tokens,width,heads,mlp,form", [
+    ("bf16", 1, 3, 64, 1, 64, "1, 64"),          # one slab of K: three of the four K groups have none
+    ("bf16", 1, 33, 256, 2, 264, "1, 64"),       # one row and one piece of columns beside the tile; rows of 512 bytes
+    ("bf16", 1, 31, 320, 3, 1280, "2, 64"),
+    ("bf16", 2, 16, 512, 2, 520, "2, 64"),       # rows of 1024 bytes, one exact tile of rows
+    ("bf16", 1, 65, 576, 2, 1032, "3, 64"),
+    ("bf16", 1, 197, 768, 4, 1536, "3, 64"),     # rows of 1536 bytes
+    ("bf16", 1, 33, 832, 1, 832, "4, 64"),
+    ("bf16", 1, 65, 1024, 2, 1032, "4, 64"),     # the longest rows
+    ("f32", 1, 3, 32, 1, 64, "1, 64"),
+    ("f32", 1, 33, 128, 2, 264, "1, 64"),
+    ("f32", 4, 65, 192, 3, 768, "2, 64"),
+    ("f32", 4, 65, 288, 3, 1032, "3, 64"),
+    ("f32", 2, 197, 384, 3, 1032, "3, 64"),
+    ("f32", 1, 197, 512, 4, 2048, "4, 64"),
+    ("bf16", 4, 197, 192, 2, 776, "1, 96"),   # a last tile of 8 columns, a last wavefront without any
+    ("bf16", 2, 197, 384, 3, 1600, "2, 96"),
+    ("bf16", 1, 225, 768, 3, 2648, "3, 96"),   # one row beside the tile
+    ("bf16", 1, 129, 1024, 2, 4096, "4, 96"),
+    ("f32", 5, 197, 192, 2, 768, "2, 96"),
+    ("f32", 2, 197, 384, 3, 1600, "3, 96"),
+    ("f32", 1, 257, 512, 2, 2048, "4, 96"),
 ])
-def test_tile_and_row_edges(dtype, batch, tokens, width, heads, mlp, length):
+def test_tile_and_row_edges(dtype, batch, tokens, width, heads, mlp, form):
     w = di.Workload("ln_product", batch, tokens, width, heads, 64, mlp, 1, dtype)
     names = kernels_of(lambda: run_case(w, [FULL, FWD, FULL, SKIP][:heads], seed=81))
-    assert "gemm_ln_kernel<%s, %d>" % ("__bf16" if dtype == "bf16" else "float", length) in names, names
+    assert "gemm_ln_kernel<%s, %s>" % ("__bf16" if dtype == "bf16" else "float", form) in names, names
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_gated_slices_through_the_remap(dtype):
-    w = di.Workload("ln_product_gate", 2, 65, 256, 4, 64, 1024, 1, dtype)
+@pytest.mark.parametrize("images,columns", [(2, 64), (12, 96)])   # tiles of 96 begin inside the remap's blocks
+def test_gated_slices_through_the_remap(dtype, images, columns):
+    w = di.Workload("ln_product_gate", images, 65, 256, 4, 64, 1024, 1, dtype)
     names = kernels_of(lambda: run_gated(w, [FULL, SKIP, FWD, FULL], seed=82))
-    assert [n for n in names if n.startswith("gemm_ln_kernel")], names
+    assert [n for n in names if n.startswith("gemm_ln_kernel") and n.endswith(", %d>" % columns)], names
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
@@ -58,7 +66,7 @@ def test_merged_adapter_weights(dtype):
     assert [n for n in names if n.startswith("gemm_ln_kernel")], names
 
 
-@pytest.mark.parametrize("tokens,fused", [(224, True), (257, False)])
+@pytest.mark.parametrize("tokens,fused", [(224, True), (353, False)])
 def test_line_between_one_launch_and_two(tokens, fused):
     """Width 768 in bf16: a workgroup per CU at most."""
     w = di.Workload("ln_product_line", 1, tokens, 768, 12, 64, 768, 1, "bf16")
