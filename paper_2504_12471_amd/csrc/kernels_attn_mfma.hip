@@ -332,8 +332,11 @@ __device__ __forceinline__ bool fwd_pair(const Mask& mask, int b, int slot, int 
     return true;
 }
 
-// One workgroup per (image, slot), four wavefronts that share the query tiles (tokens above 224, where the
-// kernel below would need a ninth wavefront).
+// One or two (gridDim.y) workgroups per (image, slot), four wavefronts each, that share the query tiles (tokens above 224,
+// where the kernel below would need a ninth wavefront).  The exponentials of a query tile are most of a wavefront's time, so
+// with few pairs a second workgroup takes half the tiles, at the price of loading K and V too, and the Q of a wavefront's first
+// tile is requested ahead of them.  256 tokens: 12 pairs 10.2 -> 7.4 us, 120 pairs 12.8 -> 9.8, 384 pairs (one workgroup each)
+// 24.8 -> 24.3.  Up to 224 tokens the kernel below is as fast in a pass of many kernels.
 template <int KT, typename Mask>   // KT: number of 32-token tiles
 __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __restrict__ qkv, long ldq,
                                                             bf16* __restrict__ o, long ldo, float* __restrict__ lse,
@@ -351,13 +354,15 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16* __res
     bool save_lse;
     if (!fwd_pair(mask, b, blockIdx.x % n_live, n_live, n_full, tokens, o, ldo, j, save_lse)) return;
     const bf16* Qb = qkv + row0 * ldq + j * 192;
+    const int first = blockIdx.y * 4 + wave, step = gridDim.y * 4;
+    bf16x8 qf[4];
+    load_q_frags(Qb, ldq, first * 32 + c, first * 32 + c < tokens, h, qf);   // ahead of K and V, which it would wait behind
     load_two_tiles64<TP>(Qb + 64, Qb + 128, ldq, tokens, Ks, kKS, Vs, kVS);
     __syncthreads();
-    for (int qt = wave; qt < KT; qt += 4) {
+    for (int qt = first; qt < KT; qt += step) {
         const int q = qt * 32 + c;
         const bool q_ok = q < tokens;
-        bf16x8 qf[4];
-        load_q_frags(Qb, ldq, q, q_ok, h, qf);
+        if (qt != first) load_q_frags(Qb, ldq, q, q_ok, h, qf);
         f32x16 ot[2];
         float m, sum;
         fwd_unit<KT>(Ks, Vs, qf, tokens, lane, ot, m, sum, [] {});
@@ -477,7 +482,8 @@ hipError_t launch_fwd_kt(const bf16* qkv, long ldq, bf16* o, long ldo, float* ls
             if (e != hipSuccess) return e;
             attr_set = true;
         }
-        hipLaunchKernelGGL(kern, dim3(batch * n_live), dim3(256), lds, s, qkv, ldq, o, ldo, lse, tokens, n_live, n_full,
+        const int pairs = batch * n_live, parts = pairs <= 128 ? 2 : 1;   // two: while each finds a CU of its own
+        hipLaunchKernelGGL(kern, dim3(pairs, parts), dim3(256), lds, s, qkv, ldq, o, ldo, lse, tokens, n_live, n_full,
                            (long)batch * tokens, mask);
         return hipGetLastError();
     }
