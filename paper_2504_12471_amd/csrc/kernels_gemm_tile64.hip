@@ -443,6 +443,9 @@ hipError_t launch_form(int wk, unsigned grid, hipStream_t s, const Args& a) {
     if constexpr (TM * TN == 64 * 64) {
         if (wk == 1) return launch_wk<T, TM, TN, A_COL, B_COL, 1>(grid, s, a);
     }
+    if constexpr (TM * TN == 32 * 32 && sizeof(T) == 2) {
+        if (wk == 8) return launch_wk<T, TM, TN, A_COL, B_COL, 8>(grid, s, a);
+    }
     if (wk == 4) return launch_wk<T, TM, TN, A_COL, B_COL, 4>(grid, s, a);
     return launch_wk<T, TM, TN, A_COL, B_COL, 2>(grid, s, a);
 }
@@ -497,7 +500,8 @@ bool gemm_tile64_supported(const GemmArgs& g, int dtype) {
 // a first round that waits for its loads, further ones beside it.  Fitted on this part, bf16 to 1766 shapes (M 17 .. 12608,
 // N and K 64 .. 8192; rms error 5 to 8 %), fp32 to some 150 (M 64 .. 3152, N and K 64 .. 4096).  bf16: a CU's loads set the pace, so a slab costs in proportion to the tile's rows
 // + columns and a small tile pays where large ones leave CUs idle: 197 x 768 x 3072, 64x64 tiles 16.2 us, 64x32 12.3,
-// 32x32 8.9; 985 x 384 x 1536: 10.3, 8.6, 8.9; 985 x 2304 x 768: 13.6, 15.2, 17.2.  fp32: the matrix cores, so a slab
+// 32x32 8.9; 985 x 384 x 1536: 10.3, 8.6, 8.9; 985 x 2304 x 768: 13.6, 15.2, 17.2.  Eight K groups of a 32x32 tile have twice
+// the slabs in flight and more sums to add: 197 x 768 x 3072 8.8 -> 8.4 us, x 4096 10.4 -> 9.4, x 2304 none.  fp32: the matrix cores, so a slab
 // costs in proportion to the tile's area and what a small tile saves is the last, partly empty round: 197 x 2304 x 768:
 // 19.5, 20.7, 12.8; 3152 x 384 x 1536: 61, 51, 46; 3152 x 1536 x 384: 47.9, 52.4, 56.6.
 struct Tile64Form {
@@ -506,7 +510,8 @@ struct Tile64Form {
 };
 constexpr Tile64Form kFormsBf16[] = {{64, 64, 1, 3.71f, 0.370f, 0.183f, 0.77f, 0.77f}, {64, 64, 2, 3.91f, 0.262f, 0.208f, 1.24f, 0.77f},
                                      {64, 32, 2, 3.67f, 0.217f, 0.133f, 0.77f, 0.36f}, {64, 32, 4, 4.47f, 0.171f, 0.181f, 2.99f, 0.75f},
-                                     {32, 32, 2, 3.49f, 0.168f, 0.082f, 0.55f, 0.19f}, {32, 32, 4, 3.94f, 0.111f, 0.084f, 1.22f, 0.33f}};
+                                     {32, 32, 2, 3.49f, 0.168f, 0.082f, 0.55f, 0.19f}, {32, 32, 4, 3.94f, 0.111f, 0.084f, 1.22f, 0.33f},
+                                     {32, 32, 8, 5.55f, 0.061f, 0.1f, 10.0f, 0.33f}};   // one to a CU
 constexpr Tile64Form kFormsF32[] = {{64, 64, 1, 4.4f, 0.61f, 0.52f, 3.0f, 0.0f}, {64, 32, 2, 3.4f, 0.37f, 0.26f, 1.9f, 0.0f},
                                     {32, 32, 2, 3.2f, 0.30f, 0.145f, 1.1f, 0.0f}, {32, 32, 4, 3.9f, 0.18f, 0.145f, 1.4f, 0.0f}};
 static Tile64Form pick_form(const GemmArgs& g, int dtype, float* us) {
@@ -515,7 +520,7 @@ static Tile64Form pick_form(const GemmArgs& g, int dtype, float* us) {
     const int slabs = f32 ? (g.K + 31) / 32 : (g.K + 63) / 64;
     Tile64Form best = f[0];
     *us = 1e30f;
-    for (int i = 0; i < (f32 ? 4 : 6); ++i) {
+    for (int i = 0; i < (f32 ? 4 : 7); ++i) {
         if (g.colsum && f[i].tm != 64) continue;   // a band of column sums is 64 rows
         const long units = (long)((g.M + f[i].tm - 1) / f[i].tm) * ((g.N + f[i].tn - 1) / f[i].tn);
         const float rounds = (float)((units + 255) / 256);

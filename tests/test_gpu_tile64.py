@@ -46,6 +46,23 @@ def test_bf16_tile_edges(batch, tokens, width, heads, mlp):
     run_case(w, ops, seed=73)
 
 
+@pytest.mark.parametrize("batch,tokens,width,heads,mlp", [
+    (1, 33, 64, 1, 2568),     # 41 slabs, the last of 8: uneven over the groups
+    (1, 65, 136, 2, 4096),    # one row and one piece of columns beside the tile
+    (1, 197, 768, 12, 3072),
+])
+def test_bf16_eight_k_groups(batch, tokens, width, heads, mlp):
+    import paper_2504_12471_amd as P
+    w = di.Workload("tile64_wk8", batch, tokens, width, heads, 64, mlp, 1, "bf16")
+    P.d2ft_timing_enable(True)
+    try:
+        run_case(w, ([FULL, FWD, SKIP] * 4)[:heads], seed=76)
+        names = {r["name"] for r in P.d2ft_timing_read()}
+    finally:
+        P.d2ft_timing_enable(False)
+    assert "gemm_tile64_kernel<__bf16, 32, 32, false, false, 8, d2ft::GemmArgs>" in names, names
+
+
 def test_bf16_gated_slices_through_the_remaps():
     w = di.Workload("tile64_gate_bf16", 1, 197, 256, 4, 64, 1024, 1, "bf16")
     run_gated(w, [FULL, SKIP, FWD, FULL], seed=74)
