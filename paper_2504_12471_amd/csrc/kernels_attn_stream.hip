@@ -514,12 +514,14 @@ __device__ __forceinline__ bool fwd_body(const T* __restrict__ qkv, long ldq, T*
     return false;
 }
 
-template <typename T>
-__global__ __launch_bounds__(64 * kWaves, sizeof(T) == 4 ? 2 : 3) void attn_fwd_stream_kernel(const T* __restrict__ qkv, long ldq,
+// Op: how the operands are multiplied.  fp32 by parts falls back on the fp32 instruction, which is also a kernel of its own for
+// few tokens (fp32_by_instruction).
+template <typename T, typename Op = T>
+__global__ __launch_bounds__(64 * kWaves, (std::is_same<Op, Parts>::value ? 2 : 3)) void attn_fwd_stream_kernel(const T* __restrict__ qkv, long ldq,
                                                                          T* __restrict__ o, long ldo, float* __restrict__ lse,
                                                                          int tokens, int n_live, int n_full, long rows_total,
                                                                          int blocks) {
-    if constexpr (sizeof(T) == 4) {
+    if constexpr (std::is_same<Op, Parts>::value) {
         static_assert(lds_bytes<Parts>() >= lds_bytes<float>(), "");
         extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
         if (!fwd_body<Parts>(qkv, ldq, o, ldo, lse, tokens, n_live, n_full, rows_total, blocks, dyn)) return;
@@ -730,8 +732,8 @@ __device__ __forceinline__ bool bwd_body(const T* __restrict__ qkv, long ldq, co
     return false;
 }
 
-template <typename T, int TR_PARTS>
-__global__ __launch_bounds__(64 * kWaves, sizeof(T) == 4 ? 1 : 2) void attn_bwd_stream_kernel(const T* __restrict__ qkv, long ldq,
+template <typename T, int TR_PARTS, typename Op = T>
+__global__ __launch_bounds__(64 * kWaves, (std::is_same<Op, Parts>::value ? 1 : 2)) void attn_bwd_stream_kernel(const T* __restrict__ qkv, long ldq,
                                                                          const T* __restrict__ o, long ldo,
                                                                          const float* __restrict__ lse,
                                                                          const T* __restrict__ d_o, long ld_do,
@@ -739,7 +741,7 @@ __global__ __launch_bounds__(64 * kWaves, sizeof(T) == 4 ? 1 : 2) void attn_bwd_
                                                                          float* __restrict__ bsum, int tokens,
                                                                          int n_full, long rows_total, int blocks) {
     __shared__ __attribute__((aligned(16))) BwdShared sh;
-    if constexpr (sizeof(T) == 4) {
+    if constexpr (std::is_same<Op, Parts>::value) {
         extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
         if (!bwd_body<Parts, 1>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, tokens, n_full, rows_total, blocks, dyn, sh)) return;
         __syncthreads();   // the last stage has been read
@@ -790,35 +792,47 @@ bool attn_bwd_stream_faster(int tokens, int pairs) {
     return pairs <= 160;
 }
 
+// fp32 attention by the fp32 instruction instead of three bf16 parts of each operand.  The cutting is a fixed cost that 32 keys do
+// not repay (17 tokens, 520 pairs: forward 6.5 us by the instruction, 9.5 by parts), and the backward by parts needs the registers
+// of two wavefronts, which costs a second round of workgroups (143 pairs: 17 tokens 9.1 and 16.0 us, 33 tokens 19.8 and 21.3;
+// 1040 pairs: 33 tokens 81 and 102, 83 tokens 122 and 133, 98 tokens 154 and 158; few pairs: 33 tokens, 52 pairs 13.6 and 12.0, 83
+// tokens, 52 pairs 19.3 and 15.8; 143 pairs: 98 tokens 37.6 and 34.6).
+static bool fp32_by_instruction(int tokens, int pairs, bool backward) {
+    return tokens <= 32 || (backward && tokens <= 96 && pairs > 128);
+}
+
 hipError_t launch_attn_fwd_stream(int dtype, const void* qkv, long ldq, void* o, long ldo, float* lse, int batch, int tokens,
                                   int n_live, int n_full, hipStream_t s) {
     if (n_live <= 0) return hipSuccess;
     const int blocks = attn_stream_blocks(tokens);
     const dim3 grid((unsigned)((long)batch * n_live * blocks)), block(64 * kWaves);
     const long rows = (long)batch * tokens;
-    if (dtype == D2FT_F32) {
+    if (dtype == D2FT_F32 && fp32_by_instruction(tokens, batch * n_live, false)) {
+        hipLaunchKernelGGL((attn_fwd_stream_kernel<float>), grid, block, 0, s, (const float*)qkv, ldq, (float*)o, ldo, lse, tokens,
+                           n_live, n_full, rows, blocks);
+    } else if (dtype == D2FT_F32) {
         static std::atomic<uint32_t> set_on{0};
-        const hipError_t e = allow_lds(reinterpret_cast<const void*>(attn_fwd_stream_kernel<float>), set_on);
+        const hipError_t e = allow_lds(reinterpret_cast<const void*>(attn_fwd_stream_kernel<float, Parts>), set_on);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(attn_fwd_stream_kernel<float>, grid, block, lds_bytes<Parts>(), s, (const float*)qkv, ldq, (float*)o, ldo, lse, tokens,
+        hipLaunchKernelGGL((attn_fwd_stream_kernel<float, Parts>), grid, block, lds_bytes<Parts>(), s, (const float*)qkv, ldq, (float*)o, ldo, lse, tokens,
                            n_live, n_full, rows, blocks);
     } else
-        hipLaunchKernelGGL(attn_fwd_stream_kernel<bf16>, grid, block, 0, s, (const bf16*)qkv, ldq, (bf16*)o, ldo, lse, tokens,
+        hipLaunchKernelGGL((attn_fwd_stream_kernel<bf16>), grid, block, 0, s, (const bf16*)qkv, ldq, (bf16*)o, ldo, lse, tokens,
                            n_live, n_full, rows, blocks);
     return hipGetLastError();
 }
 
-template <typename T, int TR_PARTS>
+template <typename T, int TR_PARTS, typename Op = T>
 static hipError_t launch_bwd(const void* qkv, long ldq, const void* o, long ldo, const float* lse, const void* d_o, long ld_do,
                              void* dqkv, long ld_dqkv, float* bsum, int batch, int tokens, int n_full, hipStream_t s) {
     const int blocks = attn_stream_blocks(tokens);
     const dim3 grid((unsigned)(2L * batch * n_full * blocks)), block(64 * kWaves);
-    auto kern = attn_bwd_stream_kernel<T, TR_PARTS>;
+    auto kern = attn_bwd_stream_kernel<T, TR_PARTS, Op>;
     const T *q = (const T*)qkv, *op = (const T*)o, *dop = (const T*)d_o;
     T* dq = (T*)dqkv;
     const long rows = (long)batch * tokens;
     int lds = 0;
-    if (sizeof(T) == 4) {
+    if constexpr (std::is_same<Op, Parts>::value) {
         static std::atomic<uint32_t> set_on{0};
         const hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), set_on);
         if (e != hipSuccess) return e;
@@ -835,7 +849,11 @@ hipError_t launch_attn_bwd_stream(int dtype, const void* qkv, long ldq, const vo
                                   const void* d_o, long ld_do, void* dqkv, long ld_dqkv, float* bsum, int batch, int tokens,
                                   int n_full, hipStream_t s) {
     if (n_full <= 0) return hipSuccess;
-    if (dtype == D2FT_F32) return launch_bwd<float, 1>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, batch, tokens, n_full, s);
+    if (dtype == D2FT_F32) {
+        if (fp32_by_instruction(tokens, batch * n_full, true))
+            return launch_bwd<float, 1>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, batch, tokens, n_full, s);
+        return launch_bwd<float, 1, Parts>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, batch, tokens, n_full, s);
+    }
     if (tokens <= 224) return launch_bwd<bf16, 1>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, batch, tokens, n_full, s);
     return launch_bwd<bf16, 3>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, batch, tokens, n_full, s);
 }

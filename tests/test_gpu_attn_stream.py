@@ -17,6 +17,11 @@ def test_fp32_token_edges(tokens):
     run_case(di.Workload("stream_f32", 2, tokens, 128, 3, 64, 64, 1, "f32"), [FULL, FWD, FULL], seed=81)
 
 
+@pytest.mark.parametrize("tokens", [17, 32, 33, 96, 97])   # with 130 pairs: the fp32 instruction, its edges, and parts beyond
+def test_fp32_many_pairs(tokens):
+    run_case(di.Workload("stream_f32_many", 65, tokens, 128, 2, 64, 64, 1, "f32"), [FULL, FULL], seed=86)
+
+
 @pytest.mark.parametrize("tokens", [225, 256, 257, 289, 320, 577])
 def test_bf16_token_edges(tokens):
     run_case(di.Workload("stream_bf16", 2, tokens, 128, 3, 64, 64, 1, "bf16"), [FWD, FULL, FULL], seed=82)
