@@ -244,13 +244,16 @@ __global__ __launch_bounds__((64 * group_waves<TM, TN>() * WK), TM == 64 && TN =
     unsigned char* const mine = smem + kg * group_bytes<TM, TN>();
     unroll<kAhead>([&](auto i) { fetch(i.value, ra[i.value], rb[i.value]); });
     // The thread's piece of the tile and what the epilogue reads for it, requested here, so that a launch of few workgroups
-    // does not end with the latency of one more load.  The larger tiles have no registers for it.
+    // does not end with the latency of one more load.  The larger tiles have no registers for it.  fp32: only where each
+    // workgroup has a CU of its own; in later rounds others cover that latency, and the slabs wait behind these loads (913 x 832 x
+    // 3328 with bias and residual, 754 workgroups, 48.4 us without and 51.8 with).
     constexpr bool kEarly = !GROUPED && TN == 32 && (TM == 32 || sizeof(T) == 2);
+    const bool ahead = sizeof(T) == 2 || gridDim.x <= 256;
     constexpr int kThreads = GT * WK, kPieces = TM * TN / 8, kRowPieces = TN / 8;
     const int r0 = threadIdx.x / kRowPieces, c0 = threadIdx.x % kRowPieces * 8;
     EpilogueOperands<T> early;
     if constexpr (kEarly) {
-        if (!g.partial && (kThreads <= kPieces || (int)threadIdx.x < kPieces) && m0 + r0 < M && n0 + c0 < N) early.request(g, m0 + r0, n0 + c0);
+        if (ahead && !g.partial && (kThreads <= kPieces || (int)threadIdx.x < kPieces) && m0 + r0 < M && n0 + c0 < N) early.request(g, m0 + r0, n0 + c0);
     }
     f32x16 acc;
 #pragma unroll
@@ -334,6 +337,7 @@ __global__ __launch_bounds__((64 * group_waves<TM, TN>() * WK), TM == 64 && TN =
             }
             if constexpr (kEarly) {
                 static_assert(kThreads >= kPieces, "one piece per thread");
+                if (!ahead) early.request(g, m, n);
                 emit<T>(g, m, n, v, early);
             } else {
                 emit<T>(g, m, n, v);
