@@ -1,6 +1,6 @@
 // LayerNorm forward/backward, column sums, split reductions, gradient-slice fills and the
 // small LoRA helpers.  All of these are bandwidth-bound: one wavefront owns one row and
-// reduces with cross-lane shuffles; column reductions write fp32 partials per row chunk and
+// reduces with cross-lane sums; column reductions write fp32 partials per row chunk and
 // a second kernel sums the partials in a fixed order, so results do not depend on timing.
 #include "d2ft_common.h"
 #include "tail_jobs.h"
