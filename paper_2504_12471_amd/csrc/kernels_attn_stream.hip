@@ -25,8 +25,10 @@
 // dQ partial sums instead would mean fp32 atomics, whose order is not fixed, or a pass over them.
 //
 // Bound: fp32 by the matrix cores (a 32 x 32 tile pair is 48 products of 32 cycles forward, 168 backward) and by what runs
-// between them: a part of an infinity is a NaN and an operand of 2^104 and more has no parts, so a workgroup with a result
-// that is not finite forms its rows again with the fp32 instruction.  The backward holds two row operands in parts (96
+// between them: a part of an infinity is a NaN, an operand of 2^104 and more has no parts, and sums end at 2^80, as products
+// carry 2^48.  So a workgroup with a result that is not finite, with a Q or K above 2^36 or with a query whose log-sum-exp is beyond
+// 1024 forms its rows again with the fp32 instruction.  (These tests cost 1 %: 197 tokens, 260 pairs, forward 38.7 -> 38.8
+// us, backward 136.0 -> 136.6; a test of the log-sum-exp where it is fetched, not where it is stored, 5 %.)  The backward holds two row operands in parts (96
 // registers): one wavefront per SIMD.  bf16 by the
 // matrix cores and the vector ALUs alike (forward 16 products of 32 cycles per tile pair, beside 16 exponentials, twice as
 // many subtractions and multiplications, maxima, sums and the cutting into parts, 5.5 operations for each of 16 elements).
@@ -71,6 +73,19 @@ template <typename Op> constexpr float unscale() { return 1.f; }
 template <> constexpr float unscale<Parts>() { return kDown; }
 // pairs of parts that are multiplied, the small products first (what is left out is below 2^-25 of the product)
 constexpr int kPa[6] = {2, 0, 1, 1, 0, 0}, kPb[6] = {0, 2, 1, 0, 1, 0};
+// Largest log-sum-exp of a query by parts.  A probability is rebuilt by subtracting it from a score, whose bits must be those that
+// went into it: scores of 800 by parts and by the fp32 instruction leave probabilities up to 1.8e-4 apart, scores of 2^20 nothing.
+// Beyond it every workgroup that meets the query uses the instruction, in the forward and the backward call.
+constexpr float kMostLse = 1024.f;
+__device__ __forceinline__ bool beyond_parts(float lse) { return !(fabsf(lse) <= kMostLse); }
+// Largest Q and K by parts: 64 products of 2^72 are below 2^80, where a sum of 2^48 times the size ends.  A score of minus infinity in
+// place of a finite one would show in no result: its probability is zero.
+constexpr float kMostScoreOperand = 68719476736.f;   // 2^36
+template <int N>
+__device__ __forceinline__ void largest(float& most, const float (&x)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) most = fmaxf(most, fabsf(x[i]));
+}
 
 constexpr float kScale = 0.125f;   // 1/sqrt(64)
 constexpr float kLog2e = 1.4426950408889634f;
@@ -167,16 +182,19 @@ template <> struct RowOp<float> {
 
 template <> struct RowOp<Parts> {
     bf16x8 f[3][4];   // [part]: channels 16 kk + 8h .. + 7
+    float most = 0.f;   // largest magnitude in this lane
     __device__ __forceinline__ void load(const float* row, bool ok, int h) {
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
             float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
             if (ok) load8(row + kk * 16 + 8 * h, x);
+            largest(most, x);
             uint32_t part[3][4];
             cut_up(x, part);
 #pragma unroll
             for (int k = 0; k < 3; ++k) f[k][kk] = __builtin_bit_cast(bf16x8, u32x4{part[k][0], part[k][1], part[k][2], part[k][3]});
         }
+        asm volatile("" : "+v"(most));   // formed here: at its use, behind the loops, it would keep the row in registers
     }
 };
 
@@ -349,6 +367,7 @@ struct Stream {
     __amdgpu_buffer_rsrc_t rsrc;
     uint32_t off, ld_bytes, last;
     u32x4 v[kPer];
+    float most = 0.f;   // Parts: largest magnitude that this thread has stored
     __device__ __forceinline__ void init(const T* p, long ld, int tokens) {
         ld_bytes = (uint32_t)ld * (uint32_t)sizeof(T);
         rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(p), 0, (uint32_t)(tokens - 1) * ld_bytes + 64u * (uint32_t)sizeof(T), 0x00020000);
@@ -362,12 +381,13 @@ struct Stream {
             v[k] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, REPEAT ? min(at, last) : at, 0, 0);
         }
     }
-    __device__ __forceinline__ void store(typename InTile<Op>::type* lds) const {   // lds: kStage tiles, one after the other
+    __device__ __forceinline__ void store(typename InTile<Op>::type* lds) {   // lds: kStage tiles, one after the other
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {
             const int r = threadIdx.x / Tile<Op>::kPieces + k * kStep;
             if constexpr (std::is_same<Op, Parts>::value) {
                 const float x[4] = {__uint_as_float(v[k][0]), __uint_as_float(v[k][1]), __uint_as_float(v[k][2]), __uint_as_float(v[k][3])};
+                largest(most, x);   // dead code where nothing asks for it
                 uint32_t part[3][2];
                 cut_up(x, part);
                 bf16* const to = lds + Tile<Op>::at(r) + (threadIdx.x % Tile<Op>::kPieces) * 4;
@@ -413,7 +433,7 @@ __device__ __forceinline__ int xcd_order(int pid, int total) {
 // ---------------------------------------------------------------------------
 template <typename Op> constexpr int lds_bytes() { return 4 * Tile<Op>::kStage * tile_elems<Op>() * (int)sizeof(typename InTile<Op>::type); }
 
-// true, for Parts: a result is not finite and nothing has been written
+// true, for Parts: not in their range, and nothing has been written
 template <typename Op, typename T>
 __device__ __forceinline__ bool fwd_body(const T* __restrict__ qkv, long ldq, T* __restrict__ o, long ldo, float* __restrict__ lse,
                                          int tokens, int n_live, int n_full, long rows_total, int blocks, unsigned char* smem) {
@@ -502,15 +522,16 @@ __device__ __forceinline__ bool fwd_body(const T* __restrict__ qkv, long ldq, T*
         }
     }
     sum += __shfl_xor(sum, 32, 64);   // the two lanes of a query hold different keys
+    const float l = m * kScale + __logf(sum);
     if constexpr (std::is_same<Op, Parts>::value) {
-        float odd = fmaf(sum, 0.f, 0.f);   // stays 0, or becomes NaN
+        float odd = 0.f;   // stays 0, or becomes NaN
 #pragma unroll
         for (int e = 0; e < 16; ++e) odd = fmaf(ot[0][e], 0.f, fmaf(ot[1][e], 0.f, odd));
-        if (__syncthreads_or(q < tokens && (odd != 0.f || sum == 0.f))) return true;
+        if (__syncthreads_or(sk.most > kMostScoreOperand || (q < tokens && (odd != 0.f || qf.most > kMostScoreOperand || beyond_parts(l))))) return true;
     }
     if (q0 >= tokens) return false;
     store_row(ot, unscale<Op>() / sum, o + (row0 + q) * ldo + j * 64, h, q < tokens);
-    if (q < tokens && h == 0 && j < n_full) lse[(long)j * rows_total + row0 + q] = m * kScale + __logf(sum);
+    if (q < tokens && h == 0 && j < n_full) lse[(long)j * rows_total + row0 + q] = l;
     return false;
 }
 
@@ -542,7 +563,7 @@ struct BwdShared {
     float red[kWaves][64];
 };
 
-// true, for Parts: a result is not finite and nothing has been written
+// true, for Parts: not in their range, and nothing has been written
 template <typename Op, int TR_PARTS, typename T>
 __device__ __forceinline__ bool bwd_body(const T* __restrict__ qkv, long ldq, const T* __restrict__ o, long ldo,
                                          const float* __restrict__ lse, const T* __restrict__ d_o, long ld_do,
@@ -596,6 +617,7 @@ __device__ __forceinline__ bool bwd_body(const T* __restrict__ qkv, long ldq, co
         sd.init(dOb, ld_do, tokens);
         so.init(Ob, ldo, tokens);
         float l = 0.f;
+        bool beyond = false;   // of the queries whose log-sum-exp this thread fetches
         auto fetch = [&](int s) {
             sq.fetch(s * ST * kRows);
             sd.fetch(s * ST * kRows);
@@ -605,10 +627,12 @@ __device__ __forceinline__ bool bwd_body(const T* __restrict__ qkv, long ldq, co
                 l = q < tokens ? lse_b[q] * kLse : INFINITY;   // a query past the last token: P = 0
             }
         };
-        auto store = [&](int buf) {
+        auto store = [&](int s) {
+            const int buf = s & 1;
             sq.store(lds[buf][0]);
             sd.store(lds[buf][1]);
             if (threadIdx.x < ST * kRows) consts[buf][0][threadIdx.x] = l;
+            if (kParts && threadIdx.x < ST * kRows && s * ST * kRows + (int)threadIdx.x < tokens) beyond |= beyond_parts(l);
             // delta of the rows this thread holds a piece of: the lanes of a row are neighbours
 #pragma unroll
             for (int k = 0; k < Stream<Op>::kPer; ++k) {
@@ -655,11 +679,11 @@ __device__ __forceinline__ bool bwd_body(const T* __restrict__ qkv, long ldq, co
                     mma_tr<Op, TR_PARTS>(dk, Qs, dp, lane);
                 }
             }
-            if (s + 1 < stages) store((s + 1) & 1);
+            if (s + 1 < stages) store(s + 1);
         }
         const float odd = odd_of(dk);
         if constexpr (kParts) {
-            if (__syncthreads_or(ok && (odd != 0.f || odd_of(dv) != 0.f))) return true;
+            if (__syncthreads_or(beyond || sq.most > kMostScoreOperand || (ok && (odd != 0.f || odd_of(dv) != 0.f || kf.most > kMostScoreOperand)))) return true;
         }
         if (i0 < tokens) {
             store_row(dk, kScale * kBack, dQb + (long)i * ld_dqkv + 64, h, ok);
@@ -724,7 +748,7 @@ __device__ __forceinline__ bool bwd_body(const T* __restrict__ qkv, long ldq, co
             }
         }
         if constexpr (kParts) {
-            if (__syncthreads_or(ok && odd_of(dq) != 0.f)) return true;
+            if (__syncthreads_or(sk.most > kMostScoreOperand || (ok && (odd_of(dq) != 0.f || qf.most > kMostScoreOperand || beyond_parts(lq))))) return true;
         }
         if (i0 < tokens) store_row(dq, kScale * kBack, dQb + (long)i * ld_dqkv, h, ok);
         if (bsum) store_colsum(dq, kScale * kBack, ok, reinterpret_cast<float*>(lds), red, bsum + ((long)b * blocks + id % blocks) * n_full * 192 + j * 192);

@@ -207,3 +207,58 @@ def test_fp32_values_without_bf16_parts(tokens):
     keep = [c for c in range(128) if c != 64 + 7]
     assert rel_inf(g["w_o"][:, keep], rg["w_o"][:, keep]) < TOL["f32"]
     assert rel_inf(g["w_o"][:, 64 + 7], rg["w_o"][:, 64 + 7]) < TOL["f32"]
+
+
+# ---------------------------------------------------------------------------
+# fp32 by bf16 parts: scores whose sums in parts leave fp32's range
+# ---------------------------------------------------------------------------
+def positions(tokens):
+    """x of one image whose first ten channels are the bits of the position (+-1), which LayerNorm returns as they are."""
+    n = np.arange(tokens)
+    bits = np.where((n[:, None] >> np.arange(10)) & 1, 1.0, -1.0)
+    return np.concatenate([bits, -bits, np.broadcast_to(E[:44], (tokens, 44))], 1).astype(np.float32)[None]
+
+
+def check_values(w, wt, x, dy):
+    """y and what reaches the values; the other gradients are what rounding leaves of zero, times the scores' size."""
+    y, _, g = gpu_block(w, wt, [FULL], x, dy, ("w_qkv", "b_qkv", "w_o"))
+    ry, _, rg, _ = oracle_block(w, wt, [FULL], x, dy)
+    errs = {"y": rel_inf(y, ry), "w_o": rel_inf(g["w_o"], rg["w_o"])}
+    errs.update({k: rel_inf(g[k][2], rg[k][2]) for k in ("w_qkv", "b_qkv")})
+    print(errs, flush=True)
+    assert max(errs.values()) < TOL["f32"], errs
+
+
+@pytest.mark.parametrize("tokens", [33, 65, 197])
+@pytest.mark.parametrize("first,unit,q", [
+    (1, -2.0 ** 90, 2.0 ** 45),         # every score of every query below -2^80, the largest at the first key
+    (1024, 2.0 ** 90, 2.0 ** 45),       # .. at the last
+    (383, 2.0 ** 72 * 1.00167, 2.0 ** 36 * 1.0011),   # of 197 keys the first 128 below -2^80, the largest above it, at the last
+])
+def test_fp32_scores_below_the_range_of_parts(tokens, first, unit, q):
+    """Score n is -first * |unit| + n * unit: the softmax is one key's, whose values get the whole gradient."""
+    rng = np.random.default_rng(93)
+    w, wt, _ = crafted([1.0] * tokens, "f32", (0, 0), (0, 0), (0, 0), 1.0, ln_eps=1e-30)
+    x = positions(tokens)
+    q = np.float32(q)
+    k = np.float32(abs(unit) / float(q))
+    wt["b_qkv"][0, 0, :11] = q
+    half = np.float32(np.sign(unit)) * k * (2.0 ** np.arange(10) / 2).astype(np.float32)   # key channel b: bit b, times 2^b
+    wt["b_qkv"][1, 0, :10] = half
+    wt["w_qkv"][1, 0, np.arange(10), np.arange(10)] = half
+    wt["b_qkv"][1, 0, 10] = -first * k
+    wt["w_qkv"][2, 0] = np.sign(rng.standard_normal((64, 64))) / 8
+    check_values(w, wt, x, np.sign(rng.standard_normal(x.shape)).astype(np.float32))
+
+
+@pytest.mark.parametrize("tokens", [33, 65, 197])
+def test_fp32_partial_sums_below_the_range_of_parts(tokens):
+    """Scores of zero as -3 * 2^79 over the first 16 channels and 2^79 in each of three later ones, beside keys of -1.  (1 + eps
+    is 1 for the oracle too, or its scores would be what rounding leaves of 2^79.)"""
+    s = np.where(np.arange(tokens) % 3 == 0, 1.0, -1.0)
+    big = np.zeros(64)
+    big[:16] = -3 * 2.0 ** 36
+    big[[16, 32, 48]] = 2.0 ** 40
+    w, wt, x = crafted(s, "f32", (np.where(big != 0, 2.0 ** 39, 0) + channel(63, 1.0), 0),
+                       (big / 2 - channel(63, 4.0), big / 2 + channel(63, 4.0)), (0.5, 1.0), 4.0, ln_eps=1e-30)
+    check_values(w, wt, x, ((2 + s)[:, None] * np.ones((1, 64)))[None].astype(np.float32))
