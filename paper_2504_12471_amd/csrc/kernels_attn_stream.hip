@@ -816,13 +816,18 @@ bool attn_bwd_stream_faster(int tokens, int pairs) {
     return pairs <= 160;
 }
 
-// fp32 attention by the fp32 instruction instead of three bf16 parts of each operand.  The cutting is a fixed cost that 32 keys do
-// not repay (17 tokens, 520 pairs: forward 6.5 us by the instruction, 9.5 by parts), and the backward by parts needs the registers
-// of two wavefronts, which costs a second round of workgroups (143 pairs: 17 tokens 9.1 and 16.0 us, 33 tokens 19.8 and 21.3;
-// 1040 pairs: 33 tokens 81 and 102, 83 tokens 122 and 133, 98 tokens 154 and 158; few pairs: 33 tokens, 52 pairs 13.6 and 12.0, 83
-// tokens, 52 pairs 19.3 and 15.8; 143 pairs: 98 tokens 37.6 and 34.6).
-static bool fp32_by_instruction(int tokens, int pairs, bool backward) {
-    return tokens <= 32 || (backward && tokens <= 96 && pairs > 128);
+// fp32 attention by the fp32 instruction instead of three bf16 parts of each operand, the same in the forward and the backward call
+// (kMostLse says why), so by the pairs of the backward.  The cutting is a fixed cost that 32 keys do not repay, and the backward by
+// parts needs the registers of two wavefronts, so that beyond 128 pairs it takes a round of workgroups more; the forward gains at
+// all sizes above.  Forward + backward, instruction against parts, us:
+//   17 tokens: 52 pairs 15.6 and 16.8, 520 pairs 29 and 51; 32 tokens: 128 pairs 17.4 and 17.5, 144 pairs 18 and 24
+//   33: 128 pairs 24.4 and 22.9, 144 pairs 30 and 32, 1040 pairs 107 and 128; 64: 128 pairs 25.2 and 23.7, 640 pairs 81 and 86
+//   65: 144 pairs 40.8 and 40.1, 640 pairs 112 and 104, 780 pairs 136 and 136, 1040 pairs 166 and 172
+//   96: 640 pairs 119 and 113, 780 pairs 146 and 147, 1040 pairs 178 and 188
+//   97: 780 pairs 183 and 172, 1040 pairs 228 and 222, 2080 pairs 421 and 438; 128: 1040 pairs 244 and 242, 2080 pairs 447 and 470
+//   197: 1040 pairs 675 and 621, 2080 pairs 1295 and 1205
+static bool fp32_by_instruction(int tokens, int pairs) {
+    return tokens <= (pairs > 1536 ? 128 : pairs > 768 ? 96 : pairs > 128 ? 64 : 32);
 }
 
 hipError_t launch_attn_fwd_stream(int dtype, const void* qkv, long ldq, void* o, long ldo, float* lse, int batch, int tokens,
@@ -831,7 +836,7 @@ hipError_t launch_attn_fwd_stream(int dtype, const void* qkv, long ldq, void* o,
     const int blocks = attn_stream_blocks(tokens);
     const dim3 grid((unsigned)((long)batch * n_live * blocks)), block(64 * kWaves);
     const long rows = (long)batch * tokens;
-    if (dtype == D2FT_F32 && fp32_by_instruction(tokens, batch * n_live, false)) {
+    if (dtype == D2FT_F32 && fp32_by_instruction(tokens, batch * n_full)) {
         hipLaunchKernelGGL((attn_fwd_stream_kernel<float>), grid, block, 0, s, (const float*)qkv, ldq, (float*)o, ldo, lse, tokens,
                            n_live, n_full, rows, blocks);
     } else if (dtype == D2FT_F32) {
@@ -874,7 +879,7 @@ hipError_t launch_attn_bwd_stream(int dtype, const void* qkv, long ldq, const vo
                                   int n_full, hipStream_t s) {
     if (n_full <= 0) return hipSuccess;
     if (dtype == D2FT_F32) {
-        if (fp32_by_instruction(tokens, batch * n_full, true))
+        if (fp32_by_instruction(tokens, batch * n_full))
             return launch_bwd<float, 1>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, batch, tokens, n_full, s);
         return launch_bwd<float, 1, Parts>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, batch, tokens, n_full, s);
     }

@@ -210,7 +210,7 @@ def test_fp32_values_without_bf16_parts(tokens):
 
 
 # ---------------------------------------------------------------------------
-# fp32 by bf16 parts: scores whose sums in parts leave fp32's range
+# fp32 by bf16 parts: scores whose sums in parts leave fp32's range, and scores that forward and backward must round alike
 # ---------------------------------------------------------------------------
 def positions(tokens):
     """x of one image whose first ten channels are the bits of the position (+-1), which LayerNorm returns as they are."""
@@ -262,3 +262,37 @@ def test_fp32_partial_sums_below_the_range_of_parts(tokens):
     w, wt, x = crafted(s, "f32", (np.where(big != 0, 2.0 ** 39, 0) + channel(63, 1.0), 0),
                        (big / 2 - channel(63, 4.0), big / 2 + channel(63, 4.0)), (0.5, 1.0), 4.0, ln_eps=1e-30)
     check_values(w, wt, x, ((2 + s)[:, None] * np.ones((1, 64)))[None].astype(np.float32))
+
+
+@pytest.mark.parametrize("heads,tokens,size,seed", [   # 64 pairs per head; sizes of 10 and 110: scores of some 800 and 1e5
+    (1, 33, 10.0, 94), (1, 130, 10.0, 94), (8, 33, 10.0, 94), (8, 33, 110.0, 94), (8, 64, 10.0, 94), (8, 65, 10.0, 94), (8, 130, 110.0, 94),
+    (13, 96, 10.0, 94), (13, 97, 110.0, 94),
+])
+def test_fp32_probability_of_one_key_among_many_is_one(heads, tokens, size, seed):
+    """Each query has a single key, whose probability is one if the backward forms its score with the forward's bits: a unit
+    in the last place of a score of 800 is 6e-5 of it.  Image c has its gradient in channel c of each head."""
+    rng = np.random.default_rng(seed)
+    D = 64 * heads
+    w = di.Workload("one_of_many", 64, tokens, D, heads, 64, 64, 1, "f32", ln_eps=1e-30)
+    z = lambda *sh: np.zeros(sh, np.float32)
+    wt = {"ln1_g": z(D) + 1, "ln1_b": z(D), "w_qkv": z(3, heads, 64, D), "b_qkv": z(3, heads, 64), "w_o": np.eye(D, dtype=np.float32),
+          "b_o": z(D), "ln2_g": z(D) + 1, "ln2_b": z(D), "w1": z(64, D), "b1": z(64), "w2": z(D, 64), "b2": z(D)}
+    code = np.where(rng.random((64, D // 2)) < 0.5, -1.0, 1.0)
+    code = np.concatenate([code, -code], 1)                     # mean 0, variance 1: LayerNorm gives x itself
+    x = np.repeat(-code[:, None, :], tokens, 1)
+    x[:, tokens // 2] = code                                    # one key unlike the others
+    x = x.astype(np.float32)
+    for h in range(heads):
+        wt["b_qkv"][0, h] = rng.uniform(0.5, 1.0, 64) * size
+        # key channels: a part that all images share in sign, through a channel of x that is +1 in token `tokens // 2`
+        wt["w_qkv"][1, h] = rng.standard_normal((64, D)) * (0.05 * size / np.sqrt(D))
+    x[:, :, 0], x[:, :, D // 2] = -1.0, 1.0
+    x[:, tokens // 2, 0], x[:, tokens // 2, D // 2] = 1.0, -1.0
+    wt["w_qkv"][1, :, :, 0] += rng.uniform(0.8, 1.6, (heads, 64)).astype(np.float32) * np.float32(size)
+    dy = z(64, tokens, D)
+    for h in range(heads):
+        dy[np.arange(64), :, 64 * h + np.arange(64)] = 1.0
+    g = gpu_block(w, wt, [FULL] * heads, x, dy, ("w_qkv",))[2]["w_qkv"][2]     # [heads][channel = image][D]
+    err = np.abs(g / (tokens * x[:, tokens // 2][None]) - 1).max(-1)
+    print("off by more than 1e-5:", int((err > 1e-5).sum()), "of", err.size, "largest", err.max(), flush=True)
+    assert err.max() < 1e-5   # sums of up to 130 fp32 products that are all one
