@@ -200,14 +200,16 @@ template <> struct RowOp<Parts> {
 
 // acc[row of the tile][this wavefront's row] += tile . op^T; CHAINS: of sums along the channels, for fp32.  Two halve the
 // roundings of the scores, which an exponential follows; for both products of the backward they would not fit the registers.
-template <int CHAINS>
+// SWAP: the tile holds the queries.  Products of parts are then added in the order in which the transposed product adds
+// them, so that a score has the same bits wherever it is formed.
+template <int CHAINS, bool SWAP = false>
 __device__ __forceinline__ void mma_rows(f32x16& acc, const bf16* tile, const RowOp<bf16>& op, int lane) {
     const bf16* p = tile + Tile<bf16>::at(lane & 31) + 8 * (lane >> 5);
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(p + kk * 16), op.f[kk], acc, 0, 0, 0);
 }
-template <int CHAINS>
+template <int CHAINS, bool SWAP = false>
 __device__ __forceinline__ void mma_rows(f32x16& acc, const float* tile, const RowOp<float>& op, int lane) {
     const float* p = tile + Tile<float>::at(lane & 31) + 4 * (lane >> 5);
     f32x16 other = zero16();
@@ -221,7 +223,7 @@ __device__ __forceinline__ void mma_rows(f32x16& acc, const float* tile, const R
     if constexpr (CHAINS == 2) acc += other;
 }
 
-template <int CHAINS>   // acc: zero
+template <int CHAINS, bool SWAP = false>   // acc: zero
 __device__ __forceinline__ void mma_rows(f32x16& acc, const bf16* tile, const RowOp<Parts>& op, int lane) {
     const bf16* p = tile + Tile<Parts>::at(lane & 31) + 8 * (lane >> 5);
     f32x16 low = zero16();   // the small products have an accumulator of their own
@@ -233,7 +235,7 @@ __device__ __forceinline__ void mma_rows(f32x16& acc, const bf16* tile, const Ro
 #pragma unroll
         for (int q = 0; q < 6; ++q) {
             f32x16& to = q == 5 ? acc : low;
-            to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kPa[q]], op.f[kPb[q]][kk], to, 0, 0, 0);
+            to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[SWAP ? kPb[q] : kPa[q]], op.f[SWAP ? kPa[q] : kPb[q]][kk], to, 0, 0, 0);
         }
     }
     acc = (acc + low) * kDown;
@@ -663,8 +665,8 @@ __device__ __forceinline__ bool bwd_body(const T* __restrict__ qkv, long ldq, co
                     const E* Qs = lds[s & 1][0] + u * tile_elems<Op>();
                     const E* dOs = lds[s & 1][1] + u * tile_elems<Op>();
                     f32x16 p = zero16(), dp = zero16();   // element e: query 8*(e/4) + 4h + e%4 of the tile
-                    mma_rows<2>(p, Qs, kf, lane);
-                    mma_rows<1>(dp, dOs, vf, lane);
+                    mma_rows<2, true>(p, Qs, kf, lane);
+                    mma_rows<1, true>(dp, dOs, vf, lane);
 #pragma unroll
                     for (int g = 0; g < 4; ++g) {
                         const f32x4 lq = *reinterpret_cast<const f32x4*>(&consts[s & 1][0][u * kRows + 8 * g + 4 * h]);

@@ -267,6 +267,7 @@ def test_fp32_partial_sums_below_the_range_of_parts(tokens):
 @pytest.mark.parametrize("heads,tokens,size,seed", [   # 64 pairs per head; sizes of 10 and 110: scores of some 800 and 1e5
     (1, 33, 10.0, 94), (1, 130, 10.0, 94), (8, 33, 10.0, 94), (8, 33, 110.0, 94), (8, 64, 10.0, 94), (8, 65, 10.0, 94), (8, 130, 110.0, 94),
     (13, 96, 10.0, 94), (13, 97, 110.0, 94),
+    (8, 97, 10.0, 3), (8, 97, 10.0, 25),   # one of the 512 scores has other bits if the products of parts are added in another order
 ])
 def test_fp32_probability_of_one_key_among_many_is_one(heads, tokens, size, seed):
     """Each query has a single key, whose probability is one if the backward forms its score with the forward's bits: a unit
