@@ -2,6 +2,8 @@
 // the patch embedding at the start and the pooling + classification layer at the end.  The patch
 // projection and its weight gradient run on the GEMM kernels; what is here is the bandwidth-bound
 // data movement around them and the small per-image arithmetic of the classifier.
+#include <type_traits>
+
 #include "d2ft_common.h"
 
 namespace d2ft {
@@ -49,32 +51,31 @@ __global__ __launch_bounds__(256) void assemble_tokens_kernel(const T* __restric
 }
 
 // backward of the assembly: dproj[b * Np + p] = dtokens[b][1 + p]; dpos[t] = sum_b dtokens[b][t]; dcls = dpos[0].
-// A workgroup owns 32 pieces of 8 channels and has 8 lanes of images: lane l takes images l, l + 8, ..., four in flight,
-// and the lanes' sums are added in lane order.  With one thread per piece and all of its images, 80 images of 197 x 384
-// (37 workgroups) took 26.3 us; now 7.9.
-constexpr int kImageLanes = 8;
-template <typename T>
+// A workgroup owns 256 / LANES pieces of 8 channels and has LANES lanes of images: lane l takes images l, l + LANES, ..., four in
+// flight, and the lanes' sums are added in lane order.
+template <typename T, int LANES>
 __global__ __launch_bounds__(256) void embed_bwd_gather_kernel(const T* __restrict__ dtokens, T* __restrict__ dproj,
                                                                T* g_pos, T* g_cls, int B, int Np, int D, int accumulate) {
-    __shared__ __attribute__((aligned(16))) float part[kImageLanes][32][8];
+    constexpr int kPieces = 256 / LANES;
+    __shared__ __attribute__((aligned(16))) float part[LANES][kPieces][8];   // one lane: not used
     const int d8 = D / 8, Tn = Np + 1;
-    const int lane = threadIdx.x >> 5, at = threadIdx.x & 31, i = blockIdx.x * 32 + at;
+    const int lane = threadIdx.x / kPieces, at = threadIdx.x % kPieces, i = blockIdx.x * kPieces + at;
     const bool on = i < Tn * d8;
     const int dc = (i % d8) * 8, t = i / d8;
     float s[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) s[j] = 0.f;
     if (on) {
-        for (int b0 = lane; b0 < B; b0 += 4 * kImageLanes) {
+        for (int b0 = lane; b0 < B; b0 += 4 * LANES) {
             float v[4][8];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int b = b0 + q * kImageLanes;
+                const int b = b0 + q * LANES;
                 if (b < B) load8(dtokens + ((long)b * Tn + t) * D + dc, v[q]);
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int b = b0 + q * kImageLanes;
+                const int b = b0 + q * LANES;
                 if (b < B) {
                     if (t > 0) store8(dproj + ((long)b * Np + t - 1) * D + dc, v[q]);
 #pragma unroll
@@ -83,16 +84,19 @@ __global__ __launch_bounds__(256) void embed_bwd_gather_kernel(const T* __restri
             }
         }
     }
-    store8(part[lane][at], s);
-    __syncthreads();
-    if (lane != 0 || !on) return;
+    if constexpr (LANES > 1) {
+        store8(part[lane][at], s);
+        __syncthreads();
+        if (lane != 0) return;
 #pragma unroll
-    for (int l = 1; l < kImageLanes; ++l) {
-        float v[8];
-        load8(part[l][at], v);
+        for (int l = 1; l < LANES; ++l) {
+            float v[8];
+            load8(part[l][at], v);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) s[j] += v[j];
+            for (int j = 0; j < 8; ++j) s[j] += v[j];
+        }
     }
+    if (!on) return;
     auto emit = [&](T* out) {
         float o[8];
 #pragma unroll
@@ -341,8 +345,19 @@ hipError_t launch_assemble_tokens(int dtype, const void* proj, const void* cls, 
 hipError_t launch_embed_bwd_gather(int dtype, const void* dtokens, void* dproj, void* g_pos, void* g_cls, int B, int Np, int D,
                                    int accumulate, hipStream_t s) {
     const int items = (Np + 1) * (D / 8);
-    D2FT_HEAD_DISPATCH(dtype, hipLaunchKernelGGL(embed_bwd_gather_kernel<T>, dim3((items + 31) / 32), dim3(256), 0, s,
-                                                 (const T*)dtokens, (T*)dproj, (T*)g_pos, (T*)g_cls, B, Np, D, accumulate);)
+    auto launch = [&](auto lanes) {
+        constexpr int kLanes = decltype(lanes)::value, kPieces = 256 / kLanes;
+        D2FT_HEAD_DISPATCH(dtype, hipLaunchKernelGGL((embed_bwd_gather_kernel<T, kLanes>), dim3((items + kPieces - 1) / kPieces), dim3(256), 0,
+                                                     s, (const T*)dtokens, (T*)dproj, (T*)g_pos, (T*)g_cls, B, Np, D, accumulate);)
+    };
+    // Lanes shorten the chain of loads of a piece, which is the time of many images (80 images of 197 x 384, 37 workgroups with one
+    // lane, 26.3 -> 7.9 us), and cost workgroups where there is no chain.  bf16, one, two and eight lanes: 577 x 768, 4 images
+    // 3.4, 3.2 and 3.9 us, 8 images 4.7, 4.1 and 5.0, 32 images 13.2, 10.9 and 10.0; 577 x 1024, 8 images 5.0, 5.0 and 5.8, 16 images
+    // 8.4, 5.9 and 6.8; 4097 x 1024, 1 image 5.7, 6.1 and 12.1, 4 images 12.3, 12.9 and 16.0, 8 images 21.9, 22.6 and 21.9; below
+    // 50000 pieces: 197 x 768, 4 images 2.9, 2.8 and 3.1, 8 images 3.8, 3.3 and 3.4, 96 images 30.9, 18.2 and 10.5.
+    if (B <= 4) launch(std::integral_constant<int, 1>{});
+    else if (B <= 16 && items >= 50000) launch(std::integral_constant<int, 2>{});
+    else launch(std::integral_constant<int, 8>{});
     return hipGetLastError();
 }
 

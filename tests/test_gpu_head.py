@@ -118,6 +118,12 @@ def test_embed_images_over_the_lanes(B):
     run_embed("f32", B, 1, 16, 24, 8, 40, 126)              # 7 tokens x 5 pieces: the second workgroup is part empty
 
 
+@pytest.mark.parametrize("dtype,B,accumulate", [("f32", 4, True), ("f32", 5, False), ("bf16", 16, True), ("f32", 17, False)])
+def test_embed_lanes_by_images_and_pieces(dtype, B, accumulate):
+    """4097 tokens x 13 pieces: one, two and eight lanes of images."""
+    run_embed(dtype, B, 1, 512, 512, 8, 104, 128, accumulate)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_head_takes_pointers_of_element_alignment(dtype):
     """Every tensor one element past a 16-byte boundary: the same bits as from aligned ones."""
