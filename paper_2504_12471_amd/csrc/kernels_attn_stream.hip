@@ -831,6 +831,11 @@ bool attn_bwd_stream_faster(int tokens, int pairs) {
 static bool fp32_by_instruction(int tokens, int pairs) {
     return tokens <= (pairs > 1536 ? 128 : pairs > 768 ? 96 : pairs > 128 ? 64 : 32);
 }
+// The same of a forward call that no backward call follows, for want of p_f heads.  By parts it wins beyond 32 tokens except where
+// its 512 workgroups a round need a round more than the 768 by the instruction, and few tokens make little of it: 33 tokens, 260
+// pairs 12.4 us by the instruction and 10.8 by parts, 520 pairs 14.3 and 16.3, 640 pairs 14.8 and 16.8, 780 pairs 19.5 and 19.1; 64
+// tokens, 520 pairs 16.4 and 18.4, 640 pairs 17.5 and 19.1; 65 tokens, 520 pairs 25.7 and 22.3.
+static bool fp32_forward_by_instruction(int tokens, int pairs) { return tokens <= 32 || (tokens <= 64 && pairs > 512 && pairs <= 768); }
 
 hipError_t launch_attn_fwd_stream(int dtype, const void* qkv, long ldq, void* o, long ldo, float* lse, int batch, int tokens,
                                   int n_live, int n_full, hipStream_t s) {
@@ -838,7 +843,7 @@ hipError_t launch_attn_fwd_stream(int dtype, const void* qkv, long ldq, void* o,
     const int blocks = attn_stream_blocks(tokens);
     const dim3 grid((unsigned)((long)batch * n_live * blocks)), block(64 * kWaves);
     const long rows = (long)batch * tokens;
-    if (dtype == D2FT_F32 && fp32_by_instruction(tokens, batch * n_full)) {
+    if (dtype == D2FT_F32 && (n_full ? fp32_by_instruction(tokens, batch * n_full) : fp32_forward_by_instruction(tokens, batch * n_live))) {
         hipLaunchKernelGGL((attn_fwd_stream_kernel<float>), grid, block, 0, s, (const float*)qkv, ldq, (float*)o, ldo, lse, tokens,
                            n_live, n_full, rows, blocks);
     } else if (dtype == D2FT_F32) {

@@ -22,6 +22,12 @@ def test_fp32_many_pairs(tokens):
     run_case(di.Workload("stream_f32_many", 65, tokens, 128, 2, 64, 64, 1, "f32"), [FULL, FULL], seed=86)
 
 
+@pytest.mark.parametrize("tokens", [33, 64, 65])
+def test_fp32_forward_alone(tokens):
+    """Without p_f heads, 576 pairs: the fp32 instruction up to 64 tokens."""
+    run_case(di.Workload("stream_f32_forward", 144, tokens, 64, 4, 64, 64, 1, "f32"), [FWD] * 4, seed=95)
+
+
 @pytest.mark.parametrize("tokens", [225, 256, 257, 289, 320, 577])
 def test_bf16_token_edges(tokens):
     run_case(di.Workload("stream_bf16", 2, tokens, 128, 3, 64, 64, 1, "bf16"), [FWD, FULL, FULL], seed=82)
