@@ -336,11 +336,14 @@ hipError_t run_gemm(const GemmArgs& g, const d2ft_block_desc* d, hipStream_t s, 
     return e;
 }
 
+// what LayerNorm of g's rows moves: the rows in and out, their mean and 1/std
+double ln_bytes(const GemmArgs& g, const d2ft_block_desc* d) { return 2.0 * g.M * g.K * elem_size(d->dtype) + 8.0 * g.M; }
+
 // LayerNorm of the rows of x into n.y, g's A operand
 hipError_t run_ln(const void* x, const LnArgs& n, const GemmArgs& g, const d2ft_block_desc* d, hipStream_t s) {
     timing_begin(s, "launch_ln_fwd");
     const hipError_t e = launch_ln_fwd(d->dtype, x, n.gamma, n.beta, n.y, n.mean, n.rstd, g.M, g.K, n.eps, s);
-    g_timing.bytes = 2.0 * g.M * g.K * (d->dtype == D2FT_F32 ? 4 : 2) + 8.0 * g.M;
+    g_timing.bytes = ln_bytes(g, d);
     timing_end(s);
     return e;
 }
@@ -352,6 +355,7 @@ hipError_t run_ln_gemm(const void* x, const LnArgs& n, const GemmArgs& g, const 
     if (!(d->flags & D2FT_FLAG_NO_MFMA) && gemm_ln_faster(f, n, d->dtype)) {
         timing_begin(s, "gemm");
         g_timing.flops = 2.0 * g.M * g.N * g.K;
+        g_timing.bytes = ln_bytes(g, d);
         const hipError_t e = launch_gemm_ln(f, n, d->dtype, s);
         timing_end(s);
         return e;

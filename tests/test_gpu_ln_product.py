@@ -12,14 +12,18 @@ pytestmark = pytest.mark.gpu
 FULL, FWD, SKIP = di.OP_FULL, di.OP_FWD, di.OP_SKIP
 
 
-def kernels_of(run):
+def records_of(run):
     import paper_2504_12471_amd as P
     P.d2ft_timing_enable(True)
     try:
         run()
-        return {r["name"] for r in P.d2ft_timing_read()}
+        return P.d2ft_timing_read()
     finally:
         P.d2ft_timing_enable(False)
+
+
+def kernels_of(run):
+    return {r["name"] for r in records_of(run)}
 
 
 @pytest.mark.parametrize("dtype,batch,tokens,width,heads,mlp,form", [
@@ -64,6 +68,14 @@ def test_merged_adapter_weights(dtype):
     w = di.Workload("ln_product_lora", 2, 65, 256, 4, 64, 512, 1, dtype, lora_rank=4, lora_b_zero=False)
     names = kernels_of(lambda: run_case(w, [FULL, SKIP, FWD, FULL], seed=83))
     assert [n for n in names if n.startswith("gemm_ln_kernel")], names
+
+
+def test_timing_records_hold_the_norm_and_the_product():
+    w = di.Workload("ln_product_records", 1, 33, 256, 2, 64, 264, 1, "f32")
+    rec = [r for r in records_of(lambda: run_case(w, [FULL, FWD], seed=85)) if r["name"].startswith("gemm_ln_kernel")]
+    assert sum(r["launches"] for r in rec) == 2   # before the QKV product and the first of the feed-forward network
+    assert sum(r["bytes"] for r in rec) == 2 * (2 * 33 * 256 * 4 + 8 * 33)
+    assert sum(r["flops"] for r in rec) == 2.0 * 33 * 256 * (2 * 192 + 264)
 
 
 @pytest.mark.parametrize("tokens,fused", [(224, True), (353, False)])
