@@ -483,6 +483,7 @@ hipError_t launch_fwd_kt(const bf16* qkv, long ldq, bf16* o, long ldo, float* ls
             attr_set = true;
         }
         const int pairs = batch * n_live, parts = pairs <= 128 ? 2 : 1;   // two: while each finds a CU of its own
+        if (parts == 2) launch_label("attn_fwd_mfma, two per pair");
         hipLaunchKernelGGL(kern, dim3(pairs, parts), dim3(256), lds, s, qkv, ldq, o, ldo, lse, tokens, n_live, n_full,
                            (long)batch * tokens, mask);
         return hipGetLastError();

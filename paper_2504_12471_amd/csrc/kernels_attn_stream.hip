@@ -844,12 +844,14 @@ hipError_t launch_attn_fwd_stream(int dtype, const void* qkv, long ldq, void* o,
     const dim3 grid((unsigned)((long)batch * n_live * blocks)), block(64 * kWaves);
     const long rows = (long)batch * tokens;
     if (dtype == D2FT_F32 && (n_full ? fp32_by_instruction(tokens, batch * n_full) : fp32_forward_by_instruction(tokens, batch * n_live))) {
+        launch_label("attn_fwd_stream_kernel<float>");
         hipLaunchKernelGGL((attn_fwd_stream_kernel<float>), grid, block, 0, s, (const float*)qkv, ldq, (float*)o, ldo, lse, tokens,
                            n_live, n_full, rows, blocks);
     } else if (dtype == D2FT_F32) {
         static std::atomic<uint32_t> set_on{0};
         const hipError_t e = allow_lds(reinterpret_cast<const void*>(attn_fwd_stream_kernel<float, Parts>), set_on);
         if (e != hipSuccess) return e;
+        launch_label("attn_fwd_stream_kernel<float, Parts>");
         hipLaunchKernelGGL((attn_fwd_stream_kernel<float, Parts>), grid, block, lds_bytes<Parts>(), s, (const float*)qkv, ldq, (float*)o, ldo, lse, tokens,
                            n_live, n_full, rows, blocks);
     } else
@@ -886,7 +888,9 @@ hipError_t launch_attn_bwd_stream(int dtype, const void* qkv, long ldq, const vo
                                   int n_full, hipStream_t s) {
     if (n_full <= 0) return hipSuccess;
     if (dtype == D2FT_F32) {
-        if (fp32_by_instruction(tokens, batch * n_full))
+        const bool instruction = fp32_by_instruction(tokens, batch * n_full);
+        launch_label(instruction ? "attn_bwd_stream_kernel<float, 1>" : "attn_bwd_stream_kernel<float, 1, Parts>");
+        if (instruction)
             return launch_bwd<float, 1>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, batch, tokens, n_full, s);
         return launch_bwd<float, 1, Parts>(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, batch, tokens, n_full, s);
     }

@@ -6,6 +6,7 @@ import pytest
 import d2ft_inputs as di
 from helpers import TOL, gpu_block, oracle_block, rel_inf
 from test_gpu_block import draw_block, run_case
+from test_gpu_ln_product import kernels_of
 
 pytestmark = pytest.mark.gpu
 
@@ -17,15 +18,31 @@ def test_fp32_token_edges(tokens):
     run_case(di.Workload("stream_f32", 2, tokens, 128, 3, 64, 64, 1, "f32"), [FULL, FWD, FULL], seed=81)
 
 
-@pytest.mark.parametrize("tokens", [17, 32, 33, 96, 97])   # with 130 pairs: the fp32 instruction, its edges, and parts beyond
+@pytest.mark.parametrize("tokens", [17, 32, 33, 96, 97])   # with 130 pairs: the fp32 instruction up to 64 tokens, parts beyond
 def test_fp32_many_pairs(tokens):
-    run_case(di.Workload("stream_f32_many", 65, tokens, 128, 2, 64, 64, 1, "f32"), [FULL, FULL], seed=86)
+    names = kernels_of(lambda: run_case(di.Workload("stream_f32_many", 65, tokens, 128, 2, 64, 64, 1, "f32"), [FULL, FULL], seed=86))
+    assert names >= fp32_kernels(tokens > 64), names
+
+
+def fp32_kernels(parts):
+    return {"attn_fwd_stream_kernel<float%s>" % (", Parts" if parts else ""), "attn_bwd_stream_kernel<float, 1%s>" % (", Parts" if parts else "")}
+
+
+@pytest.mark.parametrize("tokens,images,parts", [(32, 1, False), (33, 64, True), (33, 65, False), (64, 65, False), (65, 384, True),
+                                                 (65, 385, False), (96, 385, False), (97, 768, True), (97, 769, False),
+                                                 (128, 769, False), (129, 769, True)])
+def test_which_products_fp32_attention_takes(tokens, images, parts):
+    """Two p_f heads and one p_o head per image; forward and backward take the same."""
+    w = di.Workload("which_f32", images, tokens, 64, 3, 64, 64, 1, "f32")
+    names = kernels_of(lambda: run_case(w, [FULL, FWD, FULL], seed=96))
+    assert names >= fp32_kernels(parts) and not names & fp32_kernels(not parts), names
 
 
 @pytest.mark.parametrize("tokens", [33, 64, 65])
 def test_fp32_forward_alone(tokens):
     """Without p_f heads, 576 pairs: the fp32 instruction up to 64 tokens."""
-    run_case(di.Workload("stream_f32_forward", 144, tokens, 64, 4, 64, 64, 1, "f32"), [FWD] * 4, seed=95)
+    names = kernels_of(lambda: run_case(di.Workload("stream_f32_forward", 144, tokens, 64, 4, 64, 64, 1, "f32"), [FWD] * 4, seed=95))
+    assert "attn_fwd_stream_kernel<float%s>" % (", Parts" if tokens == 65 else "") in names, names
 
 
 @pytest.mark.parametrize("tokens", [225, 256, 257, 289, 320, 577])
@@ -203,7 +220,10 @@ def test_fp32_values_without_bf16_parts(tokens):
     wt["b_qkv"][2, 1, 7] = np.float32(2.0 ** 105)
     wt["w_o"][:, 64 + 7] *= np.float32(2.0 ** -105)
     fields = ("w_qkv", "b_qkv", "w_o")
-    y, dx, g = gpu_block(w, wt, [FULL, FULL], x, dy, fields)
+    out = []
+    names = kernels_of(lambda: out.extend(gpu_block(w, wt, [FULL, FULL], x, dy, fields)))
+    assert names >= fp32_kernels(parts=True), names
+    y, dx, g = out
     ry, rdx, rg, _ = oracle_block(w, wt, [FULL, FULL], x, dy)
     assert rel_inf(y, ry) < TOL["f32"] and rel_inf(dx, rdx) < TOL["f32"]
     for k in ("w_qkv", "b_qkv"):
@@ -227,7 +247,10 @@ def positions(tokens):
 
 def check_values(w, wt, x, dy):
     """y and what reaches the values; the other gradients are what rounding leaves of zero, times the scores' size."""
-    y, _, g = gpu_block(w, wt, [FULL], x, dy, ("w_qkv", "b_qkv", "w_o"))
+    out = []
+    names = kernels_of(lambda: out.extend(gpu_block(w, wt, [FULL], x, dy, ("w_qkv", "b_qkv", "w_o"))))
+    assert names >= fp32_kernels(parts=True), names
+    y, _, g = out
     ry, _, rg, _ = oracle_block(w, wt, [FULL], x, dy)
     errs = {"y": rel_inf(y, ry), "w_o": rel_inf(g["w_o"], rg["w_o"])}
     errs.update({k: rel_inf(g[k][2], rg[k][2]) for k in ("w_qkv", "b_qkv")})

@@ -48,6 +48,15 @@ def test_bf16_lora_weight_scores(gate):
     check(w, wt, gate)
 
 
+def test_more_chunks_than_the_host_adds():
+    """64 heads of 148 chunks, 74 KB of sums: they are added on the device."""
+    w = di.Workload("scores_wide", 1, 1, 3072, 64, 64, 4096, 1, "bf16")
+    rng = np.random.default_rng(56)
+    grid = lambda *s: di.round_to_bf16(rng.standard_normal(s, dtype=np.float32))
+    check(w, {"w_qkv": grid(3, 64, 64, 3072), "b_qkv": grid(3, 64, 64), "w_o": grid(3072, 4096), "w1": grid(4096, 3072), "b1": grid(4096),
+              "w2": grid(3072, 4096), **{k: None for k in ("b_o", "b2", "ln1_g", "ln1_b", "ln2_g", "ln2_b")}}, True)
+
+
 def test_null_fields_are_skipped():
     w = di.WORKLOADS["vit_tiny_fp32"]
     wt = di.draw_block_weights(np.random.default_rng(53), w)
