@@ -18,7 +18,7 @@
 // Relative 2-norm error against fp64 of O / dQ / dV, N(0, 1) operands, 577 tokens: bf16 1.66e-3 / 1.68e-3 / 1.66e-3, the
 // same as the vector-ALU kernels (with P and dS rounded to bf16 2.18e-3 / 2.39e-3 / 2.38e-3); fp32 4.0e-7 / 5.4e-7 /
 // 5.3e-7 (by the fp32 instruction 4.8e-7 / 6.1e-7 / 5.8e-7, the vector-ALU kernels 5.3e-7 / 6.5e-7 / 6.3e-7); with scores of
-// 16 times the spread 5.5e-7 / 1.9e-6 / 1.2e-6 (8.5e-7 / 2.5e-6 / 1.4e-6 and 1.5e-6 / 3.8e-6 / 1.8e-6).
+// 16 times the spread 5.6e-7 / 1.8e-6 / 1.2e-6 (8.7e-7 / 2.4e-6 / 1.4e-6 and 1.5e-6 / 3.8e-6 / 1.8e-6).
 //
 // dQ and dK/dV workgroups are independent (both form delta_q = sum_d dO[q][d] O[q][d] for the rows they touch) and
 // share one launch, so that the second kind fills the last round of the first.  S and dP are formed twice, 7 products of 64 x 32 x 32 per tile pair instead of 5: keeping
@@ -28,7 +28,8 @@
 // between them: a part of an infinity is a NaN, an operand of 2^104 and more has no parts, and sums end at 2^80, as products
 // carry 2^48.  So a workgroup with a result that is not finite, with a Q or K above 2^36 or with a query whose log-sum-exp is beyond
 // 1024 forms its rows again with the fp32 instruction.  (These tests cost 1 %: 197 tokens, 260 pairs, forward 38.7 -> 38.8
-// us, backward 136.0 -> 136.6; a test of the log-sum-exp where it is fetched, not where it is stored, 5 %.)  The backward holds two row operands in parts (96
+// us, backward 136.0 -> 136.6; a test of the log-sum-exp where it is fetched, not where it is stored, 5 %.  Where every pair
+// falls back, 400 pairs take 107 and 396 us instead of 48 and 176.)  The backward holds two row operands in parts (96
 // registers): one wavefront per SIMD.  bf16 by the
 // matrix cores and the vector ALUs alike (forward 16 products of 32 cycles per tile pair, beside 16 exponentials, twice as
 // many subtractions and multiplications, maxima, sums and the cutting into parts, 5.5 operations for each of 16 elements).
@@ -538,7 +539,7 @@ __device__ __forceinline__ bool fwd_body(const T* __restrict__ qkv, long ldq, T*
 }
 
 // Op: how the operands are multiplied.  fp32 by parts falls back on the fp32 instruction, which is also a kernel of its own for
-// few tokens (fp32_by_instruction).
+// the calls that fp32_by_instruction names.
 template <typename T, typename Op = T>
 __global__ __launch_bounds__(64 * kWaves, (std::is_same<Op, Parts>::value ? 2 : 3)) void attn_fwd_stream_kernel(const T* __restrict__ qkv, long ldq,
                                                                          T* __restrict__ o, long ldo, float* __restrict__ lse,

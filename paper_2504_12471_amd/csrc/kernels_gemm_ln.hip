@@ -4,7 +4,7 @@
 //   C = epilogue( y B^T )
 //
 // One image (197 tokens) through the base model, whose QKV and first feed-forward products take this form: 581 -> 521 us; one fp32 block of 260 tokens
-// of width 192, forward and backward: 100.9 -> 98.9 us.
+// of width 192, forward and backward: 100.9 -> 98.7 us.
 //
 // What bounds it: latency.  As two launches the norm takes 3.2 us, nearly all of it the way to the first load and back,
 // and the product then waits for its first slabs again.  Here a workgroup (32 x 64 or 96 of C) requests everything it will ever

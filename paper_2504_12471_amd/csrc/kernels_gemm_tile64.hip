@@ -244,9 +244,11 @@ __global__ __launch_bounds__((64 * group_waves<TM, TN>() * WK), TM == 64 && TN =
     unsigned char* const mine = smem + kg * group_bytes<TM, TN>();
     unroll<kAhead>([&](auto i) { fetch(i.value, ra[i.value], rb[i.value]); });
     // The thread's piece of the tile and what the epilogue reads for it, requested here, so that a launch of few workgroups
-    // does not end with the latency of one more load.  The larger tiles have no registers for it.  fp32: only where each
-    // workgroup has a CU of its own; in later rounds others cover that latency, and the slabs wait behind these loads (913 x 832 x
-    // 3328 with bias and residual, 754 workgroups, 48.4 us without and 51.8 with).
+    // does not end with the latency of one more load.  The larger tiles have no registers for it.  bf16, in passes of eight
+    // models: 248 workgroups of 32x32 5.30 -> 4.91 us, 186 of 64x32 5.61 -> 5.40, three rounds (768 of 64x32) 10.26 -> 10.07, none slower
+    // by more than its runs differ.  fp32: only where each workgroup has a CU of its own; in later
+    // rounds others cover that latency, and the slabs wait behind these loads (913 x 832 x 3328 with bias and residual, 754
+    // workgroups, 48.4 us without and 51.8 with).
     constexpr bool kEarly = !GROUPED && TN == 32 && (TM == 32 || sizeof(T) == 2);
     const bool ahead = sizeof(T) == 2 || gridDim.x <= 256;
     constexpr int kThreads = GT * WK, kPieces = TM * TN / 8, kRowPieces = TN / 8;
