@@ -247,6 +247,12 @@ hipError_t launch_gemm_tile64_grouped(const GemmArgs& g, const ReduceGroupedArgs
                                       size_t partial_floats, TailJobs* tail, hipStream_t s);
 // rows of the output tile launch_gemm_mfma would pick (a tile makes two bands of g.colsum)
 int gemm_mfma_tile_rows(const GemmArgs& g);
+// 128x256 tiles, two workgroups to a CU (kernels_gemm_pair.hip), of what gemm_mfma_supported takes: whether there is a form
+// for it, its time in microseconds, the kernel's name as a profiler prints it, and the launch
+bool gemm_pair_supported(const GemmArgs& g);
+float gemm_pair_us(const GemmArgs& g);
+const char* gemm_pair_name(const GemmArgs& g);
+hipError_t launch_gemm_pair(const GemmArgs& g, hipStream_t s);
 // > 0: better as two launches, this many rows on 256x256 tiles (tile_hint 1) and the rest on 128x128 tiles (2)
 int gemm_mfma_split_rows(const GemmArgs& g);
 // static string naming the kernel instantiation launch_gemm_mfma would pick (for timing records)

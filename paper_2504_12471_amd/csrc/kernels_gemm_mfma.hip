@@ -22,6 +22,7 @@
 #include <type_traits>
 
 #include "d2ft_common.h"
+#include "gemm_epilogue.h"
 
 namespace d2ft {
 
@@ -158,30 +159,6 @@ __device__ __forceinline__ bf16x8 read_fragment(const lds_bf16* lane_base, int i
         r[4] = hi[0]; r[5] = hi[1]; r[6] = hi[2]; r[7] = hi[3];
         return __builtin_bit_cast(bf16x8, r);
     }
-}
-
-// ---- GELU for the bf16 epilogues ----
-// The epilogue of FC1 (and of its backward) evaluates Phi on 65536 elements per tile, which on the
-// vector ALUs costs as much time as the tile's MFMAs if done with erff (a reciprocal, an
-// exponential and a polynomial).  Here Phi(z) = 0.5 + z * Q(z^2) with Q a degree-8 polynomial fitted
-// on |z| <= 4 (Chebyshev fit of (Phi(z) - 0.5) / z; max absolute error 3.3e-5 including the clamp
-// of |z| to 4), i.e. more than an order of magnitude below bf16 resolution: 11 FMA-class
-// instructions and no transcendental.  The forward epilogue also evaluates GELU'(z) = Phi(z) + z phi(z)
-// (one exponential for the density) and saves it in place of z, so the backward epilogue is one
-// multiplication per element.
-__device__ __forceinline__ float phi_poly(float z) {
-    const float zc = fminf(fmaxf(z, -4.0f), 4.0f);
-    const float u = zc * zc;
-    float q = 1.043768652e-10f;
-    q = fmaf(q, u, -8.556765862e-09f);
-    q = fmaf(q, u, 3.133464190e-07f);
-    q = fmaf(q, u, -6.888049885e-06f);
-    q = fmaf(q, u, 1.036909179e-04f);
-    q = fmaf(q, u, -1.155711931e-03f);
-    q = fmaf(q, u, 9.929860060e-03f);
-    q = fmaf(q, u, -6.646679917e-02f);
-    q = fmaf(q, u, 3.989401704e-01f);
-    return fmaf(zc, q, 0.5f);
 }
 
 // ---- issue order of one MFMA group ----
@@ -688,13 +665,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_mfma_kernel(GemmArgs g
                     if (g.act == ACT_GELU) {
                         // Z <- GELU'(z), C <- GELU(z), both of the fp32 pre-activation
                         float gp[8];
-#pragma unroll
-                        for (int i = 0; i < 8; ++i) {
-                            const float zr = v[i];
-                            const float ph = phi_poly(zr);
-                            gp[i] = fmaf(zr * 0.39894228040143267794f, __builtin_amdgcn_exp2f(-0.72134752044448170368f * zr * zr), ph);
-                            v[i] = zr * ph;
-                        }
+                        gelu_pair8(v, gp);
                         if (SEGMENTS && !alive) {
 #pragma unroll
                             for (int i = 0; i < 8; ++i) gp[i] = 0.f;
@@ -1017,7 +988,7 @@ static float small_us(const GemmArgs& g) {
     return product_us(g, 0, g.M);
 }
 
-static int pick_tile(const GemmArgs& g) {
+static int pick_one(const GemmArgs& g) {
     if (g.tile_hint) return g.tile_hint == 2 ? 0 : g.tile_hint;
     if (g.N < 256 || g.M < 192) return 0;
     const float small = small_us(g), mid = product_us(g, 3, g.M);
@@ -1027,7 +998,7 @@ static int pick_tile(const GemmArgs& g) {
 
 // The rows of the whole rounds of 256x256 tiles if those, with the remaining rows on 128x128 tiles, are cheaper than any
 // one tile for all rows; 0 otherwise.
-int gemm_mfma_split_rows(const GemmArgs& g) {
+static int split_rows(const GemmArgs& g, float* us) {
     const long tn = (g.N + 255) / 256, total = (long)((g.M + 255) / 256) * tn;
     if (g.partial || g.tile_hint || g.M < 512 || g.N < 256 || total <= 256) return 0;
     const int rows = (int)(total / 256 * 256 / tn * 256);
@@ -1035,7 +1006,31 @@ int gemm_mfma_split_rows(const GemmArgs& g) {
     // the second launch waits for the first one's last tile; and near a tie one launch: 9232 x 1920 x 768 takes 34.6 us on
     // 192x256 tiles and 36.2 in two launches, 4096 x 4992 x 2048 77.9 and 84.2
     const float two = (product_us(g, 1, rows) + product_us(g, 0, g.M - rows) + 2.5f) * 1.015f;
+    *us = two;
     return two < small_us(g) && two < product_us(g, 1, g.M) && two < product_us(g, 3, g.M) ? rows : 0;
+}
+
+// Two workgroups to a CU (kernels_gemm_pair.hip) where that is cheaper than the large tiles in one launch or two.  Below 640
+// of its tiles, a round and a quarter, the costs do not tell the two apart; of 26 products of more that it takes by this
+// rule the slowest is at 1.04 of the other's time, their mean at 0.94 (12608 x 3072 x 768 with GELU 90 -> 78 us, 15760 x
+// 1536 x 384 43 -> 36).  Not beside another stream's launches: the backward's dz on this kernel (then with a form for it)
+// took 12.6 us off by itself and nothing off a pass.
+static bool pair_faster(const GemmArgs& g) {
+    if (g.tile_hint || g.shared || !gemm_pair_supported(g) || (long)((g.M + 127) / 128) * ((g.N + 255) / 256) <= 640) return false;
+    float us = 1e30f;
+    if (!split_rows(g, &us)) {
+        const int tile = pick_one(g);
+        us = product_us(g, tile, g.M);
+    }
+    return gemm_pair_us(g) < 0.96f * us;
+}
+
+// the tile of launch_gemm_mfma: 0 = 128x128, 1 = 256x256, 3 = 192x256, 4 = 128x256 with two workgroups to a CU
+static int pick_tile(const GemmArgs& g) { return pair_faster(g) ? 4 : pick_one(g); }
+
+int gemm_mfma_split_rows(const GemmArgs& g) {
+    float us;
+    return pair_faster(g) ? 0 : split_rows(g, &us);
 }
 
 int gemm_mfma_tile_rows(const GemmArgs& g) {
@@ -1050,6 +1045,7 @@ const char* gemm_mfma_config_name(const GemmArgs& g) {
     const bool tail = (g.K % 64) != 0;
     const int epi = (!a_col && b_col && dgelu_only(g) && g.remap != REMAP_B_K) ? EPI_DGELU
                     : (!a_col && !b_col && residual_only(g) && g.remap != REMAP_B_N) ? EPI_RESIDUAL : EPI_ANY;
+    if (tile == 4) return gemm_pair_name(g);
     static char names[4][3][3][2][3][88];
     char* name = names[tile][a_col ? 2 : (b_col ? 1 : 0)][g.remap == REMAP_B_N ? 1 : (g.remap == REMAP_B_K ? 2 : 0)][tail][epi];
     if (!name[0]) {
@@ -1174,6 +1170,7 @@ hipError_t launch_gemm_grouped(GemmArgs* g, hipStream_t s) {
 hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {
     if (!gemm_mfma_supported(g)) return hipErrorNotSupported;
     switch (pick_tile(g)) {
+        case 4: return launch_gemm_pair(g, s);
         case 1: return launch_layout<256, 256, 64, 2, 4>(g, s);
         case 3: return launch_layout<192, 256, 64, 2, 4>(g, s);
         default: return launch_layout<128, 128, 64, 2, 2>(g, s);
