@@ -226,7 +226,6 @@ hipError_t launch_gemm_mfma_seg(const GemmArgs& g, hipStream_t s);
 // ldb, M, N}; the launcher fills the tile bookkeeping and returns it in *g for the reduction.  partial must hold
 // gemm_grouped_slots(g) tiles of 256 x 256 floats.  hipErrorNotSupported if an operand does not fit the kernel.
 size_t gemm_grouped_slots(const GemmArgs& g);
-hipError_t launch_gemm_grouped(GemmArgs* g, hipStream_t s);
 // out_g[r'][c'] (=|+=) sum over the slots of each tile, (r', c') through the group's remap
 struct ReduceGroup {
     void* out;
@@ -238,7 +237,8 @@ struct ReduceGroupedArgs {
     ReduceGroup grp[kMaxGemmGroups];
     Remap64 tbl[3];
 };
-hipError_t launch_reduce_grouped(int dtype, const GemmArgs& g, const ReduceGroupedArgs& r, int accumulate, hipStream_t s);
+hipError_t launch_gemm_grouped(GemmArgs* g, const ReduceGroupedArgs& r, hipStream_t s);
+hipError_t launch_reduce_grouped(const GemmArgs& g, const ReduceGroupedArgs& r, int accumulate, hipStream_t s);
 // the weight gradients of g.grp over the same K on 64x64 tiles, written through r (with a reduction of its own if it
 // splits K): takes g.n_groups, grp[].{A, B, lda, ldb, M, N}, K and partial (partial_floats long); tail, if given, rides
 // along

@@ -384,8 +384,8 @@ hipError_t run_gemm_segments(GemmArgs g, const d2ft_block_desc* d, const MicroMa
     if (colsum_bands) *colsum_bands = 2 * ((g.M + 255) / 256);
     if (done) launch_signal_next(done);
     timing_begin(s, "gemm");
-    g_timing.label = g.b_rs != 1 ? "gemm_mfma_kernel<256, 256, 64, 2, 4, false, true, 1, false, false, true, 1>"
-                                 : "gemm_mfma_kernel<256, 256, 64, 2, 4, false, false, 1, false, false, true, 0>";
+    g_timing.label = g.b_rs != 1 ? "gemm_mfma_kernel<256, 256, 64, 2, 4, false, true, 1, false, true, 1>"
+                                 : "gemm_mfma_kernel<256, 256, 64, 2, 4, false, false, 1, false, true, 0>";
     g_timing.flops = 2.0 * cols * g.K;
     const hipError_t e = launch_gemm_mfma_seg(g, s);
     timing_end(s);
@@ -699,15 +699,15 @@ d2ft_status weight_grad_flush(WeightGradBatch* b, const d2ft_block_desc* d, cons
         }
     } else if (gemm_grouped_slots(g) * 65536 <= part_floats) {
         timing_begin(st, "gemm");
-        g_timing.label = "gemm_mfma_kernel<256, 256, 64, 2, 4, true, true, 0, false, true, false, 0>";
+        g_timing.label = g.K % 32 ? "gemm_wgrad_kernel<true>" : "gemm_wgrad_kernel<false>";
         for (int i = 0; i < g.n_groups; ++i) g_timing.flops += 2.0 * g.grp[i].M * g.grp[i].N * s.M;
-        e = launch_gemm_grouped(&g, st);
+        e = launch_gemm_grouped(&g, b->r, st);
         timing_end(st);
     }
     if (e == hipSuccess) {
         // every (workgroup, tile) partial is read once, every output element written once
         const double nbytes = 4.0 * 65536 * g.total_tiles * g.splits;
-        D2FT_TRY_BYTES(nbytes, launch_reduce_grouped(s.dtype, g, b->r, accum, st));
+        D2FT_TRY_BYTES(nbytes, launch_reduce_grouped(g, b->r, accum, st));
     } else if (e == hipErrorNotSupported) {   // an operand the grouped kernel does not take: one launch per gradient
         for (int i = 0; i < g.n_groups; ++i) {
             const GemmGroup& G = g.grp[i];

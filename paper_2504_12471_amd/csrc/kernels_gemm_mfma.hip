@@ -217,13 +217,13 @@ __device__ __forceinline__ void tile_of_block(int pid, int total, int tiles_m, i
 // products that close a residual branch); both fetch their operand a band ahead
 enum { EPI_ANY = 0, EPI_DGELU = 1, EPI_RESIDUAL = 2 };
 
-template <int BM, int BN, int BK, int WGM, int WGN, bool A_COL, bool B_COL, int REMAP, bool KTAIL, bool GROUPED = false,
-          bool SEGMENTS = false, int EPI = EPI_ANY>
+template <int BM, int BN, int BK, int WGM, int WGN, bool A_COL, bool B_COL, int REMAP, bool KTAIL, bool SEGMENTS = false,
+          int EPI = EPI_ANY>
 __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_mfma_kernel(GemmArgs g) {
     constexpr int kThreads = 64 * WGM * WGN;    // WGM x WGN wavefronts
     constexpr bool KSEG = REMAP == REMAP_B_KSEG;    // K walk over the positions of the tile's row segments
     constexpr bool REMAP_BK = REMAP == REMAP_B_K || KSEG;
-    static_assert(!KSEG || (!KTAIL && !GROUPED && !SEGMENTS && !A_COL), "the K-segment form: A row-major, K a multiple of 64");
+    static_assert(!KSEG || (!KTAIL && !SEGMENTS && !A_COL), "the K-segment form: A row-major, K a multiple of 64");
     constexpr int WTM = BM / WGM, WTN = BN / WGN;   // wavefront tile
     constexpr int MT = WTM / 32, NT = WTN / 32; // MFMA tiles per wavefront
     constexpr int A_ELEMS = slab_elems<BM, BK, A_COL>();
@@ -263,37 +263,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_mfma_kernel(GemmArgs g
         } else {
             kseg_k += BK;
         }
-    };
-    // Grouped mode (weight gradients of several layers in one launch, all reducing over the same K): the work
-    // is the list of units (tile, split) = unit % total_tiles, unit / total_tiles; every tile's K is cut into
-    // g.splits equal runs of slabs.  Workgroup ids are renumbered so that the units of one XCD's workgroups are
-    // neighbouring tiles of the same split (they share operand slabs through its L2); a workgroup takes units
-    // id, id + grid, ... and leaves each unit's raw sums in partial slot `unit`.
-    constexpr bool grouped = GROUPED;
-    int unit = 0;
-    if constexpr (grouped) unit = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-    int piece_slot = 0;
-    auto setup_piece = [&]() -> bool {   // false when the workgroup's units are used up
-        if (!grouped || unit >= g.total_tiles * g.splits) return false;
-        const int t = unit % g.total_tiles, sp = unit / g.total_tiles;
-        int gi = 0;
-        while (gi + 1 < g.n_groups && t >= g.grp[gi + 1].tile0) ++gi;
-        const GemmGroup& G = g.grp[gi];
-        const int lt = t - G.tile0;
-        m0 = (lt % G.tiles_m) * BM;
-        n0 = (lt / G.tiles_m) * BN;
-        kb = sp * g.units_per_wg * BK;                    // units_per_wg: slabs per split
-        ke = min(g.K, kb + g.units_per_wg * BK);
-        la.template init<false>(static_cast<const bf16*>(G.A), 1, G.lda, m0, G.M, g.tbl);
-        lb.template init<false>(static_cast<const bf16*>(G.B), 1, G.ldb, n0, G.N, g.tbl);
-        nslabs = (ke > kb) ? (ke - kb + BK - 1) / BK : 0;
-        if (nslabs > 0) {
-            la.template load<false, KTAIL>(kb, ke, g.tbl);
-            lb.template load<false, KTAIL>(kb, ke, g.tbl);
-        }
-        piece_slot = unit;
-        unit += gridDim.x;
-        return true;
     };
     auto setup_tile = [&](int pid) {
         int tile_m, tile_n;
@@ -402,12 +371,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_mfma_kernel(GemmArgs g
 
     int pid = blockIdx.x;
     bool have_work = true;
-    if constexpr (grouped) {
-        have_work = setup_piece();
-    } else {
-        if constexpr (SEGMENTS) have_work = pid < total;
-        if (have_work) setup_tile(pid);
-    }
+    if constexpr (SEGMENTS) have_work = pid < total;
+    if (have_work) setup_tile(pid);
     while (have_work) {
 #pragma unroll
     for (int t = 0; t < MT; ++t)
@@ -485,17 +450,13 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_mfma_kernel(GemmArgs g
         if (s < nslabs) slab(s, no, no);
     }
     __syncthreads();   // the epilogue reuses the operand buffers
-    const int em0 = m0, en0 = n0, esplit = split, eslot = piece_slot;
+    const int em0 = m0, en0 = n0, esplit = split;
     int m_lim = g.M;   // rows of the tile below it are written
     if constexpr (KSEG) m_lim = mlim;
     // the next tile's first slab arrives under the epilogue
-    if constexpr (grouped) {
-        have_work = setup_piece();
-    } else {
-        pid += gridDim.x;
-        have_work = pid < total;
-        if (have_work) setup_tile(pid);
-    }
+    pid += gridDim.x;
+    have_work = pid < total;
+    if (have_work) setup_tile(pid);
 
     // ---- epilogue ----
     // Accumulator element e of MFMA tile (t,u) is row 8*(e/4) + 4*(lane/32) + e%4, column lane%32.
@@ -512,7 +473,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_mfma_kernel(GemmArgs g
     const bf16* R = SEGMENTS ? nullptr : static_cast<const bf16*>(g.residual);   // the segment form takes neither
     bf16* Z = static_cast<bf16*>(g.Z);
     float* P = (!SEGMENTS && g.partial) ? g.partial + (long)esplit * g.M * g.N : nullptr;
-    float* const Pslot = g.partial + (long)eslot * (BM * BN);   // grouped mode: a whole tile per slot
     // a lane reads back the same 8 columns in every chunk (64 is a multiple of the chunks per row),
     // so its bias values are fetched once per tile
     static_assert(64 % CPR == 0, "a lane keeps its columns over the chunks of a band");
@@ -568,7 +528,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_mfma_kernel(GemmArgs g
     // (Z or R) is fetched a band ahead - each chunk's registers are refilled for the next band as soon as the
     // chunk is stored - instead of one dependent load per chunk.
     if constexpr (EPI != EPI_ANY) {
-        static_assert(!GROUPED && !A_COL, "a plain product with A row-major");
+        static_assert(!A_COL, "a plain product with A row-major");
         const int mrow = em0 + wm * WTM + lane / CPR;           // the lane's row of chunk 0 in band 0
         const int n = en0 + wn * WTN + (lane % CPR) * 8;        // its columns in every chunk
         const long ldop = EPI == EPI_DGELU ? g.ldz : g.ldr;
@@ -640,13 +600,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_mfma_kernel(GemmArgs g
             const int r = id / CPR, cc = (id % CPR) * 8;
             const int m = em0 + wm * WTM + t * 32 + r;
             const int n = en0 + wn * WTN + cc;
-            if constexpr (grouped) {   // raw sums of the whole tile (rows and columns outside the problem are zeros)
-                float v[8];
-                const float4 lo = *reinterpret_cast<const float4*>(stage + r * SST + cc);
-                const float4 hi = *reinterpret_cast<const float4*>(stage + r * SST + cc + 4);
-                v[0] = lo.x; v[1] = lo.y; v[2] = lo.z; v[3] = lo.w; v[4] = hi.x; v[5] = hi.y; v[6] = hi.z; v[7] = hi.w;
-                store8(Pslot + (wm * WTM + t * 32 + r) * BN + wn * WTN + cc, v);
-            } else if (m < m_lim && n < g.N) {
+            if (m < m_lim && n < g.N) {
                 float v[8];
                 const float4 lo = *reinterpret_cast<const float4*>(stage + r * SST + cc);
                 const float4 hi = *reinterpret_cast<const float4*>(stage + r * SST + cc + 4);
@@ -771,7 +725,7 @@ constexpr size_t lds_bytes() {
 template <int BM, int BN, int BK, int WGM, int WGN, bool A_COL, bool B_COL, int REMAP, bool KTAIL, int EPI = EPI_ANY>
 hipError_t launch_cfg(const GemmArgs& g, hipStream_t s) {
     constexpr size_t lds = lds_bytes<BM, BN, BK, WGM, WGN, A_COL, B_COL>();
-    auto kern = gemm_mfma_kernel<BM, BN, BK, WGM, WGN, A_COL, B_COL, REMAP, KTAIL, false, false, EPI>;
+    auto kern = gemm_mfma_kernel<BM, BN, BK, WGM, WGN, A_COL, B_COL, REMAP, KTAIL, false, EPI>;
     static int resident = 0;   // per instantiation: workgroups the chip holds at once, a multiple of 8
     if (resident == 0) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -792,55 +746,6 @@ hipError_t launch_cfg(const GemmArgs& g, hipStream_t s) {
     return hipGetLastError();
 }
 
-constexpr int kGroupedMaxSplits = 8;
-
-// grouped launch: always the 256x256 tile with both operands K-strided; the grid is what the chip holds
-template <bool KTAIL>
-hipError_t launch_grouped_cfg(GemmArgs* g, hipStream_t s) {
-    constexpr int BM = 256, BN = 256, BK = 64, WGM = 2, WGN = 4;
-    constexpr size_t lds = lds_bytes<BM, BN, BK, WGM, WGN, true, true>();
-    auto kern = gemm_mfma_kernel<BM, BN, BK, WGM, WGN, true, true, REMAP_NONE, KTAIL, true>;
-    static int resident = 0;
-    if (resident == 0) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        int dev = 0, cus = 0, per_cu = 0;
-        if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
-        if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
-        if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64 * WGM * WGN, lds)) != hipSuccess) return e;
-        if (per_cu < 1) per_cu = 1;
-        resident = cus * per_cu / 8 * 8;
-        if (resident < 8) resident = 8;
-    }
-    int tile = 0;
-    for (int i = 0; i < g->n_groups; ++i) {
-        GemmGroup& G = g->grp[i];
-        G.tiles_m = (G.M + BM - 1) / BM;
-        G.tile0 = tile;
-        tile += G.tiles_m * ((G.N + BN - 1) / BN);
-    }
-    g->total_tiles = tile;
-    g->slabs_per_tile = (g->K + BK - 1) / BK;
-    // Split count: the cheapest of 1 .. 8 in slab times - rounds of the grid, each a run of slabs plus a unit's
-    // fixed cost (first-slab latency, writing the partial tile), plus the reduction's pass over the partials.
-    const int S = g->slabs_per_tile;
-    int best = 1;
-    double best_cost = 1e30;
-    for (int sp = 1; sp <= kGroupedMaxSplits && sp <= S; ++sp) {
-        const long units = (long)tile * sp;
-        if (sp > 1 && g->max_units > 0 && units > g->max_units) break;   // the caller wants CUs left over
-        const long rounds = (units + resident - 1) / resident;
-        const double cost = rounds * ((S + sp - 1) / sp + 8.0) + 0.04 * units;
-        if (cost < best_cost) { best_cost = cost; best = sp; }
-    }
-    g->splits = best;
-    g->units_per_wg = (S + best - 1) / best;
-    const long units = (long)tile * best;
-    long grid = units < resident ? (units + 7) / 8 * 8 : resident;
-    launch_kernel(kern, dim3((unsigned)grid), dim3(64 * WGM * WGN), lds, s, *g);
-    return hipGetLastError();
-}
-
 // C = (A B) * Z and nothing else in the epilogue: the instantiations with the band-ahead fetch of Z
 inline bool dgelu_only(const GemmArgs& g) {
     return g.act == ACT_DGELU && !g.partial && !g.bias && !g.residual && g.a_cs == 1 && g.b_rs != 1;
@@ -856,7 +761,7 @@ template <bool B_COL, int REMAP>
 hipError_t launch_seg_cfg(const GemmArgs& g, hipStream_t s) {
     constexpr int BM = 256, BN = 256, BK = 64, WGM = 2, WGN = 4;
     constexpr size_t lds = lds_bytes<BM, BN, BK, WGM, WGN, false, B_COL>();
-    auto kern = gemm_mfma_kernel<BM, BN, BK, WGM, WGN, false, B_COL, REMAP, false, false, true, B_COL ? EPI_DGELU : EPI_ANY>;
+    auto kern = gemm_mfma_kernel<BM, BN, BK, WGM, WGN, false, B_COL, REMAP, false, true, B_COL ? EPI_DGELU : EPI_ANY>;
     static int resident = 0;
     if (resident == 0) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1050,22 +955,11 @@ const char* gemm_mfma_config_name(const GemmArgs& g) {
     char* name = names[tile][a_col ? 2 : (b_col ? 1 : 0)][g.remap == REMAP_B_N ? 1 : (g.remap == REMAP_B_K ? 2 : 0)][tail][epi];
     if (!name[0]) {
         const int bm = tile == 0 ? 128 : (tile == 3 ? 192 : 256), bn = tile == 0 ? 128 : 256;
-        snprintf(name, sizeof(names[0][0][0][0][0]), "gemm_mfma_kernel<%d, %d, 64, 2, %d, %s, %s, %d, %s, false, false, %d>", bm, bn,
+        snprintf(name, sizeof(names[0][0][0][0][0]), "gemm_mfma_kernel<%d, %d, 64, 2, %d, %s, %s, %d, %s, false, %d>", bm, bn,
                  tile == 0 ? 2 : 4, a_col ? "true" : "false", b_col ? "true" : "false",
                  g.remap == REMAP_B_N ? 1 : (g.remap == REMAP_B_K ? 2 : 0), tail ? "true" : "false", epi);
     }
     return name;
-}
-
-static bool grouped_ok(const GemmArgs& g) {
-    if (g.n_groups < 1 || g.n_groups > kMaxGemmGroups || g.K <= 0 || !g.partial || !al16(g.partial)) return false;
-    for (int i = 0; i < g.n_groups; ++i) {
-        const GemmGroup& G = g.grp[i];
-        if (G.M <= 0 || G.N <= 0 || !G.A || !G.B || !al16(G.A) || !al16(G.B)) return false;
-        if (!mult8(G.M) || !mult8(G.N) || !mult8(G.lda) || !mult8(G.ldb)) return false;
-        if ((long)g.K * G.lda * 2 >= (1L << 31) || (long)g.K * G.ldb * 2 >= (1L << 31)) return false;   // 32-bit offsets
-    }
-    return true;
 }
 
 hipError_t gemm_mfma_seg_prepare(GemmArgs* g) {
@@ -1150,21 +1044,6 @@ hipError_t launch_gemm_mfma_seg(const GemmArgs& g, hipStream_t s) {
     const bool b_col = (g.b_rs != 1);
     if (g.remap != REMAP_B_N || g.seg.n < 1) return hipErrorNotSupported;
     return b_col ? launch_seg_cfg<true, REMAP_B_N>(g, s) : launch_seg_cfg<false, REMAP_B_N>(g, s);
-}
-
-size_t gemm_grouped_slots(const GemmArgs& g) {
-    size_t tiles = 0;
-    for (int i = 0; i < g.n_groups; ++i)
-        tiles += (size_t)((g.grp[i].M + 255) / 256) * ((g.grp[i].N + 255) / 256);
-    return tiles * kGroupedMaxSplits;   // one slot per (tile, split)
-}
-
-hipError_t launch_gemm_grouped(GemmArgs* g, hipStream_t s) {
-    if (!grouped_ok(*g)) return hipErrorNotSupported;
-    g->M = g->N = 0;
-    g->remap = REMAP_NONE;
-    if (g->K % 64) return launch_grouped_cfg<true>(g, s);
-    return launch_grouped_cfg<false>(g, s);
 }
 
 hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s) {

@@ -1,0 +1,61 @@
+"""The weight gradients of a backward call in one launch of 256x256 tiles (gemm_wgrad_kernel), and their reduction."""
+import numpy as np
+import pytest
+
+import d2ft_inputs as di
+from helpers import TOL, gpu_block, oracle_block, rel_inf
+from test_gpu_block import draw_block, run_case
+
+pytestmark = pytest.mark.gpu
+
+FULL, FWD, SKIP = di.OP_FULL, di.OP_FWD, di.OP_SKIP
+
+
+# rows a multiple of the 32 of a slab, or 5 or 24 more; tiles with remainders both ways; rows and columns through the remaps;
+# added to what is there; the adapters' product, whose sums stay fp32; one tile in eight runs of K
+@pytest.mark.parametrize("B,T,D,heads,Dm,lora,accumulate", [
+    (70, 64, 384, [FULL, SKIP, FULL, FWD, FULL, FULL], 1536, 0, False),
+    (69, 65, 384, [FULL, FULL, SKIP, FULL, FULL, FULL], 1544, 0, True),
+    (79, 104, 72, [FULL], 264, 0, False),
+    (79, 104, 64, [SKIP, FULL], 64, 8, False)])
+def test_weight_gradients(B, T, D, heads, Dm, lora, accumulate):
+    import paper_2504_12471_amd as P
+    w = di.Workload("wgrad", B, T, D, len(heads), 64, Dm, 1, "bf16", lora_rank=lora, lora_b_zero=False)
+    fields = [k for k in di.WEIGHT_FIELDS if k.startswith("lora") == (lora > 0)]
+    P.d2ft_timing_enable(True)
+    try:
+        if accumulate:
+            x, wt, dy = draw_block(w, B + D)
+            ref = oracle_block(w, wt, heads, x, dy)[2]
+            init = {k: di.round_to_bf16(np.roll(ref[k].ravel(), 1).reshape(ref[k].shape)) for k in ("w1", "w2", "w_qkv", "w_o")}
+            got = gpu_block(w, wt, heads, x, dy, list(init), 1, init)[2]
+            for k, v in init.items():
+                assert rel_inf(got[k], ref[k] + v) < TOL["bf16"], k
+        else:
+            run_case(w, heads, seed=B + D, grad_fields=fields)
+        names = {r["name"] for r in P.d2ft_timing_read()}
+    finally:
+        P.d2ft_timing_enable(False)
+    assert ("gemm_wgrad_kernel<%s>" % ("true" if B * T % 32 else "false")) in names, names
+
+
+def test_infinity_stays_in_its_row_and_column():
+    """An infinite dy of one token and channel: dw2's row of that channel and what dv carries on, nothing beyond."""
+    import torch
+    import paper_2504_12471_amd as P
+    B, T, D, H, Dm = 70, 64, 384, 6, 1536
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    mk = lambda *s, std=0.02: (torch.randn(s, generator=gen, device="cuda") * std).to(torch.bfloat16)
+    wt = {"ln1_g": 1 + mk(D), "ln1_b": mk(D), "w_qkv": mk(3, H, 64, D), "b_qkv": mk(3, H, 64), "w_o": mk(D, 64 * H), "b_o": mk(D),
+          "ln2_g": 1 + mk(D), "ln2_b": mk(D), "w1": mk(Dm, D), "b1": mk(Dm), "w2": mk(D, Dm), "b2": mk(D)}
+    x, dy = mk(B, T, D, std=1.0), mk(B, T, D, std=1.0)
+    ops = np.full((1, H), FULL, dtype=np.uint8)
+    st = P.BlockStack(P.make_desc(B, T, D, H, Dm, "bf16"), [wt], "bf16", [])
+    st.grads = [{n: (torch.zeros_like(wt[n]) if n in ("w1", "w2") else None) for n in P.WEIGHT_FIELDS}]
+    st.step(x, dy, ops)
+    clean = st.grads[0]["w2"].clone()
+    dy[69, 63, 130] = float("inf")
+    st.step(x, dy, ops)
+    got = st.grads[0]["w2"]
+    rest = torch.arange(D, device="cuda") != 130
+    assert torch.equal(got[rest], clean[rest]) and not torch.isfinite(got[130]).any()
