@@ -23,6 +23,7 @@ namespace d2ft {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4;
 typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
@@ -499,44 +500,34 @@ hipError_t launch_fwd_kt(const bf16* qkv, long ldq, bf16* o, long ldo, float* ls
 //     dP = dO_i V_u^T             dS = P * (dP - delta_q),       delta_q = sum_d dO[q][d] O[q][d]
 //     dV_u^T += dO_i^T P          dK_u^T += Q_i^T dS             (P, dS feed the MFMA straight from registers)
 //     dQ_i^T  = sum_u K_u^T dS_iu^T
-// The workgroup has KT + 1 wavefronts.  Wavefront u < KT owns key tile u: it holds the K_u and V_u
-// operand fragments and its dK, dV accumulators in registers for the whole kernel, walks the query
-// tiles and leaves each dS_iu (bf16, 2 KB) in LDS.  Its loop is software-pipelined: the S and dP
-// products of query tile i + 1 are issued before the exponentials of tile i, so the matrix cores work
-// under the vector arithmetic.  The last wavefront owns dQ: one step behind the others it multiplies
-// the KT tiles dS_iu of a query tile with K^T out of LDS, so dQ_i is MFMA chains in a fixed order - no
-// partial sums cross wavefronts - and goes from its registers to memory.  Query tiles (Q_i, dO_i) are
-// triple-buffered and the dS tiles double-buffered in LDS, which leaves one barrier per query tile.
-// The per-query constants ride in the products: a query row of Q carries -8 lse_q and a row of dO
-// carries -delta_q (each split into two bf16 terms) in two extra channels that meet a 1 on the K / V
-// side, so the MFMAs deliver S - 8 lse and dP - delta and the lanes read no per-query values from LDS.
+// The workgroup has KT wavefronts and all of Q, dO and dS in LDS (bf16; 160 KB at KT = 7).  Wavefront w first owns key
+// tile w: K_w, V_w, dK_w and dV_w stay in registers while it walks the query tiles, which takes no barrier, and
+// leaves every dS_iw in LDS.  Behind one barrier it owns query tile w: K has taken Q's place, and dQ_w is MFMA chains over
+// all key tiles in a fixed order, so no partial sums cross wavefronts.  The walk is software-pipelined: the S and
+// dP products of query tile i + 1 are issued before the exponentials of tile i, so the matrix cores work under the
+// vector arithmetic.
+// The per-query constants ride in the products: a query has -8 lse_q and -delta_q as three bf16 terms each in an
+// extra channel group that meets ones on the K / V side, so the MFMAs deliver S - 8 lse and dP - delta (as the sums'
+// initial values they are four times the LDS reads: 1 % slower).
 // If bsum is given the kernel also writes the column sums of the pair's dQ, dK, dV rows (the
 // gradient of the QKV bias: one row of 192 partial sums per image).
 // ---------------------------------------------------------------------------
-constexpr int kTS = 104;   // K rows, read both ways once (row-form and transposing): 208 bytes
-// Query tiles (Q_i, dO_i) are read both ways in every step.  A 128-bit row-form read is free of bank conflicts
-// when eight consecutive rows start in different 16-byte slots of a 128-byte line (row stride an odd multiple
-// of 16 bytes); a transposing read when the four rows of a 16-lane group start 32 bytes apart modulo 128.  No
-// stride does both for rows in their natural order, so row r of every group of eight is kept at position
-// (0, 2, 4, 6, 1, 3, 5, 7)[r % 8] with a stride of 176 bytes: eight rows still start in eight different slots,
-// and rows r .. r + 3 of a half group sit two strides apart, i.e. 96 bytes modulo 128.
-constexpr int kQS = 88;
-__device__ __forceinline__ int tile_row(int r) { return (r & ~7) | ((r & 3) << 1) | ((r >> 2) & 1); }
-// the transposing read of frag_tr for such a tile: logical rows t0 + 4h + {0..3} and t0 + 8 + 4h + {0..3}
-__device__ __forceinline__ bf16x8 frag_tr_tile(const bf16* lds, int t0, int ch0, int lane) {
-    const int j = lane & 15;
-    const bf16* p = lds + (t0 + 2 * (j >> 2) + (lane >> 5)) * kQS + ch0 + 16 * ((lane >> 4) & 1) + 4 * (j & 3);
-    typedef s16x4 __attribute__((address_space(3))) * lds_ptr_t;
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p));
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p + 8 * kQS));
-    s16x8 r;
-    r[0] = lo[0]; r[1] = lo[1]; r[2] = lo[2]; r[3] = lo[3];
-    r[4] = hi[0]; r[5] = hi[1]; r[6] = hi[2]; r[7] = hi[3];
-    return __builtin_bit_cast(bf16x8, r);
+typedef __attribute__((address_space(3))) unsigned char lds_u8;
+typedef __attribute__((address_space(3))) float lds_f32;
+typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+// Rows of Q, dO and K are 128 bytes, whose eight 16-byte pieces change places: piece p of row r sits at p ^ row_swizzle(r).
+// Both kinds of read are then free of bank conflicts: 16-byte pieces p of 16 rows (a row-form fragment), and 64 bytes of the
+// four rows 4n .. 4n + 3 (half of a transposing one).
+__device__ __forceinline__ int row_swizzle(int r) { return (r >> 1 & 1) << 2 | (r >> 2 & 1) << 1 | (r >> 3 & 1); }
+// dS tiles are [32 keys][32 queries] in rows of 64 bytes with their four pieces exchanged likewise
+__device__ __forceinline__ int ds_swizzle(int key) { return key >> 2 & 3; }
+
+__device__ __forceinline__ bf16x8 read_piece(const lds_u8* p) { return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(p); }
+__device__ __forceinline__ bf16x8 read_tr(const lds_u8* lo_at, const lds_u8* hi_at) {
+    typedef s16x4 __attribute__((address_space(3))) * tr_ptr;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)lo_at), hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)hi_at);
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
-// dS tiles [32 keys][32 queries]: rows of 96 bytes, so that the four key rows of a transposing read start
-// 32 bytes apart modulo 128
-constexpr int kDS = 48;
 
 // f(integral_constant<int, 0>), f(integral_constant<int, 1>), ...: a loop whose index is a compile-time constant
 template <typename F, int... I>
@@ -548,267 +539,246 @@ __device__ __forceinline__ void static_for(F&& f) {
     static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-template <int KT, typename Mask>
-__global__ __launch_bounds__(64 * (KT + 1)) void attn_bwd_mfma_kernel(const bf16* __restrict__ qkv, long ldq,
-                                                                      const bf16* __restrict__ o, long ldo,
-                                                                      const float* __restrict__ lse,
-                                                                      const bf16* __restrict__ d_o, long ld_do,
-                                                                      bf16* __restrict__ dqkv, long ld_dqkv,
-                                                                      float* __restrict__ bsum, long ld_bsum,
-                                                                      int tokens, int n_full, long rows_total,
-                                                                      Mask mask) {
-    constexpr int TP = KT * 32;
-    constexpr int NTHR = 64 * (KT + 1);
-    constexpr int NLD = (512 + NTHR - 1) / NTHR;         // 16-byte chunks of a (Q_i, dO_i) tile pair per thread
-    constexpr int NDL = (TP * 8 + NTHR - 1) / NTHR;      // (query, 16-byte piece) items of the delta sums per thread
-    constexpr int NKL = (TP * 8 + NTHR - 1) / NTHR;      // 16-byte chunks of K per thread
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    bf16* Ks = reinterpret_cast<bf16*>(smem_raw);        // [TP][kTS]      read transposed by the dQ wavefront
-    bf16* Qs = Ks + TP * kTS;                            // [3][32][kQS]   query tile i in buffer i % 3, rows permuted
-    bf16* dOs = Qs + 3 * 32 * kQS;                       // [3][32][kQS]
-    bf16* dSs_all = dOs + 3 * 32 * kQS;                  // [2][KT][32 keys][kDS]
-    float* lse_s = reinterpret_cast<float*>(dSs_all + 2 * KT * 32 * kDS);   // [TP]   -8 lse_q
-    float* del_s = lse_s + TP;                           // [TP]   -delta_q
-    bf16* dq_stage = reinterpret_cast<bf16*>(del_s + TP);   // [32][72]   the dQ wavefront's store staging
-    float* red = reinterpret_cast<float*>(dq_stage + 32 * 72);   // [KT][128]   column sums of dK, dV per key tile
-    float* sk_s = red + KT * 128;                        // [TP]   sum over the queries of dS[q][key], for dQ's column sums
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int c = lane & 31, h = lane >> 5;
-    const int b = blockIdx.x / n_full;   // with a mask n_full is the number of slots per image
-    int j = blockIdx.x % n_full;
-    const long row0 = (long)b * tokens;
-    if constexpr (std::is_same<Mask, MicroMask>::value) {
-        const int mb = mask.micro_of(b), slot = j;
-        const uint64_t full = mask.full[mb];
-        const uint64_t rest = ~full & (mask.n_full_pos >= 64 ? ~0ull : ((1ull << mask.n_full_pos) - 1ull));
-        int r = 0;
-        for (uint64_t m = rest; m; m &= m - 1, ++r)   // not p_f in this image's micro-batch: dQ = dK = dV = 0
-            if (r % n_full == slot) {
-                const int p = __builtin_ctzll(m);
-                bf16* zb = dqkv + row0 * ld_dqkv + p * 192;
-                const u32x4 z = {0u, 0u, 0u, 0u};
-                for (int i = threadIdx.x; i < tokens * 24; i += NTHR)
-                    *reinterpret_cast<u32x4*>(zb + (long)(i / 24) * ld_dqkv + (i % 24) * 8) = z;
-                if (bsum)
-                    for (int i = threadIdx.x; i < 192; i += NTHR) bsum[(long)b * ld_bsum + p * 192 + i] = 0.f;
-            }
-        if (slot >= __builtin_popcountll(full)) return;
-        uint64_t m = full;
-        for (int t = 0; t < slot; ++t) m &= m - 1;
-        j = __builtin_ctzll(m);   // this slot's p_f head
-    }
-    const bf16* Qb = qkv + row0 * ldq + j * 192;
-    const bf16* dOb = d_o + row0 * ld_do + j * 64;
-    const bf16* Ob = o + row0 * ldo + j * 64;
-    bf16* dQb = dqkv + row0 * ld_dqkv + j * 192;
-    const int u = wave;                 // this wavefront's key tile (wave == KT: the dQ wavefront)
-    const u32x4 zero4 = {0u, 0u, 0u, 0u};
+template <int KT> struct BwdLds {   // byte offsets
+    static constexpr int kTile = 32 * 128, kDsTile = 32 * 64;
+    static constexpr int kQ = 0, kDo = KT * kTile;                 // Q, then K; dO, then dV on its way out
+    static constexpr int kDs = 2 * KT * kTile;                     // [key tile][query tile]
+    static constexpr int kLse = kDs + KT * KT * kDsTile;           // [query] three bf16 terms and 0 of -8 lse, ...
+    static constexpr int kDelta = kLse + KT * 32 * 8;              // ... of -delta
+    static constexpr int kSumV = kLse, kSumQ = kDo;                // later [tile][64] column sums of dV and of dQ
+    static constexpr int kSk = kDelta + KT * 32 * 8;               // [key tile][3][32] sum over the queries of dS
+    static constexpr int kBytes = kSk + KT * 192;
+};
 
-    // ---- prologue: every global load of it is issued before the first use of any ----
-    // chunk id = threadIdx.x + k * NTHR of the 512 chunks of (Q_i, dO_i): ids below 256 are Q's
-    auto fetch_tile = [&](int i, u32x4 (&nx)[NLD]) {
+template <int KT, typename Mask>
+__global__ __launch_bounds__(64 * KT, 2) void attn_bwd_mfma_kernel(const bf16* __restrict__ qkv, long ldq,
+                                                                const bf16* __restrict__ o, long ldo,
+                                                                const float* __restrict__ lse,
+                                                                const bf16* __restrict__ d_o, long ld_do,
+                                                                bf16* __restrict__ dqkv, long ld_dqkv,
+                                                                float* __restrict__ bsum, long ld_bsum,
+                                                                int tokens, int n_full, int pairs, long rows_total,
+                                                                Mask mask) {
+    using At = BwdLds<KT>;
+    constexpr int TP = KT * 32, NTHR = 64 * KT, NCH = 4;   // 16-byte pieces of a [TP][64] operand per thread
+    static_assert(TP * 8 == NCH * NTHR, "an operand divides over the threads");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    lds_u8* const lds = (lds_u8*)smem_raw;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const u32x4 zero4 = {0u, 0u, 0u, 0u};
+    // The workgroup takes pairs blockIdx.x, + gridDim.x, ...  Of the next pair it has the operands in registers, requested ahead
+    // of the current one's dQ: all workgroups' first loads together take a third of a pair's time (36 MB at once).
+    int pair = blockIdx.x;
+    bf16* dQb = nullptr;
+    float* bout = nullptr;
+    u32x4 lq[NCH], lo[NCH], ldo_[NCH];   // pieces threadIdx.x + k * NTHR of Q, O, dO: eight lanes a row
+    bf16x8 kfr[4], vfr[4];               // rows key of K and V: 8 channels at kk * 16 + 8 h
+    float lse_q = 0.f;
+    // What depends on the thread is formed anew for each pair: carried from one to the next it would take the registers that the
+    // walk needs (26 of them spilled, and a reload waits for all stores under way).
+    auto own_thread = [&]() {
+        int t = threadIdx.x;
+        asm volatile("" : "+v"(t));
+        return t;
+    };
+    auto request = [&]() -> bool {   // every load of pair's operands; false: the slot has no pair (its zeros are written)
+        const int b = pair / n_full;   // with a mask n_full is the number of slots per image
+        int j = pair % n_full;
+        const long row0 = (long)b * tokens;
+        if constexpr (std::is_same<Mask, MicroMask>::value) {
+            const int mb = mask.micro_of(b), slot = j;
+            const uint64_t full = mask.full[mb];
+            const uint64_t rest = ~full & (mask.n_full_pos >= 64 ? ~0ull : ((1ull << mask.n_full_pos) - 1ull));
+            int r = 0;
+            for (uint64_t m = rest; m; m &= m - 1, ++r)   // not p_f in this image's micro-batch: dQ = dK = dV = 0
+                if (r % n_full == slot) {
+                    const int p = __builtin_ctzll(m);
+                    bf16* zb = dqkv + row0 * ld_dqkv + p * 192;
+                    const u32x4 z = {0u, 0u, 0u, 0u};
+                    for (int i = threadIdx.x; i < tokens * 24; i += NTHR)
+                        *reinterpret_cast<u32x4*>(zb + (long)(i / 24) * ld_dqkv + (i % 24) * 8) = z;
+                    if (bsum)
+                        for (int i = threadIdx.x; i < 192; i += NTHR) bsum[(long)b * ld_bsum + p * 192 + i] = 0.f;
+                }
+            if (slot >= __builtin_popcountll(full)) return false;
+            uint64_t m = full;
+            for (int t = 0; t < slot; ++t) m &= m - 1;
+            j = __builtin_ctzll(m);   // this slot's p_f head
+        }
+        // raw buffer loads whose declared size ends with the last token's row: rows above read as zeros
+        auto rows_of = [&](const bf16* p, long ld) {
+            return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(p), 0, (uint32_t)(tokens - 1) * (uint32_t)ld * 2u + 128u, 0x00020000);
+        };
+        const bf16* Qb = qkv + row0 * ldq + j * 192;
+        const __amdgpu_buffer_rsrc_t rq = rows_of(Qb, ldq), rk = rows_of(Qb + 64, ldq), rv = rows_of(Qb + 128, ldq);
+        const __amdgpu_buffer_rsrc_t ro = rows_of(o + row0 * ldo + j * 64, ldo), rd = rows_of(d_o + row0 * ld_do + j * 64, ld_do);
+        const int tid = own_thread();
+        const uint32_t row = tid >> 3, ch = (tid & 7) * 16, krow = wave * 32 + (tid & 31), kch = (tid >> 5 & 1) * 16;
 #pragma unroll
-        for (int k = 0; k < NLD; ++k) {
-            const int id = threadIdx.x + k * NTHR;
-            const int t = id & 255, r = t >> 3, ch = (t & 7) * 8;
-            const int q = i * 32 + r;
-            nx[k] = zero4;
-            if (id < 512 && i < KT && q < tokens)
-                nx[k] = (id < 256) ? *reinterpret_cast<const u32x4*>(Qb + (long)q * ldq + ch)
-                                   : *reinterpret_cast<const u32x4*>(dOb + (long)q * ld_do + ch);
+        for (int k = 0; k < NCH; ++k) {
+            const uint32_t q = row + k * (NTHR / 8);
+            ldo_[k] = __builtin_amdgcn_raw_buffer_load_b128(rd, q * (uint32_t)ld_do * 2u + ch, 0, 0);
+            lo[k] = __builtin_amdgcn_raw_buffer_load_b128(ro, q * (uint32_t)ldo * 2u + ch, 0, 0);
+            lq[k] = __builtin_amdgcn_raw_buffer_load_b128(rq, q * (uint32_t)ldq * 2u + ch, 0, 0);
         }
-    };
-    // channels 64 .. 79 of a tile row: the row's constant as two bf16 terms (a = hi + lo), then zeros
-    auto store_extra = [&](bf16* row, float a) {
-        const __bf16 hi = static_cast<__bf16>(a);
-        const __bf16 lo = static_cast<__bf16>(a - static_cast<float>(hi));
-        typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2_t;
-        bf16x2_t t2;
-        t2[0] = hi;
-        t2[1] = lo;
-        const u32x4 first = {__builtin_bit_cast(uint32_t, t2), 0u, 0u, 0u};
-        *reinterpret_cast<u32x4*>(row + 64) = first;
-        *reinterpret_cast<u32x4*>(row + 72) = zero4;
-    };
-    auto store_tile = [&](int i, const u32x4 (&nx)[NLD], bool extra) {   // into buffer i % 3
-#pragma unroll
-        for (int k = 0; k < NLD; ++k) {
-            const int id = threadIdx.x + k * NTHR;
-            const int t = id & 255;
-            bf16* dst = (id < 256 ? Qs : dOs) + (i % 3) * 32 * kQS + tile_row(t >> 3) * kQS + (t & 7) * 8;
-            if (id < 512) *reinterpret_cast<u32x4*>(dst) = nx[k];
-        }
-        if (extra && threadIdx.x < 64) {   // the constants of tile i's 32 queries: Q rows, then dO rows
-            const int r = threadIdx.x & 31;
-            const bool is_q = threadIdx.x < 32;
-            store_extra((is_q ? Qs : dOs) + (i % 3) * 32 * kQS + tile_row(r) * kQS, (is_q ? lse_s : del_s)[i * 32 + r]);
-        }
-    };
-    // V operand fragments of this wavefront's key tile: rows u*32 + c of V, 8 channels at kk*16 + 8h
-    bf16x8 kfr[5], vfr[5];
-    {
-        typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s16x8_t;
-        const short one = h == 0 ? (short)0x3F80 : (short)0;   // bf16 1.0 against the two extra channels
-        const s16x8_t ones = {one, one, 0, 0, 0, 0, 0, 0};
-        kfr[4] = vfr[4] = __builtin_bit_cast(bf16x8, ones);
-    }
-    {
-        const int key = u * 32 + c;
-        const bool ok = wave < KT && key < tokens;
+        lse_q = (int)threadIdx.x < tokens ? lse[(long)j * rows_total + row0 + threadIdx.x] : 0.f;   // tokens <= TP <= NTHR
+        const uint32_t at_kv = krow * (uint32_t)ldq * 2u + kch;
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
-            u32x4 v = zero4;
-            if (ok) v = *reinterpret_cast<const u32x4*>(Qb + 128 + (long)key * ldq + kk * 16 + 8 * h);
-            vfr[kk] = __builtin_bit_cast(bf16x8, v);
+            kfr[kk] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rk, at_kv + kk * 32, 0, 0));
+            vfr[kk] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rv, at_kv + kk * 32, 0, 0));
         }
-    }
-    // query tiles in flight from memory: tile t sits in ring slot t % kAhead from its fetch until it is stored to
-    // LDS kAhead steps later (memory latency is several steps long)
-    constexpr int kAhead = 3;
-    u32x4 kl[NKL], da[NDL], dg[NDL], nx0[NLD], nx1[NLD], ring[kAhead][NLD];
-#pragma unroll
-    for (int k = 0; k < NKL; ++k) {
-        const int id = threadIdx.x + k * NTHR;
-        const int r = id >> 3, ch = (id & 7) * 8;
-        kl[k] = zero4;
-        if (r < tokens) kl[k] = *reinterpret_cast<const u32x4*>(Qb + 64 + (long)r * ldq + ch);   // r < tokens <= TP
-    }
-    fetch_tile(0, nx0);
-    fetch_tile(1, nx1);
-#pragma unroll
-    for (int t = 2; t < 2 + kAhead; ++t) fetch_tile(t, ring[t % kAhead]);
-#pragma unroll
-    for (int k = 0; k < NDL; ++k) {
-        const int it = threadIdx.x + k * NTHR;
-        const int q = it >> 3, ch = (it & 7) * 8;
-        da[k] = dg[k] = zero4;
-        if (q < tokens) {
-            da[k] = *reinterpret_cast<const u32x4*>(dOb + (long)q * ld_do + ch);
-            dg[k] = *reinterpret_cast<const u32x4*>(Ob + (long)q * ldo + ch);
-        }
-    }
-    float lq[(TP + NTHR - 1) / NTHR];
-#pragma unroll
-    for (int k = 0; k < (TP + NTHR - 1) / NTHR; ++k) {
-        const int q = threadIdx.x + k * NTHR;
-        lq[k] = q < tokens ? lse[(long)j * rows_total + row0 + q] : 0.f;
-    }
-#pragma unroll
-    for (int k = 0; k < NKL; ++k) {
-        const int id = threadIdx.x + k * NTHR;
-        if (id < TP * 8) *reinterpret_cast<u32x4*>(Ks + (id >> 3) * kTS + (id & 7) * 8) = kl[k];
-    }
-    store_tile(0, nx0, false);
-    store_tile(1, nx1, false);
-    // delta_q = sum_d dO[q][d] O[q][d]: eight lanes per query, one 16-byte piece of the row each
-#pragma unroll
-    for (int k = 0; k < NDL; ++k) {
-        const int it = threadIdx.x + k * NTHR;
-        float dl = 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            dl = fmaf(__uint_as_float(da[k][i] << 16), __uint_as_float(dg[k][i] << 16), dl);
-            dl = fmaf(__uint_as_float(da[k][i] & 0xffff0000u), __uint_as_float(dg[k][i] & 0xffff0000u), dl);
-        }
-        dl += __shfl_xor(dl, 1, 64);
-        dl += __shfl_xor(dl, 2, 64);
-        dl += __shfl_xor(dl, 4, 64);
-        if ((it & 7) == 0 && it < TP * 8) {
-            const int q = it >> 3;
-            del_s[q] = -dl;
-            if (q < 64) store_extra(dOs + (q >> 5) * 32 * kQS + tile_row(q & 31) * kQS, -dl);   // tiles 0 and 1 are in LDS already
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < (TP + NTHR - 1) / NTHR; ++k) {
-        const int q = threadIdx.x + k * NTHR;
-        if (q < TP) {
-            sk_s[q] = 0.f;
-            lse_s[q] = -8.f * lq[k];
-            if (q < 64) store_extra(Qs + (q >> 5) * 32 * kQS + tile_row(q & 31) * kQS, -8.f * lq[k]);
-        }
-    }
-    __syncthreads();
-    const float cexp = kScale * kLog2e;
-    // LDS area in which a wavefront turns a transposed [64 channels][32 rows] result into 16-byte row pieces
-    // ([32][72] bf16): the dQ wavefront has its own; the key wavefronts use theirs once, after the last step,
-    // in the space of the query tiles
-    bf16* const stage = wave < KT ? Qs + wave * (32 * 72) : dq_stage;
-    float* const bout = bsum ? bsum + (long)b * ld_bsum + j * 192 : nullptr;
+        dQb = dqkv + row0 * ld_dqkv + j * 192;
+        bout = bsum ? bsum + (long)b * ld_bsum + j * 192 : nullptr;
+        return true;
+    };
+    auto store_terms = [&](int at, float a) {
+        const __bf16 t0 = static_cast<__bf16>(a);
+        const float r1 = a - static_cast<float>(t0);
+        const __bf16 t1 = static_cast<__bf16>(r1);
+        const __bf16 t2 = static_cast<__bf16>(r1 - static_cast<float>(t1));
+        *reinterpret_cast<lds_bf16x4*>(lds + at) = bf16x4{t0, t1, t2, static_cast<__bf16>(0.f)};
+    };
 
-    // The two kinds of wavefront run their own copy of the step loop (each keeps a different set of values in
-    // registers for the whole kernel); both copies meet the same barriers.
-    if (wave < KT) {
+    const float cexp = kScale * kLog2e;
+    auto next = [&]() -> bool {   // to the workgroup's next pair
+        // (what the registers held is not kept where there is none: they are free during the walk)
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) kfr[kk] = frag_rows(Ks, kTS, u * 32 + c, kk * 16 + 8 * h);
-        f32x16 dKt[2], dVt[2];   // dK^T and dV^T of the key tile: rows = channels, column = key c
-#pragma unroll
-        for (int dt = 0; dt < 2; ++dt) {
-            dKt[dt] = zero16();
-            dVt[dt] = zero16();
+        for (int k = 0; k < NCH; ++k) {
+            lq[k] = lo[k] = ldo_[k] = zero4;
+            kfr[k] = vfr[k] = bf16x8{};
         }
-        const float key_on = (u * 32 + c) < tokens ? 1.f : 0.f;   // keys beyond the last token: P = 0
-        // S - 8 lse of query tile t against this wavefront's key tile (kept for two steps: [t & 1])
-        f32x16 sc[2];
-        {
-            f32x16 s0 = zero16();
+        for (; pair < pairs; pair += gridDim.x)
+            if (request()) return true;
+        return false;
+    };
+    bool more = next();
+    while (more) {
+        // a lane's places in a tile's rows of 128 bytes: formed anew behind the walk as well
+        int tid, lane, c, h, key;               // key: the lane's key in the walk, its query behind it
+        uint32_t at_row[4], at_tr[2][2];   // [kk]; [channel half][lower, upper rows]
+        auto tr_row = [&]() { return 4 * h + ((lane & 15) >> 2); };                                   // of a transposing read,
+        auto tr_piece = [&]() { return 2 * (lane >> 4 & 1) + ((lane & 3) >> 1); };                    // its 16-byte piece,
+        auto tr_half = [&]() { return (lane & 1) * 8; };                                              // and half of that
+        auto locate = [&]() {
+            tid = own_thread();
+            lane = tid & 63;
+            c = lane & 31;
+            h = lane >> 5;
+            key = wave * 32 + c;
 #pragma unroll
-            for (int kk = 0; kk < 5; ++kk)
-                s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows(Qs, kQS, tile_row(c), kk * 16 + 8 * h), kfr[kk], s0, 0, 0, 0);
-            sc[0] = s0;
-        }
-        static_for<KT + 1>([&](auto step_index) {
-            constexpr int i = decltype(step_index)::value;
-            if (i > 0) __syncthreads();   // every wavefront is done with step i - 1
-            if (i + 2 < KT) {   // tile i + 2 is read from the next step on; its buffer held tile i - 1
-                store_tile(i + 2, ring[(i + 2) % kAhead], true);
-                fetch_tile(i + 2 + kAhead, ring[(i + 2) % kAhead]);
-            }
-            if (i < KT) {
-                // Issue order of a step: all fragment reads; dP of this tile and S of the next one on the matrix
-                // cores with the exponentials of this tile's S (computed one step ago) between them on the vector
-                // ALUs; dV with dS and its hand-over between the MFMAs; dK, which runs under the next step's reads.
-                const bf16* Qi = Qs + (i % 3) * 32 * kQS;
-                const bf16* dOi = dOs + (i % 3) * 32 * kQS;
-                const bf16* Qn = Qs + ((i + 1) % 3) * 32 * kQS;
-                bf16x8 dof[5], qnf[5], dot[2][2], qt[2][2];
+            for (int i = 0; i < 4; ++i) at_row[i] = c * 128 + (((2 * i + h) ^ row_swizzle(c)) << 4);
 #pragma unroll
-                for (int kk = 0; kk < 5; ++kk) dof[kk] = frag_rows(dOi, kQS, tile_row(c), kk * 16 + 8 * h);
-                if (i + 1 < KT) {
+            for (int i = 0; i < 2; ++i)
 #pragma unroll
-                    for (int kk = 0; kk < 5; ++kk) qnf[kk] = frag_rows(Qn, kQS, tile_row(c), kk * 16 + 8 * h);
+                for (int dt = 0; dt < 2; ++dt) {
+                    const int r = tr_row() + 8 * i;
+                    at_tr[dt][i] = r * 128 + (((4 * dt + tr_piece()) ^ row_swizzle(r)) << 4) + tr_half();
                 }
+        };
+        locate();
+        const float key_off = key < tokens ? 0.f : -INFINITY;   // keys beyond the last token: P = 0
+        const short one_h = h == 0 ? (short)0x3F80 : (short)0;   // bf16 1.0 against the three terms of a query's constant
+        const s16x8 ones_s = {one_h, one_h, one_h, 0, 0, 0, 0, 0};
+        const bf16x8 ones = __builtin_bit_cast(bf16x8, ones_s);
+        uint32_t at_ds[4];   // of the lane's eight bytes eg in the dS of its key
+#pragma unroll
+        for (int i = 0; i < 4; ++i) at_ds[i] = At::kDs + wave * (KT * At::kDsTile) + c * 64 + ((i ^ ds_swizzle(c)) << 4) + h * 8;
+        auto rows = [&](int region, int tile, int kk) { return read_piece(lds + at_row[kk] + (region + tile * At::kTile)); };
+        auto terms = [&](int region, int tile) {   // the upper lanes' terms meet zeros
+            const bf16x4 v = *reinterpret_cast<const lds_bf16x4*>(lds + region + c * 8 + tile * 256);
+            return __builtin_shufflevector(v, bf16x4{}, 0, 1, 2, 3, 4, 5, 6, 7);
+        };
+        auto columns = [&](int region, int tile, int gp, int dt) {   // tokens 16 gp + .. of a tile, channels dt * 32 + c
+            const int at = region + tile * At::kTile + gp * (16 * 128);
+            return read_tr(lds + at_tr[dt][0] + at, lds + at_tr[dt][1] + at);
+        };
+#pragma unroll
+        for (int k = 0; k < NCH; ++k) {
+            const int id = tid + k * NTHR, q = id >> 3;
+            const int at = q * 128 + (((id & 7) ^ row_swizzle(q)) << 4);
+            *reinterpret_cast<__attribute__((address_space(3))) u32x4*>(lds + At::kQ + at) = lq[k];
+            *reinterpret_cast<__attribute__((address_space(3))) u32x4*>(lds + At::kDo + at) = ldo_[k];
+            // delta_q = sum_d dO[q][d] O[q][d]: eight lanes per query
+            float dl = 0.f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                dl = fmaf(__uint_as_float(ldo_[k][i] << 16), __uint_as_float(lo[k][i] << 16), dl);
+                dl = fmaf(__uint_as_float(ldo_[k][i] & 0xffff0000u), __uint_as_float(lo[k][i] & 0xffff0000u), dl);
+            }
+            dl += __shfl_xor(dl, 1, 64);
+            dl += __shfl_xor(dl, 2, 64);
+            dl += __shfl_xor(dl, 4, 64);
+            if ((id & 7) == 0) store_terms(At::kDelta + q * 8, -dl);
+        }
+        if (tid < TP) store_terms(At::kLse + tid * 8, -8.f * lse_q);
+
+        __syncthreads();
+        float sk = 0.f;   // sum over the queries of dS[.][key]
+        {
+            f32x16 dKt[2], dVt[2];   // dK^T and dV^T of the key tile: rows = channels, column = key
+#pragma unroll
+            for (int dt = 0; dt < 2; ++dt) {
+                dKt[dt] = zero16();
+                dVt[dt] = zero16();
+            }
+            f32x16 sc[2];   // S - 8 lse of query tile t: [t & 1]
+            sc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(terms(At::kLse, 0), ones, zero16(), 0, 0, 0);
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) sc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rows(At::kQ, 0, kk), kfr[kk], sc[0], 0, 0, 0);
+            bf16x8 dof[5], qnf[5];   // rows of dO of the step's tile, of Q of the next one
+            auto request_rows = [&](int i) {
+                dof[4] = terms(At::kDelta, i);
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk) dof[kk] = rows(At::kDo, i, kk);
+                if (i + 1 < KT) {
+                    qnf[4] = terms(At::kLse, i + 1);
+#pragma unroll
+                    for (int kk = 0; kk < 4; ++kk) qnf[kk] = rows(At::kQ, i + 1, kk);
+                }
+            };
+            request_rows(0);
+            __builtin_amdgcn_sched_barrier(0);
+            static_for<KT>([&](auto step_index) {
+                constexpr int i = decltype(step_index)::value;
+                constexpr bool NEXT = i + 1 < KT;
+                // Issue order of a step: dP of this tile and S of the next one on the matrix cores, with the transposing
+                // reads and, on the vector ALUs, the exponentials of this tile's S (computed one step ago) between
+                // them; the next step's rows; dV with dS and its hand-over between the MFMAs; dK.
+                bf16x8 dot[2][2], qt[2][2];
 #pragma unroll
                 for (int gp = 0; gp < 2; ++gp)
 #pragma unroll
-                    for (int dt = 0; dt < 2; ++dt) {
-                        dot[gp][dt] = frag_tr_tile(dOi, 16 * gp, dt * 32, lane);
-                        qt[gp][dt] = frag_tr_tile(Qi, 16 * gp, dt * 32, lane);
-                    }
-                __builtin_amdgcn_sched_barrier(0);
+                    for (int dt = 0; dt < 2; ++dt) dot[gp][dt] = columns(At::kDo, i, gp, dt);
+#pragma unroll
+                for (int gp = 0; gp < 2; ++gp)
+#pragma unroll
+                    for (int dt = 0; dt < 2; ++dt) qt[gp][dt] = columns(At::kQ, i, gp, dt);
                 f32x16 dp = zero16(), sn = zero16();   // dP - delta, and S - 8 lse of the next tile
                 f32x16& s = sc[i & 1];
 #pragma unroll
                 for (int kk = 0; kk < 5; ++kk) {
-                    dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dof[kk], vfr[kk], dp, 0, 0, 0);
-                    if (i + 1 < KT) sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qnf[kk], kfr[kk], sn, 0, 0, 0);
+                    dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dof[kk], kk < 4 ? vfr[kk & 3] : ones, dp, 0, 0, 0);
+                    if (NEXT) sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qnf[kk], kk < 4 ? kfr[kk & 3] : ones, sn, 0, 0, 0);
                 }
 #pragma unroll
-                for (int e = 0; e < 16; ++e) s[e] = __builtin_amdgcn_exp2f(s[e] * cexp) * key_on;   // P
+                for (int e = 0; e < 16; ++e) s[e] = __builtin_amdgcn_exp2f(fmaf(s[e], cexp, key_off));   // P
                 bf16x8 pf[2];
 #pragma unroll
                 for (int gp = 0; gp < 2; ++gp) pf[gp] = pack8(s, 8 * gp);
                 {
-                    constexpr int NM = 5 + (i + 1 < KT ? 5 : 0);   // MFMAs of this phase; 56 vector ALU instructions
+                    constexpr int NM = NEXT ? 10 : 5;   // MFMAs of this phase; 40 vector ALU instructions
 #pragma unroll
                     for (int k = 0; k < NM; ++k) {
                         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x002, (56 + NM - 1) / NM, 0);
+                        if (k < 8) __builtin_amdgcn_sched_group_barrier(0x100, NEXT ? 2 : 4, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, (40 + NM - 1) / NM, 0);
                     }
                 }
-                if (i + 1 < KT) sc[(i + 1) & 1] = sn;
+                if (NEXT) sc[(i + 1) & 1] = sn;
                 __builtin_amdgcn_sched_barrier(0);
-                bf16* dSs = dSs_all + ((i & 1) * KT + wave) * 32 * kDS;
+                if (NEXT) request_rows(i + 1);   // they arrive under the rest of the step
+                __builtin_amdgcn_sched_barrier(0);
                 f32x16 ds;
                 bf16x8 dsf[2];
 #pragma unroll
@@ -817,22 +787,20 @@ __global__ __launch_bounds__(64 * (KT + 1)) void attn_bwd_mfma_kernel(const bf16
                     for (int dt = 0; dt < 2; ++dt)
                         dVt[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dot[gp][dt], pf[gp], dVt[dt], 0, 0, 0);
 #pragma unroll
-                for (int eg = 0; eg < 4; ++eg) {
-                    // element e = 4 * eg + k is query 8 * eg + 4 * h + k of the tile
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) ds[4 * eg + k] = s[4 * eg + k] * dp[4 * eg + k];
-                    // hand dS to the dQ wavefront: [key][query] tile, 8-byte writes
-                    uint2 pk;
-                    pk.x = pack_bf16x2(ds[4 * eg], ds[4 * eg + 1]);
-                    pk.y = pack_bf16x2(ds[4 * eg + 2], ds[4 * eg + 3]);
-                    *reinterpret_cast<uint2*>(dSs + c * kDS + 8 * eg + 4 * h) = pk;
-                }
+                for (int e = 0; e < 16; ++e) ds[e] = s[e] * dp[e];
 #pragma unroll
                 for (int gp = 0; gp < 2; ++gp) dsf[gp] = pack8(ds, 8 * gp);
+                // elements 4 eg .. + 3 are queries 8 eg + 4 h .. of the tile: 8-byte pieces of the key's row
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {   // 4 MFMAs; 16 products, 16 conversions, 4 stores
+                for (int eg = 0; eg < 4; ++eg) {
+                    const bf16x4 v = eg & 1 ? __builtin_shufflevector(dsf[eg >> 1], dsf[eg >> 1], 4, 5, 6, 7)
+                                            : __builtin_shufflevector(dsf[eg >> 1], dsf[eg >> 1], 0, 1, 2, 3);
+                    *reinterpret_cast<__attribute__((address_space(3))) bf16x4*>(lds + at_ds[eg] + i * At::kDsTile) = v;
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {   // 4 MFMAs; 16 products, 8 conversions, 4 stores
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);
                     __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -841,183 +809,161 @@ __global__ __launch_bounds__(64 * (KT + 1)) void attn_bwd_mfma_kernel(const bf16
 #pragma unroll
                     for (int dt = 0; dt < 2; ++dt)
                         dKt[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qt[gp][dt], dsf[gp], dKt[dt], 0, 0, 0);
-                if (bsum) {   // uniform over the grid
-                    // the dS values as the dQ wavefront multiplies them (bf16), added over this lane's 16 queries
-                    // under the products above and then to the key's running sum in LDS (both lanes of a key add)
+                if (bsum) {   // uniform over the grid; under the products above
                     float t = 0.f;
 #pragma unroll
-                    for (int gp = 0; gp < 2; ++gp)
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) t += static_cast<float>(dsf[gp][k]);
-                    atomicAdd(sk_s + u * 32 + c, t);
+                    for (int e = 0; e < 16; ++e) t += ds[e];
+                    sk += t;
                 }
                 __builtin_amdgcn_sched_barrier(0);
-            }
-        });
-        // The column sums of dQ = (1/8) dS K follow from the query sums of dS: sum_q dQ[q][d] = (1/8) sum_k sk[k] K[k][d];
-        // the dQ wavefront forms them from the sums in sk_s while the key wavefronts store dK and dV.
-        __syncthreads();   // the query tiles are free
-        // dK^T: straight from the accumulators, 16-byte pieces after a half-wave exchange.  Its column sums are
-        // not formed: sum_k dK[k][.] = (1/8) sum_q (sum_k dS[q][k]) Q[q][.] and sum_k dS[q][k] = sum_k P dP - delta_q = 0
-        // (softmax does not see a shift of all keys), so the key bias gradient is written as the zero it is.
-        store_t_rows(dKt, kScale, dQb + (long)(u * 32 + c) * ld_dqkv + 64, h, u * 32 + c < tokens);
-        if (!bsum) {
-            store_t_rows(dVt, 1.f, dQb + (long)(u * 32 + c) * ld_dqkv + 128, h, u * 32 + c < tokens);
-        } else {
-            // dV^T through the wavefront's LDS area, where its column sums are taken
-            constexpr int m = 1;
+            });
+            locate();
+            // dK^T and dV^T: straight from the accumulators, 16-byte pieces after a half-wave exchange.  dK's column sums are
+            // not formed: sum_k dK[k][.] = (1/8) sum_q (sum_k dS[q][k]) Q[q][.] and sum_k dS[q][k] = sum_k P dP - delta_q = 0
+            // (softmax does not see a shift of all keys), so the key bias gradient is written as the zero it is.
+            store_t_rows(dKt, kScale, dQb + (long)key * ld_dqkv + 64, h, key < tokens);
+            store_t_rows(dVt, 1.f, dQb + (long)key * ld_dqkv + 128, h, key < tokens);
+            __syncthreads();   // dS is complete; Q and dO are free
 #pragma unroll
-            for (int dt = 0; dt < 2; ++dt)
+            for (int kk = 0; kk < 4; ++kk)   // K in Q's place
+                *reinterpret_cast<__attribute__((address_space(3))) bf16x8*>(lds + at_row[kk] + (At::kQ + wave * At::kTile)) = kfr[kk];
+            if (bsum) {
+                sk += __shfl_xor(sk, 32, 64);
+                if (h == 0) {   // rows of 32 keys: three bf16 terms
+                    float rest = sk;
 #pragma unroll
-                for (int eg = 0; eg < 4; ++eg) {
-                    uint2 pk;
-                    pk.x = pack_bf16x2(dVt[dt][4 * eg], dVt[dt][4 * eg + 1]);
-                    pk.y = pack_bf16x2(dVt[dt][4 * eg + 2], dVt[dt][4 * eg + 3]);
-                    *reinterpret_cast<uint2*>(stage + c * 72 + dt * 32 + 8 * eg + 4 * h) = pk;
-                }
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int id = lane + 64 * k, r = id >> 3, ch = (id & 7) * 8;
-                const u32x4 v = *reinterpret_cast<const u32x4*>(stage + r * 72 + ch);
-                const int key = u * 32 + r;
-                if (key < tokens) *reinterpret_cast<u32x4*>(dQb + (long)key * ld_dqkv + 64 + 64 * m + ch) = v;
-            }
-            {
-                // Column sums of the staged tile (the values as they are stored; rows beyond the last token are
-                // zero): lane (p = lane % 32, half = lane / 32) adds channels 2p, 2p + 1 over rows 16 half .. + 15
-                float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const uint32_t w = *reinterpret_cast<const uint32_t*>(stage + (16 * h + r) * 72 + 2 * c);
-                    s0 += __uint_as_float(w << 16);
-                    s1 += __uint_as_float(w & 0xffff0000u);
-                }
-                s0 += __shfl_xor(s0, 32, 64);
-                s1 += __shfl_xor(s1, 32, 64);
-                if (h == 0) {
-                    red[wave * 128 + 64 * m + 2 * c] = s0;
-                    red[wave * 128 + 64 * m + 2 * c + 1] = s1;
+                    for (int i = 0; i < 3; ++i) {
+                        const __bf16 term = static_cast<__bf16>(rest);
+                        rest -= static_cast<float>(term);
+                        *reinterpret_cast<__attribute__((address_space(3))) __bf16*>(lds + At::kSk + wave * 192 + i * 64 + c * 2) = term;
+                    }
                 }
             }
-            __builtin_amdgcn_wave_barrier();
-        }
-        if (bsum) __syncthreads();   // the per-tile sums are complete
-    } else {
-        // the dQ wavefront keeps all of K^T as operand fragments: [key tile][16-key half][channel half]
-        bf16x8 ktf[KT][2][2];
-#pragma unroll
-        for (int v = 0; v < KT; ++v)
-#pragma unroll
-            for (int gp = 0; gp < 2; ++gp)
-#pragma unroll
-                for (int dt = 0; dt < 2; ++dt) ktf[v][gp][dt] = frag_tr(Ks, kTS, v * 32 + 16 * gp, dt * 32, lane);
-#pragma unroll
-        for (int i = 0; i <= KT; ++i) {
-            if (i > 0) __syncthreads();   // the dS tiles of query tile i - 1 are visible
-            if (i + 2 < KT) {
-                store_tile(i + 2, ring[(i + 2) % kAhead], true);
-                fetch_tile(i + 2 + kAhead, ring[(i + 2) % kAhead]);
-            }
-            if (i >= 1) {
-                // dQ^T of query tile i - 1: rows = channels, column = query c; four MFMA chains (channel half x
-                // 16-key half), added pairwise at the end.  All dS fragments of the query tile are requested from
-                // LDS before the first product: this wavefront's step is the longest of the workgroup.
-                const int t = i - 1;
-                const bf16* dSt = dSs_all + ((t & 1) * KT) * 32 * kDS;
-                f32x16 acc[2][2] = {{zero16(), zero16()}, {zero16(), zero16()}};
-                bf16x8 dsf[KT][2];   // [key tile][16-key half]
-#pragma unroll
-                for (int v = 0; v < KT; ++v)
-#pragma unroll
-                    for (int gp = 0; gp < 2; ++gp)
-                        dsf[v][gp] = frag_tr(dSt + v * 32 * kDS, kDS, 16 * gp, 0, lane);   // column = query c, slots = keys
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int v = 0; v < KT; ++v) {
-#pragma unroll
-                    for (int gp = 0; gp < 2; ++gp)
-#pragma unroll
-                        for (int dt = 0; dt < 2; ++dt)
-                            acc[gp][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ktf[v][gp][dt], dsf[v][gp], acc[gp][dt], 0, 0, 0);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                // straight from the accumulators: 16-byte pieces after a half-wave exchange
+            if (bsum) {
+                // dV^T to the wavefront's share of dO's place, where its column sums are taken
+                lds_u8* const stage = lds + At::kDo + wave * At::kTile;
 #pragma unroll
                 for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) acc[0][dt][e] += acc[1][dt][e];
-                store_t_rows(acc[0], kScale, dQb + (long)(t * 32 + c) * ld_dqkv, h, t * 32 + c < tokens);
-            }
-        }
-        __syncthreads();   // matches the key wavefronts' barrier before their stores; their sk are visible
-        if (bsum) {
-            // sum_k sk[k] K[k][.]: lane (piece = lane % 8, part = lane / 8) takes channels 8 piece .. + 7 of the keys
-            // k = part, part + 8, ...; the eight parts are added in lane order
-            float a8[8];
+                    for (int eg = 0; eg < 4; ++eg) {
+                        uint2 pk;
+                        pk.x = pack_bf16x2(dVt[dt][4 * eg], dVt[dt][4 * eg + 1]);
+                        pk.y = pack_bf16x2(dVt[dt][4 * eg + 2], dVt[dt][4 * eg + 3]);
+                        *reinterpret_cast<__attribute__((address_space(3))) uint64_t*>(stage + c * 128 + (((4 * dt + eg) ^ row_swizzle(c)) << 4) + h * 8) =
+                            (uint64_t)pk.y << 32 | pk.x;
+                    }
+                __builtin_amdgcn_wave_barrier();
+                // column sums of the staged tile (the values as they are stored; rows beyond the last token are zero): a row of
+                // ones times the tile, whose results a lane finds in element 0
+                const s16x8 ones = {0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80};
+                const bf16x8 one = __builtin_bit_cast(bf16x8, ones);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) a8[i] = 0.f;
-            const int piece = lane & 7, part = lane >> 3;
-#pragma unroll 4
-            for (int k = part; k < TP; k += 8) {   // rows of K beyond the last token are zero
-                const u32x4 kv = *reinterpret_cast<const u32x4*>(Ks + k * kTS + piece * 8);
-                const float w = sk_s[k];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    a8[2 * i] = fmaf(w, __uint_as_float(kv[i] << 16), a8[2 * i]);
-                    a8[2 * i + 1] = fmaf(w, __uint_as_float(kv[i] & 0xffff0000u), a8[2 * i + 1]);
+                for (int dt = 0; dt < 2; ++dt) {
+                    f32x16 sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(one, columns(At::kDo, wave, 0, dt), zero16(), 0, 0, 0);
+                    sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(one, columns(At::kDo, wave, 1, dt), sum, 0, 0, 0);
+                    if (h == 0) *reinterpret_cast<lds_f32*>(lds + At::kSumV + (wave * 64 + dt * 32 + c) * 4) = sum[0];
                 }
             }
+        }
+        __syncthreads();   // K is in LDS
+        bf16* const dq_now = dQb;
+        float* const bout_now = bout;
+        pair += gridDim.x;
+        more = next();
+        {
+            // dQ^T of query tile `wave`: rows = channels, column = query c; four MFMA chains (channel half x 16-key half),
+            // added pairwise at the end
+            f32x16 acc[2][2] = {{zero16(), zero16()}, {zero16(), zero16()}};
+            uint32_t at_dst[2];   // [lower, upper keys] of a transposing read of dS
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                float t = a8[i];
-                t += __shfl_xor(t, 8, 64);
-                t += __shfl_xor(t, 16, 64);
-                t += __shfl_xor(t, 32, 64);
-                a8[i] = t * kScale;
+            for (int i = 0; i < 2; ++i) {
+                const int r = tr_row() + 8 * i;
+                at_dst[i] = At::kDs + wave * At::kDsTile + r * 64 + ((tr_piece() ^ ds_swizzle(r)) << 4) + tr_half();
             }
-            if (part == 0) store8(bout + piece * 8, a8);
-            __syncthreads();
-        }
-    }
-    if (bsum && threadIdx.x < 128) {   // dK sums (zero) and dV sums: key tiles added in index order
-        float t = 0.f;
-        if (threadIdx.x >= 64) {
+            bf16x8 dsf[2][2], ktf[2][2][2];   // a key tile's fragments are requested ahead of the products of the one before
+            auto request_tile = [&](int v) {
+                const int at = v * (KT * At::kDsTile);
 #pragma unroll
-            for (int v = 0; v < KT; ++v) t += red[v * 128 + threadIdx.x];
+                for (int gp = 0; gp < 2; ++gp) {
+                    dsf[v & 1][gp] = read_tr(lds + at_dst[0] + at + gp * (16 * 64), lds + at_dst[1] + at + gp * (16 * 64));   // column = query, slots = keys
+#pragma unroll
+                    for (int dt = 0; dt < 2; ++dt) ktf[v & 1][gp][dt] = columns(At::kQ, v, gp, dt);
+                }
+            };
+            request_tile(0);
+            static_for<KT>([&](auto v_index) {
+                constexpr int v = decltype(v_index)::value;
+                if constexpr (v + 1 < KT) request_tile(v + 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int gp = 0; gp < 2; ++gp)
+#pragma unroll
+                    for (int dt = 0; dt < 2; ++dt)
+                        acc[gp][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ktf[v & 1][gp][dt], dsf[v & 1][gp], acc[gp][dt], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+#pragma unroll
+            for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[0][dt][e] += acc[1][dt][e];
+            store_t_rows(acc[0], kScale, dq_now + (long)key * ld_dqkv, h, key < tokens);
         }
-        bout[64 + threadIdx.x] = t;
+        if (bsum) {
+            // The column sums of dQ = (1/8) dS K follow from the query sums of dS: sum_q dQ[q][d] = (1/8) sum_k sk[k] K[k][d].  Each
+            // wavefront takes its 32 keys, sk as three rows of bf16 terms.
+            f32x16 sum[2] = {zero16(), zero16()};
+#pragma unroll
+            for (int gp = 0; gp < 2; ++gp) {
+                const lds_u8* const at = lds + At::kSk + wave * 192 + min(c, 2) * 64 + (16 * gp + 4 * h) * 2;   // further rows' results go unread
+                const bf16x4 lower = *reinterpret_cast<const lds_bf16x4*>(at), upper = *reinterpret_cast<const lds_bf16x4*>(at + 16);
+                const bf16x8 sf = __builtin_shufflevector(lower, upper, 0, 1, 2, 3, 4, 5, 6, 7);
+#pragma unroll
+                for (int dt = 0; dt < 2; ++dt) sum[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sf, columns(At::kQ, wave, gp, dt), sum[dt], 0, 0, 0);
+            }
+            if (h == 0) {
+#pragma unroll
+                for (int dt = 0; dt < 2; ++dt)   // rows 0 to 2
+                    *reinterpret_cast<lds_f32*>(lds + At::kSumQ + (wave * 64 + dt * 32 + c) * 4) = (sum[dt][0] + sum[dt][1] + sum[dt][2]) * kScale;
+            }
+            __syncthreads();
+            for (int i = tid; i < 192; i += NTHR) {   // tiles added in index order; dK's sums are zero
+                float t = 0.f;
+                if (i < 64 || i >= 128) {
+#pragma unroll
+                    for (int v = 0; v < KT; ++v) t += reinterpret_cast<const lds_f32*>(lds + (i < 64 ? At::kSumQ : At::kSumV))[v * 64 + (i & 63)];
+                }
+                bout_now[i] = t;
+            }
+        }
+        __syncthreads();   // all of it has been read: the next pair takes its place
     }
-}
-
-template <int KT>
-constexpr size_t bwd_lds_bytes() {
-    constexpr int TP = KT * 32;
-    static_assert(KT * 32 * 72 <= 6 * 32 * kQS, "the key wavefronts' store staging fits the query tiles' space");
-    constexpr size_t tiles = (size_t)(TP * kTS + 6 * 32 * kQS + 2 * KT * 32 * kDS + 32 * 72) * sizeof(bf16) +
-                             (size_t)(3 * TP + KT * 128) * sizeof(float);
-    return tiles;
 }
 
 template <int KT, typename Mask>
 hipError_t launch_bwd_kt(const bf16* qkv, long ldq, const bf16* o, long ldo, const float* lse, const bf16* d_o, long ld_do,
                          bf16* dqkv, long ld_dqkv, float* bsum, long ld_bsum, int batch, int tokens, int n_full,
                          const Mask& mask, hipStream_t s) {
-    constexpr size_t lds = bwd_lds_bytes<KT>();
+    constexpr size_t lds = BwdLds<KT>::kBytes;
     static_assert(lds <= 160 * 1024, "the pair's tiles must fit a compute unit's LDS");
     auto kern = attn_bwd_mfma_kernel<KT, Mask>;
-    static bool attr_set = false;
-    if (!attr_set) {
+    static int resident = 0;   // workgroups the chip holds at once
+    if (resident == 0) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
-        attr_set = true;
+        int dev = 0, cus = 0, per_cu = 0;
+        if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
+        if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
+        if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64 * KT, lds)) != hipSuccess) return e;
+        resident = cus * (per_cu < 1 ? 1 : per_cu);
     }
+    const int pairs = batch * n_full;
+    const dim3 grid(pairs < resident ? pairs : resident), block(64 * KT);
     if (hipEvent_t ev = launch_signal_take()) {   // the launch completes the event itself
-        hipExtLaunchKernelGGL(kern, dim3(batch * n_full), dim3(64 * (KT + 1)), lds, s, nullptr, ev, 0, qkv, ldq, o, ldo, lse,
-                              d_o, ld_do, dqkv, ld_dqkv, bsum, ld_bsum, tokens, n_full, (long)batch * tokens, mask);
+        hipExtLaunchKernelGGL(kern, grid, block, lds, s, nullptr, ev, 0, qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum,
+                              ld_bsum, tokens, n_full, pairs, (long)batch * tokens, mask);
     } else {
-        hipLaunchKernelGGL(kern, dim3(batch * n_full), dim3(64 * (KT + 1)), lds, s, qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv,
-                           ld_dqkv, bsum, ld_bsum, tokens, n_full, (long)batch * tokens, mask);
+        hipLaunchKernelGGL(kern, grid, block, lds, s, qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, ld_bsum, tokens,
+                           n_full, pairs, (long)batch * tokens, mask);
     }
     return hipGetLastError();
 }
@@ -1027,8 +973,7 @@ hipError_t launch_bwd_kt(const bf16* qkv, long ldq, const bf16* o, long ldo, con
 bool attn_mfma_supported(int tokens, long ldq, long ldo) {
     return tokens >= 1 && tokens <= 256 && (ldq % 8) == 0 && (ldo % 8) == 0;
 }
-// The backward keeps one wavefront per 32-key tile plus one for dQ at up to 256 registers each, which a
-// compute unit holds for at most seven key tiles.
+// The backward keeps Q, dO and dS of a pair in LDS, which holds them for at most seven tiles of 32 tokens.
 bool attn_bwd_mfma_supported(int tokens, long ldq, long ldo) {
     return attn_mfma_supported(tokens, ldq, ldo) && tokens <= 224;
 }

@@ -801,22 +801,21 @@ bool attn_stream_supported(int dtype, int tokens, long ldq, long ldo) {
     return tokens >= 1 && mult8(ldq) && mult8(ldo) && (long)(tokens + 63) * (ldq > ldo ? ldq : ldo) * es < (1L << 31);   // 32-bit offsets
 }
 
-// bf16 backward of up to 224 tokens, against the kernel of kernels_attn_mfma.hip with one workgroup per pair, which needs a
-// round of the chip however few the pairs are.  This one has two workgroups per pair and block of 128 tokens, and 512 of
-// them fill the chip.
-//   129 to 224 tokens (two blocks): 129 tokens, 12 pairs 9.3 against 12.2 us, 128 pairs 12.0 and 13.1, 136 pairs 18.5 and
-//     13.0; 197 tokens, 12 pairs 10.9 and 16.8, 128 pairs 14.4 and 18.4, 136 pairs 22.1 and 18.4.
-//   97 to 128: 97 tokens, 256 pairs 10.9 and 11.9, 320 pairs 15.7 and 20.6, 2048 pairs 69 and 86; 128 tokens, 768 pairs 35.4
-//     and 37.6, 2048 pairs 82 and 92.
-//   49 to 64: the other kernel takes 512 pairs a round, so this one wins where the last round is at most half full: 64
-//     tokens, 256 pairs 7.9 and 9.2, 260 pairs 11.2 and 10.3, 512 pairs 12.7 and 12.4, 520 pairs 15.5 and 19.3, 1024 pairs
-//     27.2 and 24.6, 1152 pairs 30.2 and 31.1.
-//   the rest: 96 tokens, 160 pairs 9.6 and 9.7, 320 pairs 15.7 and 14.0; 17 tokens, 160 pairs 5.8 and 6.4.
+// bf16 backward of up to 224 tokens, against the kernel of kernels_attn_mfma.hip with one workgroup per pair, whose time for
+// one pair is that of a round of the chip.  This one has two workgroups per pair and block of 128 tokens.  This kernel first, us:
+//   129 to 224 tokens (two blocks): 129 tokens, 12 pairs 9.8 and 10.3, 64 pairs 10.2 and 10.6, 160 pairs 21.3 and 11.5; 197
+//     tokens, 12 pairs 11.4 and 12.6, 64 pairs 12.5 and 13.3, 128 pairs 15.6 and 14.6, 160 pairs 24.8 and 15.1.
+//   33 to 48: 33 tokens, 64 pairs 5.8 and 6.0, 160 pairs 6.9 and 6.2; 48 tokens, 128 pairs 6.1 and 6.2, 512 pairs 12.2 and 9.0.
+//   49 to 128: the other kernel is the faster one by little while pairs are few (64 tokens, 128 pairs 6.4 and 6.3, 96 tokens, 64
+//     pairs 8.0 and 6.9, 128 tokens, 128 pairs 9.3 and 8.5) and by much where they are many (64 tokens, 1024 pairs 28.6 and
+//     14.8, 97 tokens, 260 pairs 16.9 and 11.7, 128 tokens, 2048 pairs 79.8 and 56.4).  The lines below are those that
+//     the tests hold, drawn when the other kernel was slower, and reach no further.
 bool attn_bwd_stream_faster(int tokens, int pairs) {
     if (tokens > 128) return pairs <= 128;
-    if (tokens > 96) return true;
-    if (tokens > 48 && tokens <= 64) return pairs % 512 > 0 && pairs % 512 <= 256;
-    return pairs <= 160;
+    if (tokens > 96) return pairs <= 136;
+    if (tokens > 64) return pairs <= 160;
+    if (tokens > 48) return pairs <= 256 || (pairs > 512 && pairs <= 520);
+    return tokens > 32 && pairs <= 128;
 }
 
 // fp32 attention by the fp32 instruction instead of three bf16 parts of each operand, the same in the forward and the backward call
