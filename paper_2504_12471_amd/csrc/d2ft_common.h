@@ -125,6 +125,8 @@ struct GemmGroup {
     long lda, ldb;
     int M, N;
     int tiles_m, tile0;   // 256-row tiles of this problem; index of its first tile in the launch's tile list
+    int two_of_three;     // grouped launch: A has 64 columns of Q, K and V a head, of which K's stay out; M counts the others
+    __host__ __device__ __forceinline__ int column(int m) const { return two_of_three ? (m >> 7) * 192 + (m & 64) * 2 + (m & 63) : m; }
 };
 constexpr int kMaxGemmGroups = 4;
 

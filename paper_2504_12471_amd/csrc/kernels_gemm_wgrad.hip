@@ -106,7 +106,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void gemm_wgrad_kernel(GemmArgs g) 
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int col = ((lane & 31) ^ swizzle(wave * 8 + i * 2 + h)) * 8;
-            off_a[i] = m0 + col < G.M ? (uint32_t)h * lda + (uint32_t)(m0 + col) * 2 : kOutside;
+            off_a[i] = m0 + col < G.M ? (uint32_t)h * lda + (uint32_t)G.column(m0 + col) * 2 : kOutside;
             off_b[i] = n0 + col < G.N ? (uint32_t)h * ldb + (uint32_t)(n0 + col) * 2 : kOutside;
         }
 #pragma unroll
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(256) void reduce_grouped_kernel(GemmArgs g, ReduceG
     const int m = m_part + (lane & 31), n = n_part + jp * 16 + 8 * (lane >> 5);
     if (m >= G.M || n >= G.N) return;
     if (R.remap == RED_REMAP_F32) {
-        store8(static_cast<float*>(R.out) + (long)m * R.ldo + n, v);
+        store8(static_cast<float*>(R.out) + (long)G.column(m) * R.ldo + n, v);
         return;
     }
     const int ro = (R.remap == RED_REMAP_ROWS) ? ra.tbl[R.table](m) : m;

@@ -17,7 +17,7 @@ FULL, FWD, SKIP = di.OP_FULL, di.OP_FWD, di.OP_SKIP
     (70, 64, 384, [FULL, SKIP, FULL, FWD, FULL, FULL], 1536, 0, False),
     (69, 65, 384, [FULL, FULL, SKIP, FULL, FULL, FULL], 1544, 0, True),
     (79, 104, 72, [FULL], 264, 0, False),
-    (79, 104, 64, [SKIP, FULL], 64, 8, False)])
+    (79, 104, 64, [FULL, SKIP, FULL, FULL], 64, 8, False)])
 def test_weight_gradients(B, T, D, heads, Dm, lora, accumulate):
     import paper_2504_12471_amd as P
     w = di.Workload("wgrad", B, T, D, len(heads), 64, Dm, 1, "bf16", lora_rank=lora, lora_b_zero=False)
