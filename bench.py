@@ -56,7 +56,8 @@ def recorded_traffic(kernel: str, workload: str):
     summary is for another kernel / workload or the kernel source has changed since it was taken."""
     import hashlib
     path = os.path.join(ROOT, "profiles", "gemm_hbm_traffic_vit_b16.txt")
-    src = os.path.join(ROOT, "paper_2504_12471_amd", "csrc", "kernels_gemm_mfma.hip")
+    family = next((f for f in ("wgrad", "pair") if kernel.startswith("gemm_" + f)), "mfma")
+    src = os.path.join(ROOT, "paper_2504_12471_amd", "csrc", f"kernels_gemm_{family}.hip")
     try:
         rec = None
         for line in open(path):
@@ -64,7 +65,7 @@ def recorded_traffic(kernel: str, workload: str):
                 rec = json.loads(line)
         if rec is None or rec["workload"] != workload or kernel not in rec["kernels"]:
             return None
-        if hashlib.sha256(open(src, "rb").read()).hexdigest() != rec["source_sha256"]:
+        if hashlib.sha256(open(src, "rb").read()).hexdigest() != rec["source_sha256"].get(os.path.basename(src)):
             return None
         k = rec["kernels"][kernel]
         return {"bytes_per_launch": k["bytes_per_launch"], "fetch_bytes": k["fetch_bytes"],
