@@ -533,6 +533,31 @@ __device__ __forceinline__ bf16x8 read_tr(const lds_u8* lo_at, const lds_u8* hi_
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
+// Sums over the 32 columns of a transposed result t[2] (rows = channels, a column per lane of each half): lane l of a half gets
+// channel 32 * (l / 16) + 8 * (l % 16 / 4) + 4 h + l % 4.  Each step adds lane to lane and halves the values that a lane keeps.
+__device__ __forceinline__ float column_sum(const f32x16 (&t)[2], int lane) {
+    float v[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {   // rows of 16 lanes: even ones keep t[0], odd ones t[1]
+        const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(t[0][e]), __float_as_uint(t[1][e]), false, false);
+        v[e] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+    }
+    auto halve = [&](auto n_tag, auto ctrl_tag, bool upper) {   // the lane across has `upper` the other way
+        constexpr int N = decltype(n_tag)::value, CTRL = decltype(ctrl_tag)::value;
+#pragma unroll
+        for (int e = 0; e < N; ++e) {
+            const float keep = upper ? v[e + N] : v[e], give = upper ? v[e] : v[e + N];
+            v[e] = keep + dpp<CTRL>(give);
+        }
+    };
+    constexpr int kDppRor8 = 0x128;
+    halve(std::integral_constant<int, 8>{}, std::integral_constant<int, kDppRor8>{}, (lane & 8) != 0);
+    halve(std::integral_constant<int, 4>{}, std::integral_constant<int, kDppHalfMirror>{}, (lane & 4) != 0);
+    halve(std::integral_constant<int, 2>{}, std::integral_constant<int, kDppXor2>{}, (lane & 2) != 0);
+    halve(std::integral_constant<int, 1>{}, std::integral_constant<int, kDppXor1>{}, (lane & 1) != 0);
+    return v[0];
+}
+
 // f(integral_constant<int, 0>), f(integral_constant<int, 1>), ...: a loop whose index is a compile-time constant
 template <typename F, int... I>
 __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
@@ -549,7 +574,7 @@ template <int KT> struct BwdLds {   // byte offsets
     static constexpr int kDs = 2 * KT * kTile;                     // [key tile][query tile]
     static constexpr int kLse = kDs + KT * KT * kDsTile;           // [query] three bf16 terms and 0 of -8 lse, ...
     static constexpr int kDelta = kLse + KT * 32 * 8;              // ... of -delta
-    static constexpr int kSumV = kLse, kSumQ = kDo;                // later [tile][64] column sums of dV and of dQ
+    static constexpr int kSumV = kLse, kSumK = kDelta, kSumQ = kDo;   // later [tile][64] column sums of dV, dK and dQ
     static constexpr int kSk = kDelta + KT * 32 * 8;               // [key tile][3][32] sum over the queries of dS
     static constexpr int kBytes = kSk + KT * 192;
 };
@@ -822,11 +847,24 @@ __global__ __launch_bounds__(64 * KT, 2) void attn_bwd_mfma_kernel(const bf16* _
                 __builtin_amdgcn_sched_barrier(0);
             });
             locate();
-            // dK^T and dV^T: straight from the accumulators, 16-byte pieces after a half-wave exchange.  dK's column sums are
-            // not formed: sum_k dK[k][.] = (1/8) sum_q (sum_k dS[q][k]) Q[q][.] and sum_k dS[q][k] = sum_k P dP - delta_q = 0
-            // (softmax does not see a shift of all keys), so the key bias gradient is written as the zero it is.
+            // dK^T and dV^T: straight from the accumulators, 16-byte pieces after a half-wave exchange.  dK's column sums are not
+            // formed: sum_k dK[k][.] = (1/8) sum_q (sum_k dS[q][k]) Q[q][.] and sum_k dS[q][k] = sum_k P dP - delta_q = 0 (softmax
+            // does not see a shift of all keys), so the key bias gradient is written as the zero it is, but for channels in which a
+            // dK is not finite: those show it.
             store_t_rows(dKt, kScale, dQb + (long)key * ld_dqkv + 64, h, key < tokens);
             store_t_rows(dVt, 1.f, dQb + (long)key * ld_dqkv + 128, h, key < tokens);
+            float sum_k = 0.f;   // of channel sum_channel
+            if (bsum) {
+                float odd = 0.f;   // stays 0, or becomes NaN
+#pragma unroll
+                for (int e = 0; e < 16; ++e) odd = fmaf(dKt[0][e], 0.f, fmaf(dKt[1][e], 0.f, odd));
+                if (__any(key < tokens && odd != 0.f)) {
+                    if (key >= tokens) dKt[0] = dKt[1] = zero16();
+                    sum_k = column_sum(dKt, lane);
+                    if (fabsf(sum_k) < INFINITY) sum_k = 0.f;
+                }
+            }
+            const int sum_channel = (lane >> 4 & 1) * 32 + (lane >> 2 & 3) * 8 + h * 4 + (lane & 3);
             __syncthreads();   // dS is complete; Q and dO are free
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk)   // K in Q's place
@@ -844,6 +882,7 @@ __global__ __launch_bounds__(64 * KT, 2) void attn_bwd_mfma_kernel(const bf16* _
                 }
             }
             if (bsum) {
+                *reinterpret_cast<lds_f32*>(lds + At::kSumK + (wave * 64 + sum_channel) * 4) = sum_k;
                 // dV^T to the wavefront's share of dO's place, where its column sums are taken
                 lds_u8* const stage = lds + At::kDo + wave * At::kTile;
 #pragma unroll
@@ -930,12 +969,11 @@ __global__ __launch_bounds__(64 * KT, 2) void attn_bwd_mfma_kernel(const bf16* _
                     *reinterpret_cast<lds_f32*>(lds + At::kSumQ + (wave * 64 + dt * 32 + c) * 4) = (sum[dt][0] + sum[dt][1] + sum[dt][2]) * kScale;
             }
             __syncthreads();
-            for (int i = tid; i < 192; i += NTHR) {   // tiles added in index order; dK's sums are zero
+            for (int i = tid; i < 192; i += NTHR) {   // tiles added in index order
                 float t = 0.f;
-                if (i < 64 || i >= 128) {
+                const lds_u8* const at = lds + (i < 64 ? At::kSumQ : i < 128 ? At::kSumK : At::kSumV);
 #pragma unroll
-                    for (int v = 0; v < KT; ++v) t += reinterpret_cast<const lds_f32*>(lds + (i < 64 ? At::kSumQ : At::kSumV))[v * 64 + (i & 63)];
-                }
+                for (int v = 0; v < KT; ++v) t += reinterpret_cast<const lds_f32*>(at)[v * 64 + (i & 63)];
                 bout_now[i] = t;
             }
         }

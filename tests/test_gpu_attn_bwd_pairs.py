@@ -1,9 +1,11 @@
 """The bf16 attention backward of up to 224 tokens with more pairs than the chip holds at once, so that workgroups take a second
 and third one, at token counts on and beside the edges of its 32-token tiles."""
+import numpy as np
 import pytest
 
 import d2ft_inputs as di
-from test_gpu_block import run_case
+from helpers import gpu_block
+from test_gpu_block import draw_block, run_case
 from test_gpu_microbatch import run_mb
 
 pytestmark = pytest.mark.gpu
@@ -29,3 +31,27 @@ def test_micro_batches_whose_slots_have_no_pair():
     """Slots are as many as the busiest micro-batch has p_f heads: workgroups skip the other images' empty ones."""
     w = di.Workload("attn_bwd_slots", 150, 193, 64, 3, 64, 64, 1, "bf16")
     run_mb(w, [[FULL, FULL, FULL], [SKIP, FWD, FULL], [FWD, SKIP, FWD]], [40, 60, 50], seed=5)
+
+
+# lengths on both sides of the 32, 96 and 128 tokens, few pairs and more than two rounds of the chip
+@pytest.mark.parametrize("tokens", [17, 40, 65, 128, 197])
+@pytest.mark.parametrize("images", [2, 140])
+def test_key_bias_gradient_shows_what_is_not_finite(tokens, images):
+    w = di.Workload("nan_token", images, tokens, 128, 2, 64, 64, 1, "bf16")
+    x, wt, dy = draw_block(w, 89)
+    assert np.all(gpu_block(w, wt, [FULL, FULL], x, dy, ("b_qkv",))[2]["b_qkv"][1] == 0)   # a common shift of the keys changes nothing
+    x[1, 3, 5] = np.nan
+    assert np.isnan(gpu_block(w, wt, [FULL, FULL], x, dy, ("b_qkv",))[2]["b_qkv"]).all()
+
+
+@pytest.mark.parametrize("tokens,images", [(24, 3), (64, 3), (100, 150), (197, 150)])
+def test_only_the_channel_that_overflows_shows_it(tokens, images):
+    """Queries of 2^127 in a channel whose keys are zero leave the scores alone, and dK = sum_q dS Q overflows in that channel."""
+    w = di.Workload("overflow", images, tokens, 128, 2, 64, 64, 1, "bf16")
+    x, wt, dy = draw_block(w, 90)
+    for plane, bias in ((0, 2.0 ** 127), (1, 0.0)):
+        wt["w_qkv"][plane, 1, 7], wt["b_qkv"][plane, 1, 7] = 0.0, bias
+    b = gpu_block(w, wt, [FULL, FULL], x, dy * 2.0 ** 12, ("b_qkv",))[2]["b_qkv"]
+    assert not np.isfinite(b[1, 1, 7])
+    b[1, 1, 7] = 0.0
+    assert np.isfinite(b).all()
