@@ -570,7 +570,7 @@ __device__ __forceinline__ void static_for(F&& f) {
 
 template <int KT> struct BwdLds {   // byte offsets
     static constexpr int kTile = 32 * 128, kDsTile = 32 * 64;
-    static constexpr int kQ = 0, kDo = KT * kTile;                 // Q, then K; dO, then dV on its way out
+    static constexpr int kQ = 0, kDo = KT * kTile;                 // Q, then K; dO
     static constexpr int kDs = 2 * KT * kTile;                     // [key tile][query tile]
     static constexpr int kLse = kDs + KT * KT * kDsTile;           // [query] three bf16 terms and 0 of -8 lse, ...
     static constexpr int kDelta = kLse + KT * 32 * 8;              // ... of -delta
@@ -853,18 +853,20 @@ __global__ __launch_bounds__(64 * KT, 2) void attn_bwd_mfma_kernel(const bf16* _
             // dK is not finite: those show it.
             store_t_rows(dKt, kScale, dQb + (long)key * ld_dqkv + 64, h, key < tokens);
             store_t_rows(dVt, 1.f, dQb + (long)key * ld_dqkv + 128, h, key < tokens);
-            float sum_k = 0.f;   // of channel sum_channel
+            // the column sums of the wavefront's dV and dK, fp32; this lane's channel
+            const int sum_channel = (lane >> 4 & 1) * 32 + (lane >> 2 & 3) * 8 + h * 4 + (lane & 3);
+            float sum_v = 0.f, sum_k = 0.f;
             if (bsum) {
+                if (key >= tokens) dKt[0] = dKt[1] = dVt[0] = dVt[1] = zero16();   // zeros, or NaN
+                sum_v = column_sum(dVt, lane);
                 float odd = 0.f;   // stays 0, or becomes NaN
 #pragma unroll
                 for (int e = 0; e < 16; ++e) odd = fmaf(dKt[0][e], 0.f, fmaf(dKt[1][e], 0.f, odd));
-                if (__any(key < tokens && odd != 0.f)) {
-                    if (key >= tokens) dKt[0] = dKt[1] = zero16();
+                if (__any(odd != 0.f)) {
                     sum_k = column_sum(dKt, lane);
                     if (fabsf(sum_k) < INFINITY) sum_k = 0.f;
                 }
             }
-            const int sum_channel = (lane >> 4 & 1) * 32 + (lane >> 2 & 3) * 8 + h * 4 + (lane & 3);
             __syncthreads();   // dS is complete; Q and dO are free
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk)   // K in Q's place
@@ -883,29 +885,7 @@ __global__ __launch_bounds__(64 * KT, 2) void attn_bwd_mfma_kernel(const bf16* _
             }
             if (bsum) {
                 *reinterpret_cast<lds_f32*>(lds + At::kSumK + (wave * 64 + sum_channel) * 4) = sum_k;
-                // dV^T to the wavefront's share of dO's place, where its column sums are taken
-                lds_u8* const stage = lds + At::kDo + wave * At::kTile;
-#pragma unroll
-                for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-                    for (int eg = 0; eg < 4; ++eg) {
-                        uint2 pk;
-                        pk.x = pack_bf16x2(dVt[dt][4 * eg], dVt[dt][4 * eg + 1]);
-                        pk.y = pack_bf16x2(dVt[dt][4 * eg + 2], dVt[dt][4 * eg + 3]);
-                        *reinterpret_cast<__attribute__((address_space(3))) uint64_t*>(stage + c * 128 + (((4 * dt + eg) ^ row_swizzle(c)) << 4) + h * 8) =
-                            (uint64_t)pk.y << 32 | pk.x;
-                    }
-                __builtin_amdgcn_wave_barrier();
-                // column sums of the staged tile (the values as they are stored; rows beyond the last token are zero): a row of
-                // ones times the tile, whose results a lane finds in element 0
-                const s16x8 ones = {0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80};
-                const bf16x8 one = __builtin_bit_cast(bf16x8, ones);
-#pragma unroll
-                for (int dt = 0; dt < 2; ++dt) {
-                    f32x16 sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(one, columns(At::kDo, wave, 0, dt), zero16(), 0, 0, 0);
-                    sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(one, columns(At::kDo, wave, 1, dt), sum, 0, 0, 0);
-                    if (h == 0) *reinterpret_cast<lds_f32*>(lds + At::kSumV + (wave * 64 + dt * 32 + c) * 4) = sum[0];
-                }
+                *reinterpret_cast<lds_f32*>(lds + At::kSumV + (wave * 64 + sum_channel) * 4) = sum_v;
             }
         }
         __syncthreads();   // K is in LDS

@@ -5,6 +5,7 @@ import pytest
 
 import d2ft_inputs as di
 from helpers import gpu_block
+from test_gpu_attn_stream import channel, crafted
 from test_gpu_block import draw_block, run_case
 from test_gpu_microbatch import run_mb
 
@@ -55,3 +56,30 @@ def test_only_the_channel_that_overflows_shows_it(tokens, images):
     assert not np.isfinite(b[1, 1, 7])
     b[1, 1, 7] = 0.0
     assert np.isfinite(b).all()
+
+
+def images_of(n, w, x):
+    return di.Workload(w.name, n, w.tokens, 64, 1, 64, 64, 1, w.dtype, ln_eps=w.ln_eps), np.repeat(x, n, 0)
+
+
+@pytest.mark.parametrize("tokens,images", [(16, 2), (32, 2), (64, 2), (64, 600), (128, 2), (128, 300)])
+def test_value_bias_gradient_adds_unrounded_dv(tokens, images):
+    """dV = 1 + 2^-8 in one half of the images, which bf16 rounds to 1, and -1 in the others: every step is exact in fp32."""
+    w, wt, x = crafted(np.ones(tokens), "bf16", (0, 0), (0, 0), (0, 1.0), 1.0)
+    w, x = images_of(images, w, x)
+    dy = np.full(x.shape, -1.0, np.float32)
+    dy[::2] = np.where(np.arange(tokens) % 2 == 0, 1.0, 1.0 + 2.0 ** -7)[None, :, None]
+    b = gpu_block(w, wt, [FULL], x, dy, ("b_qkv",))[2]["b_qkv"]
+    assert np.all(b[2] == images / 2 * tokens * 2.0 ** -8)
+
+
+@pytest.mark.parametrize("tokens,images", [(24, 1), (100, 1), (100, 300), (197, 1), (197, 300)])
+def test_value_bias_gradient_of_an_infinite_dv_is_infinite(tokens, images):
+    """Places of keys beyond the last token have probability zero: zero times infinity is not part of the sum."""
+    w, wt, x = crafted(np.ones(tokens), "bf16", (0, 0), (0, 0), (0, 0), 1.0)
+    w, x = images_of(images, w, x)
+    wt["w_o"][:, 7] = 2.0 ** 127   # dO of the first token overflows in one channel
+    dy = np.zeros_like(x)
+    dy[:, 0] = 1.0
+    b = gpu_block(w, wt, [FULL], x, dy, ("b_qkv",))[2]["b_qkv"][2, 0]
+    assert b[7] == np.inf and np.isfinite(np.delete(b, 7)).all()
