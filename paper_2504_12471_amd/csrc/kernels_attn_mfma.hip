@@ -878,7 +878,7 @@ __global__ __launch_bounds__(64 * KT, 2) void attn_bwd_mfma_kernel(const bf16* _
 #pragma unroll
                     for (int i = 0; i < 3; ++i) {
                         const __bf16 term = static_cast<__bf16>(rest);
-                        rest -= static_cast<float>(term);
+                        rest = fabsf(static_cast<float>(term)) < INFINITY ? rest - static_cast<float>(term) : 0.f;   // infinity is one term
                         *reinterpret_cast<__attribute__((address_space(3))) __bf16*>(lds + At::kSk + wave * 192 + i * 64 + c * 2) = term;
                     }
                 }

@@ -83,3 +83,13 @@ def test_value_bias_gradient_of_an_infinite_dv_is_infinite(tokens, images):
     dy[:, 0] = 1.0
     b = gpu_block(w, wt, [FULL], x, dy, ("b_qkv",))[2]["b_qkv"][2, 0]
     assert b[7] == np.inf and np.isfinite(np.delete(b, 7)).all()
+
+
+@pytest.mark.parametrize("tokens,images", [(16, 1), (64, 1), (64, 600), (128, 300)])
+def test_query_bias_gradient_of_infinite_score_gradients_is_infinite(tokens, images):
+    """dP of +-2^130 overflows, O and delta are zero, and every dS * K is +infinity in one channel."""
+    s = np.where(np.arange(tokens) % 2 == 0, 1.0, -1.0)
+    w, wt, x = crafted(s, "bf16", (0, 0), (0, channel(1, 1.0)), (0, channel(0, 2.0 ** 100)), 1.0)
+    w, x = images_of(images, w, x)
+    b = gpu_block(w, wt, [FULL], x, np.full_like(x, 2.0 ** 30), ("b_qkv",))[2]["b_qkv"][0, 0]
+    assert b[1] == np.inf
