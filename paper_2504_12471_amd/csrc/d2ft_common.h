@@ -415,10 +415,10 @@ struct MicroMask {
 bool attn_mfma_supported(int tokens, long ldq, long ldo);       // forward: up to 256 tokens
 bool attn_bwd_mfma_supported(int tokens, long ldq, long ldo);   // backward: up to 224 tokens
 // with a mask: pairs that are not live get a zero O block (forward), pairs that are not p_f a zero dQKV
-// block (backward); the log-sum-exp is saved for p_f pairs.  The grid has one workgroup per image and
-// "slot" (as many slots as the busiest micro-batch has pairs that take part): slot s of an image works
+// block (backward); the log-sum-exp is saved for p_f pairs.  The forward's grid goes over images and
+// "slots" (as many slots as the busiest micro-batch has pairs that take part): slot s of an image works
 // on its micro-batch's s-th such pair, and the zero blocks are dealt round-robin over the slots, so no
-// workgroup exists only to write zeros.
+// workgroup exists only to write zeros.  The backward numbers the pairs that are p_f and, apart, the zero blocks.
 hipError_t launch_attn_fwd_mfma_masked(const void* qkv, long ldq, void* o, long ldo, float* lse, int batch, int tokens,
                                        int n_live, const MicroMask& mask, hipStream_t s);
 hipError_t launch_attn_bwd_mfma_masked(const void* qkv, long ldq, const void* o, long ldo, const float* lse,

@@ -568,6 +568,35 @@ __device__ __forceinline__ void static_for(F&& f) {
     static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
+// Pair n of those that are p_f (FULL) or of the others: its image and its position in the union layout.  n is below their number.
+// A persistent workgroup takes every so many-th pair, so only those with work are numbered: dealt by image and slot, slots being
+// the busiest micro-batch's p_f heads, 64 images of 9, 7, 7, 7 and 6 p_f heads made three rounds of the chip of 462 pairs.
+template <bool FULL>
+__host__ __device__ __forceinline__ uint64_t pairs_of(const MicroMask& mask, int micro) {
+    return FULL ? mask.full[micro] : ~mask.full[micro] & (mask.n_full_pos >= 64 ? ~0ull : (1ull << mask.n_full_pos) - 1);
+}
+template <bool FULL>
+__device__ __forceinline__ void nth_pair(const MicroMask& mask, int n, int& image, int& position) {
+    int micro = 0, first = 0, count;   // of the micro-batch: its first image and its pairs per image
+    for (;; ++micro) {
+        count = __builtin_popcountll(pairs_of<FULL>(mask, micro));
+        const int all = (mask.img_end[micro] - first) * count;
+        if (n < all || micro + 1 >= mask.n) break;
+        n -= all;
+        first = mask.img_end[micro];
+    }
+    image = first + n / count;
+    uint64_t m = pairs_of<FULL>(mask, micro);
+    for (int k = n % count; k > 0; --k) m &= m - 1;
+    position = __builtin_ctzll(m);
+}
+template <bool FULL>
+int number_of_pairs(const MicroMask& mask) {
+    int n = 0;
+    for (int i = 0; i < mask.n; ++i) n += (mask.img_end[i] - (i ? mask.img_end[i - 1] : 0)) * __builtin_popcountll(pairs_of<FULL>(mask, i));
+    return n;
+}
+
 template <int KT> struct BwdLds {   // byte offsets
     static constexpr int kTile = 32 * 128, kDsTile = 32 * 64;
     static constexpr int kQ = 0, kDo = KT * kTile;                 // Q, then K; dO
@@ -586,9 +615,10 @@ __global__ __launch_bounds__(64 * KT, 2) void attn_bwd_mfma_kernel(const bf16* _
                                                                 const bf16* __restrict__ d_o, long ld_do,
                                                                 bf16* __restrict__ dqkv, long ld_dqkv,
                                                                 float* __restrict__ bsum, long ld_bsum,
-                                                                int tokens, int n_full, int pairs, long rows_total,
+                                                                int tokens, int n_full, int pairs, int zeros, long rows_total,
                                                                 Mask mask) {
     using At = BwdLds<KT>;
+    constexpr bool kMasked = std::is_same<Mask, MicroMask>::value;
     constexpr int TP = KT * 32, NTHR = 64 * KT, NCH = 4;   // 16-byte pieces of a [TP][64] operand per thread
     static_assert(TP * 8 == NCH * NTHR, "an operand divides over the threads");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -610,30 +640,15 @@ __global__ __launch_bounds__(64 * KT, 2) void attn_bwd_mfma_kernel(const bf16* _
         asm volatile("" : "+v"(t));
         return t;
     };
-    auto request = [&]() -> bool {   // every load of pair's operands; false: the slot has no pair (its zeros are written)
-        const int b = pair / n_full;   // with a mask n_full is the number of slots per image
-        int j = pair % n_full;
-        const long row0 = (long)b * tokens;
-        if constexpr (std::is_same<Mask, MicroMask>::value) {
-            const int mb = mask.micro_of(b), slot = j;
-            const uint64_t full = mask.full[mb];
-            const uint64_t rest = ~full & (mask.n_full_pos >= 64 ? ~0ull : ((1ull << mask.n_full_pos) - 1ull));
-            int r = 0;
-            for (uint64_t m = rest; m; m &= m - 1, ++r)   // not p_f in this image's micro-batch: dQ = dK = dV = 0
-                if (r % n_full == slot) {
-                    const int p = __builtin_ctzll(m);
-                    bf16* zb = dqkv + row0 * ld_dqkv + p * 192;
-                    const u32x4 z = {0u, 0u, 0u, 0u};
-                    for (int i = threadIdx.x; i < tokens * 24; i += NTHR)
-                        *reinterpret_cast<u32x4*>(zb + (long)(i / 24) * ld_dqkv + (i % 24) * 8) = z;
-                    if (bsum)
-                        for (int i = threadIdx.x; i < 192; i += NTHR) bsum[(long)b * ld_bsum + p * 192 + i] = 0.f;
-                }
-            if (slot >= __builtin_popcountll(full)) return false;
-            uint64_t m = full;
-            for (int t = 0; t < slot; ++t) m &= m - 1;
-            j = __builtin_ctzll(m);   // this slot's p_f head
+    auto request = [&]() {   // every load of pair's operands
+        int b, j;
+        if constexpr (kMasked) {
+            nth_pair<true>(mask, pair, b, j);
+        } else {
+            b = pair / n_full;
+            j = pair % n_full;
         }
+        const long row0 = (long)b * tokens;
         // raw buffer loads whose declared size ends with the last token's row: rows above read as zeros
         auto rows_of = [&](const bf16* p, long ld) {
             return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(p), 0, (uint32_t)(tokens - 1) * (uint32_t)ld * 2u + 128u, 0x00020000);
@@ -659,7 +674,22 @@ __global__ __launch_bounds__(64 * KT, 2) void attn_bwd_mfma_kernel(const bf16* _
         }
         dQb = dqkv + row0 * ld_dqkv + j * 192;
         bout = bsum ? bsum + (long)b * ld_bsum + j * 192 : nullptr;
-        return true;
+    };
+    // Pairs that are not p_f in their image's micro-batch: dQ = dK = dV = 0.  The workgroups take them in turn from the last one on,
+    // whose list of pairs may be the shorter one, and write one block with each pair and the rest at the end.
+    int zero = (int)(gridDim.x - 1 - blockIdx.x);
+    auto zero_next = [&]() {
+        if constexpr (kMasked) {
+            if (zero >= zeros) return;
+            int b, j;
+            nth_pair<false>(mask, zero, b, j);
+            zero += gridDim.x;
+            bf16* const zb = dqkv + (long)b * tokens * ld_dqkv + j * 192;
+            const int t = own_thread();
+            for (int i = t; i < tokens * 24; i += NTHR) *reinterpret_cast<u32x4*>(zb + (long)(i / 24) * ld_dqkv + (i % 24) * 8) = zero4;
+            if (bsum)
+                for (int i = t; i < 192; i += NTHR) bsum[(long)b * ld_bsum + j * 192 + i] = 0.f;
+        }
     };
     auto store_terms = [&](int at, float a) {
         const __bf16 t0 = static_cast<__bf16>(a);
@@ -677,9 +707,9 @@ __global__ __launch_bounds__(64 * KT, 2) void attn_bwd_mfma_kernel(const bf16* _
             lq[k] = lo[k] = ldo_[k] = zero4;
             kfr[k] = vfr[k] = bf16x8{};
         }
-        for (; pair < pairs; pair += gridDim.x)
-            if (request()) return true;
-        return false;
+        if (pair >= pairs) return false;
+        request();
+        return true;
     };
     bool more = next();
     while (more) {
@@ -891,6 +921,7 @@ __global__ __launch_bounds__(64 * KT, 2) void attn_bwd_mfma_kernel(const bf16* _
         __syncthreads();   // K is in LDS
         bf16* const dq_now = dQb;
         float* const bout_now = bout;
+        zero_next();
         pair += gridDim.x;
         more = next();
         {
@@ -959,6 +990,8 @@ __global__ __launch_bounds__(64 * KT, 2) void attn_bwd_mfma_kernel(const bf16* _
         }
         __syncthreads();   // all of it has been read: the next pair takes its place
     }
+    if constexpr (kMasked)
+        while (zero < zeros) zero_next();
 }
 
 template <int KT, typename Mask>
@@ -978,14 +1011,18 @@ hipError_t launch_bwd_kt(const bf16* qkv, long ldq, const bf16* o, long ldo, con
         if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64 * KT, lds)) != hipSuccess) return e;
         resident = cus * (per_cu < 1 ? 1 : per_cu);
     }
-    const int pairs = batch * n_full;
-    const dim3 grid(pairs < resident ? pairs : resident), block(64 * KT);
+    int pairs = batch * n_full, zeros = 0;
+    if constexpr (std::is_same<Mask, MicroMask>::value) {
+        pairs = number_of_pairs<true>(mask);
+        zeros = number_of_pairs<false>(mask);
+    }
+    const dim3 grid(pairs + zeros < resident ? pairs + zeros : resident), block(64 * KT);
     if (hipEvent_t ev = launch_signal_take()) {   // the launch completes the event itself
         hipExtLaunchKernelGGL(kern, grid, block, lds, s, nullptr, ev, 0, qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum,
-                              ld_bsum, tokens, n_full, pairs, (long)batch * tokens, mask);
+                              ld_bsum, tokens, n_full, pairs, zeros, (long)batch * tokens, mask);
     } else {
         hipLaunchKernelGGL(kern, grid, block, lds, s, qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, ld_bsum, tokens,
-                           n_full, pairs, (long)batch * tokens, mask);
+                           n_full, pairs, zeros, (long)batch * tokens, mask);
     }
     return hipGetLastError();
 }
@@ -1071,10 +1108,7 @@ hipError_t launch_attn_bwd_mfma_masked(const void* qkv, long ldq, const void* o,
                                        const void* d_o, long ld_do, void* dqkv, long ld_dqkv, float* bsum, long ld_bsum,
                                        int batch, int tokens, int n_full, const MicroMask& mask, hipStream_t s) {
     if (n_full != mask.n_full_pos) return hipErrorInvalidValue;
-    if (n_full <= 0) return hipSuccess;
-    const int slots = busiest(mask.full, mask.n);
-    return attn_bwd_dispatch(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, ld_bsum, batch, tokens,
-                             slots > 0 ? slots : 1, mask, s);
+    return attn_bwd_dispatch(qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, ld_bsum, batch, tokens, n_full, mask, s);
 }
 
 }  // namespace d2ft

@@ -34,6 +34,21 @@ def test_micro_batches_whose_slots_have_no_pair():
     run_mb(w, [[FULL, FULL, FULL], [SKIP, FWD, FULL], [FWD, SKIP, FWD]], [40, 60, 50], seed=5)
 
 
+def codes(heads, full):
+    """Micro-batch i: full[i] p_f heads from head i on, the others forward-only and skipped in turn."""
+    return [[FULL if (h - i) % heads < n else (FWD, SKIP)[h % 2] for h in range(heads)] for i, n in enumerate(full)]
+
+
+# pairs and zero blocks: uneven counts; eight positions, which divide the workgroups; more zero blocks than workgroups and a few
+# pairs; workgroups that only write zeros; a last micro-batch without a pair
+@pytest.mark.parametrize("tokens,heads,full,images", [(177, 12, (9, 7, 7, 7, 6), (13, 13, 13, 13, 12)), (200, 8, (8, 3, 3, 3, 0), (9, 20, 13, 13, 12)),
+                                                      (33, 12, (1, 0, 0, 0, 12), (60, 64, 50, 3, 2)), (70, 5, (1, 4, 2), (3, 1, 5)),
+                                                      (20, 3, (0, 3, 0), (200, 1, 180))])
+def test_micro_batches_with_uneven_pairs(tokens, heads, full, images):
+    w = di.Workload("attn_bwd_uneven", sum(images), tokens, 64, heads, 64, 64, 1, "bf16")
+    run_mb(w, codes(heads, full), list(images), seed=tokens)
+
+
 # lengths on both sides of the 32, 96 and 128 tokens, few pairs and more than two rounds of the chip
 @pytest.mark.parametrize("tokens", [17, 40, 65, 128, 197])
 @pytest.mark.parametrize("images", [2, 140])
