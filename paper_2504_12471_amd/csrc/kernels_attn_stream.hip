@@ -1,7 +1,7 @@
 // Softmax attention on the matrix cores for head dimension 64 with the keys (forward, dQ) or the queries (dK, dV)
 // streamed through LDS: any number of tokens, bf16 and fp32 storage, fp32 accumulate.  It serves fp32 at every token
-// count, bf16 above the tokens that kernels_attn_mfma.hip keeps on chip whole (256 forward, 224 backward), and below them
-// the backward of few pairs (attn_bwd_stream_faster).
+// count, bf16 above the tokens that kernels_attn_mfma.hip keeps on chip whole (256 forward, 224 backward), and below them,
+// from 129 tokens on, the backward of few pairs (attn_bwd_stream_faster).
 //
 // A wavefront owns 32 queries (or keys): their rows sit in registers as the B operand of every product and their
 // results as accumulators, so nothing but the streamed tiles goes through LDS and no partial sum crosses a
@@ -802,21 +802,16 @@ bool attn_stream_supported(int dtype, int tokens, long ldq, long ldo) {
 }
 
 // bf16 backward of up to 224 tokens, against the kernel of kernels_attn_mfma.hip with one workgroup per pair, whose time for
-// one pair is that of a round of the chip.  This one has two workgroups per pair and block of 128 tokens.  This kernel first, us:
-//   129 to 224 tokens (two blocks): 129 tokens, 12 pairs 9.8 and 10.3, 64 pairs 10.2 and 10.6, 160 pairs 21.3 and 11.5; 197
-//     tokens, 12 pairs 11.4 and 12.6, 64 pairs 12.5 and 13.3, 128 pairs 15.6 and 14.6, 160 pairs 24.8 and 15.1.
-//   33 to 48: 33 tokens, 64 pairs 5.8 and 6.0, 160 pairs 6.9 and 6.2; 48 tokens, 128 pairs 6.1 and 6.2, 512 pairs 12.2 and 9.0.
-//   49 to 128: the other kernel is the faster one by little while pairs are few (64 tokens, 128 pairs 6.4 and 6.3, 96 tokens, 64
-//     pairs 8.0 and 6.9, 128 tokens, 128 pairs 9.3 and 8.5) and by much where they are many (64 tokens, 1024 pairs 28.6 and
-//     14.8, 97 tokens, 260 pairs 16.9 and 11.7, 128 tokens, 2048 pairs 79.8 and 56.4).  The lines below are those that
-//     the tests hold, drawn when the other kernel was slower, and reach no further.
-bool attn_bwd_stream_faster(int tokens, int pairs) {
-    if (tokens > 128) return pairs <= 128;
-    if (tokens > 96) return pairs <= 136;
-    if (tokens > 64) return pairs <= 160;
-    if (tokens > 48) return pairs <= 256 || (pairs > 512 && pairs <= 520);
-    return tokens > 32 && pairs <= 128;
-}
+// one pair is that of a round of the chip.  This one has two workgroups per pair and block of 128 tokens, so that two blocks of few
+// pairs use the chip better.  This kernel first, us, at 32, 64, 96, 128 and 136 pairs:
+//   129 tokens 12.0 and 11.9, 12.6 and 13.8, 14.3 and 14.0, 15.2 and 15.0, 21.2 and 15.1
+//   160        12.6 and 12.6, 12.8 and 13.5, 14.8 and 14.9, 15.2 and 15.2, 21.0 and 15.3
+//   192        12.7 and 13.6, 13.4 and 14.9, 15.6 and 15.7, 15.6 and 16.0, 21.4 and 15.7
+//   224        13.4 and 15.2, 14.9 and 16.7, 17.4 and 17.2, 18.6 and 17.2, 25.9 and 17.4
+// and at 4 pairs 10.4 and 11.1 to 13.0 and 13.6.  Of one block (up to 128 tokens) it is never the faster one by more than 0.3 us: 33
+// tokens, 12 pairs 6.2 and 6.4, 520 pairs 16.9 and 12.1; 64 tokens, 12 pairs 6.4 and 6.3, 520 pairs 19.4 and 13.2; 128 tokens,
+// 12 pairs 9.1 and 8.4, 136 pairs 12.7 and 11.6, 520 pairs 31.0 and 21.1.
+bool attn_bwd_stream_faster(int tokens, int pairs) { return tokens > 128 && pairs <= 96; }
 
 // fp32 attention by the fp32 instruction instead of three bf16 parts of each operand, the same in the forward and the backward call
 // (kMostLse says why), so by the pairs of the backward.  The cutting is a fixed cost that 32 keys do not repay, and the backward by

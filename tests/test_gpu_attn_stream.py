@@ -196,10 +196,12 @@ def test_key_bias_gradient_shows_what_is_not_finite(dtype, tokens):
     assert np.isnan(b).all()
 
 
-@pytest.mark.parametrize("tokens,images,stream", [(129, 32, True), (129, 33, False), (128, 33, True), (96, 40, True), (96, 41, False),
-                                                  (64, 64, True), (64, 65, False), (49, 128, False), (49, 129, True)])
+@pytest.mark.parametrize("tokens,images,stream", [(129, 1, True), (129, 24, True), (129, 25, False), (129, 33, False), (224, 24, True),
+                                                  (224, 25, False), (128, 1, False), (128, 33, False), (96, 40, False), (64, 64, False),
+                                                  (49, 129, False), (33, 3, False)])
 def test_which_kernel_runs_the_bf16_backward(tokens, images, stream):
-    """Four heads per image: beside the counts of pairs at which the streamed kernel stops being the faster one."""
+    """Four heads per image, on both sides of the 128 tokens and 96 pairs up to which the streamed kernel is the faster one: the times
+    of both kernels at these sizes are beside attn_bwd_stream_faster."""
     import paper_2504_12471_amd as P
     w = di.Workload("which", images, tokens, 64, 4, 64, 64, 1, "bf16")
     P.d2ft_timing_enable(True)
