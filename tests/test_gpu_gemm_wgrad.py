@@ -59,3 +59,38 @@ def test_infinity_stays_in_its_row_and_column():
     got = st.grads[0]["w2"]
     rest = torch.arange(D, device="cuda") != 130
     assert torch.equal(got[rest], clean[rest]) and not torch.isfinite(got[130]).any()
+
+
+def units_of(records):
+    """(256x256 tile, run of K) units of the one weight-gradient launch in the timing records: its reduction reads each once."""
+    reads = [r for r in records if r["name"].startswith("launch_reduce_grouped")]
+    assert len(reads) == 1 and reads[0]["launches"] == 1, records
+    return round(reads[0]["bytes"] / (4 * 65536))
+
+
+def weight_gradients_of(B, T, D, H, Dm, full, flags=0):
+    """One backward call on random operands: its weights' gradients, the block's operands, the timing records."""
+    import torch
+    import paper_2504_12471_amd as P
+    gen = torch.Generator(device="cuda").manual_seed(B * T + D)
+    mk = lambda *s, std=0.02: (torch.randn(s, generator=gen, device="cuda") * std).to(torch.bfloat16)
+    wt = {"ln1_g": 1 + mk(D), "ln1_b": mk(D), "w_qkv": mk(3, H, 64, D), "b_qkv": mk(3, H, 64), "w_o": mk(D, 64 * H), "b_o": mk(D),
+          "ln2_g": 1 + mk(D), "ln2_b": mk(D), "w1": mk(Dm, D), "b1": mk(Dm), "w2": mk(D, Dm), "b2": mk(D)}
+    x, dy = mk(B, T, D, std=1.0), mk(B, T, D, std=1.0)
+    ops = np.array([[FULL] * full + [SKIP] * (H - full)], np.uint8)
+    st = P.BlockStack(P.make_desc(B, T, D, H, Dm, "bf16", flags=flags), [wt], "bf16", [])
+    st.grads = [{n: (torch.zeros_like(wt[n]) if n in ("w_qkv", "w_o", "w1", "w2") else None) for n in P.WEIGHT_FIELDS}]
+    st.forward(x, ops)
+    P.d2ft_timing_enable(True)
+    try:
+        st.backward(dy, ops)
+        records = P.d2ft_timing_read()
+    finally:
+        P.d2ft_timing_enable(False)
+    return st.grads[0], wt, x, dy, ops, records
+
+
+# 93 tiles in one launch: two runs of K take 152.5 us with their reduction, five 167.6; 33 tiles: seven runs 63, eight 91
+@pytest.mark.parametrize("H,Dm,full,tiles,runs", [(12, 3072, 6, 93, 2), (12, 3072, 4, 84, 3), (4, 1024, 2, 33, 7)])
+def test_runs_per_tile(H, Dm, full, tiles, runs):
+    assert units_of(weight_gradients_of(64, 197, 768, H, Dm, full)[5]) == tiles * runs
