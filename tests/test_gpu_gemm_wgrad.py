@@ -94,3 +94,30 @@ def weight_gradients_of(B, T, D, H, Dm, full, flags=0):
 @pytest.mark.parametrize("H,Dm,full,tiles,runs", [(12, 3072, 6, 93, 2), (12, 3072, 4, 84, 3), (4, 1024, 2, 33, 7)])
 def test_runs_per_tile(H, Dm, full, tiles, runs):
     assert units_of(weight_gradients_of(64, 197, 768, H, Dm, full)[5]) == tiles * runs
+
+
+# rows, hidden units, tiles, 32-deep slabs of K: more tiles than the chip has CUs, so that a workgroup takes up to ten units, each
+# with its first slabs requested ahead of the stores of the one before; runs of 2 to 10 slabs, i.e. fewer than, as many as and more than
+# the five that are in LDS; rows that are no multiple of the 32 of a slab
+@pytest.mark.parametrize("rows,Dm,tiles,slabs", [(303, 8192, 512, 10), (192, 13056, 816, 6), (160, 16384, 1024, 5), (97, 25600, 1600, 4), (64, 40960, 2560, 2)])
+def test_more_units_than_workgroups_and_short_runs(rows, Dm, tiles, slabs):
+    import torch
+    D = 2048
+    grads, wt, x, dy, _, records = weight_gradients_of(1, rows, D, 1, Dm, 0)
+    assert ("gemm_wgrad_kernel<%s>" % ("true" if rows % 32 else "false")) in {r["name"] for r in records}
+    assert units_of(records) == tiles and -(-rows // 32) == slabs   # one run of all slabs per tile
+
+    r16 = lambda t: t.to(torch.bfloat16).float()
+    f = {k: t.float() for k, t in wt.items()}
+    x, dy = x[0].float(), dy[0].float()   # no head is live: the residual stream is x
+    v = r16(torch.nn.functional.layer_norm(x, (D,), f["ln2_g"], f["ln2_b"], 1e-6))
+    z = v @ f["w1"].T + f["b1"]
+    phi = 0.5 * (1 + torch.erf(z * 0.5 ** 0.5))
+    slope = r16(phi + z * torch.exp(-0.5 * z * z) * 0.3989422804014327)
+    dz = r16((dy @ f["w2"]) * slope)
+    # operands and results are rounded to bf16: 2^-9 each, up to four of them, adding in quadrature, is below 4e-3 in the norm
+    # of any part; a slab left out is off by a third or more, a tile in another's place by more than one
+    for name, ref in (("w2", dy.T @ r16(z * phi)), ("w1", dz.T @ v)):
+        err = (grads[name].float() - ref).reshape(ref.shape[0] // 64, 64, ref.shape[1] // 64, 64).pow(2).sum((1, 3)).sqrt()
+        size = ref.reshape(ref.shape[0] // 64, 64, ref.shape[1] // 64, 64).pow(2).sum((1, 3)).sqrt()
+        assert (err / size).max() < 1e-2, (name, float((err / size).max()))
