@@ -18,6 +18,7 @@
 #include <utility>
 
 #include "d2ft_common.h"
+#include "launch.h"
 
 namespace d2ft {
 
@@ -457,16 +458,9 @@ hipError_t launch_fwd_kt(const bf16* qkv, long ldq, bf16* o, long ldo, float* ls
         constexpr size_t lds = 2 * (size_t)KT * 32 * (kKS + kVS) * sizeof(bf16);
         constexpr int threads = 64 * (KT + 1);
         auto kern = attn_fwd_pipe_kernel<KT, Mask>;
-        static int resident = 0;   // workgroups the chip holds at once
-        if (resident == 0) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-            int dev = 0, cus = 0, per_cu = 0;
-            if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
-            if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
-            if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, threads, lds)) != hipSuccess) return e;
-            resident = cus * (per_cu < 1 ? 1 : per_cu);
-        }
+        static KernelLimits limits;
+        int resident = 0;
+        if (const hipError_t e = limits.get(reinterpret_cast<const void*>(kern), threads, lds, &resident); e != hipSuccess) return e;
         const int n_pos = batch * n_live;
         // every workgroup gets the same number of positions, give or take one
         const int rounds = (n_pos + resident - 1) / resident;
@@ -477,12 +471,9 @@ hipError_t launch_fwd_kt(const bf16* qkv, long ldq, bf16* o, long ldo, float* ls
     } else {
         constexpr size_t lds = (size_t)KT * 32 * (kKS + kVS) * sizeof(bf16);
         auto kern = attn_fwd_mfma_kernel<KT, Mask>;
-        static bool attr_set = false;
-        if (!attr_set) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-            attr_set = true;
-        }
+        static KernelLimits limits;
+        int resident = 0;   // not persistent
+        if (const hipError_t e = limits.get(reinterpret_cast<const void*>(kern), 256, lds, &resident); e != hipSuccess) return e;
         const int pairs = batch * n_live, parts = pairs <= 128 ? 2 : 1;   // two: while each finds a CU of its own
         if (parts == 2) launch_label("attn_fwd_mfma, two per pair");
         hipLaunchKernelGGL(kern, dim3(pairs, parts), dim3(256), lds, s, qkv, ldq, o, ldo, lse, tokens, n_live, n_full,
@@ -1001,16 +992,9 @@ hipError_t launch_bwd_kt(const bf16* qkv, long ldq, const bf16* o, long ldo, con
     constexpr size_t lds = BwdLds<KT>::kBytes;
     static_assert(lds <= 160 * 1024, "the pair's tiles must fit a compute unit's LDS");
     auto kern = attn_bwd_mfma_kernel<KT, Mask>;
-    static int resident = 0;   // workgroups the chip holds at once
-    if (resident == 0) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        int dev = 0, cus = 0, per_cu = 0;
-        if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
-        if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
-        if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64 * KT, lds)) != hipSuccess) return e;
-        resident = cus * (per_cu < 1 ? 1 : per_cu);
-    }
+    static KernelLimits limits;
+    int resident = 0;
+    if (const hipError_t e = limits.get(reinterpret_cast<const void*>(kern), 64 * KT, lds, &resident); e != hipSuccess) return e;
     int pairs = batch * n_full, zeros = 0;
     if constexpr (std::is_same<Mask, MicroMask>::value) {
         pairs = number_of_pairs<true>(mask);

@@ -23,6 +23,7 @@
 
 #include "d2ft_common.h"
 #include "gemm_epilogue.h"
+#include "launch.h"
 
 namespace d2ft {
 
@@ -726,18 +727,10 @@ template <int BM, int BN, int BK, int WGM, int WGN, bool A_COL, bool B_COL, int 
 hipError_t launch_cfg(const GemmArgs& g, hipStream_t s) {
     constexpr size_t lds = lds_bytes<BM, BN, BK, WGM, WGN, A_COL, B_COL>();
     auto kern = gemm_mfma_kernel<BM, BN, BK, WGM, WGN, A_COL, B_COL, REMAP, KTAIL, false, EPI>;
-    static int resident = 0;   // per instantiation: workgroups the chip holds at once, a multiple of 8
-    if (resident == 0) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        int dev = 0, cus = 0, per_cu = 0;
-        if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
-        if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
-        if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64 * WGM * WGN, lds)) != hipSuccess) return e;
-        if (per_cu < 1) per_cu = 1;
-        resident = cus * per_cu / 8 * 8;
-        if (resident < 8) resident = 8;
-    }
+    static KernelLimits limits;
+    int resident = 0;
+    if (const hipError_t e = limits.get(reinterpret_cast<const void*>(kern), 64 * WGM * WGN, lds, &resident); e != hipSuccess) return e;
+    resident = in_eights(resident);
     const int splits = g.partial ? g.splits : 1;
     const long tiles = (long)((g.N + BN - 1) / BN) * (REMAP == REMAP_B_KSEG ? g.seg.live_tiles : (g.M + BM - 1) / BM) * splits;
     // persistent: no more workgroups than are resident together; each walks tiles b, b + grid, ...
@@ -762,18 +755,10 @@ hipError_t launch_seg_cfg(const GemmArgs& g, hipStream_t s) {
     constexpr int BM = 256, BN = 256, BK = 64, WGM = 2, WGN = 4;
     constexpr size_t lds = lds_bytes<BM, BN, BK, WGM, WGN, false, B_COL>();
     auto kern = gemm_mfma_kernel<BM, BN, BK, WGM, WGN, false, B_COL, REMAP, false, true, B_COL ? EPI_DGELU : EPI_ANY>;
-    static int resident = 0;
-    if (resident == 0) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        int dev = 0, cus = 0, per_cu = 0;
-        if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
-        if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
-        if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64 * WGM * WGN, lds)) != hipSuccess) return e;
-        if (per_cu < 1) per_cu = 1;
-        resident = cus * per_cu / 8 * 8;
-        if (resident < 8) resident = 8;
-    }
+    static KernelLimits limits;
+    int resident = 0;
+    if (const hipError_t e = limits.get(reinterpret_cast<const void*>(kern), 64 * WGM * WGN, lds, &resident); e != hipSuccess) return e;
+    resident = in_eights(resident);
     const long tiles = (long)((g.N + BN - 1) / BN) * ((g.M + BM - 1) / BM);
     const long grid = tiles < resident ? (tiles + 7) / 8 * 8 : resident;
     launch_kernel(kern, dim3((unsigned)grid), dim3(64 * WGM * WGN), lds, s, g);

@@ -18,13 +18,12 @@
 // 128-byte lines: rows of 64 bytes, which a slab of 32 k would have, load at half the rate (24 against 41 bytes per clock
 // and CU).
 #include <hip/hip_ext.h>
-#include <stdio.h>
 
-#include <atomic>
 #include <type_traits>
 
 #include "d2ft_common.h"
 #include "gemm_epilogue.h"
+#include "launch.h"
 
 namespace d2ft {
 
@@ -265,20 +264,12 @@ __global__ __launch_bounds__(64 * kWaves, 2) void gemm_pair_kernel(GemmArgs g) {
 template <int ACT, bool REMAP>
 hipError_t launch_form(const GemmArgs& g, hipStream_t s) {
     auto kern = gemm_pair_kernel<ACT, REMAP>;
-    static std::atomic<uint32_t> set_on{0};   // devices, one bit each: the attribute belongs to a device's copy of the kernel
-    static std::atomic<int> cus{0};
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    if (dev >= 32 || !(set_on.load() >> dev & 1)) {
-        int n = 0;
-        if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kLds)) != hipSuccess) return e;
-        if ((e = hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
-        cus.store(n);
-        if (dev < 32) set_on.fetch_or(1u << dev);
-    }
-    const long tiles = (long)((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN), resident = 2L * cus.load() / 8 * 8;
-    const dim3 grid((unsigned)(tiles < resident || resident < 8 ? tiles : resident)), block(64 * kWaves);
+    static KernelLimits limits;
+    int resident = 0;
+    if (const hipError_t e = limits.get(reinterpret_cast<const void*>(kern), 64 * kWaves, kLds, &resident); e != hipSuccess) return e;
+    resident = in_eights(resident);
+    const long tiles = (long)((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
+    const dim3 grid((unsigned)(tiles < resident ? tiles : resident)), block(64 * kWaves);
     if (hipEvent_t ev = launch_signal_take()) {   // the launch completes the event itself
         hipExtLaunchKernelGGL(kern, grid, block, kLds, s, nullptr, ev, 0, g);
     } else {

@@ -14,10 +14,10 @@
 // the attention half's (768 x 768, 2304 x 768) 173 -> 161, 1024 x 768 twice 60 -> 56; 8192^3 900 -> 852.
 #include <hip/hip_ext.h>
 
-#include <atomic>
 #include <type_traits>
 
 #include "d2ft_common.h"
+#include "launch.h"
 
 namespace d2ft {
 
@@ -295,19 +295,10 @@ __global__ __launch_bounds__(256) void reduce_grouped_kernel(GemmArgs g, ReduceG
 template <bool KTAIL>
 hipError_t launch_form(GemmArgs* g, hipStream_t s) {
     auto kern = gemm_wgrad_kernel<KTAIL>;
-    static std::atomic<uint32_t> set_on{0};   // devices, one bit each: the attribute belongs to a device's copy of the kernel
-    static std::atomic<int> cus{0};
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    if (dev >= 32 || !(set_on.load() >> dev & 1)) {
-        int n = 0;
-        if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kLds)) != hipSuccess) return e;
-        if ((e = hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
-        cus.store(n);
-        if (dev < 32) set_on.fetch_or(1u << dev);
-    }
-    const int resident = cus.load() / 8 * 8 < 8 ? 8 : cus.load() / 8 * 8;
+    static KernelLimits limits;
+    int resident = 0;
+    if (const hipError_t e = limits.get(reinterpret_cast<const void*>(kern), 64 * kWaves, kLds, &resident); e != hipSuccess) return e;
+    resident = in_eights(resident);
     int tile = 0;
     for (int i = 0; i < g->n_groups; ++i) {
         GemmGroup& G = g->grp[i];
