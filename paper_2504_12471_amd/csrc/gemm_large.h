@@ -1,9 +1,13 @@
-// What the epilogues of the large bf16 products (kernels_gemm_mfma.hip, kernels_gemm_pair.hip) share.
+// What the large bf16 products (kernels_gemm_mfma.hip, kernels_gemm_pair.hip, kernels_gemm_wgrad.hip) share.
 #pragma once
 
-#include "d2ft_common.h"
+#include "gemm_map.h"
+#include "launch.h"
 
 namespace d2ft {
+
+// all but the N youngest of the wavefront's vector memory operations are complete (they complete in order)
+template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
 // ---- GELU for the bf16 epilogues ----
 // The epilogue of FC1 (and of its backward) evaluates Phi on 65536 elements per tile, which on the

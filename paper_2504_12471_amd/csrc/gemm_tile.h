@@ -2,6 +2,8 @@
 // arguments of a grouped weight-gradient launch, the order in which workgroups take tiles, and what happens to results.
 #pragma once
 
+#include "gemm_map.h"
+#include "launch.h"
 #include "tail_jobs.h"
 
 namespace d2ft {
@@ -24,31 +26,11 @@ struct Tile64Grouped {
     uint16_t tbl[3][kMaxBlocks64];   // the remap tables in units of 64
 };
 
-constexpr uint32_t kBufBytes = 0x80000000u;   // declared buffer size; operands are checked to be smaller
-constexpr uint32_t kOutside = 0x80000000u;    // any offset >= kBufBytes reads as zero
-
 // scalar offset of the loads of the slab at k0 (valid k < k_end), whose first k sits at k_at in memory.  The next slabs'
 // loads run past the end of K; there it is 0 and the lanes' own offsets are kOutside.  An offset beyond the buffer's size
 // must not be asked for: the bounds check compares the lane's offset with the size less the scalar one.
 __host__ __device__ __forceinline__ uint32_t slab_offset(int k0, int k_at, int k_end, uint32_t sk_bytes) {
     return k0 < k_end ? (uint32_t)k_at * sk_bytes : 0u;
-}
-
-// workgroup -> tile: workgroup ids with the same value mod 8 (one XCD) get a contiguous range of tiles, walked in
-// groups of 8 tile rows, so that an XCD's workgroups share operand slabs through its L2
-__device__ __forceinline__ void tile_of_block(int pid, int total, int tiles_m, int tiles_n, int& tm, int& tn, int& split) {
-    const int xcd = pid & 7, idx = pid >> 3;
-    const int lid = xcd * (total >> 3) + min(xcd, total & 7) + idx;
-    const int per_split = tiles_m * tiles_n;
-    split = lid / per_split;
-    const int rem = lid - split * per_split;
-    constexpr int GM = 8;
-    const int group = rem / (GM * tiles_n);
-    const int first = group * GM;
-    const int gsize = min(tiles_m - first, GM);
-    const int in_group = rem - group * GM * tiles_n;
-    tm = first + in_group % gsize;
-    tn = in_group / gsize;
 }
 
 // What the epilogue reads for columns n .. n + 7 of row m, as it lies in memory: the bias, and Z or the residual

@@ -13,7 +13,6 @@
 // MFMA 32x32x16 bf16 layouts used throughout (h = lane / 32, c = lane % 32):
 //   operand:  row-or-column c, k-slots 8h .. 8h+7
 //   result :  column c, element e <-> row 8*(e/4) + 4h + e%4
-#include <hip/hip_ext.h>
 #include <type_traits>
 #include <utility>
 
@@ -1001,14 +1000,8 @@ hipError_t launch_bwd_kt(const bf16* qkv, long ldq, const bf16* o, long ldo, con
         zeros = number_of_pairs<false>(mask);
     }
     const dim3 grid(pairs + zeros < resident ? pairs + zeros : resident), block(64 * KT);
-    if (hipEvent_t ev = launch_signal_take()) {   // the launch completes the event itself
-        hipExtLaunchKernelGGL(kern, grid, block, lds, s, nullptr, ev, 0, qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum,
-                              ld_bsum, tokens, n_full, pairs, zeros, (long)batch * tokens, mask);
-    } else {
-        hipLaunchKernelGGL(kern, grid, block, lds, s, qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, ld_bsum, tokens,
-                           n_full, pairs, zeros, (long)batch * tokens, mask);
-    }
-    return hipGetLastError();
+    return launch_signalling(kern, grid, block, lds, s, qkv, ldq, o, ldo, lse, d_o, ld_do, dqkv, ld_dqkv, bsum, ld_bsum, tokens, n_full, pairs,
+                             zeros, (long)batch * tokens, mask);
 }
 
 }  // namespace

@@ -41,11 +41,11 @@
 // tokens, 8 / 4 pairs 10.3 -> 8.9 and 18.2 -> 14.9.
 //
 // Result layout of both products: column c = lane % 32, element e <-> row 8*(e/4) + 4h + e%4, h = lane / 32.
-#include <hip/hip_ext.h>
 #include <atomic>
 #include <type_traits>
 
 #include "d2ft_common.h"
+#include "launch.h"
 
 namespace d2ft {
 
@@ -780,8 +780,6 @@ __global__ __launch_bounds__(64 * kWaves, (std::is_same<Op, Parts>::value ? 1 : 
 }
 
 
-inline bool mult8(long v) { return (v & 7) == 0; }
-
 // The fp32 kernels' dynamic LDS is above the default limit: raised once per device.
 hipError_t allow_lds(const void* kern, std::atomic<uint32_t>& set_on) {   // set_on: devices, one bit each
     int dev = 0;
@@ -871,11 +869,7 @@ static hipError_t launch_bwd(const void* qkv, long ldq, const void* o, long ldo,
         if (e != hipSuccess) return e;
         lds = lds_bytes<Parts>();
     }
-    if (hipEvent_t ev = launch_signal_take())   // the launch completes the event itself
-        hipExtLaunchKernelGGL(kern, grid, block, lds, s, nullptr, ev, 0, q, ldq, op, ldo, lse, dop, ld_do, dq, ld_dqkv, bsum, tokens, n_full, rows, blocks);
-    else
-        hipLaunchKernelGGL(kern, grid, block, lds, s, q, ldq, op, ldo, lse, dop, ld_do, dq, ld_dqkv, bsum, tokens, n_full, rows, blocks);
-    return hipGetLastError();
+    return launch_signalling(kern, grid, block, lds, s, q, ldq, op, ldo, lse, dop, ld_do, dq, ld_dqkv, bsum, tokens, n_full, rows, blocks);
 }
 
 hipError_t launch_attn_bwd_stream(int dtype, const void* qkv, long ldq, const void* o, long ldo, const float* lse,

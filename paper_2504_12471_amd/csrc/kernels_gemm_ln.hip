@@ -261,7 +261,6 @@ hipError_t launch(const GemmArgs& g, const LnArgs& n, hipStream_t s) {
     return launch_form<T, 4, TN>(g, n, s);
 }
 
-inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 }  // namespace
 

@@ -18,12 +18,9 @@
 // B's n or k index may go through a 64-granular remap table: that is how the compacted
 // live-head list selects rows / columns of the full weight tensors without copying them.
 #include <cstdio>
-#include <hip/hip_ext.h>
 #include <type_traits>
 
-#include "d2ft_common.h"
-#include "gemm_epilogue.h"
-#include "launch.h"
+#include "gemm_large.h"
 
 namespace d2ft {
 
@@ -57,11 +54,6 @@ typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 // constant offsets fold into the instructions' offset fields (generic pointers cost a null check and a
 // 64-bit select per use)
 typedef __attribute__((address_space(3))) bf16 lds_bf16;
-constexpr uint32_t kBufBytes = 0x80000000u;   // declared buffer size; operands are checked to be smaller
-// Any offset >= kBufBytes reads as zero, under any scalar offset below kBufBytes: the bounds check compares the lane's
-// offset with the size less the scalar one.
-constexpr uint32_t kOutside = 0x80000000u;
-
 template <int BI, int BK, bool COL, int kThreads>
 struct SlabLoader {
     static constexpr int kChunks = BI * BK / 8;
@@ -192,26 +184,6 @@ __device__ __forceinline__ void pace_group() {
 // bytes of the epilogue's fp32 stage: one 32-row band of every wavefront's tile, rows padded by 4 floats
 template <int BN, int WGM, int WGN> constexpr size_t stage_bytes() {
     return (size_t)WGM * WGN * 32 * (BN / WGN + 4) * sizeof(float);
-}
-
-// ---- workgroup -> tile mapping ----
-// The chip has 8 XCDs with one L2 each and workgroup ids are dealt to them round-robin, so ids
-// with the same value mod 8 are renumbered to a contiguous range of tiles; inside that range
-// tiles are walked in groups of 8 tile rows so that the workgroups resident on one XCD share
-// A and B slabs through its L2.
-__device__ __forceinline__ void tile_of_block(int pid, int total, int tiles_m, int tiles_n, int& tm, int& tn, int& split) {
-    const int xcd = pid & 7, idx = pid >> 3;
-    const int lid = xcd * (total >> 3) + min(xcd, total & 7) + idx;
-    const int per_split = tiles_m * tiles_n;
-    split = lid / per_split;
-    const int rem = lid - split * per_split;
-    constexpr int GM = 8;
-    const int group = rem / (GM * tiles_n);
-    const int first = group * GM;
-    const int gsize = min(tiles_m - first, GM);
-    const int in_group = rem - group * GM * tiles_n;
-    tm = first + in_group % gsize;
-    tn = in_group / gsize;
 }
 
 // epilogues with an instantiation of their own: C = (A B) * Z (the backward's dz) and C = A B + bias + R (the
@@ -706,16 +678,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_mfma_kernel(GemmArgs g
     }
 }
 
-// A launch that an event waits for (launch_signal_next) carries the event as its own completion signal.
-template <typename Kernel>
-void launch_kernel(Kernel kern, dim3 grid, dim3 block, size_t lds, hipStream_t s, const GemmArgs& g) {
-    if (hipEvent_t ev = launch_signal_take()) {
-        hipExtLaunchKernelGGL(kern, grid, block, lds, s, nullptr, ev, 0, g);
-    } else {
-        hipLaunchKernelGGL(kern, grid, block, lds, s, g);
-    }
-}
-
 template <int BM, int BN, int BK, int WGM, int WGN, bool A_COL, bool B_COL>
 constexpr size_t lds_bytes() {
     constexpr size_t slabs = 2 * (slab_elems<BM, BK, A_COL>() + slab_elems<BN, BK, B_COL>()) * sizeof(bf16);
@@ -735,8 +697,7 @@ hipError_t launch_cfg(const GemmArgs& g, hipStream_t s) {
     const long tiles = (long)((g.N + BN - 1) / BN) * (REMAP == REMAP_B_KSEG ? g.seg.live_tiles : (g.M + BM - 1) / BM) * splits;
     // persistent: no more workgroups than are resident together; each walks tiles b, b + grid, ...
     const dim3 grid((unsigned)(tiles < resident ? tiles : resident)), block(64 * WGM * WGN);
-    launch_kernel(kern, grid, block, lds, s, g);
-    return hipGetLastError();
+    return launch_signalling(kern, grid, block, lds, s, g);
 }
 
 // C = (A B) * Z and nothing else in the epilogue: the instantiations with the band-ahead fetch of Z
@@ -761,8 +722,7 @@ hipError_t launch_seg_cfg(const GemmArgs& g, hipStream_t s) {
     resident = in_eights(resident);
     const long tiles = (long)((g.N + BN - 1) / BN) * ((g.M + BM - 1) / BM);
     const long grid = tiles < resident ? (tiles + 7) / 8 * 8 : resident;
-    launch_kernel(kern, dim3((unsigned)grid), dim3(64 * WGM * WGN), lds, s, g);
-    return hipGetLastError();
+    return launch_signalling(kern, dim3((unsigned)grid), dim3(64 * WGM * WGN), lds, s, g);
 }
 
 // K-segment launch: A row-major, B's k through the remap table; the epilogue is the residual form (FC2 forward) or
@@ -809,8 +769,6 @@ hipError_t launch_layout(const GemmArgs& g, hipStream_t s) {
     return hipErrorNotSupported;
 }
 
-inline bool mult8(long v) { return (v & 7) == 0; }
-inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 }  // namespace
 

@@ -17,13 +17,9 @@
 // slab s, one barrier per slab.  Both are loaded straight into LDS (no registers hold them on the way), always whole
 // 128-byte lines: rows of 64 bytes, which a slab of 32 k would have, load at half the rate (24 against 41 bytes per clock
 // and CU).
-#include <hip/hip_ext.h>
-
 #include <type_traits>
 
-#include "d2ft_common.h"
-#include "gemm_epilogue.h"
-#include "launch.h"
+#include "gemm_large.h"
 
 namespace d2ft {
 
@@ -35,33 +31,16 @@ typedef __attribute__((address_space(3))) uint32_t lds_u32;
 
 namespace {
 
-constexpr uint32_t kBufBytes = 0x80000000u;   // declared buffer size; operands are checked to be smaller
-constexpr uint32_t kOutside = 0x80000000u;    // any offset >= kBufBytes reads as zero
 constexpr int BM = 128, BN = 256, BK = 64, kWaves = 4;
 constexpr int kSlabA = BM * BK * 2, kSlabB = BN * BK * 2, kLds = 3 * kSlabA + kSlabB;
 constexpr int kLoadA = kSlabA / kWaves / 1024, kLoadB = kSlabB / kWaves / 1024;   // a wavefront's loads of 1024 bytes per slab
 constexpr int MT = 4, NT = 2;   // 32x32 parts of a wavefront's 128x64
 
-// all but the N youngest of the wavefront's vector memory operations are complete (they complete in order)
-template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 // the 16-byte pieces of a slab's rows of 128 bytes change places, so that a fragment read (16 lanes want the same piece of
 // 16 rows) touches all banks: piece p of row r sits at p ^ swizzle(r)
 __device__ __forceinline__ int swizzle(int row) { return (row >> 1) & 7; }
-
-// workgroup -> tile, as in kernels_gemm_mfma.hip
-__device__ __forceinline__ void tile_of_block(int pid, int total, int tiles_m, int tiles_n, int& tm, int& tn) {
-    const int xcd = pid & 7, idx = pid >> 3;
-    const int lid = xcd * (total >> 3) + min(xcd, total & 7) + idx;
-    constexpr int GM = 8;
-    const int group = lid / (GM * tiles_n);
-    const int first = group * GM;
-    const int gsize = min(tiles_m - first, GM);
-    const int in_group = lid - group * GM * tiles_n;
-    tm = first + in_group % gsize;
-    tn = in_group / gsize;
-}
 
 // REMAP: B's row index n through g.tbl
 template <int ACT, bool REMAP>
@@ -96,7 +75,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void gemm_pair_kernel(GemmArgs g) {
     // fixes a tile's coordinates and load addresses and requests its first slabs
     auto setup = [&](int pid) {
         int tm, tn;
-        tile_of_block(pid, total, tiles_m, tiles_n, tm, tn);
+        tile_at(xcd_range(pid, total), tiles_m, tiles_n, tm, tn);
         m0 = tm * BM;
         n0 = tn * BN;
 #pragma unroll
@@ -270,12 +249,7 @@ hipError_t launch_form(const GemmArgs& g, hipStream_t s) {
     resident = in_eights(resident);
     const long tiles = (long)((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
     const dim3 grid((unsigned)(tiles < resident ? tiles : resident)), block(64 * kWaves);
-    if (hipEvent_t ev = launch_signal_take()) {   // the launch completes the event itself
-        hipExtLaunchKernelGGL(kern, grid, block, kLds, s, nullptr, ev, 0, g);
-    } else {
-        hipLaunchKernelGGL(kern, grid, block, kLds, s, g);
-    }
-    return hipGetLastError();
+    return launch_signalling(kern, grid, block, kLds, s, g);
 }
 
 }  // namespace

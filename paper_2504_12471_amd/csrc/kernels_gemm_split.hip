@@ -28,7 +28,6 @@
 // LDS layouts, per part: row form [index][32 k], rows of 64 bytes, 16-byte pieces permuted by bits 2..3 of the row; column
 // form [k][W indices], 32-byte chunks permuted by the low bits of k, read by the transposing read.  Both are free of bank
 // conflicts in stores and reads.
-#include <hip/hip_ext.h>
 #include <type_traits>
 
 #include "gemm_tile.h"
@@ -385,9 +384,7 @@ __global__ __launch_bounds__(256) void reduce_split_kernel(Tile64Grouped g) {
 template <typename Kernel, typename Args>
 hipError_t launch(const char* name, Kernel kern, unsigned grid, hipStream_t s, const Args& a) {
     launch_label(name);
-    if (hipEvent_t ev = launch_signal_take()) hipExtLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, s, nullptr, ev, 0, a);
-    else hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, s, a);
-    return hipGetLastError();
+    return launch_signalling(kern, dim3(grid), dim3(256), 0, s, a);
 }
 
 // launch + rounds of four workgroups per CU x (start + slab * slabs + epilogue), a partly filled round at no less than

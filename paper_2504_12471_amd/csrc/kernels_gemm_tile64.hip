@@ -26,7 +26,6 @@
 // Slabs are kept in LDS without padding, their 16-byte pieces permuted within a row so that both the stores and the
 // fragment reads are free of bank conflicts (piece_offset).  Operands with K strided stay in their natural
 // [k][index] layout: bf16 fragments come out of it by the transposing read, fp32 ones by plain 4-byte reads.
-#include <hip/hip_ext.h>
 #include <stdio.h>
 
 #include <atomic>
@@ -436,12 +435,7 @@ hipError_t launch_wk(unsigned grid, hipStream_t s, const Args& a) {
             if (dev < 32) set_on.fetch_or(1u << dev);
         }
     }
-    if (hipEvent_t ev = launch_signal_take()) {   // the launch completes the event itself
-        hipExtLaunchKernelGGL(kern, dim3(grid), dim3(threads), lds, s, nullptr, ev, 0, a);
-    } else {
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), lds, s, a);
-    }
-    return hipGetLastError();
+    return launch_signalling(kern, dim3(grid), dim3(threads), lds, s, a);
 }
 
 template <typename T, int TM, int TN, bool A_COL, bool B_COL, typename Args>
@@ -464,8 +458,6 @@ int pick_wk(long units, int slabs) {
     return wk;
 }
 
-inline bool mult8(long v) { return (v & 7) == 0; }
-inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 }  // namespace
 

@@ -12,12 +12,9 @@
 // nothing waits for operands that come from memory beside another stream's traffic.  Against eight wavefronts, two
 // slabs of 64 k and loads through registers, operands in no cache, 12608 tokens: 768 x 3072 twice 120 -> 109 us, with
 // the attention half's (768 x 768, 2304 x 768) 173 -> 161, 1024 x 768 twice 60 -> 56; 8192^3 900 -> 852.
-#include <hip/hip_ext.h>
-
 #include <type_traits>
 
-#include "d2ft_common.h"
-#include "launch.h"
+#include "gemm_large.h"
 
 namespace d2ft {
 
@@ -29,16 +26,11 @@ typedef __attribute__((address_space(3))) uint32_t lds_u32;
 
 namespace {
 
-constexpr uint32_t kBufBytes = 0x80000000u;   // declared buffer size; operands are checked to be smaller
-constexpr uint32_t kOutside = 0x80000000u;    // any offset >= kBufBytes reads as zero
 constexpr int BT = 256, BK = 32, kWaves = 4, kStages = 5;   // tile edge, K slab, slabs in LDS
 constexpr int kRow = BT * 2, kSlab = BK * kRow, kLds = 2 * kStages * kSlab;   // bytes: a row of k, an operand's slab, all (A and B in turn)
 constexpr int kLoads = kSlab / kWaves / 1024;                       // a wavefront's loads of 1024 bytes (two rows of k) per slab
 constexpr int kGroupedMaxSplits = 8;
 constexpr int WT = 4;                                               // 32x32 parts of a wavefront's 128x128, each way
-
-// all but the N youngest of the wavefront's vector memory operations are complete (they complete in order)
-template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
 // The 16-byte pieces of a row of k change places: piece p of row k sits at p ^ swizzle(k).  A transposing read touches 32
 // columns (64 bytes) of the rows k .. k + 3 and k + 8 .. k + 11, whose starts are all the same bank.
@@ -327,16 +319,8 @@ hipError_t launch_form(GemmArgs* g, hipStream_t s) {
     g->units_per_wg = (S + best - 1) / best;
     const long units = (long)tile * best;
     const dim3 grid((unsigned)(units < resident ? (units + 7) / 8 * 8 : resident)), block(64 * kWaves);
-    if (hipEvent_t ev = launch_signal_take()) {   // the launch completes the event itself
-        hipExtLaunchKernelGGL(kern, grid, block, kLds, s, nullptr, ev, 0, *g);
-    } else {
-        hipLaunchKernelGGL(kern, grid, block, kLds, s, *g);
-    }
-    return hipGetLastError();
+    return launch_signalling(kern, grid, block, kLds, s, *g);
 }
-
-bool mult8(long v) { return (v & 7) == 0; }
-bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 // operands in 16-byte pieces and 32-bit offsets, gradients in pieces of 8 columns
 bool grouped_ok(const GemmArgs& g, const ReduceGroupedArgs& r) {

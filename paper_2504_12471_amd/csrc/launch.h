@@ -1,5 +1,7 @@
-// What the launchers of persistent kernels share.
+// What the launchers share.
 #pragma once
+
+#include <hip/hip_ext.h>
 
 #include <atomic>
 
@@ -32,5 +34,16 @@ private:
 
 // a multiple of the eight XCDs, so that ids with the same value mod 8 stay on one of them
 inline int in_eights(int workgroups) { return workgroups < 8 ? 8 : workgroups / 8 * 8; }
+
+// A launch that an event waits for (launch_signal_next) carries the event as its own completion signal.
+template <typename Kernel, typename... Args>
+hipError_t launch_signalling(Kernel kern, dim3 grid, dim3 block, size_t lds, hipStream_t s, const Args&... args) {
+    if (hipEvent_t ev = launch_signal_take()) hipExtLaunchKernelGGL(kern, grid, block, lds, s, nullptr, ev, 0, args...);
+    else hipLaunchKernelGGL(kern, grid, block, lds, s, args...);
+    return hipGetLastError();
+}
+
+inline bool mult8(long v) { return (v & 7) == 0; }
+inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 }  // namespace d2ft
