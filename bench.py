@@ -57,7 +57,8 @@ def recorded_traffic(kernel: str, workload: str):
     import hashlib
     path = os.path.join(ROOT, "profiles", "gemm_hbm_traffic_vit_b16.txt")
     family = next((f for f in ("wgrad", "pair") if kernel.startswith("gemm_" + f)), "mfma")
-    src = os.path.join(ROOT, "paper_2504_12471_amd", "csrc", f"kernels_gemm_{family}.hip")
+    csrc = os.path.join(ROOT, "paper_2504_12471_amd", "csrc")
+    sources = [os.path.join(csrc, f) for f in (f"kernels_gemm_{family}.hip", "gemm_large.h", "gemm_map.h")]
     try:
         rec = None
         for line in open(path):
@@ -65,7 +66,7 @@ def recorded_traffic(kernel: str, workload: str):
                 rec = json.loads(line)
         if rec is None or rec["workload"] != workload or kernel not in rec["kernels"]:
             return None
-        if hashlib.sha256(open(src, "rb").read()).hexdigest() != rec["source_sha256"].get(os.path.basename(src)):
+        if any(hashlib.sha256(open(f, "rb").read()).hexdigest() != rec["source_sha256"].get(os.path.basename(f)) for f in sources):
             return None
         k = rec["kernels"][kernel]
         return {"bytes_per_launch": k["bytes_per_launch"], "fetch_bytes": k["fetch_bytes"],

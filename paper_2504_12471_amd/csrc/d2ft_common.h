@@ -173,7 +173,8 @@ struct GemmArgs {
     int shared;           // the launch has another stream's launches beside it
     // grouped mode (n_groups > 0; launch_gemm_grouped): the problems share K.  Every 256x256 tile of every
     // problem is cut into `splits` runs of units_per_wg K slabs; unit u = split * total_tiles + tile leaves its
-    // fp32 sums in slot u of `partial` ([slots][256][256]); reduce_grouped adds a tile's slots in split order.
+    // fp32 sums in slot u of `partial`, 65536 floats in the order of the kernel's lanes, which only reduce_grouped_kernel
+    // reads (kernels_gemm_wgrad.hip); it adds a tile's slots in split order.
     int n_groups, units_per_wg, slabs_per_tile, total_tiles;
     int max_units;        // grouped mode, in: if > 0, no more (tile, split) units than this unless one split exceeds it
     GemmGroup grp[kMaxGemmGroups];

@@ -861,8 +861,9 @@ static int split_rows(const GemmArgs& g, float* us) {
 // Two workgroups to a CU (kernels_gemm_pair.hip) where that is cheaper than the large tiles in one launch or two.  Below 640
 // of its tiles, a round and a quarter, the costs do not tell the two apart; of 26 products of more that it takes by this
 // rule the slowest is at 1.04 of the other's time, their mean at 0.94 (12608 x 3072 x 768 with GELU 90 -> 78 us, 15760 x
-// 1536 x 384 43 -> 36).  Not beside another stream's launches: the backward's dz on this kernel (then with a form for it)
-// took 12.6 us off by itself and nothing off a pass.
+// 1536 x 384 43 -> 36).  Of whole passes, with this rule and without: base model, 64 images (12608 rows) 7754 and 7897 us, 384
+// pixels (9232) 7277 and 7295, large model (6304) 12615 and 12669, subnets gated 7987 and 7980.  Not beside another stream's
+// launches: the backward's dz on this kernel (then with a form for it) took 12.6 us off by itself and nothing off a pass.
 static bool pair_faster(const GemmArgs& g) {
     if (g.tile_hint || g.shared || !gemm_pair_supported(g) || (long)((g.M + 127) / 128) * ((g.N + 255) / 256) <= 640) return false;
     float us = 1e30f;
