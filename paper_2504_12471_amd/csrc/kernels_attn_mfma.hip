@@ -639,7 +639,8 @@ __global__ __launch_bounds__(64 * KT, 2) void attn_bwd_mfma_kernel(const bf16* _
             j = pair % n_full;
         }
         const long row0 = (long)b * tokens;
-        // raw buffer loads whose declared size ends with the last token's row: rows above read as zeros
+        // Raw buffer loads whose declared size ends with the last token's row: rows above read as zeros.  Places of queries past
+        // the last repeat its Q and log-sum-exp under a dO of zero: with a Q of zero a key that is infinite has a score of NaN there.
         auto rows_of = [&](const bf16* p, long ld) {
             return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(p), 0, (uint32_t)(tokens - 1) * (uint32_t)ld * 2u + 128u, 0x00020000);
         };
@@ -653,9 +654,10 @@ __global__ __launch_bounds__(64 * KT, 2) void attn_bwd_mfma_kernel(const bf16* _
             const uint32_t q = row + k * (NTHR / 8);
             ldo_[k] = __builtin_amdgcn_raw_buffer_load_b128(rd, q * (uint32_t)ld_do * 2u + ch, 0, 0);
             lo[k] = __builtin_amdgcn_raw_buffer_load_b128(ro, q * (uint32_t)ldo * 2u + ch, 0, 0);
-            lq[k] = __builtin_amdgcn_raw_buffer_load_b128(rq, q * (uint32_t)ldq * 2u + ch, 0, 0);
+            const bool past = (k + 1) * (NTHR / 8) > TP - 31;   // whether some of these rows may be: tokens is TP - 31 or more
+            lq[k] = __builtin_amdgcn_raw_buffer_load_b128(rq, (past ? min(q, (uint32_t)tokens - 1u) : q) * (uint32_t)ldq * 2u + ch, 0, 0);
         }
-        lse_q = (int)threadIdx.x < tokens ? lse[(long)j * rows_total + row0 + threadIdx.x] : 0.f;   // tokens <= TP <= NTHR
+        lse_q = lse[(long)j * rows_total + row0 + min(tid, tokens - 1)];   // tokens <= TP <= NTHR
         const uint32_t at_kv = krow * (uint32_t)ldq * 2u + kch;
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {

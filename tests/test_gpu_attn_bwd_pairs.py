@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 import d2ft_inputs as di
-from helpers import gpu_block
+from helpers import TOL, gpu_block, oracle_block, rel_inf
 from test_gpu_attn_stream import channel, crafted
 from test_gpu_block import draw_block, run_case
 from test_gpu_microbatch import run_mb
@@ -108,3 +108,21 @@ def test_query_bias_gradient_of_infinite_score_gradients_is_infinite(tokens, ima
     w, x = images_of(images, w, x)
     b = gpu_block(w, wt, [FULL], x, np.full_like(x, 2.0 ** 30), ("b_qkv",))[2]["b_qkv"][0, 0]
     assert b[1] == np.inf
+
+
+@pytest.mark.parametrize("tokens,images", [(17, 1), (33, 1), (33, 200), (100, 1), (100, 200), (193, 1), (197, 150)])
+def test_keys_that_are_not_finite_reach_no_query_past_the_last(tokens, images):
+    """A key of minus infinity under positive queries has probability zero, and its dV is zero, not NaN from places of the last tile
+    that hold no query."""
+    s = np.where(np.arange(tokens) == 5, -1.0, 1.0)
+    w, wt, x = crafted(s, "bf16", (channel(0, 1.0), 0), (0, 0), (0.5, 1.0), 4.0, ln_eps=1e-12)
+    w, x = images_of(images, w, x)
+    top = float(di.round_to_bf16(np.full(1, 3.3e38, np.float32))[0])   # k of token 5: -(top + top), of the others: top - top
+    wt["w_qkv"][1, 0, 0, 0] = top
+    wt["b_qkv"][1, 0, 0] = -top
+    dy = np.ones(x.shape, np.float32)
+    y, _, g = gpu_block(w, wt, [FULL], x, dy, ("w_qkv", "b_qkv"))
+    # the same without that key: its probability is zero either way
+    wt["w_qkv"][1, 0, 0, 0], wt["b_qkv"][1, 0, 0] = 2.0 ** 20, -(2.0 ** 20)
+    ry, _, rg, _ = oracle_block(w, wt, [FULL], x, dy)
+    assert rel_inf(y, ry) < TOL["bf16"] and rel_inf(g["w_qkv"][2], rg["w_qkv"][2]) < TOL["bf16"] and rel_inf(g["b_qkv"][2], rg["b_qkv"][2]) < TOL["bf16"]
