@@ -503,7 +503,7 @@ hipError_t launch_fwd_kt(const bf16* qkv, long ldq, bf16* o, long ldo, float* ls
 // gradient of the QKV bias: one row of 192 partial sums per image).
 // What bounds it: two wavefronts of a SIMD, whose matrix and vector instructions do not overlap (a step of the walk is 1050
 // cycles for each, 576 of them of products), then memory: 215 KB a pair, 19 us for 448 pairs.  With a wavefront
-// apart for dQ and a barrier a query tile, 448 pairs of 197 tokens took 43.0 us in a block's passes; now 35.5 (0.7 of it for the
+// apart for dQ and a barrier a query tile, 448 pairs of 197 tokens took 43.0 us in a block's passes; now 36 (0.7 of it for the
 // sums of db_k and db_v as they are), 2048 pairs 165 -> 130, 1024 pairs of 64 tokens 24.4 -> 14.8.
 // ---------------------------------------------------------------------------
 typedef __attribute__((address_space(3))) unsigned char lds_u8;
